@@ -23,7 +23,7 @@
  *     GEMM kernels).  group_size g: g == K (or g <= 0) means one scale per output channel;
  *     otherwise g must be 32, 64, 128, 256, 512 or a multiple of 512 dividing K for 4-bit and 32, 64,
  *     128, 256 or a multiple of 256 dividing K for 8-bit (the paper uses 128 and per-channel; the
- *     smaller groups of Section 2.2's discussion run on the skinny kernel at every M).
+ *     smaller groups of Section 2.2's discussion run on the skinny and wide kernels at every M).
  *   - Size limits of the GEMM entry points (the kernels address each tensor with 32-bit byte offsets): packed
  *     weights N*K*bits/8 and activations M*K*2 must each stay below 0x7FFF0000 bytes (2 GiB - 64 KiB), else
  *     RTN_ERR_SHAPE; M <= 2^20; N <= 2^30; K < 2^23 (group indices come from a multiply-high division that is
@@ -159,7 +159,9 @@ rtn_status rtn_linear_ex(const void* dev_A, int64_t M, const void* dev_qweight, 
                          void* dev_workspace, size_t workspace_nbytes, void* stream,
                          const rtn_linear_cfg* cfg);
 
-/* Reports the configuration rtn_linear would use (host only, launches nothing). */
+/* Reports the configuration rtn_linear would use (host only, launches nothing).  With groups of 32 and 64 columns from 20
+ * rows, where rtn_linear takes a form of the wide kernel that no explicit configuration asks for, it is the configuration
+ * of the skinny kernel for the same problem. */
 rtn_status rtn_linear_query(int64_t M, int64_t N, int64_t K, int bits, int group_size, rtn_linear_cfg* out);
 
 /* Host-only checks, nothing is launched and no pointer is needed.  rtn_problem_status: the status every entry point
@@ -239,8 +241,8 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
  * Codes use the same packed layout (rtn_unpack returns q); dev_zeros is fp16 [N, K/g]
  * holding the integers Z; sizes as for the scales (rtn_scales_nbytes).  Group sizes, shapes,
  * alignment and error behaviour as for rtn_quantize / rtn_dequantize / rtn_linear.
- * rtn_linear_asym runs the small-batch kernel up to 16 rows and the wide MFMA kernel above (group
- * sizes that are multiples of 128; other group sizes go 16 rows at a time and re-read the weights);
+ * rtn_linear_asym runs the small-batch kernel up to 16 rows (19 with groups of 32 and 64 columns) and the wide MFMA
+ * kernel above;
  * for thousands of rows dequantise once with rtn_dequantize_asym and call rtn_gemm_fp16. */
 rtn_status rtn_quantize_asym(const void* dev_W, int64_t N, int64_t K, int bits, int group_size,
                              void* dev_qweight, void* dev_scales, void* dev_zeros, void* stream);

@@ -98,7 +98,14 @@ double wide_model_us(int64_t M, int64_t N, int64_t K, int bits, int mb, int wv, 
     return t * 1e6;
 }
 
-void wide_plan(int64_t M, int64_t N, int64_t K, int bits, LinearPlan* p) {
+// Groups of 32 and 64 columns from 20 rows up: the wide kernel with several scales per k-step.  Up to 19 rows the skinny
+// kernel still stages a 4096-column slice in one piece and is ahead on the small matrices (8B qkv, group 64: 9.3 us
+// against 11.5 at 19 rows, 15.8 against 11.4 at 20; level on the 70B ones).  Above, it runs 64 rows at a time; the wide
+// kernel takes 27 us against 44 (8B qkv), 83 against 121 (8B gate_up) and 148 against 207 (70B down) at 256 rows, 597
+// against 823 on 8B gate_up at 2048.  An explicit configuration keeps to the skinny kernel on these groups.
+bool wide_small_groups(int64_t M, int64_t g) { return (g == 64 || g == 32) && M >= 20; }
+
+void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan* p) {
     p->path = 3;
     p->m_rows16 = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
     // 48-row blocks above 64 rows where they save a fifth of the padded rows (65-96 and 129-144 rows: 96 against 128,
@@ -109,7 +116,8 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, LinearPlan* p) {
     p->m_blocks = (int)((M + 16 * p->m_rows16 - 1) / (16 * p->m_rows16));
     p->prefetch = 1; p->waves_k = 1;
     const int64_t KS = K / 128;
-    int64_t smax = (int64_t)((M >= 64 ? kWorkspaceCapTall : kWorkspaceCap) / ((size_t)M * N * sizeof(float)));
+    // groups under 128 columns keep to the small bound at every M: rtn_linear_noalloc serves them all
+    int64_t smax = (int64_t)((M >= 64 && g % 128 == 0 ? kWorkspaceCapTall : kWorkspaceCap) / ((size_t)M * N * sizeof(float)));
     if (smax > kMaxSplitK) smax = kMaxSplitK;
     if (smax > KS / 4) smax = KS / 4;
     if (smax < 1) smax = 1;
@@ -121,6 +129,7 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, LinearPlan* p) {
     for (int wv = 4; wv <= 16; wv *= 2)
         for (int nbw = 1; nbw <= 4; nbw *= 2) {
             if (p->m_rows16 * nbw > 8 || (wv == 16 && nbw > 1)) continue;
+            if (g % 128 != 0 && (wv != 8 || nbw > 2)) continue;     // the shapes built for groups of 32 and 64 columns
             for (int s = 1; s <= smax; ++s) {
                 const double t = wide_model_us(M, N, K, bits, p->m_rows16, wv, nbw, s);
                 if (((s & (s - 1)) == 0 || s == 3) && t < best) {
@@ -380,7 +389,7 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
     bool tile_by_model = false;
     if (force_path == 0 && !tile_wins && wide_wins && M >= 128 && bits == 4) {
         LinearPlan w;
-        wide_plan(M, N, K, bits, &w);
+        wide_plan(M, N, K, bits, g, &w);
         int r16 = 4, sk = 1;
         const double t_tile = tile_plan_choose(M, N, K, &r16, &sk);
         const double t_wide = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, w.split_k);
@@ -407,7 +416,7 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
         return p;
     }
     if (force_path == 3 || (force_path == 0 && wide_wins)) {
-        wide_plan(M, N, K, bits, &p);
+        wide_plan(M, N, K, bits, g, &p);
         return p;
     }
     if (M <= 16 && steps_hint == 0) {
@@ -540,7 +549,10 @@ rules:
 
 rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t workspace_nbytes, LinearPlan* out) {
     const size_t lds_limit = (size_t)device_max_lds();
-    LinearPlan p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0);
+    LinearPlan p;
+    p.n_tiles16 = 1;
+    if (!cfg && wide_small_groups(a.M, a.g)) wide_plan(a.M, a.N, a.K, a.bits, a.g, &p);
+    else p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0);
     if (cfg) {
         if (cfg->path) p.path = cfg->path;
         if (cfg->prefetch) p.prefetch = cfg->prefetch;
@@ -567,7 +579,8 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
         if ((size_t)p.split_k > fit) p.split_k = fit < 1 ? 1 : (int)fit;
     }
     if (p.path >= 3) {
-        const bool ok = p.path == 3 ? rtn::wide_plan_valid(a, p) : rtn::tile_plan_valid(a, p);
+        bool ok = p.path == 3 ? rtn::wide_plan_valid(a, p) : rtn::tile_plan_valid(a, p);
+        if (p.path == 3 && a.g % 128 != 0 && cfg && !a.zeros) ok = false;     // not for the asking, see wide_small_groups
         if (!ok || p.split_k > kMaxSplitK) return RTN_ERR_CONFIG;
         if ((uint64_t)a.N * a.K * a.bits / 8 >= 0x7FFF0000ull || (uint64_t)a.M * a.K * 2 >= 0x7FFF0000ull)
             return RTN_ERR_SHAPE;                               // 32-bit buffer offsets
@@ -1005,10 +1018,10 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
     LinearPlan p;
     rtn_linear_cfg cfg;
     bool planned = false;
-    if (M > 16 && g % 128 == 0) {
+    if (M > 16 && (g % 128 == 0 || wide_small_groups(M, g))) {
         // the wide kernel's zero-point instantiations: 8 wavefronts, at most two tile-rows per wavefront
         LinearPlan h;
-        wide_plan(M, N, K, bits, &h);
+        wide_plan(M, N, K, bits, g, &h);
         cfg.path = 3; cfg.prefetch = 1; cfg.waves_n = 8; cfg.waves_k = 1; cfg.split_k = h.split_k;
         // as many of the plan's K splits as the workspace passed can hold
         const size_t fit = dev_workspace ? workspace_nbytes / ((size_t)M * N * sizeof(float)) : 0;
@@ -1060,7 +1073,8 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
         cfg.path = h.path; cfg.prefetch = h.prefetch; cfg.waves_n = h.waves_n; cfg.waves_k = h.waves_k;
         cfg.split_k = h.split_k; cfg.m_rows16 = h.m_rows16; cfg.n_tiles16 = h.n_tiles16;
         rtn_status st = resolve_plan(a, &cfg, workspace_nbytes, &plans[i]);
-        if (st == RTN_ERR_CONFIG) st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);   // the module's own plan
+        if (st == RTN_ERR_CONFIG || wide_small_groups(a.M, a.g))
+            st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);                          // the module's own plan
         if (st != RTN_OK) return st;
     }
     hipError_t e = rtn::launch_linear_grouped(args.data(), plans.data(), n_mods, static_cast<hipStream_t>(stream));

@@ -42,7 +42,7 @@ hipError_t launch_unpack(const void* qweight, const void* scales, int64_t N, int
 hipError_t launch_linear(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
 // n independent problems with resolved plans: compatible skinny-kernel launches are merged into grouped launches.
 hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, hipStream_t st);
-// Path 3 (wide MFMA kernel): plan check (group size a multiple of 128, 2-4 row blocks, 1/2/4 tile-rows, at most 8 blocks) and launch.
+// Path 3 (wide MFMA kernel): plan check (group size 32, 64 or a multiple of 128, 2-4 row blocks, 1/2/4 tile-rows, at most 8 blocks) and launch.
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.

@@ -41,7 +41,8 @@ struct WideParams {
     float* ws;
     int M, N, K;
     int G;              // groups per row
-    int spg;            // k-steps per group (g / 128)
+    int spg;            // k-steps per group (g / 128; 1 for the smaller groups)
+    int gps;            // groups per k-step: 1, or 2 / 4 for groups of 64 / 32 columns
     int NT;             // N / 16
     int KL;             // tiles per weight row
     int KS;             // k-steps per row (K / 128)
@@ -53,19 +54,48 @@ struct WideParams {
     uint32_t qw_bytes, sc_bytes, a_bytes;
 };
 
-// G1: one k-step per group (group size 128): every k-step starts its partial sums from zero, which the
-// first MFMA of the step takes as a constant operand instead of a cleared register.
+// The scales (or zero points) of one weight row for the groups of one k-step: NG = 1, 2 or 4 consecutive fp16 values.
+// NG > 1 means group sizes 64 and 32, of which K (a multiple of 256) holds a multiple of NG: the loads are aligned.
+template <int NG> struct StepScales;
+template <> struct StepScales<1> { typedef uint16_t raw_t; };
+template <> struct StepScales<2> { typedef uint32_t raw_t; };
+template <> struct StepScales<4> { typedef u32x2_t raw_t; };
+
+template <int NG>
+__device__ __forceinline__ typename StepScales<NG>::raw_t load_step_scales(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff) {
+    if constexpr (NG == 1) return __builtin_amdgcn_raw_buffer_load_b16(r, off, soff, 0);
+    else if constexpr (NG == 2) return __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+    else return __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+}
+
+template <int NG>
+__device__ __forceinline__ half_t step_scale(const typename StepScales<NG>::raw_t& raw, int i) {
+    if constexpr (NG == 1) return __builtin_bit_cast(half_t, raw);
+    else {
+        uint32_t word;                                    // by value: bit_cast of a vector-element lvalue reads element 0
+        if constexpr (NG == 2) word = raw;
+        else word = raw[i >> 1];
+        return __builtin_bit_cast(half2_t, word)[i & 1];
+    }
+}
+
+// GPS: groups per k-step -- 1 (group size 128), 2 (64), 4 (32), or 0: a group spans several k-steps.  From 1 up every
+// group starts its partial sums from zero, which its first MFMA takes as a constant operand instead of a cleared
+// register, and is scaled as soon as its last 32-column slice is done.
 // At least two wavefronts per SIMD (256 registers each): the MFMAs then keep their accumulators in ordinary
 // vector registers, where the scale multiply-add can read them directly.
 // ZP: asymmetric variant -- the integer zero point of the step's group goes into the unpack (operand = q + Z).
 // PS: the weights are scaled in fp16 on their way into the MFMA (fp16(q S), one rounding per weight, as in the tile
 // kernel) instead of the group's partial sums in fp32: no second accumulator set, which is what lets a wavefront own
 // 128 rows (MB = 8: every unpacked operand feeds 8 MFMAs, and 4 scale multiplies replace 32 multiply-adds).
-template <int BITS, int MB, int NBW, bool G1, int WV, bool ZP = false, bool PS = false>
+template <int BITS, int MB, int NBW, int GPS, int WV, bool ZP = false, bool PS = false>
 __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(const WideParams p) {
     constexpr int TK = Layout<BITS>::TK;
     constexpr int MPT = Layout<BITS>::MFMA_PER_TILE;
     constexpr int TPS = kStepK / TK;                      // tiles per k-step and tile-row: 1 / 2
+    constexpr int NG = GPS > 1 ? GPS : 1;                 // scales per k-step and row
+    constexpr int SPG = 4 / NG;                           // 32-column slices per group, of those in one k-step
+    typedef typename StepScales<NG>::raw_t sraw_t;
     constexpr int ROWS = 16 * MB;
     constexpr int BUF_BYTES = ROWS * kStepK * 2;
     __shared__ __align__(16) uint8_t lds_a[2 * BUF_BYTES];
@@ -134,16 +164,16 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
 
     // ---- weight / scale ring, three k-steps deep ----
     u32x4_t wbuf[3][NBW][TPS];
-    uint16_t sbuf[3][NBW];
-    uint16_t zbuf[ZP ? 3 : 1][NBW];                        // zero points, same offsets as the scales
+    sraw_t sbuf[3][NBW];
+    sraw_t zbuf[ZP ? 3 : 1][NBW];                          // zero points, same offsets as the scales
     (void)zbuf;
     auto w_load = [&](int slot, int t) {
         const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
-        const uint32_t j = (G1 || p.spg_inv == 0) ? ks : __umulhi(ks, p.spg_inv);
+        const uint32_t j = GPS > 0 ? ks * NG : (p.spg_inv == 0 ? ks : __umulhi(ks, p.spg_inv));
 #pragma unroll
         for (int r = 0; r < NBW; ++r) {
-            sbuf[slot][r] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[r], (int)(j * 2u), 0);
-            if constexpr (ZP) zbuf[slot][r] = __builtin_amdgcn_raw_buffer_load_b16(rz, s_lane[r], (int)(j * 2u), 0);
+            sbuf[slot][r] = load_step_scales<NG>(rs, s_lane[r], (int)(j * 2u));
+            if constexpr (ZP) zbuf[slot][r] = load_step_scales<NG>(rz, s_lane[r], (int)(j * 2u));
 #pragma unroll
             for (int c = 0; c < TPS; ++c)
                 wbuf[slot][r][c] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane[r], (int)((ks * TPS + c) * 1024u), 2 /* nt */);
@@ -160,14 +190,14 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
             if (b < NPART) part[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
         }
 
-    auto scale_row = [&](int slot, int r) {
+    auto scale_row = [&](int slot, int r, int gi) {
         if constexpr (!PS) {
-            const float sc = (float)__builtin_bit_cast(half_t, sbuf[slot][r]);
+            const float sc = (float)step_scale<NG>(sbuf[slot][r], gi);
 #pragma unroll
             for (int b = 0; b < MB; ++b) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[b][r][e] = fmaf(sc, part[b][r][e], acc[b][r][e]);
-                if constexpr (!G1) part[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
+                if constexpr (GPS == 0) part[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
             }
         }
     };
@@ -191,7 +221,7 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
                 for (int r = 0; r < NBW; ++r) {
                     Half8Words h;
                     h.v = unpack_operand<BITS>(wbuf[slot][r][i / MPT], i % MPT, magic);
-                    const half_t sh = __builtin_bit_cast(half_t, sbuf[slot][r]);
+                    const half_t sh = step_scale<NG>(sbuf[slot][r], i / SPG);
                     const half2_t s2 = {sh, sh};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) h.h2[e] = h.h2[e] * s2;
@@ -215,13 +245,15 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
             return;
         }
         // the group, or this workgroup's share of it, ends with this step
-        const bool ends = G1 ? true : ((--left == 0) || (t == T - 1));
+        const bool ends = GPS > 0 ? true : ((--left == 0) || (t == T - 1));
         // the activation operands of a 32-column slice are read one slice ahead of the MFMAs that use them
         half8_t a_next[MB];
 #pragma unroll
         for (int b = 0; b < MB; ++b) a_next[b] = *reinterpret_cast<const half8_t*>(abase + (b * 256 + (kq ^ nl)) * 16);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            const int gi = i / SPG;                       // group of this slice within the k-step
+            const bool group_done = (i % SPG == SPG - 1) && ends;
             half8_t a[MB];
 #pragma unroll
             for (int b = 0; b < MB; ++b) a[b] = a_next[b];
@@ -233,21 +265,30 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
 #pragma unroll
             for (int r = 0; r < NBW; ++r) {
                 half8_t bw;
-                if constexpr (ZP) bw = unpack_operand_zp<BITS>(wbuf[slot][r][i / MPT], i % MPT, magic, (float)__builtin_bit_cast(half_t, zbuf[slot][r]));
+                if constexpr (ZP) bw = unpack_operand_zp<BITS>(wbuf[slot][r][i / MPT], i % MPT, magic, (float)step_scale<NG>(zbuf[slot][r], gi));
                 else bw = unpack_operand<BITS>(wbuf[slot][r][i / MPT], i % MPT, magic);
 #pragma unroll
                 for (int b = 0; b < MB; ++b) {
-                    const float4_t c_in = (G1 && i == 0) ? (float4_t){0.f, 0.f, 0.f, 0.f} : part[b][r];
+                    const float4_t c_in = (GPS > 0 && i % SPG == 0) ? (float4_t){0.f, 0.f, 0.f, 0.f} : part[b][r];
                     part[b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b], bw, c_in, 0, 0, 0);
                 }
-                if (i == 3 && ends && r > 0) scale_row(slot, r - 1);     // overlaps the next tile-row's MFMAs
+                if (group_done && r > 0) scale_row(slot, r - 1, gi);     // overlaps the next tile-row's MFMAs
+            }
+            if (group_done) scale_row(slot, NBW - 1, gi);
+            if constexpr (NG > 1) {
+                // pins this group's sums here: left alone the compiler keeps the partial sums of several groups alive and
+                // adds them up at the end of the step, which spills up to a hundred registers
+#pragma unroll
+                for (int b = 0; b < MB; ++b)
+#pragma unroll
+                    for (int r = 0; r < NBW; ++r) {
+                        if (i % SPG == SPG - 1) asm volatile("" : "+v"(acc[b][r]));
+                        else asm volatile("" : "+v"(part[b < NPART ? b : 0][r]));
+                    }
             }
             if (i < 3) __builtin_amdgcn_sched_barrier(0);                // keeps the next slice's reads ahead of this slice's MFMAs
         }
-        if (ends) {
-            scale_row(slot, NBW - 1);
-            left = p.spg;
-        }
+        if (ends) left = p.spg;
         __syncthreads();
     };
 
@@ -290,32 +331,33 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
     }
 }
 
-template <int BITS, int MB, int NBW, int WV>
-hipError_t launch_wide_g1(const WideParams& wp, dim3 grid, hipStream_t st) {
+// Groups of 64 and 32 columns, like the zero points: eight wavefronts with one or two tile-rows each.
+template <int BITS, int MB, int NBW, int WV, bool ZP = false>
+hipError_t launch_wide_gps(const WideParams& wp, dim3 grid, hipStream_t st) {
     dim3 block(64 * WV);
-    if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, true, WV>), grid, block, 0, st, wp);
-    else hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, false, WV>), grid, block, 0, st, wp);
+    if (wp.gps > 1) {
+        if constexpr (WV == 8 && NBW <= 2) {
+            if (wp.gps == 4) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, 4, WV, ZP>), grid, block, 0, st, wp);
+            else hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, 2, WV, ZP>), grid, block, 0, st, wp);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, 1, WV, ZP>), grid, block, 0, st, wp);
+    else hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, 0, WV, ZP>), grid, block, 0, st, wp);
     return hipGetLastError();
 }
 
 // Asymmetric variant: 8 wavefronts, one or two tile-rows per wavefront.
-template <int BITS, int MB, int NBW>
-hipError_t launch_wide_zp(const WideParams& wp, dim3 grid, hipStream_t st) {
-    dim3 block(64 * 8);
-    if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, true, 8, true>), grid, block, 0, st, wp);
-    else hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, NBW, false, 8, true>), grid, block, 0, st, wp);
-    return hipGetLastError();
-}
-
 template <int BITS>
 hipError_t launch_wide_zp_bits(const WideParams& wp, int mb, int nbw, dim3 grid, hipStream_t st) {
     switch (mb * 10 + nbw) {
-        case 21: return launch_wide_zp<BITS, 2, 1>(wp, grid, st);
-        case 22: return launch_wide_zp<BITS, 2, 2>(wp, grid, st);
-        case 31: return launch_wide_zp<BITS, 3, 1>(wp, grid, st);
-        case 32: return launch_wide_zp<BITS, 3, 2>(wp, grid, st);
-        case 41: return launch_wide_zp<BITS, 4, 1>(wp, grid, st);
-        case 42: return launch_wide_zp<BITS, 4, 2>(wp, grid, st);
+        case 21: return launch_wide_gps<BITS, 2, 1, 8, true>(wp, grid, st);
+        case 22: return launch_wide_gps<BITS, 2, 2, 8, true>(wp, grid, st);
+        case 31: return launch_wide_gps<BITS, 3, 1, 8, true>(wp, grid, st);
+        case 32: return launch_wide_gps<BITS, 3, 2, 8, true>(wp, grid, st);
+        case 41: return launch_wide_gps<BITS, 4, 1, 8, true>(wp, grid, st);
+        case 42: return launch_wide_gps<BITS, 4, 2, 8, true>(wp, grid, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -323,10 +365,10 @@ hipError_t launch_wide_zp_bits(const WideParams& wp, int mb, int nbw, dim3 grid,
 // Sixteen wavefronts leave 128 registers each: only the register tiles with one tile-row per wavefront.
 template <int BITS, int MB, int NBW>
 hipError_t launch_wide_wv(const WideParams& wp, int wv, dim3 grid, hipStream_t st) {
-    if (wv == 4) return launch_wide_g1<BITS, MB, NBW, 4>(wp, grid, st);
-    if (wv == 8) return launch_wide_g1<BITS, MB, NBW, 8>(wp, grid, st);
+    if (wv == 4) return launch_wide_gps<BITS, MB, NBW, 4>(wp, grid, st);
+    if (wv == 8) return launch_wide_gps<BITS, MB, NBW, 8>(wp, grid, st);
     if constexpr (NBW == 1) {
-        if (wv == 16) return launch_wide_g1<BITS, MB, NBW, 16>(wp, grid, st);
+        if (wv == 16) return launch_wide_gps<BITS, MB, NBW, 16>(wp, grid, st);
     }
     return hipErrorInvalidValue;
 }
@@ -337,8 +379,8 @@ template <int BITS>
 hipError_t launch_wide_bits(const WideParams& wp, int mb, int nbw, int wv, dim3 grid, hipStream_t st) {
     if (mb == 8) {
         if (nbw != 2 || wv != 8) return hipErrorInvalidValue;
-        if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, 8, 2, true, 8, false, true>), grid, dim3(64 * 8), 0, st, wp);
-        else hipLaunchKernelGGL((wide_mfma_kernel<BITS, 8, 2, false, 8, false, true>), grid, dim3(64 * 8), 0, st, wp);
+        if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, 8, 2, 1, 8, false, true>), grid, dim3(64 * 8), 0, st, wp);
+        else hipLaunchKernelGGL((wide_mfma_kernel<BITS, 8, 2, 0, 8, false, true>), grid, dim3(64 * 8), 0, st, wp);
         return hipGetLastError();
     }
     switch (mb * 10 + nbw) {
@@ -356,16 +398,17 @@ hipError_t launch_wide_bits(const WideParams& wp, int mb, int nbw, int wv, dim3 
 }  // namespace
 
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p) {
-    if (a.g % kStepK != 0) return false;
+    if (a.g % kStepK != 0 && a.g != 64 && a.g != 32) return false;
     if (p.m_rows16 == 8) {                                // 128 x 32 register tile, pre-scaled weights
-        return !a.zeros && p.n_tiles16 == 2 && p.waves_n == 8 && p.split_k >= 1 && p.split_k <= a.K / kStepK;
+        return !a.zeros && a.g % kStepK == 0 && p.n_tiles16 == 2 && p.waves_n == 8 && p.split_k >= 1 && p.split_k <= a.K / kStepK;
     }
     if (p.m_rows16 < 2 || p.m_rows16 > 4) return false;
     if (p.n_tiles16 != 1 && p.n_tiles16 != 2 && p.n_tiles16 != 4) return false;
     if (p.m_rows16 * p.n_tiles16 > 8) return false;       // register tile: at most 8 accumulator blocks
     if (p.waves_n != 4 && p.waves_n != 8 && !(p.waves_n == 16 && p.n_tiles16 == 1)) return false;
     if (p.split_k < 1 || p.split_k > a.K / kStepK) return false;
-    if (a.zeros && (p.waves_n != 8 || p.n_tiles16 > 2)) return false;      // the zero-point instantiations
+    // the instantiations with zero points and with groups under 128 columns
+    if ((a.zeros || a.g % kStepK != 0) && (p.waves_n != 8 || p.n_tiles16 > 2)) return false;
     return true;
 }
 
@@ -380,7 +423,8 @@ hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStrea
     wp.ws = a.workspace;
     wp.M = (int)a.M; wp.N = (int)a.N; wp.K = (int)a.K;
     wp.G = (int)(a.K / a.g);
-    wp.spg = (int)(a.g / kStepK);
+    wp.gps = a.g < kStepK ? (int)(kStepK / a.g) : 1;
+    wp.spg = a.g < kStepK ? 1 : (int)(a.g / kStepK);
     wp.spg_inv = wp.spg == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)wp.spg) + 1u;
     wp.NT = (int)(a.N / 16);
     wp.KL = (int)(a.K / tk);

@@ -260,6 +260,31 @@ def test_linear_wide_kernel(rtn, bits, g, M):
             rtn.rtn_linear(A_t, qw64, sc64, 8, 64, cfg=dict(path=3, m_rows16=2, n_tiles16=1))
 
 
+@pytest.mark.parametrize("bits,g,N,K", [(4, 64, 272, 1536), (4, 32, 272, 1536), (8, 64, 272, 768), (8, 32, 272, 768), (4, 32, 16, 512),
+                                        (4, 64, 6160, 512), (8, 32, 6160, 512), (4, 64, 80, 8704)])
+@pytest.mark.parametrize("M", [19, 20, 48, 130])
+def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
+    """Groups of 32 and 64 columns above 16 rows (from 20 rows several groups per 128-column k-step of the wide kernel): the
+    automatic plan, without a workspace too, and the zero-point variant, against the oracle.  Ragged tile-rows and rows, K
+    an odd number of k-chunks, shapes with and without K splits, one and many workgroups."""
+    codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M + g)
+    A_t = synth.activation(M, K, seed=M, device=DEV)
+    ref = O.rtn_linear(_to_np(A_t), codes, scales, gg)
+    outs = [rtn.rtn_linear(A_t, qw, sc, bits, g)]
+    if M >= 20:
+        C = torch.empty((M, N), dtype=torch.float16, device=DEV)
+        outs.append(rtn.rtn_linear(A_t, qw, sc, bits, g, out=C, workspace=torch.empty(16, dtype=torch.uint8, device=DEV)))
+    torch.cuda.synchronize()
+    for C in outs:
+        H.assert_linear_close(_to_np(C), ref, f"int{bits} g={g} M={M} N={N} K={K}")
+    W = _to_np((synth.normal_weight(N, K, 0.02, seed=M + bits, device=DEV).float() + 0.015).half())
+    codes, scales, zeros = O.rtn_quantize_asym(W, bits, gg)
+    C = rtn.rtn_linear_asym(A_t, torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV),
+                            torch.from_numpy(zeros.astype(np.float16)).to(DEV), bits, g)
+    torch.cuda.synchronize()
+    H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M}")
+
+
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 0), (8, 128), (8, 0)])
 @pytest.mark.parametrize("M", [20, 128, 130, 300])
 def test_linear_wide_kernel_128_rows(rtn, bits, g, M):
