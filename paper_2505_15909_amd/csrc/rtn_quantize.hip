@@ -35,6 +35,7 @@
 //          with a shift-add, and the constant contributed by the 768s is subtracted from the word.
 #include "rtn_device.h"
 #include "rtn_internal.h"
+#include <type_traits>
 
 namespace rtn {
 
@@ -281,15 +282,12 @@ __global__ __launch_bounds__(64 * NW) void quantize_resident_group_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Inverse of the layout: packed -> int8 codes [N, K] (test hook) or -> fp16 q * S [N, K]
+// Inverse of the layout: packed -> int8 codes [N, K] (test hook, one thread per 16-byte chunk) or -> fp16 q * S [N, K]
 // (dequantise-to-16-bit, first half of the large-input path of Section 5).
-// One thread per 16-byte chunk.
 // ---------------------------------------------------------------------------------------
-template <int BITS, bool DEQUANT>
-__global__ __launch_bounds__(256) void unpack_kernel(const uint8_t* __restrict__ qweight,
-                                                     const half_t* __restrict__ scales,
-                                                     const half_t* __restrict__ zeros, void* __restrict__ out,
-                                                     int64_t N, int64_t K, int64_t g) {
+template <int BITS>
+__global__ __launch_bounds__(256) void unpack_kernel(const uint8_t* __restrict__ qweight, int8_t* __restrict__ out,
+                                                     int64_t N, int64_t K) {
     constexpr int TK = Layout<BITS>::TK;
     constexpr int MPT = Layout<BITS>::MFMA_PER_TILE;
     const int64_t chunk_id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -306,22 +304,84 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint8_t* __restrict__
     for (int i = 0; i < MPT; ++i) {
         const half8_t v = unpack_operand<BITS>(chunk, i, magic);     // exact integers as fp16
         const int64_t k = kt * TK + i * 32 + kq * 8;
-        if constexpr (DEQUANT) {
-            const half_t s = scales[n * (K / g) + k / g];
-            const float z = zeros ? (float)zeros[n * (K / g) + k / g] : 0.0f;     // asymmetric variant: S (q + Z)
-            half8_t o;
+        u32x2_t o = {0u, 0u};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (half_t)(((float)v[e] + z) * (float)s);   // exact sum and product, one rounding
-            *reinterpret_cast<half8_t*>(reinterpret_cast<half_t*>(out) + n * K + k) = o;
-        } else {
-            u32x2_t o = {0u, 0u};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o[0] |= ((uint32_t)(int)(float)v[e] & 0xFFu) << (8 * e);
-                o[1] |= ((uint32_t)(int)(float)v[e + 4] & 0xFFu) << (8 * e);
-            }
-            *reinterpret_cast<u32x2_t*>(reinterpret_cast<int8_t*>(out) + n * K + k) = o;
+        for (int e = 0; e < 4; ++e) {
+            o[0] |= ((uint32_t)(int)(float)v[e] & 0xFFu) << (8 * e);
+            o[1] |= ((uint32_t)(int)(float)v[e + 4] & 0xFFu) << (8 * e);
         }
+        *reinterpret_cast<u32x2_t*>(out + n * K + k) = o;
+    }
+}
+
+// Packed codes -> fp16(q S) or fp16((q + Z) S), row-major [N, K].  Bound by the HBM (b/8 bytes read, 2 written per weight).
+// A wavefront takes one k-chunk (4 tiles, 16 rows x 512 or 256 columns): four 16-byte loads per lane in flight, every index
+// 32-bit and the same for the whole wavefront (one thread per 16-byte chunk with 64-bit divisions per operand spent more
+// time on those than on memory).  A tile's operands change lanes through the wavefront's own LDS rows (16-byte pieces
+// XOR-swizzled with the row), so that a store writes whole 128-byte lines instead of 64-byte halves.  8192 x 28672 int4
+// group 128: 187 us (3.1 TB/s) -> 124 with the indexing, 108 (5.45 TB/s; a copy reaches 5.1) with whole lines.
+// Non-temporal stores are 5 % faster alone and 1-5 % slower with the GEMM that reads the result.  SUB: groups per
+// tile (2 or 4: groups narrower than a tile, whose scales are consecutive and aligned), else 1.
+template <int BITS, bool ZP, int SUB>
+__global__ __launch_bounds__(256) void dequantize_kernel(const uint8_t* __restrict__ qweight, const half_t* __restrict__ scales,
+                                                         const half_t* __restrict__ zeros, half_t* __restrict__ out,
+                                                         uint32_t units, uint32_t KC, uint32_t K, uint32_t G, uint32_t g) {
+    constexpr int TK = Layout<BITS>::TK;
+    constexpr int MPT = Layout<BITS>::MFMA_PER_TILE;
+    constexpr int CT = 4;                                            // tiles per chunk
+    constexpr int PR = TK / 8, RS = 64 / PR;                          // 16-byte pieces per tile row, rows per store
+    __shared__ __align__(16) uint8_t lds[4][16 * TK * 2];
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t u = blockIdx.x * 4 + wave;
+    if (u >= units) return;
+    const uint32_t nt = u / KC, kc = u % KC;
+    const int nl = lane & 15, kq = lane >> 4;
+    const uint8_t* src = qweight + (size_t)u * (CT * 1024) + lane * 16;
+    u32x4_t raw[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) raw[t] = load_stream16(src + t * 1024);
+    const uint64_t row_g = (uint64_t)(nt * 16 + nl) * G;
+    struct alignas(2 * SUB) TileScales { half_t v[SUB]; };
+    TileScales sc[CT], zp[ZP ? CT : 1];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const uint64_t j = row_g + (kc * (CT * TK) + t * TK) / g;
+        sc[t] = *reinterpret_cast<const TileScales*>(scales + j);
+        if constexpr (ZP) zp[t] = *reinterpret_cast<const TileScales*>(zeros + j);
+    }
+    const uint32_t magic = fp16_magic_vgpr();
+    half_t* dst = out + (uint64_t)nt * 16 * K + kc * (CT * TK);
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+#pragma unroll
+        for (int i = 0; i < MPT; ++i) {
+            Half8Words o;
+            o.v = unpack_operand<BITS>(raw[t], i, magic);            // exact integers as fp16
+            const half_t s = sc[t].v[i * SUB / MPT];
+            if constexpr (ZP) {
+                const float z = (float)zp[t].v[i * SUB / MPT], sf = (float)s;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o.v[e] = (half_t)(((float)o.v[e] + z) * sf);   // exact sum and product, one rounding
+            } else {
+                const half2_t s2 = {s, s};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o.h2[e] = o.h2[e] * s2;                         // one rounding
+            }
+            *reinterpret_cast<half8_t*>(lds[wave] + nl * (TK * 2) + (((i * 4 + kq) ^ (nl & (PR - 1))) * 16)) = o.v;
+        }
+        // lanes read what other lanes of the wavefront wrote (no barrier: the rows are the wavefront's own)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int i = 0; i < MPT; ++i) {
+            const int r = i * RS + lane / PR, pc = lane % PR;
+            *reinterpret_cast<u32x4_t*>(dst + (uint64_t)r * K + t * TK + pc * 8) =
+                *reinterpret_cast<const u32x4_t*>(lds[wave] + r * (TK * 2) + ((pc ^ (r & (PR - 1))) * 16));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -722,20 +782,37 @@ hipError_t launch_quantize_asym(const void* W, int64_t N, int64_t K, int bits, i
                      : launch_quantize_asym_bits<8>(W, N, K, g, qweight, scales, zeros, st);
 }
 
+template <int BITS>
+static void launch_dequantize(const uint8_t* q, const half_t* s, const half_t* z, half_t* out, int64_t N, int64_t K, int64_t g,
+                              hipStream_t st) {
+    const uint32_t KC = (uint32_t)(K / (4 * Layout<BITS>::TK)), units = (uint32_t)(N / 16) * KC, G = (uint32_t)(K / g);
+    const dim3 grid((units + 3) / 4), block(256);
+    const uint32_t k32 = (uint32_t)K, g32 = (uint32_t)g;
+    auto launch = [&](auto sub) {
+        constexpr int SUB = decltype(sub)::value;
+        if (z) hipLaunchKernelGGL((dequantize_kernel<BITS, true, SUB>), grid, block, 0, st, q, s, z, out, units, KC, k32, G, g32);
+        else hipLaunchKernelGGL((dequantize_kernel<BITS, false, SUB>), grid, block, 0, st, q, s, z, out, units, KC, k32, G, g32);
+    };
+    if (g >= Layout<BITS>::TK) launch(std::integral_constant<int, 1>());
+    else if (g * 2 == Layout<BITS>::TK) launch(std::integral_constant<int, 2>());
+    else launch(std::integral_constant<int, 4>());               // 32 columns at 4 bit
+}
+
 hipError_t launch_unpack(const void* qweight, const void* scales, int64_t N, int64_t K, int bits, int64_t g,
                          bool dequant, void* out, hipStream_t st, const void* zeros) {
-    const int64_t chunks = N * K * bits / 8 / 16;
-    dim3 grid((unsigned)((chunks + 255) / 256)), block(256);
     const uint8_t* q = static_cast<const uint8_t*>(qweight);
     const half_t* s = static_cast<const half_t*>(scales);
     const half_t* z = static_cast<const half_t*>(zeros);
-    if (bits == 4) {
-        if (dequant) hipLaunchKernelGGL((unpack_kernel<4, true>), grid, block, 0, st, q, s, z, out, N, K, g);
-        else hipLaunchKernelGGL((unpack_kernel<4, false>), grid, block, 0, st, q, s, z, out, N, K, g);
-    } else {
-        if (dequant) hipLaunchKernelGGL((unpack_kernel<8, true>), grid, block, 0, st, q, s, z, out, N, K, g);
-        else hipLaunchKernelGGL((unpack_kernel<8, false>), grid, block, 0, st, q, s, z, out, N, K, g);
+    if (dequant) {
+        half_t* o = static_cast<half_t*>(out);
+        if (bits == 4) launch_dequantize<4>(q, s, z, o, N, K, g, st);
+        else launch_dequantize<8>(q, s, z, o, N, K, g, st);
+        return hipGetLastError();
     }
+    const int64_t chunks = N * K * bits / 8 / 16;
+    const dim3 grid((unsigned)((chunks + 255) / 256)), block(256);
+    if (bits == 4) hipLaunchKernelGGL((unpack_kernel<4>), grid, block, 0, st, q, static_cast<int8_t*>(out), N, K);
+    else hipLaunchKernelGGL((unpack_kernel<8>), grid, block, 0, st, q, static_cast<int8_t*>(out), N, K);
     return hipGetLastError();
 }
 

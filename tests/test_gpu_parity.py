@@ -121,6 +121,24 @@ def test_quantize_from_host_matches_device_quantize(rtn, bits, g, rows_per_shard
     assert np.array_equal(_to_np(q), O.pack_gfx950(codes, bits))
 
 
+@pytest.mark.parametrize("bits,g", [(4, 32), (4, 64), (4, 128), (4, 256), (4, 512), (4, 1536), (4, 0), (8, 32), (8, 64), (8, 128),
+                                    (8, 256), (8, 768), (8, 0)])
+@pytest.mark.parametrize("tile_rows", [1, 3])
+def test_dequantize_bit_exact(rtn, bits, g, tile_rows):
+    """fp16(q S) and fp16((q + Z) S) have one rounding: every element equals the oracle's, at every group size (a scale per
+    operand, per tile, per chunk and per several chunks), with whole workgroups and a last one in part."""
+    N, K = tile_rows * 16, 3 * (512 if bits == 4 else 256)
+    gg = K if g == 0 else g
+    W = _to_np((synth.normal_weight(N, K, 0.02, seed=g + bits, device=DEV).float() + 0.01).half())
+    codes, scales = O.rtn_quantize(W, bits, gg)
+    got = rtn.rtn_dequantize(torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV), K, bits, g)
+    assert np.array_equal(_to_np(got), O.rtn_dequantize(codes, scales, gg).astype(np.float16))
+    codes, scales, zeros = O.rtn_quantize_asym(W, bits, gg)
+    got = rtn.rtn_dequantize_asym(torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV),
+                                  torch.from_numpy(zeros.astype(np.float16)).to(DEV), N, K, bits, g)
+    assert np.array_equal(_to_np(got), O.rtn_dequantize_asym(codes, scales, zeros, gg).astype(np.float16))
+
+
 def test_quantize_is_deterministic_and_dequantize_matches(rtn):
     N, K = 256, 2048
     W_t = synth.heavy_tail_weight(N, K, 0.02, seed=5, device=DEV)
