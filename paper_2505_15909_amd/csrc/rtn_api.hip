@@ -171,31 +171,48 @@ int tall_wide_split(int64_t M, int64_t N, int64_t K) {
     return best_s;
 }
 
-// Tile height (128 or 256 rows) and K split of the fused tile kernel: the pair with the lowest modelled time.  One
-// workgroup runs per compute unit, so a launch takes rounds of 256 workgroups; a workgroup advances one 64-column step
-// in 0.85 us with a 128-row tile and 1.40 us with a 256-row tile (packed weights) and costs 8 us besides; a split adds
-// the reduce launch and the partial sums' trip through the workspace at 4 TB/s.  Splits need not be powers of two: what
-// pays is a split that fills the last round (144 tiles: three splits of 72 tall tiles make one round of 216).  Fitted
-// to a sweep of splits 1-8 and both heights over the 8B, 70B and 405B shapes whose tiles fill their last round
-// to less than 85 %: the pick is within 1 % of the best measured pair on average, where one split and the height rule
-// of the launch were 6 % behind (405B qkv at 256 rows: 163 us against 219).
+// Tile height (128 or 256 rows) and K split of the tile kernel: the pair with the lowest modelled time.  Splits need not
+// be powers of two: what pays is a split that fills the last round (144 tiles: three splits of 72 tall tiles make one
+// round of 216; 405B qkv at 256 rows: 163 us against 219 with one split).
 constexpr size_t kWorkspaceCapTile = (size_t)256 << 20;
-double tile_plan_choose(int64_t M, int64_t N, int64_t K, int* rows16, int* split_k) {
-    const int64_t xb = (N + 255) / 256;
+double tile_plan_choose(bool dense, int64_t M, int64_t N, int64_t K, size_t workspace_cap, int* rows16, int* split_k) {
     double best = 1e30;
     *rows16 = 4; *split_k = 1;
     for (int s = 1; s <= 8; ++s) {
-        if (s > 1 && ((size_t)M * N * sizeof(float) * s > kWorkspaceCapTile || K / 128 / s < 4)) break;
+        if (s > 1 && ((size_t)M * N * sizeof(float) * s > workspace_cap || K / 128 / s < (dense ? 8 : 4))) break;
         for (int h = 4; h <= 8; h += 4) {
             if (h == 8 && M <= 128) continue;
-            const int64_t tiles = xb * ((M + 32 * h - 1) / (32 * h));
-            const double rounds = (double)((tiles * s + 255) / 256), steps = (double)((K / 64 + s - 1) / s);
-            double t = rounds * (steps * (h == 4 ? 0.85 : 1.40) + 8.0);
-            if (s > 1) t += 2.5 + (2.0 * s * M * N * 4.0 + 2.0 * M * N) / 4.0e6;
+            const double t = rtn::tile_model_us(dense, h, M, N, K, s);
             if (t < best) { best = t; *rows16 = h; *split_k = s; }
         }
     }
     return best;
+}
+double tile_plan_choose(int64_t M, int64_t N, int64_t K, int* rows16, int* split_k) {
+    return tile_plan_choose(false, M, N, K, kWorkspaceCapTile, rows16, split_k);
+}
+
+// Problems the tile kernel may serve at all.  It rounds each scaled weight to fp16, the wide kernel scales fp32 sums of
+// exact codes (2.7e-4 against 2.0e-4 of the norm), so this line is one of precision and does not move with the kernels'
+// speed: from 144 tiles of 128 x 256 without splitting K, unless the 128-row padding costs more than 64-row padding; and
+// on 4-bit weights where rounds of 256 workgroups at 0.85 us (128 rows) or 1.40 us (256 rows) a step, the best of one to
+// eight splits, come below 1.075 x the wide plan's modelled time.
+bool tile_line(int64_t M, int64_t N, int64_t K, int bits, double t_wide) {
+    const int64_t xb = (N + 255) / 256;
+    if (xb * ((M + 127) / 128) >= 144 && (M + 127) / 128 * 2 <= (M + 63) / 64) return true;
+    if (bits != 4) return false;
+    double best = 1e30;
+    for (int s = 1; s <= 8; ++s) {
+        if (s > 1 && ((size_t)M * N * sizeof(float) * s > kWorkspaceCapTile || K / 128 / s < 4)) break;
+        for (int h = 4; h <= 8; h += 4) {
+            if (h == 8 && M <= 128) continue;
+            const double rounds = (double)((xb * ((M + 32 * h - 1) / (32 * h)) * s + 255) / 256);
+            double t = rounds * ((double)((K / 64 + s - 1) / s) * (h == 4 ? 0.85 : 1.40) + 8.0);
+            if (s > 1) t += 2.5 + (2.0 * s * M * N * 4.0 + 2.0 * M * N) / 4.0e6;
+            best = std::min(best, t);
+        }
+    }
+    return best * 0.93 < t_wide;
 }
 
 // The tile kernel in two launches: the first rows_first rows (a multiple of 256) as full rounds of workgroups, the
@@ -203,16 +220,18 @@ double tile_plan_choose(int64_t M, int64_t N, int64_t K, int* rows16, int* split
 // or 0 where one launch is modelled within 7 % of the best pair.  Measured as two calls against one on the qkv shapes:
 // 405B at 2048 rows 1044 us against 1236, at 1024 rows 565 against 641; 70B at 2048 rows 324 against 374; 8B at 4096
 // rows 208 against 232; no gain (and none modelled) where the tiles fill their rounds.
-int64_t tile_two_launches(int64_t M, int64_t N, int64_t K) {
-    if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
+int64_t tile_two_launches(int64_t M, int64_t N, int64_t K, double* time_us = nullptr) {
     int r16, sk;
     const double single = tile_plan_choose(M, N, K, &r16, &sk);
+    if (time_us) *time_us = single;
+    if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
     double best = single * 0.93;
     int64_t rows_first = 0;
     for (int64_t r1 = 256; r1 < M; r1 += 256) {
         const double t = tile_plan_choose(r1, N, K, &r16, &sk) + tile_plan_choose(M - r1, N, K, &r16, &sk);
         if (t < best) { best = t; rows_first = r1; }
     }
+    if (time_us && rows_first > 0) *time_us = best;
     return rows_first;
 }
 
@@ -371,31 +390,27 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
                                        packed_bytes > ((size_t)256 << 20));
     const bool streams_at_32 = streams16;
     const bool wide_wins = g % 128 == 0 && M > 16 && !streams_at_32;
-    // 128 rows and more, and enough 128 x 256 output tiles to fill 9/16 of the compute units without splitting K:
-    // the tile kernel (measured against the wide kernel on the 8B, 70B and 405B shapes at M = 128 ... 4096: it wins
-    // by 8-15 % from 144 tiles and loses from 128 down), unless its 128-row padding costs more than the wide
-    // kernel's 64-row padding
-    const bool tile_wins = g % 128 == 0 && M >= 128 && ((N + 255) / 256) * ((M + 127) / 128) >= 144 &&
-                           (M + 127) / 128 * 2 <= (M + 63) / 64;
-    // Below 144 tiles the tile kernel can still win by splitting K (deep matrices: the wide kernel would split as well
-    // and re-reads its activations more often): taken when its modelled time is under 1.075 x the wide plan's (the
-    // two models are calibrated apart by about that much).  Measured on the 8B, 70B and 405B shapes at 128-1024
-    // rows: 5-27 % faster on the points this picks (8B down from 384 rows, 70B qkv at 256, 70B down from 256, 405B
-    // qkv at 128, 405B o and down from 192; 8B gate_up at 320 is 6 % slower).  Where the 128-row wide variant
-    // (below) applies under 192 rows it keeps the matrix.  8-bit weights: level on average (+12 % to -9 %), so they
-    // keep the 144-tile rule.
     const bool tall_wide = wide_wins && bits == 4 && M >= 128 && (M + 127) / 128 * 2 <= (M + 63) / 64 &&
                            packed_bytes >= ((size_t)40 << 20) && K > N;
-    bool tile_by_model = false;
-    if (force_path == 0 && !tile_wins && wide_wins && M >= 128 && bits == 4) {
-        LinearPlan w;
-        wide_plan(M, N, K, bits, g, &w);
-        int r16 = 4, sk = 1;
-        const double t_tile = tile_plan_choose(M, N, K, &r16, &sk);
+    // The tile kernel may serve what tile_line admits.  Of that it leaves to the wide kernel what does not give it a full
+    // round of 128 x 256 tiles and is not below 1.15 x the wide plan's modelled time (in one launch or two; the wide
+    // kernel's model, fitted at 32 to 256 rows, is about that much short of the measured times here): 8B qkv at 1024 rows
+    // 64 us against 68, 4096 x 4096 at 1536 66 against 71.
+    bool tile_wins = false;
+    LinearPlan w;
+    if (force_path == 3 || (force_path == 0 && wide_wins)) wide_plan(M, N, K, bits, g, &w);
+    if (force_path == 0 && wide_wins && M >= 128) {
         const double t_wide = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, w.split_k);
-        tile_by_model = t_tile * 0.93 < t_wide && !(tall_wide && M < 192);
+        if (tile_line(M, N, K, bits, t_wide) && !(tall_wide && M < 192 && ((N + 255) / 256) * ((M + 127) / 128) < 144)) {
+            tile_wins = ((N + 255) / 256) * ((M + 127) / 128) >= 256;
+            if (!tile_wins) {
+                double t_tile = 0;
+                tile_two_launches(M, N, K, &t_tile);
+                tile_wins = t_tile * 0.87 < t_wide;
+            }
+        }
     }
-    if (force_path == 4 || (force_path == 0 && (tile_wins || tile_by_model))) {
+    if (force_path == 4 || tile_wins) {
         p.path = 4;
         p.prefetch = 1; p.waves_n = 8; p.waves_k = 1;
         tile_plan_choose(M, N, K, &p.m_rows16, &p.split_k);
@@ -415,10 +430,7 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
         p.split_k = tall_wide_split(M, N, K);
         return p;
     }
-    if (force_path == 3 || (force_path == 0 && wide_wins)) {
-        wide_plan(M, N, K, bits, g, &p);
-        return p;
-    }
+    if (force_path == 3 || (force_path == 0 && wide_wins)) return w;
     if (M <= 16 && steps_hint == 0) {
         // the table lookup costs tens of microseconds of host time (logarithms over ~800 entries): remembered per problem
         struct Key { int64_t M, N, K; int bits; size_t lds; };
@@ -775,7 +787,9 @@ rtn_status rtn_linear_noalloc(const void* dev_A, int64_t M, const void* dev_qwei
     rtn_status st = check_problem(N, K, bits, group_size, &g);
     if (st != RTN_OK) return st;
     if (M <= 0 || M > (1 << 20)) return RTN_ERR_SHAPE;
-    if (rtn_workspace_nbytes(M, N, K, bits, group_size) > kScratchBytes) return RTN_ERR_WORKSPACE;
+    // from 144 tiles of 128 x 256, which occupy the chip without a split, the call runs with the splits that fit the array
+    if (rtn_workspace_nbytes(M, N, K, bits, group_size) > kScratchBytes && ((N + 255) / 256) * ((M + 127) / 128) < 144)
+        return RTN_ERR_WORKSPACE;
     void* ptr = nullptr;
     st = scratch_for_current_device(&ptr);
     if (st != RTN_OK) return st;
@@ -881,45 +895,17 @@ rtn_status rtn_quantize_from_host(const void* host_W, int64_t N, int64_t K, int 
     return ok ? RTN_OK : RTN_ERR_HIP;
 }
 
-// K split of the dense GEMM: the candidate (1-8 splits, not only powers of two) with the lowest modelled time, as for
-// the fused tile kernel.  A 128 x 256 tile advances one 64-column step per ~1 us whether or not all compute units
-// have a tile (measured: 59-62 us at K = 4096 for 24 to 192 tiles), a 256-row tile takes 1.7 times as long (the
-// launch picks the height from the rounds of 256 workgroups each would take); a workgroup costs 8 us besides, and a
-// split adds the partials' round trip through the workspace (write and read of split x M x N fp32 at ~4.5 TB/s) and
-// the reduce launch.
-static int dense_split(int64_t M, int64_t N, int64_t K, size_t workspace_nbytes, double* time_us = nullptr) {
-    const int64_t xb = (N + 255) / 256;
-    int best = 1;
-    double best_t = 1e30;
-    for (int s = 1; s <= 8; ++s) {
-        if (s > 1 && (K / 128 / s < 8 || (size_t)M * N * sizeof(float) * s > workspace_nbytes)) break;
-        const double r_short = (double)((xb * ((M + 127) / 128) * s + 255) / 256);
-        const double r_tall = (double)((xb * ((M + 255) / 256) * s + 255) / 256);
-        const bool tall = M > 128 && 1.7 * r_tall < r_short;
-        const double steps = (double)((K / 64 + s - 1) / s);
-        double t = tall ? r_tall * (steps * 1.7 + 8.0) : r_short * (steps * 1.0 + 8.0);
-        if (s > 1) t += 2.5 + (2.0 * s * M * N * 4.0 + 2.0 * M * N) / 4.5e6;
-        if (t < best_t) {
-            best_t = t;
-            best = s;
-        }
-    }
-    if (time_us) *time_us = best_t;
-    return best;
-}
-
 // The dense GEMM in two launches, as rtn_linear does with the fused tile kernel: the first rows (a multiple of 256) as
 // full rounds, the rest with the K split that fills its round; 0 where one launch is modelled within 7 % of that.
 static int64_t dense_two_launches(int64_t M, int64_t N, int64_t K, size_t workspace_nbytes) {
     if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
-    double single = 0, t1 = 0, t2 = 0;
-    dense_split(M, N, K, workspace_nbytes, &single);
-    double best = single * 0.93;
+    int r16, sk;
+    double best = 0.93 * tile_plan_choose(true, M, N, K, workspace_nbytes, &r16, &sk);
     int64_t rows_first = 0;
     for (int64_t r1 = 256; r1 < M; r1 += 256) {
-        dense_split(r1, N, K, workspace_nbytes, &t1);
-        dense_split(M - r1, N, K, workspace_nbytes, &t2);
-        if (t1 + t2 < best) { best = t1 + t2; rows_first = r1; }
+        const double t = tile_plan_choose(true, r1, N, K, workspace_nbytes, &r16, &sk) +
+                         tile_plan_choose(true, M - r1, N, K, workspace_nbytes, &r16, &sk);
+        if (t < best) { best = t; rows_first = r1; }
     }
     return rows_first;
 }
@@ -931,19 +917,16 @@ rtn_status rtn_gemm_fp16(const void* dev_A, int64_t M, const void* dev_W_fp16, i
     if ((uint64_t)K * 2 * 128 >= 0x7FFF0000ull) return RTN_ERR_SHAPE;          // one 128-row slab per buffer resource
     if (!aligned16(dev_A) || !aligned16(dev_W_fp16) || !aligned16(dev_C) || !aligned16(dev_workspace)) return RTN_ERR_ALIGN;
     const int64_t rows_first = dev_workspace ? dense_two_launches(M, N, K, workspace_nbytes) : 0;
-    for (int part = 0; rows_first > 0 && part < 2; ++part) {
-        const int64_t r0 = part == 0 ? 0 : rows_first, rows = part == 0 ? rows_first : M - rows_first;
-        const int s = dense_split(rows, N, K, workspace_nbytes);
+    for (int part = 0; part < (rows_first > 0 ? 2 : 1); ++part) {
+        const int64_t r0 = part == 0 ? 0 : rows_first, rows = rows_first == 0 ? M : part == 0 ? rows_first : M - rows_first;
+        int r16, split;
+        tile_plan_choose(true, rows, N, K, dev_workspace ? workspace_nbytes : 0, &r16, &split);
         if (rtn::launch_gemm_fp16(static_cast<const char*>(dev_A) + (size_t)r0 * K * 2, dev_W_fp16,
                                   static_cast<char*>(dev_C) + (size_t)r0 * N * 2, static_cast<float*>(dev_workspace),
-                                  rows, N, K, s, static_cast<hipStream_t>(stream)) != hipSuccess)
+                                  rows, N, K, r16, split, static_cast<hipStream_t>(stream)) != hipSuccess)
             return RTN_ERR_HIP;
     }
-    if (rows_first > 0) return RTN_OK;
-    const int split = dev_workspace ? dense_split(M, N, K, workspace_nbytes) : 1;
-    hipError_t e = rtn::launch_gemm_fp16(dev_A, dev_W_fp16, dev_C, static_cast<float*>(dev_workspace), M, N, K, split,
-                                         static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
+    return RTN_OK;
 }
 
 size_t rtn_dense_weight_nbytes(int64_t N, int64_t K) {

@@ -6,22 +6,32 @@
 //
 // A workgroup of 8 wavefronts (2 along M x 4 along N) computes a TM x 256 tile of C, TM = 128 or 256; a
 // wavefront owns (TM / 2) x 64 of it as MBW x 4 v_mfma_f32_16x16x32_f16 blocks (MBW = 4 or 8: 64 or 128 fp32
-// accumulator registers).  What bounds a GEMM of this kind on this chip is the traffic from L2 to the compute
-// units (about 11 TB/s in aggregate): a TM x 256 x 64 step moves (TM + 256) x 128 bytes of fp16 operands for
-// 2 x TM x 256 x 64 flops, 85 flop/B at TM = 128 and 128 flop/B at TM = 256 (packed int4 weights: 175 and
-// 210 flop/B), against 64 flop/B for 128 x 128 tiles.
-// K advances in steps of 64 columns through two LDS stages (one barrier per step); a row of a staged tile is
-// 128 bytes = eight 16-byte pieces, stored at piece ^ (row & 7): conflict-free for the row-wise staging writes, for
-// the b128 operand reads (lane -> row nl, piece 4 i + kq) and for the stores of dequantised weights, which have the
-// operand pattern (16-byte stores go through 128 bytes per cycle, eight lanes at a time: with piece ^ ((row >> 1) & 7)
-// every such store took twice as long, by the bank-conflict counter).  Global loads run two steps
-// (activations, dense weights) or one 128-column chunk (packed weights) ahead of their LDS stores, in registers.
+// accumulator registers).  K advances in steps of 64 columns; a row of a staged tile is 128 bytes = eight 16-byte
+// pieces, piece p stored at slot p ^ (row & 7): conflict-free for the b128 operand reads (lane -> row nl, piece
+// 4 i + kq) and for the stores of dequantised weights, which have the operand pattern.
+//
+// What bounds it: with the whole chip busy, power.  The clock falls from 2.4 to about 1.55 GHz under this kernel (1.33
+// under the vendor library's GEMM, whose matrix cores are busier per cycle, at the same time per product); on a quarter
+// of the chip a step is 20 % faster.  So the design spends as little as it can per MFMA:
+//   - fp16 tiles (activations, dense weights) go from global memory straight into LDS, no registers and no LDS store
+//     instructions (the swizzle is in which piece a lane fetches);
+//   - a step runs in phases of 16 MFMAs; each phase reads the operands of the next one, so no MFMA waits for the LDS;
+//   - the one barrier of a step stands before its last phase, whose operands are in registers by then.  From there on
+//     the step's stage is free: the last phase reads the next step's first operands and requests a later step's tiles
+//     into the freed stage, so a request has a step (two, where the stages are short) to arrive and the matrix cores
+//     work across the barrier;
+//   - the MFMAs take the weights as their first operand: a lane then holds four consecutive columns of a row and the
+//     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
+// Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
+// 440 -> 395 us; 8192 x 28672 at 4096: int4 1556 -> 1445, dense 1490 -> 1376; 8192 x 8192 x 8192 dense 905 -> 770 us =
+// 1.43 PFLOP/s, where the vendor library reached 1.57 in bursts).  v_mfma_f32_32x32x16_f16 is 6 % faster on a quarter of
+// the chip and 5 % slower on all of it (twice the accumulator traffic per flop); a raised wavefront priority around the
+// MFMAs is 5-8 % slower.
 //
 // Fused dequantisation: a packed tile is unpacked once per workgroup (not once per wavefront), multiplied by
 // its group's scale in fp16 (one rounding per weight, relative error 2^-11, far inside the layer's tolerance)
 // and written to LDS as ordinary fp16, so the inner loop is that of the dense GEMM and carries no
-// per-accumulator scale arithmetic.  The vector ALU and the matrix cores of a SIMD overlap little on this chip
-// (measured), so vector instructions per MFMA are what this layout minimises.
+// per-accumulator scale arithmetic.
 #include "rtn_device.h"
 #include "rtn_internal.h"
 
@@ -33,9 +43,8 @@ constexpr int kTN = 256;                        // columns of C per workgroup
 constexpr int kBK = 64;                         // columns of K per step
 constexpr int kChunkK = 128;                    // packed weights are fetched in 128-column chunks (two steps)
 constexpr int kThreads = 512;
-constexpr uint32_t kOutOfRange = 0x7FFF0000u;
 constexpr int kBufferFlags = 0x00020000;
-constexpr int kXcds = 8;
+constexpr int kZGroup = 4;                      // row tiles in a group (1, 2, 8: within 1 %; 16: 1-2 % slower)
 
 struct TileParams {
     const half_t* A;
@@ -59,14 +68,35 @@ __device__ __forceinline__ uint32_t swizzled(int row, int piece) {      // byte 
     return (uint32_t)(row * 128 + ((piece ^ (row & 7)) * 16));
 }
 
+// 16 bytes per lane from global memory into 1 KiB of LDS at a wave-uniform address
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, uint8_t* lds, uint32_t lane_off, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, lane_off, off, 0, 0);
+}
+
+// Workgroup barrier behind the loads older than the N newest ones and every LDS access.  __syncthreads() would wait for
+// all loads into LDS, those of the stages to come included.
+template <int N>
+__device__ __forceinline__ void wait_and_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
 // BSRC: 0 = dense fp16 weights, 4 / 8 = packed codes.  MBW: 16-row blocks per wavefront along M (4 or 8).
-// PD: prefetch distance of the global loads in steps (activations, dense weights) or chunks (packed weights):
-// 2 with the 64-register accumulator tile, 1 with the 128-register one (256 registers per wavefront in all).
-template <int BSRC, int MBW, int PD = (MBW == 4 ? 2 : 1)>
+template <int BSRC, int MBW>
 __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams p) {
     constexpr int TM = 32 * MBW;
-    constexpr int A_BYTES = TM * 128, B_BYTES = kTN * 128, STAGE = A_BYTES + B_BYTES;
-    extern __shared__ __align__(16) uint8_t lds[];           // two stages: [A tile][B tile]
+    constexpr int A_BYTES = TM * 128, B_BYTES = kTN * 128;
+    constexpr int HB = MBW / 4;                              // phases per 32-column slice (four row blocks each)
+    constexpr int PH = 2 * HB;                               // phases per step
+    // Stages in LDS (a request has SA or SB steps less a phase to arrive), at most 160 KiB in all.  Dense weights stream
+    // from HBM and get three; three for the short dense tile's activations, whose steps are half as long (4096 x 14336 at
+    // 2048 rows: 223 -> 190 us).  Four for the short packed tile gained nothing.
+    constexpr int SA = BSRC == 0 && MBW == 4 ? 3 : 2, SB = BSRC == 0 ? 3 : 2;
+    constexpr int U = BSRC == 0 ? 6 : 4;                     // steps per turn of the loop: every stage index is a literal
+    // one object per stage: the compiler then knows that a load into one stage cannot touch reads of the other
+    __shared__ __align__(16) uint8_t lds_a0[A_BYTES], lds_a1[A_BYTES], lds_a2[SA > 2 ? A_BYTES : 16];
+    __shared__ __align__(16) uint8_t lds_b0[B_BYTES], lds_b1[B_BYTES], lds_b2[SB > 2 ? B_BYTES : 16];
+    auto stage_a = [&](int i) { return i == 0 ? lds_a0 : i == 1 ? lds_a1 : lds_a2; };
+    auto stage_b = [&](int i) { return i == 0 ? lds_b0 : i == 1 ? lds_b1 : lds_b2; };
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -74,21 +104,17 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams
     const int wm = wave >> 2, wn = wave & 3;
     const int nl = lane & 15, kq = lane >> 4;
 
-    // workgroup index -> (N tile, M tile): the ZB row tiles that share a weight tile are dispatched back to
-    // back on one XCD
-    const int L = blockIdx.x;
-    const int xcd = L % kXcds, idx = L / kXcds;
-    const int zb = idx % p.ZB;
-    const int xb = (idx / p.ZB) * kXcds + xcd;
-    if (xb >= p.XB) return;
+    int xb, zb;                                              // tile along N, along M
+    if (!xcd_tile(blockIdx.x, p.XB, p.ZB, kZGroup, &xb, &zb)) return;
     const int m0 = zb * TM, n0 = xb * kTN;
     const int sg = blockIdx.y;
     const int kc0 = sg * p.kc_base + min(sg, p.kc_rem);      // first 128-column chunk
     const int T = 2 * (p.kc_base + (sg < p.kc_rem ? 1 : 0)); // 64-column steps of this workgroup
     const int ks0 = 2 * kc0;
 
-    // Row-major fp16 operands are addressed through a resource that starts at this workgroup's first row and
-    // ends after its last valid one (rows past M or N read as zeros; no 32-bit limit on the whole matrix).
+    // Row-major fp16 operands are addressed through a resource that starts at this workgroup's first row (no 32-bit
+    // limit on the whole matrix).  Rows past M or N read the last valid row, steps past the last one the last step:
+    // every load is in bounds, and those rows are never stored, those steps never used.
     const int a_rows = min(TM, p.M - m0), b_rows = min(kTN, p.N - n0);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<half_t*>(p.A) + (int64_t)m0 * p.K, 0, (uint32_t)a_rows * (uint32_t)p.K * 2u, kBufferFlags);
@@ -99,80 +125,63 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(p.scales), 0, p.sc_bytes, kBufferFlags);
     const uint32_t magic = fp16_magic_vgpr();
 
-    // ---- staging of row-major fp16 tiles (A always, B when dense): thread -> piece st_p of rows st_r + 64 i ----
-    const int st_p = tid & 7, st_r = tid >> 3;               // (st_r + 64 i) & 7 does not depend on i
-    const uint32_t st_off = swizzled(st_r, st_p);            // + i * 64 rows * 128 bytes
-    constexpr int NA = TM / 64;                              // pieces per thread per step
-    u32x4_t areg[PD][NA];
-    auto a_load = [&](int set, int t, int i0 = 0, int i1 = 2 * MBW / 4) {
+    // ---- staging of row-major fp16 tiles (A always, B when dense): straight into LDS, 1 KiB (8 rows) per instruction;
+    // lane l fills slot l & 7 of row l >> 3, so it fetches the piece that the swizzle puts there ----
+    constexpr int NA = TM / 64, NB = kTN / 64;               // instructions per wavefront and step
+    uint32_t a_lane[NA], b_lane[NB];
+    const int st_row = lane >> 3, st_piece = (lane & 7) ^ (lane >> 3);
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-            const int row = st_r + 64 * i;
-            const bool ok = t < T && row < a_rows;
-            const uint32_t off = ok ? ((uint32_t)row * (uint32_t)p.K + (uint32_t)(ks0 + t) * kBK + st_p * 8) * 2u : kOutOfRange;
-            areg[set][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0);
-        }
+    for (int i = 0; i < NA; ++i)
+        a_lane[i] = ((uint32_t)min((wave * NA + i) * 8 + st_row, a_rows - 1) * (uint32_t)p.K + st_piece * 8) * 2u;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+        b_lane[i] = ((uint32_t)min((wave * NB + i) * 8 + st_row, b_rows - 1) * (uint32_t)p.K + st_piece * 8) * 2u;
+    auto a_dma = [&](int stage, int t, int i) {
+        load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, a_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
     };
-    auto a_store = [&](int set, int stage, int i0 = 0, int i1 = 2 * MBW / 4) {
-#pragma unroll
-        for (int i = i0; i < i1; ++i) *reinterpret_cast<u32x4_t*>(lds + stage * STAGE + st_off + i * 8192) = areg[set][i];
+    auto b_dma = [&](int stage, int t, int i) {
+        load_to_lds(rb, stage_b(stage) + (wave * NB + i) * 1024, b_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
     };
 
-    // ---- weights ----
-    // dense: four pieces per thread per step, two steps ahead (set = step & 1)
-    // packed: wavefront w dequantises tile-rows 2w and 2w+1 of the 16 in the weight tile; a 128-column chunk
-    // (one int4 tile or two int8 tiles per tile-row, plus its scale) is fetched two chunks ahead (set = chunk & 1)
-    constexpr int TPC = BSRC == 8 ? 2 : 1;                   // packed tiles per chunk and tile-row
-    constexpr int NBR = BSRC == 0 ? 4 : 2 * TPC;
-    u32x4_t breg[PD][NBR];
-    uint16_t sreg[PD][2];
-    auto b_load_dense = [&](int set, int t, int i0 = 0, int i1 = 4) {
+    // ---- packed weights: wavefront w dequantises tile-rows 2w and 2w+1 of the 16 in the weight tile.  A unit is one
+    // packed tile per tile-row -- two steps at 4 bit, one at 8 bit -- and its scales; two units are in registers ----
+    constexpr int SPU = BSRC == 4 ? 2 : 1;                   // steps per unit
+    u32x4_t breg[2][2];
+    uint16_t sreg[2][2];
+    uint32_t w_lane[2], s_lane[2];
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-            const int row = st_r + 64 * i;
-            const bool ok = t < T && row < b_rows;
-            const uint32_t off = ok ? ((uint32_t)row * (uint32_t)p.K + (uint32_t)(ks0 + t) * kBK + st_p * 8) * 2u : kOutOfRange;
-            breg[set][i] = __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, 0);
-        }
-    };
-    auto b_load_packed = [&](int set, int c) {               // chunk c of this workgroup
-        const bool in = 2 * c < T;
-        const uint32_t kc = (uint32_t)(kc0 + c);
-        // branch-free in wave-uniform values (a branch here would split the loop body and make its waits
-        // conservative): group index by multiply-high plus a masked term, out of range by an added constant
-        const uint32_t j = __umulhi(kc, p.cpg_inv) + (kc & p.cpg_one);
+    for (int q = 0; q < 2; ++q) {
+        const int nt = min(n0 / 16 + 2 * wave + q, p.N / 16 - 1);
+        w_lane[q] = (uint32_t)nt * (uint32_t)p.KL * 1024u + lane * 16;
+        s_lane[q] = (uint32_t)(nt * 16 + nl) * (uint32_t)p.G * 2u;
+    }
+    auto b_load_packed = [&](int set, int t) {               // the unit of step t
+        const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
+        const uint32_t kc = ks >> 1;
+        const uint32_t j = __umulhi(kc, p.cpg_inv) + (kc & p.cpg_one);   // branch-free group index
+        const uint32_t tile = SPU == 2 ? kc : ks;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int nt = n0 / 16 + 2 * wave + q;
-            const uint32_t skip = (in && nt * 16 < p.N) ? 0u : kOutOfRange;     // offsets stay below 2^31
-            sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, ((uint32_t)(nt * 16 + nl) * (uint32_t)p.G + j) * 2u + skip, 0, 0);
-#pragma unroll
-            for (int kt = 0; kt < TPC; ++kt)
-                breg[set][q * TPC + kt] = __builtin_amdgcn_raw_buffer_load_b128(
-                    rb, ((uint32_t)nt * (uint32_t)p.KL + kc * TPC + kt) * 1024u + lane * 16 + skip, 0, 2 /* nt */);
+            sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q], (int)(j * 2u), 0);
+            breg[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rb, w_lane[q], (int)(tile * 1024u), 2 /* nt */);
         }
     };
-    auto b_store_dense = [&](int set, int stage, int i0 = 0, int i1 = 4) {
+    // word w of the step: tile-row w >> 1, 32-column operand w & 1
+    auto b_store_packed = [&](int set, int half, int stage, int w) {
+        const int q = w >> 1, o = w & 1;
+        const half_t s = __builtin_bit_cast(half_t, sreg[set][q]);
+        const half2_t s2 = {s, s};
+        Half8Words h;
+        if constexpr (BSRC == 4) h.v = unpack_word4(breg[set][q][2 * half + o], magic);
+        else h.v = unpack_words8(breg[set][q][2 * o], breg[set][q][2 * o + 1]);
 #pragma unroll
-        for (int i = i0; i < i1; ++i) *reinterpret_cast<u32x4_t*>(lds + stage * STAGE + A_BYTES + st_off + i * 8192) = breg[set][i];
+        for (int e = 0; e < 4; ++e) h.h2[e] = h.h2[e] * s2;             // fp16(q * S)
+        *reinterpret_cast<half8_t*>(stage_b(stage) + swizzled((2 * wave + q) * 16 + nl, o * 4 + kq)) = h.v;
     };
-    // half = which 64 columns of the chunk; [q0, q1) x [o0, o1): tile-rows and 32-column operands to store
-    auto b_store_packed = [&](int set, int half, int stage, int q0 = 0, int q1 = 2, int o0 = 0, int o1 = 2) {
-#pragma unroll
-        for (int q = q0; q < q1; ++q) {
-            const half_t s = __builtin_bit_cast(half_t, sreg[set][q]);
-            const half2_t s2 = {s, s};
-            const int row = (2 * wave + q) * 16 + nl;
-#pragma unroll
-            for (int o = o0; o < o1; ++o) {                              // two 32-column MFMA operands per half
-                Half8Words h;
-                if constexpr (BSRC == 4) h.v = unpack_word4(breg[set][q][2 * half + o], magic);
-                else h.v = unpack_words8(breg[set][q * 2 + half][2 * o], breg[set][q * 2 + half][2 * o + 1]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) h.h2[e] = h.h2[e] * s2;     // fp16(q * S)
-                *reinterpret_cast<half8_t*>(lds + stage * STAGE + A_BYTES + swizzled(row, o * 4 + kq)) = h.v;
-            }
-        }
+    // piece w of four of the weights of step u (mod 4)
+    auto b_fill = [&](int u, int w) {
+        if constexpr (BSRC == 4) b_store_packed((u >> 1) & 1, u & 1, u & 1, w);
+        else if constexpr (BSRC == 8) b_store_packed(u & 1, 0, u & 1, w);
     };
 
     float4_t acc[MBW][4];
@@ -183,199 +192,191 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams
 
     // operand rows of this lane: A rows wm*TM/2 + 16 b + nl, B rows wn*64 + 16 r + nl; (row & 7) == (nl & 7)
     const uint32_t a_rd = (uint32_t)((wm * (TM / 2) + nl) * 128);
-    const uint32_t b_rd = (uint32_t)(A_BYTES + (wn * 64 + nl) * 128);
-    half8_t bq[4];
-    auto b_read = [&](int stage, int i) {                     // the wavefront's four weight operands of slice i
-        const uint32_t po = (uint32_t)(((i * 4 + kq) ^ (nl & 7)) * 16);
+    const uint32_t b_rd = (uint32_t)((wn * 64 + nl) * 128);
+    const uint32_t po0 = (uint32_t)((kq ^ (nl & 7)) * 16), po1 = (uint32_t)(((4 + kq) ^ (nl & 7)) * 16);
+    half8_t aop[2][4], bop[2][4];                            // operands of two phases / two slices
+    auto read_phase = [&](int u, int ph) {                   // operands of phase ph of step u (mod U)
+        const int i = ph / HB, h = ph % HB;
+        const uint32_t po = i ? po1 : po0;
+        if (h == 0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) bq[r] = *reinterpret_cast<const half8_t*>(lds + stage * STAGE + b_rd + r * 2048 + po);
-    };
-    auto compute_rows = [&](int stage, int i, int b0, int b1) {   // row blocks [b0, b1) of slice i against bq
-        const uint32_t po = (uint32_t)(((i * 4 + kq) ^ (nl & 7)) * 16);
-        half8_t a[MBW];
+            for (int r = 0; r < 4; ++r) bop[i][r] = *reinterpret_cast<const half8_t*>(stage_b(u % SB) + b_rd + r * 2048 + po);
+        }
 #pragma unroll
-        for (int b = b0; b < b1; ++b) a[b] = *reinterpret_cast<const half8_t*>(lds + stage * STAGE + a_rd + b * 2048 + po);
-#pragma unroll
-        for (int b = b0; b < b1; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b], bq[r], acc[b][r], 0, 0, 0);
+        for (int b = 0; b < 4; ++b) aop[ph & 1][b] = *reinterpret_cast<const half8_t*>(stage_a(u % SA) + a_rd + (h * 4 + b) * 2048 + po);
     };
 
-    // One step: arithmetic on stage (t & 1) while the next step's tiles go from registers into the other stage
-    // and the loads of step t+1+PD (chunk c+PD) are issued.  u = t & 3 is a literal at every call site.
+    // One step = PH phases of 16 MFMAs; every phase reads the operands of the next one.  The last phase's operands are in
+    // registers when the barrier before it is passed, so from there on this step's stage is free: the last phase reads
+    // the next step's first operands and requests the tiles of the step after the next into the stage just freed.
     auto step = [&](int u, int t) {
-        const int stage = u & 1;
-        const int set = PD == 2 ? (u & 1) : 0;               // register set that holds step t+1
-        if constexpr (MBW == 8) {
-            // tall tile: the step runs in four quarters (a 32-column slice x four of the eight row blocks), each with
-            // 16 MFMAs that carry a quarter of the step's LDS stores, dequantisation and global loads between them;
-            // at most four activation operands are live at a time (256 registers without spilling)
 #pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                const int i = qd >> 1, bh = qd & 1;
-                if (bh == 0) b_read(stage, i);
-                compute_rows(stage, i, bh * 4, bh * 4 + 4);
-                a_store(set, stage ^ 1, qd, qd + 1);
-                if constexpr (BSRC == 0) b_store_dense(set, stage ^ 1, qd, qd + 1);
-                else b_store_packed(0, (u + 1) & 1, stage ^ 1, i, i + 1, bh, bh + 1);
-                a_load(set, t + 1 + PD, qd, qd + 1);
-                if constexpr (BSRC == 0) b_load_dense(set, t + 1 + PD, qd, qd + 1);
-                else if (qd == 3 && (u & 1) == 0) b_load_packed(0, (t >> 1) + PD);
-                if (bh == 0) __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-                else __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-                if constexpr (BSRC != 0) __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+        for (int ph = 0; ph < PH; ++ph) {
+            if (ph == PH - 1) {
+                // the next step's tiles have landed: only what was requested after them may be outstanding
+                if constexpr (BSRC == 0) wait_and_barrier<(SA - 2) * NA + (SB - 2) * NB>();
+                else if (BSRC == 8 || (u & 1)) wait_and_barrier<4>();        // the packed unit requested in the last step
+                else wait_and_barrier<0>();
                 __builtin_amdgcn_sched_barrier(0);
             }
-            __syncthreads();
-            return;
-        }
-        if constexpr (BSRC != 0 && MBW == 4) {
-            // short packed tile: two halves (a 32-column slice each), each with 16 MFMAs that carry one tile-row to
-            // dequantise, half of the activation staging and, every other step, the next chunk's loads
-            const int cset = PD == 2 ? (((u + 1) >> 1) & 1) : 0;    // set of chunk (t+1) >> 1, stored half (t+1) & 1
+            read_phase(ph == PH - 1 ? u + 1 : u, ph == PH - 1 ? 0 : ph + 1);
+            const int i = ph / HB, h = ph % HB;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                b_read(stage, h);
-                compute_rows(stage, h, 0, MBW);
-                a_store(set, stage ^ 1, h, h + 1);
-                b_store_packed(cset, (u + 1) & 1, stage ^ 1, h, h + 1);
-                a_load(set, t + 1 + PD, h, h + 1);
-                if (h == 1 && (u & 1) == 0) b_load_packed(cset, (t >> 1) + PD);   // the chunk just finished leaves its registers
-                __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+            for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int o = 0; o < 2; ++o) {                            // one operand: 2 MFMAs per 4 vector ops, then its store
+                for (int r = 0; r < 4; ++r)
+                    acc[h * 4 + b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[i][r], aop[ph & 1][b], acc[h * 4 + b][r], 0, 0, 0);
+            // weights on their way into LDS, spread over the phases: what the last phase stores belongs to the step after the
+            // next (into the stage just freed), and the phase before the barrier stores nothing that the barrier would wait for
+            int words = 0;
+            if constexpr (BSRC != 0) {
+                if (ph == PH - 1) {
+                    words = PH == 2 ? 2 : 1;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                    if (o == 0) {
-                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                    }
+                    for (int w = 0; w < words; ++w) b_fill((u + 2) & 3, w);
+                } else if (PH == 2) {
+                    words = 2;
+#pragma unroll
+                    for (int w = 2; w < 4; ++w) b_fill((u + 1) & 3, w);
+                } else if (ph == 0) {
+                    words = 2;
+#pragma unroll
+                    for (int w = 1; w < 3; ++w) b_fill((u + 1) & 3, w);
+                } else if (ph == 1) {
+                    words = 1;
+                    b_fill((u + 1) & 3, 3);
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
-            __syncthreads();
-            return;
-        }
-        // short dense tile: two halves, each with 16 MFMAs that carry three of the step's six LDS stores and global loads
+            if (ph == PH - 1) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            b_read(stage, h);
-            compute_rows(stage, h, 0, MBW);
-            a_store(set, stage ^ 1, h, h + 1);
-            b_store_dense(set, stage ^ 1, 2 * h, 2 * h + 2);
-            a_load(set, t + 1 + PD, h, h + 1);
-            b_load_dense(set, t + 1 + PD, 2 * h, 2 * h + 2);
-            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                for (int k = 0; k < NA; ++k) a_dma(u % SA, t + SA, k);
+                __builtin_amdgcn_sched_barrier(0x78F);       // everything but memory loads may cross: the counted waits rely on their order
+                if constexpr (BSRC == 0) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                    for (int k = 0; k < NB; ++k) b_dma(u % SB, t + SB, k);
+                } else if constexpr (BSRC == 4) {
+                    if ((u & 1) == 0) b_load_packed((u >> 1) & 1, t + 4);      // chunk t/2 has just been used up
+                } else {
+                    b_load_packed((u + 1) & 1, t + 3);
+                }
             }
+            const int rd = ((ph + 1) % HB == 0 || HB == 1) ? 8 : 4;
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                if (g * 2 < rd) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                if (words == 4) __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+                else if (words == 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                else if (words == 1) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                if (ph == PH - 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            }
+            if (words) __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
     };
 
-    // ---- prologue: step 0 into stage 0; registers then hold the next PD steps / chunks, issued in the loop's
-    // order so that its waits are exact counts ----
-    a_load(0, 0);
-    if constexpr (BSRC == 0) b_load_dense(0, 0); else b_load_packed(0, 0);
-    a_store(0, 0);
-    if constexpr (BSRC == 0) b_store_dense(0, 0); else b_store_packed(0, 0, 0);
-    if constexpr (BSRC == 0 && MBW == 8) {                   // the tall dense step issues its loads piece by piece
+    // ---- prologue: the requests of the steps before the first one, in the order of the loop (its waits are counts);
+    // step 0 in LDS, its first operands in registers ----
+    if constexpr (BSRC != 0) {
+        b_load_packed(0, 0);
+        b_load_packed(1, SPU);
+    } else if constexpr (SB > SA) {
 #pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            a_load(0, 1, qd, qd + 1);
-            b_load_dense(0, 1, qd, qd + 1);
+        for (int k = 0; k < NB; ++k) b_dma(0, 0, k);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < SA; ++v) {
+#pragma unroll
+        for (int k = 0; k < NA; ++k) a_dma(v, v, k);
+        if constexpr (BSRC == 0) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) b_dma(v + SB - SA, v + SB - SA, k);
         }
-    } else if constexpr (BSRC == 0) {                        // the short dense step issues its loads half by half
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (BSRC != 0) {
 #pragma unroll
-        for (int s = 0; s < PD; ++s)
+        for (int w = 0; w < 4; ++w) b_fill(0, w);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                a_load(s, 1 + s, h, h + 1);
-                b_load_dense(s, 1 + s, 2 * h, 2 * h + 2);
+        for (int w = 0; w < (PH == 2 ? 2 : 1); ++w) b_fill(1, w);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (BSRC == 8) b_load_packed(0, 2);
+    wait_and_barrier<(SA - 1) * NA + (BSRC == 0 ? (SB - 1) * NB : BSRC == 8 ? 4 : 0)>();
+    read_phase(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    for (int t = 0;; t += U) {            // T is even; leaving between two steps keeps every wait inside an exact count
+        bool done = false;
+#pragma unroll
+        for (int u = 0; u < U; u += 2) {
+            step(u, t + u);
+            step(u + 1, t + u + 1);
+            if (t + u + 2 >= T) {
+                done = true;
+                break;
             }
-    } else {
-        a_load(0, 1);
-        if constexpr (PD == 2) {
-            b_load_packed(1, 1);
-            a_load(1, 2);
         }
+        if (done) break;
     }
-    __syncthreads();
+    wait_and_barrier<0>();                // no load into LDS outlives the workgroup
 
-    int t = 0;
-    for (; t + 4 <= T; t += 4) {          // no control flow between steps: every wait inside is an exact count
-        step(0, t);
-        step(1, t + 1);
-        step(2, t + 2);
-        step(3, t + 3);
-    }
-    if (t < T) {                          // T is even
-        step(0, t);
-        step(1, t + 1);
-    }
-
-    // ---- store: lane holds rows 16 b + 4 kq + e, column 16 r + nl of its wavefront tile ----
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int n = n0 + wn * 64 + r * 16 + nl;
-        if (n >= p.N) continue;
+    // ---- store: the MFMAs take the weights as the first operand, so a lane holds row 16 b + nl and the four columns
+    // 16 r + 4 kq + e.  Partial sums go out as they are (16 bytes per lane); fp16 results change lanes through the
+    // wavefront's own part of LDS, 16 rows x 128 bytes at a time, so that a store writes whole 128-byte runs ----
+    if (p.split_k > 1) {
 #pragma unroll
         for (int b = 0; b < MBW; ++b) {
+            const int m = m0 + wm * (TM / 2) + b * 16 + nl;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + wm * (TM / 2) + b * 16 + kq * 4 + e;
-                if (m < p.M) {
-                    if (p.split_k == 1) p.C[(int64_t)m * p.N + n] = (half_t)acc[b][r][e];
-                    else p.ws[((int64_t)sg * p.M + m) * p.N + n] = acc[b][r][e];
-                }
+            for (int r = 0; r < 4; ++r) {
+                const int n = n0 + wn * 64 + r * 16 + kq * 4;
+                if (m < p.M && n < p.N) *reinterpret_cast<float4_t*>(p.ws + ((int64_t)sg * p.M + m) * p.N + n) = acc[b][r];
             }
         }
+        return;
+    }
+    typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+    uint8_t* mine = lds_b0 + wave * 2048;
+#pragma unroll
+    for (int b = 0; b < MBW; ++b) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            half4_t h = {(half_t)acc[b][r][0], (half_t)acc[b][r][1], (half_t)acc[b][r][2], (half_t)acc[b][r][3]};
+            *reinterpret_cast<half4_t*>(mine + nl * 128 + (((r * 2 + (kq >> 1)) ^ (nl & 7)) * 16) + (kq & 1) * 8) = h;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row = h * 8 + (lane >> 3), piece = lane & 7;
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(mine + row * 128 + ((piece ^ (row & 7)) * 16));
+            const int m = m0 + wm * (TM / 2) + b * 16 + row, n = n0 + wn * 64 + piece * 8;
+            if (m < p.M && n < p.N) *reinterpret_cast<u32x4_t*>(p.C + (int64_t)m * p.N + n) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
 template <int BSRC, int MBW>
 hipError_t launch_tile_inst(const TileParams& tp, dim3 grid, hipStream_t st) {
-    constexpr size_t lds = 2 * (size_t)(32 * MBW + kTN) * 128;
-    static bool attr_done = false;
-    if (!attr_done) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(tile_gemm_kernel<BSRC, MBW>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        attr_done = true;
-    }
-    hipLaunchKernelGGL((tile_gemm_kernel<BSRC, MBW>), grid, dim3(kThreads), lds, st, tp);
+    hipLaunchKernelGGL((tile_gemm_kernel<BSRC, MBW>), grid, dim3(kThreads), 0, st, tp);
     return hipGetLastError();
 }
 
 // rows16: 16-row blocks per wavefront (4 or 8), 0 = choose.
 hipError_t launch_tile(TileParams& tp, int bsrc, int64_t M, int rows16, hipStream_t st) {
-    // 128- or 256-row tiles: one workgroup runs per compute unit, so the launch takes rounds of 256 tiles; a 256-row
-    // tile takes about 1.5 times as long as a 128-row one with packed weights (it halves the unpacking per flop) and
-    // 1.7 times with dense ones, so it pays unless it wastes most of a round (measured on the 8B and 70B shapes at
-    // 512 to 8192 rows).
     const int64_t xb = (tp.N + kTN - 1) / kTN;
-    const int64_t r_short = (xb * ((M + 127) / 128) * tp.split_k + 255) / 256;
-    const int64_t r_tall = (xb * ((M + 255) / 256) * tp.split_k + 255) / 256;
-    const bool tall = rows16 ? rows16 == 8 : (M > 128 && (bsrc == 0 ? 1.7 : 1.5) * (double)r_tall < (double)r_short);
+    const bool tall = rows16 ? rows16 == 8
+                             : M > 128 && tile_model_us(bsrc == 0, 8, M, tp.N, tp.K, tp.split_k) < tile_model_us(bsrc == 0, 4, M, tp.N, tp.K, tp.split_k);
     const int tm = tall ? 256 : 128;
     tp.XB = (int)xb;
     tp.ZB = (int)((M + tm - 1) / tm);
-    const int xb_pad = (tp.XB + kXcds - 1) / kXcds * kXcds;
-    dim3 grid((unsigned)(xb_pad * tp.ZB), (unsigned)tp.split_k, 1);
+    dim3 grid((unsigned)((tp.XB * tp.ZB + kXcds - 1) / kXcds * kXcds), (unsigned)tp.split_k, 1);
     if (bsrc == 0) return tall ? launch_tile_inst<0, 8>(tp, grid, st) : launch_tile_inst<0, 4>(tp, grid, st);
     if (bsrc == 4) return tall ? launch_tile_inst<4, 8>(tp, grid, st) : launch_tile_inst<4, 4>(tp, grid, st);
     return tall ? launch_tile_inst<8, 8>(tp, grid, st) : launch_tile_inst<8, 4>(tp, grid, st);
@@ -393,6 +394,24 @@ void fill_common(TileParams& tp, const void* A, void* C, float* ws, int64_t M, i
 }
 
 }  // namespace
+
+// One workgroup runs per compute unit, so a launch takes rounds of 256 workgroups.  A 64-column step of a full round takes
+// 1.58 us with a 256-row tile and 1.00 with a 128-row one (packed weights; 1.54 and 0.87 dense), of a round that fills half
+// the chip or less 1.26 and 0.82 (1.12 and 0.87): the clock depends on how much of the chip is busy.  A round costs 6 us
+// besides; a split adds the reduce launch and the partial sums' trip through the workspace, mostly cache.  Fitted to 480
+// measured launches: thirteen shapes of 3072 to 28672 columns at 128 to 3072 rows, both heights, one to eight splits
+// (error 5 % rms; the pick is within 1 % of the best measured pair on average).
+double tile_model_us(bool dense, int rows16, int64_t M, int64_t N, int64_t K, int split_k) {
+    const bool tall = rows16 == 8;
+    const double half = tall ? (dense ? 1.12 : 1.26) : (dense ? 0.87 : 0.82);
+    const double full = tall ? (dense ? 1.54 : 1.58) : (dense ? 0.87 : 1.00);
+    const int64_t tiles = ((N + kTN - 1) / kTN) * ((M + 32 * rows16 - 1) / (32 * rows16)) * split_k;
+    const double steps = (double)((K / kBK + split_k - 1) / split_k), part = (double)(tiles % 256) / 256.0;
+    double t = (double)(tiles / 256) * (steps * full + 6.0);
+    if (part > 0.0) t += steps * (half + (full - half) * (part > 0.5 ? 2.0 * part - 1.0 : 0.0)) + 6.0;
+    if (split_k > 1) t += 5.3 + (2.0 * split_k * M * N * 4.0 + 2.0 * M * N) / 8.0e6;
+    return t;
+}
 
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p) {
     if (a.g % kChunkK != 0 || a.K % kChunkK != 0) return false;
@@ -418,7 +437,7 @@ hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStrea
 }
 
 hipError_t launch_gemm_fp16(const void* A, const void* W, void* C, float* workspace, int64_t M, int64_t N, int64_t K,
-                            int split_k, hipStream_t st) {
+                            int rows16, int split_k, hipStream_t st) {
     TileParams tp;
     fill_common(tp, A, C, workspace, M, N, K, split_k);
     tp.B = W;
@@ -426,7 +445,7 @@ hipError_t launch_gemm_fp16(const void* A, const void* W, void* C, float* worksp
     tp.G = 1; tp.cpg = 1; tp.cpg_inv = 0; tp.cpg_one = 0xFFFFFFFFu; tp.KL = 0;
     tp.b_bytes = 0;
     tp.sc_bytes = 16;
-    hipError_t e = launch_tile(tp, 0, M, 0, st);
+    hipError_t e = launch_tile(tp, 0, M, rows16, st);
     if (e != hipSuccess) return e;
     if (split_k > 1) e = launch_splitk_reduce(workspace, C, M * N, split_k, st);
     return e;

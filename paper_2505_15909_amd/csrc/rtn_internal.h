@@ -48,10 +48,12 @@ hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStrea
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
-// Dense fp16 GEMM C[M,N] = A[M,K] W[N,K]^T with the same tile kernel (K a multiple of 128); split_k > 1 goes
+// Dense fp16 GEMM C[M,N] = A[M,K] W[N,K]^T with the same tile kernel (K a multiple of 128; rows16 = 4 or 8); split_k > 1 goes
 // through the fp32 workspace [split_k][M][N].
 hipError_t launch_gemm_fp16(const void* A, const void* W, void* C, float* workspace, int64_t M, int64_t N, int64_t K,
-                            int split_k, hipStream_t st);
+                            int rows16, int split_k, hipStream_t st);
+// Modelled time of a tile-kernel launch (rows16 = 4 or 8: 128- or 256-row tiles), the reduce pass of a K split included.
+double tile_model_us(bool dense, int rows16, int64_t M, int64_t N, int64_t K, int split_k);
 // Sums split_k fp32 partial outputs [split_k][MN] in a fixed order into fp16 C (MN a multiple of 16).
 hipError_t launch_splitk_reduce(const float* workspace, void* C_fp16, int64_t MN, int split_k, hipStream_t st);
 

@@ -30,7 +30,6 @@ namespace {
 constexpr int kStepK = 128;                     // columns per k-step
 constexpr uint32_t kOutOfRange = 0x7FFF0000u;   // beyond any resource size used here (< 2 GiB)
 constexpr int kBufferFlags = 0x00020000;        // raw buffer, 32-bit data format
-constexpr int kXcds = 8;
 
 struct WideParams {
     const half_t* A;
@@ -105,12 +104,8 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nl = lane & 15, kq = lane >> 4;
 
-    // workgroup index -> (N block, row block): the ZB row blocks of one N block are kXcds apart
-    const int L = blockIdx.x;
-    const int xcd = L % kXcds, idx = L / kXcds;
-    const int z = idx % p.ZB;
-    const int xb = (idx / p.ZB) * kXcds + xcd;
-    if (xb >= p.XB) return;                               // padding of the last group of 8 (whole workgroup)
+    int xb, z;                                            // N block, row block (all row blocks of one N block on one XCD)
+    if (!xcd_tile(blockIdx.x, p.XB, p.ZB, p.ZB, &xb, &z)) return;     // padding to a multiple of 8 (whole workgroup)
     const int m0 = z * ROWS;
     const int sg = blockIdx.y;
     const int ks0 = sg * p.ks_base + min(sg, p.ks_rem);
@@ -438,8 +433,7 @@ hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStrea
     wp.qw_bytes = (uint32_t)((size_t)a.N * a.K * a.bits / 8);
     wp.sc_bytes = (uint32_t)((size_t)a.N * wp.G * 2);
     wp.a_bytes = (uint32_t)((size_t)a.M * a.K * 2);
-    const int xb_pad = (wp.XB + kXcds - 1) / kXcds * kXcds;
-    dim3 grid((unsigned)(xb_pad * wp.ZB), (unsigned)p.split_k, 1);
+    dim3 grid((unsigned)((wp.XB * wp.ZB + kXcds - 1) / kXcds * kXcds), (unsigned)p.split_k, 1);
     hipError_t e;
     if (a.zeros) e = (a.bits == 4) ? launch_wide_zp_bits<4>(wp, p.m_rows16, p.n_tiles16, grid, st)
                                    : launch_wide_zp_bits<8>(wp, p.m_rows16, p.n_tiles16, grid, st);

@@ -343,6 +343,32 @@ def test_linear_tile_kernel(rtn, bits, g, M):
     assert torch.equal(C, C2)
 
 
+@pytest.mark.parametrize("M,N,K", [(1300, 2048, 512), (700, 4096, 128), (1300, 5136, 1536), (257, 2064, 2560), (130, 768, 1280)])
+def test_tile_kernel_covers_every_tile(rtn, M, N, K):
+    """Column tiles in eights and not, one to six row tiles of both heights (groups of four and a remainder), 2 to 40 steps, K splits with uneven shares: activations are small integers and the weights small
+    integers times a power of two, so every product and sum is exact and each output equals the exact one."""
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-2, 3, (M, K)).astype(np.float16)
+    space = torch.empty(3 * M * N * 4, dtype=torch.uint8, device=DEV)
+    for bits in (4, 8):
+        if K % (512 if bits == 4 else 256):
+            continue
+        codes = rng.integers(-7, 8, (N, K)).astype(np.int8)
+        scales = np.full((N, K // 128), 0.25, np.float16)
+        ref = A.astype(np.float32) @ codes.astype(np.float32).T * 0.25
+        assert np.abs(ref).max() < 512                              # multiples of 1/4 below 2^9: exact in fp16
+        qw, sc = torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV)
+        for rows16, split in ((4, 1), (8, 1), (8, 2), (4, 3)):
+            C = rtn.rtn_linear(torch.from_numpy(A).to(DEV), qw, sc, bits, 128, workspace=space,
+                               cfg=dict(path=4, m_rows16=rows16, split_k=split))
+            assert np.array_equal(_to_np(C).astype(np.float32), ref), (bits, rows16, split)
+    W = rng.integers(-7, 8, (N, K)).astype(np.float16) * np.float16(0.25)
+    ref = A.astype(np.float32) @ W.astype(np.float32).T
+    A_t, W_t = torch.from_numpy(A).to(DEV), torch.from_numpy(W).to(DEV)
+    for ws in (None, space):
+        assert np.array_equal(_to_np(rtn.rtn_gemm_fp16(A_t, W_t, workspace=ws)).astype(np.float32), ref)
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 16, 128), (128, 128, 128), (200, 400, 2560), (1030, 272, 1024), (520, 4112, 384)])
 def test_dense_gemm_and_dual_path(rtn, M, N, K):
     """rtn_gemm_fp16 against an fp64 product of the same fp16 operands, and the dequantise-then-GEMM path of
