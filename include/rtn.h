@@ -227,7 +227,10 @@ typedef struct {
  * 8-bit modules): runs the n_mods modules in order on `stream`, each with the kernel
  * instantiation of its own (bits, group_size).  The workspace must cover the largest
  * rtn_workspace_nbytes() of the modules; it is reused, which is safe because the launches
- * are ordered on one stream.  Stops at, and returns, the first error. */
+ * are ordered on one stream.  Stops at, and returns, the first error.
+ * Small layers (up to 8 rows, one precision and group size, under 256 MB of weights) whose outputs overlap no operand and
+ * no output of another module go out as one launch, with a plan of its own: the same result as in order, up to the
+ * summation order of a single call. */
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace,
                              size_t workspace_nbytes, void* stream);
 

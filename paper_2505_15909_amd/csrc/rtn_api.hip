@@ -563,7 +563,9 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     const size_t lds_limit = (size_t)device_max_lds();
     LinearPlan p;
     p.n_tiles16 = 1;
-    if (!cfg && wide_small_groups(a.M, a.g)) wide_plan(a.M, a.N, a.K, a.bits, a.g, &p);
+    const bool whole = cfg && cfg->path && cfg->prefetch && cfg->waves_n && cfg->waves_k && cfg->split_k && cfg->m_rows16 && cfg->n_tiles16;
+    if (whole) p.m_blocks = 1;                                  // every field comes from the caller
+    else if (!cfg && wide_small_groups(a.M, a.g)) wide_plan(a.M, a.N, a.K, a.bits, a.g, &p);
     else p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0);
     if (cfg) {
         if (cfg->path) p.path = cfg->path;
@@ -944,10 +946,101 @@ rtn_status rtn_linear_dense(const void* dev_A, int64_t M, const void* dev_qweigh
     return rtn_gemm_fp16(dev_A, M, dev_W_tmp, N, K, dev_C, dev_workspace, workspace_nbytes, stream);
 }
 
+// Checks of one module that need no plan, and its kernel arguments.
+static rtn_status module_args(const rtn_module& m, void* dev_workspace, LinearArgs* a) {
+    if (!m.dev_A || !m.dev_qweight || !m.dev_scales || !m.dev_C) return RTN_ERR_NULL;
+    int64_t g;
+    rtn_status st = check_problem(m.N, m.K, m.bits, m.group_size, &g);
+    if (st != RTN_OK) return st;
+    if (m.M <= 0 || m.M > (1 << 20)) return RTN_ERR_SHAPE;
+    if (!aligned16(m.dev_A) || !aligned16(m.dev_qweight) || !aligned16(m.dev_scales) || !aligned16(m.dev_C)) return RTN_ERR_ALIGN;
+    a->A = m.dev_A; a->qweight = m.dev_qweight; a->scales = m.dev_scales; a->C = m.dev_C;
+    a->workspace = static_cast<float*>(dev_workspace);
+    a->M = m.M; a->N = m.N; a->K = m.K; a->g = g; a->bits = m.bits;
+    return RTN_OK;
+}
+
+// Whether running the modules in any order, or at once, gives what running them in order gives: no output overlaps an
+// operand or an output of another module.
+static bool modules_independent(const LinearArgs* a, int n) {
+    struct Range { uintptr_t lo, hi; };
+    auto range = [](const void* p, size_t bytes) { const uintptr_t lo = reinterpret_cast<uintptr_t>(p); return Range{lo, lo + bytes}; };
+    auto meet = [](const Range& x, const Range& y) { return x.lo < y.hi && y.lo < x.hi; };
+    for (int i = 0; i < n; ++i) {
+        const Range out = range(a[i].C, (size_t)a[i].M * a[i].N * 2);
+        for (int j = 0; j < n; ++j) {
+            if (j == i) continue;
+            if (meet(out, range(a[j].A, (size_t)a[j].M * a[j].K * 2)) || meet(out, range(a[j].C, (size_t)a[j].M * a[j].N * 2)) ||
+                meet(out, range(a[j].qweight, (size_t)a[j].N * a[j].K * a[j].bits / 8)) ||
+                meet(out, range(a[j].scales, (size_t)a[j].N * (a[j].K / a[j].g) * 2)))
+                return false;
+        }
+    }
+    return true;
+}
+
+// Independent modules of one precision and group size in one launch, up to eight rows and 256 MB of weights: a launch costs
+// 4-5 us of start, ramp and drain around its weight stream, which one grid over all modules pays once.  Plan of the merged
+// modules: a wavefront takes so many k-chunks that there are about 3456 of them in all (6912 from five rows), in
+// workgroups of up to 16 (13) wavefronts, fewer where that leaves compute units without one; two chunks in flight, one at
+// 4 bit from five rows.  From sweeps over 4-16 wavefronts per workgroup and 2-28 chunks per wavefront.  Graph replay over
+// rotating copies, single launches against one: 8B layer int4 30.8 -> 22.5 us at one row, 32.8 -> 23.5 at four, 35.5 ->
+// 30.9 at eight; int8 44.4 -> 37.5, 47.1 -> 38.4, 49.5 -> 43.0; four 2048 x 2048 modules 12.7 -> 4.6, two of 1024 x 4096
+// 7.6 -> 4.3 at one row.  Beyond the line the modules' own plans are better: from nine rows the staged activations want
+// their shapes (8B int4 at 16: 38.5 us against 38.9 at best), 70B and 405B modules lose more by a common shape than they
+// gain (82 -> 86 and 268 -> 297 at two rows), and so do slices that do not fit the LDS at once (28672 columns at four
+// rows, int8: 30 -> 36).
+static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbytes, LinearPlan* plans) {
+    int64_t rows = 0;
+    size_t bytes = 0;
+    for (int i = 0; i < n; ++i) {
+        rows = std::max(rows, a[i].M);
+        bytes += (size_t)a[i].N * a[i].K * a[i].bits / 8;
+    }
+    if (rows > 8 || bytes >= ((size_t)256 << 20)) return false;
+    for (int i = 0; i < n; ++i)
+        if ((size_t)a[i].M * a[i].K * 2 > (size_t)140 << 10) return false;
+    auto same_class = [](const LinearArgs& x, const LinearArgs& y) {       // one kernel instantiation: bits and groups per chunk
+        const int64_t ck = chunk_k(x.bits);
+        return x.bits == y.bits && (x.g >= ck ? 1 : ck / x.g) == (y.g >= ck ? 1 : ck / y.g);
+    };
+    int64_t steps = 0, waves = 0;
+    for (int i = 0; i < n; ++i) steps += a[i].N / 16 * (a[i].K / chunk_k(a[i].bits));
+    const double chunks = std::max(1.0, (double)steps / (rows <= 4 ? 3456.0 : 6912.0));
+    auto waves_k = [&](const LinearArgs& x) {
+        return (int)std::max(1.0, std::min(16.0, std::floor((double)(x.K / chunk_k(x.bits)) / chunks + 0.5)));
+    };
+    for (int i = 0; i < n; ++i) waves += a[i].N / 16 * waves_k(a[i]);
+    const int64_t width = rows <= 4 ? std::min<int64_t>(16, std::max<int64_t>(1, waves / 216)) : std::min<int64_t>(13, std::max<int64_t>(1, waves / 256));
+    for (int i = 0; i < n; ++i) {
+        if (!same_class(a[0], a[i])) return false;
+        // the module's own plan: its errors (a workspace too small) are those of the call in order
+        if (resolve_plan(a[i], nullptr, workspace_nbytes, &plans[i]) != RTN_OK) return false;
+        rtn_linear_cfg cfg;
+        cfg.path = 1; cfg.prefetch = chunks >= 2 && (rows <= 4 || a[i].bits == 8) ? 2 : 1;
+        cfg.waves_k = waves_k(a[i]);
+        cfg.waves_n = (int)std::max<int64_t>(1, std::min<int64_t>(width / cfg.waves_k, a[i].N / 16));
+        cfg.split_k = 1; cfg.m_rows16 = 1; cfg.n_tiles16 = 1;
+        if (resolve_plan(a[i], &cfg, workspace_nbytes, &plans[i]) != RTN_OK) return false;
+    }
+    return true;
+}
+
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
                              void* stream) {
     if (!mods) return RTN_ERR_NULL;
     if (n_mods <= 0) return RTN_ERR_SHAPE;
+    constexpr int kMerge = 16;
+    if (n_mods > 1 && n_mods <= kMerge && aligned16(dev_workspace)) {
+        LinearArgs args[kMerge];
+        LinearPlan plans[kMerge];
+        bool ok = true;
+        for (int i = 0; i < n_mods && ok; ++i) ok = mods[i].M <= 8 && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
+        if (ok && modules_independent(args, n_mods) && merged_layer_plans(args, n_mods, workspace_nbytes, plans)) {
+            hipError_t e = rtn::launch_linear_grouped(args, plans, n_mods, static_cast<hipStream_t>(stream));
+            return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
+        }
+    }
     for (int i = 0; i < n_mods; ++i) {
         const rtn_module& m = mods[i];
         rtn_status st = rtn_linear(m.dev_A, m.M, m.dev_qweight, m.dev_scales, m.N, m.K, m.bits, m.group_size,
@@ -1035,17 +1128,8 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
     int64_t steps_total = 0;                                   // of the modules the skinny kernel will serve
     for (int i = 0; i < n_mods; ++i) {
         const rtn_module& m = mods[i];
-        if (!m.dev_A || !m.dev_qweight || !m.dev_scales || !m.dev_C) return RTN_ERR_NULL;
-        int64_t g;
-        rtn_status st = check_problem(m.N, m.K, m.bits, m.group_size, &g);
+        const rtn_status st = module_args(m, dev_workspace, &args[i]);
         if (st != RTN_OK) return st;
-        if (m.M <= 0 || m.M > (1 << 20)) return RTN_ERR_SHAPE;
-        if (!aligned16(m.dev_A) || !aligned16(m.dev_qweight) || !aligned16(m.dev_scales) || !aligned16(m.dev_C))
-            return RTN_ERR_ALIGN;
-        LinearArgs& a = args[i];
-        a.A = m.dev_A; a.qweight = m.dev_qweight; a.scales = m.dev_scales; a.C = m.dev_C;
-        a.workspace = static_cast<float*>(dev_workspace);
-        a.M = m.M; a.N = m.N; a.K = m.K; a.g = g; a.bits = m.bits;
         if (m.M <= 16) steps_total += (m.N / 16) * (m.K / chunk_k(m.bits));
     }
     for (int i = 0; i < n_mods; ++i) {

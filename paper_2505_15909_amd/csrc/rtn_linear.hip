@@ -409,12 +409,20 @@ struct GroupedParams {
     SkinnyParams p[kMaxGroup];
 };
 
-template <int BITS, int NGC, bool MULTI>
+template <int BITS, int NGC, int NB, bool MULTI>
 __global__ __launch_bounds__(1024) void skinny_grouped_kernel(const GroupedParams gp) {
     const int b = blockIdx.x;
     int g = 0;
     for (int i = 1; i < gp.n; ++i) g = (b >= gp.first_block[i]) ? i : g;     // uniform
-    skinny_body<BITS, NGC, 1, MULTI, 1, false>(gp.p[g], b - gp.first_block[g], 0, 0);
+    const SkinnyParams& p = gp.p[g];
+    // requested together, as in the single launch
+    asm volatile("" :: "s"(p.A), "s"(p.qw), "s"(p.scales), "s"(p.M), "s"(p.K), "s"(p.G), "s"(p.NT), "s"(p.KL), "s"(p.WN), "s"(p.WK), "s"(p.wn_inv),
+                 "s"(p.kc_base), "s"(p.kc_rem), "s"(p.cpg_inv), "s"(p.per), "s"(p.sc), "s"(p.sc_inv), "s"(p.rpr_inv), "s"(p.stage_row_step),
+                 "s"(p.lds_stride), "s"(p.qw_bytes), "s"(p.sc_bytes), "s"(p.a_bytes));
+    // the launch has the wavefronts of its largest problem: the others leave at once (an ended wavefront is not waited
+    // for at a barrier)
+    if ((int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= p.WN * p.WK) return;
+    skinny_body<BITS, NGC, NB, MULTI, 1, false>(p, b - gp.first_block[g], 0, 0);
 }
 
 // Sums the split-K partials in a fixed order (s = 0, 1, 2, ...) and rounds once to fp16.  The partials of a batch of up
@@ -681,29 +689,29 @@ hipError_t launch_linear(const LinearArgs& a, const LinearPlan& p, hipStream_t s
     return e;
 }
 
-template <int BITS, int NGC>
+template <int BITS, int NGC, int NB>
 static void launch_grouped_inst(const GroupedParams& gp, bool multi, unsigned blocks, unsigned threads, size_t lds,
                                 hipStream_t st) {
     if constexpr (NGC <= Geom<BITS>::NM) {
         if (multi) {
-            allow_large_lds(skinny_grouped_kernel<BITS, NGC, true>);
-            hipLaunchKernelGGL((skinny_grouped_kernel<BITS, NGC, true>), dim3(blocks), dim3(threads), lds, st, gp);
+            allow_large_lds(skinny_grouped_kernel<BITS, NGC, NB, true>);
+            hipLaunchKernelGGL((skinny_grouped_kernel<BITS, NGC, NB, true>), dim3(blocks), dim3(threads), lds, st, gp);
         } else {
-            allow_large_lds(skinny_grouped_kernel<BITS, NGC, false>);
-            hipLaunchKernelGGL((skinny_grouped_kernel<BITS, NGC, false>), dim3(blocks), dim3(threads), lds, st, gp);
+            allow_large_lds(skinny_grouped_kernel<BITS, NGC, NB, false>);
+            hipLaunchKernelGGL((skinny_grouped_kernel<BITS, NGC, NB, false>), dim3(blocks), dim3(threads), lds, st, gp);
         }
     }
 }
 
-template <int BITS>
+template <int BITS, int NB>
 static hipError_t launch_grouped_bits(const GroupedParams& gp, int ngc, bool multi, unsigned blocks, unsigned threads,
                                       size_t lds, hipStream_t st) {
     switch (ngc) {
-        case 1: launch_grouped_inst<BITS, 1>(gp, multi, blocks, threads, lds, st); break;
-        case 2: launch_grouped_inst<BITS, 2>(gp, multi, blocks, threads, lds, st); break;
-        case 4: launch_grouped_inst<BITS, 4>(gp, multi, blocks, threads, lds, st); break;
-        case 8: launch_grouped_inst<BITS, 8>(gp, multi, blocks, threads, lds, st); break;
-        case 16: launch_grouped_inst<BITS, 16>(gp, multi, blocks, threads, lds, st); break;
+        case 1: launch_grouped_inst<BITS, 1, NB>(gp, multi, blocks, threads, lds, st); break;
+        case 2: launch_grouped_inst<BITS, 2, NB>(gp, multi, blocks, threads, lds, st); break;
+        case 4: launch_grouped_inst<BITS, 4, NB>(gp, multi, blocks, threads, lds, st); break;
+        case 8: launch_grouped_inst<BITS, 8, NB>(gp, multi, blocks, threads, lds, st); break;
+        case 16: launch_grouped_inst<BITS, 16, NB>(gp, multi, blocks, threads, lds, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -718,7 +726,7 @@ hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans
     std::vector<char> eligible((size_t)n, 0);
     for (int i = 0; i < n; ++i) {
         const LinearPlan& p = plans[i];
-        if (p.path != 1 || p.split_k != 1 || p.m_blocks != 1 || p.prefetch != 1 || p.m_rows16 != 1) continue;
+        if (p.path != 1 || p.split_k != 1 || p.m_blocks != 1 || p.prefetch > 2 || p.m_rows16 != 1) continue;
         prep[i] = prepare_skinny(args[i], p);
         eligible[i] = 1;
     }
@@ -734,19 +742,27 @@ hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans
         gp.n = 0;
         gp.first_block[0] = 0;
         size_t lds = 0;
+        unsigned threads = 0;
         for (int j = i; j < n && gp.n < kMaxGroup; ++j) {
             if (done[j] || !eligible[j] || args[j].bits != args[i].bits || prep[j].ngc != prep[i].ngc ||
-                prep[j].block.x != prep[i].block.x || prep[j].multi != prep[i].multi)
+                plans[j].prefetch != plans[i].prefetch || prep[j].multi != prep[i].multi)
                 continue;
             gp.p[gp.n] = prep[j].sp;
             gp.first_block[gp.n + 1] = gp.first_block[gp.n] + (int)prep[j].grid.x;
             lds = prep[j].lds > lds ? prep[j].lds : lds;
+            threads = prep[j].block.x > threads ? prep[j].block.x : threads;
             ++gp.n;
             done[j] = 1;
         }
-        const hipError_t e = (args[i].bits == 4)
-            ? launch_grouped_bits<4>(gp, prep[i].ngc, prep[i].multi, (unsigned)gp.first_block[gp.n], prep[i].block.x, lds, st)
-            : launch_grouped_bits<8>(gp, prep[i].ngc, prep[i].multi, (unsigned)gp.first_block[gp.n], prep[i].block.x, lds, st);
+        const unsigned blocks = (unsigned)gp.first_block[gp.n];
+        hipError_t e;
+        if (plans[i].prefetch == 1) {
+            e = (args[i].bits == 4) ? launch_grouped_bits<4, 1>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st)
+                                    : launch_grouped_bits<8, 1>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st);
+        } else {
+            e = (args[i].bits == 4) ? launch_grouped_bits<4, 2>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st)
+                                    : launch_grouped_bits<8, 2>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st);
+        }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -763,6 +763,52 @@ def test_grouped_forward_expert_modules(rtn):
             H.assert_linear_close(_to_np(mods[i]["C"]), refs[i], f"grouped subset module {i}")
 
 
+@pytest.mark.parametrize("bits,g", [(4, 128), (4, 32), (8, 0)])
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9])
+def test_layer_forward_of_independent_and_dependent_modules(rtn, bits, g, M):
+    """Modules of different N and K (workgroups of different widths in one grid, partly filled, several wavefronts along K)
+    with ragged rows: every output against the oracle, also when a graph replays the call.  The same kernel on modules
+    chained through their buffers -- an output that is another's input, an output written twice -- gives what running
+    them one by one gives, bit for bit."""
+    shapes = [(48, 1024, M), (272, 4096, max(1, M - 3)), (16, 1024, M), (2064, 2048, M), (80, 14336, M)]
+    mods, refs = [], []
+    for i, (N, K, rows) in enumerate(shapes):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=31 + i)
+        A_t = synth.activation(rows, K, seed=60 + i, device=DEV)
+        mods.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.empty((rows, N), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A_t), codes, scales, gg))
+    plan = rtn.LayerPlan(mods)
+
+    def check(what):
+        torch.cuda.synchronize()
+        for i, m in enumerate(mods):
+            H.assert_linear_close(_to_np(m["C"]), refs[i], f"{what} int{bits} g={g} M={M} module {i}")
+            m["C"].fill_(float("nan"))
+
+    plan.run()
+    check("direct")
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            plan.run()
+    for _ in range(3):
+        graph.replay()
+        check("graph")
+    # module 1 reads module 0's output, module 2 reads module 1's and overwrites module 0's
+    K = 1024
+    ops = [_oracle_operands(K, K, bits, g, seed=91 + i)[2:4] for i in range(3)]
+    A_t = synth.activation(M, K, seed=77, device=DEV)
+    C0, C1 = (torch.empty((M, K), dtype=torch.float16, device=DEV) for _ in range(2))
+    chain = [dict(A=A, qweight=ops[i][0], scales=ops[i][1], bits=bits, group_size=g, C=C) for i, (A, C) in enumerate(((A_t, C0), (C0, C1), (C1, C0)))]
+    want, x = [], A_t
+    for i in range(3):
+        x = rtn.rtn_linear(x, ops[i][0], ops[i][1], bits, g)
+        want.append(x)
+    rtn.rtn_layer_forward(chain)
+    torch.cuda.synchronize()
+    assert torch.equal(C1, want[1]) and torch.equal(C0, want[2])
+
+
 def test_selective_precision_layer(rtn):
     """Mixed 4-/8-bit decoder layer through rtn_layer_forward (Section 4.3), 405B-shaped at 1/8 width
     here; the full-width layer is exercised by the benchmark."""
