@@ -188,9 +188,6 @@ double tile_plan_choose(bool dense, int64_t M, int64_t N, int64_t K, size_t work
     }
     return best;
 }
-double tile_plan_choose(int64_t M, int64_t N, int64_t K, int* rows16, int* split_k) {
-    return tile_plan_choose(false, M, N, K, kWorkspaceCapTile, rows16, split_k);
-}
 
 // Problems the tile kernel may serve at all.  It rounds each scaled weight to fp16, the wide kernel scales fp32 sums of
 // exact codes (2.7e-4 against 2.0e-4 of the norm), so this line is one of precision and does not move with the kernels'
@@ -220,15 +217,16 @@ bool tile_line(int64_t M, int64_t N, int64_t K, int bits, double t_wide) {
 // or 0 where one launch is modelled within 7 % of the best pair.  Measured as two calls against one on the qkv shapes:
 // 405B at 2048 rows 1044 us against 1236, at 1024 rows 565 against 641; 70B at 2048 rows 324 against 374; 8B at 4096
 // rows 208 against 232; no gain (and none modelled) where the tiles fill their rounds.
-int64_t tile_two_launches(int64_t M, int64_t N, int64_t K, double* time_us = nullptr) {
+int64_t tile_two_launches(bool dense, int64_t M, int64_t N, int64_t K, size_t workspace_cap, double* time_us = nullptr) {
     int r16, sk;
-    const double single = tile_plan_choose(M, N, K, &r16, &sk);
+    const double single = tile_plan_choose(dense, M, N, K, workspace_cap, &r16, &sk);
     if (time_us) *time_us = single;
     if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
     double best = single * 0.93;
     int64_t rows_first = 0;
     for (int64_t r1 = 256; r1 < M; r1 += 256) {
-        const double t = tile_plan_choose(r1, N, K, &r16, &sk) + tile_plan_choose(M - r1, N, K, &r16, &sk);
+        const double t = tile_plan_choose(dense, r1, N, K, workspace_cap, &r16, &sk) +
+                         tile_plan_choose(dense, M - r1, N, K, workspace_cap, &r16, &sk);
         if (t < best) { best = t; rows_first = r1; }
     }
     if (time_us && rows_first > 0) *time_us = best;
@@ -375,9 +373,12 @@ bool skinny_plan_from_table(int64_t M, int64_t N, int64_t K, int bits, size_t ld
     return false;
 }
 
-// force_path: 0 = choose the path, otherwise the default plan of that path.
+// force_path: 0 = choose the path, otherwise the default plan of that path.  workspace: bytes at hand for the tile kernel's
+// partial sums (by default what its best plan may take): kernel, height, split and cut are chosen within it, instead of
+// the unconstrained plan with its split cut down.  Within 16 MiB, cut down against chosen: 1011 rows of 4608 x 5120 104 us
+// against 77, 2921 of 1792 x 5120 105 against 84, 2048 of 4096 x 14336 321 against 236, 256 of 16384 x 53248 1010 against 734.
 LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path = 0,
-                     int64_t steps_hint = 0) {
+                     int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile) {
     LinearPlan p;
     p.n_tiles16 = 1;
     // more than 16 rows: the wide kernel, except at 17-32 rows on large matrices, where the skinny kernel's pure
@@ -404,16 +405,18 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
         if (tile_line(M, N, K, bits, t_wide) && !(tall_wide && M < 192 && ((N + 255) / 256) * ((M + 127) / 128) < 144)) {
             tile_wins = ((N + 255) / 256) * ((M + 127) / 128) >= 256;
             if (!tile_wins) {
-                double t_tile = 0;
-                tile_two_launches(M, N, K, &t_tile);
-                tile_wins = t_tile * 0.87 < t_wide;
+                const int64_t fit = std::max<int64_t>(1, (int64_t)(workspace / ((size_t)M * N * sizeof(float))));
+                double t_tile = 0, t_wide_fit = t_wide;         // of what resolve_plan leaves of the wide plan's split
+                if (w.split_k > fit) t_wide_fit = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, (int)fit);
+                tile_two_launches(false, M, N, K, workspace, &t_tile);
+                tile_wins = t_tile * 0.87 < t_wide_fit;
             }
         }
     }
     if (force_path == 4 || tile_wins) {
         p.path = 4;
         p.prefetch = 1; p.waves_n = 8; p.waves_k = 1;
-        tile_plan_choose(M, N, K, &p.m_rows16, &p.split_k);
+        tile_plan_choose(false, M, N, K, workspace, &p.m_rows16, &p.split_k);
         p.m_blocks = (int)((M + 32 * p.m_rows16 - 1) / (32 * p.m_rows16));
         return p;
     }
@@ -559,6 +562,11 @@ rules:
     return p;
 }
 
+// Bytes of the workspace passed that the tile kernel's plans may count on.
+size_t tile_workspace(const LinearArgs& a, size_t workspace_nbytes) {
+    return a.workspace ? std::min(workspace_nbytes, kWorkspaceCapTile) : 0;
+}
+
 rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t workspace_nbytes, LinearPlan* out) {
     const size_t lds_limit = (size_t)device_max_lds();
     LinearPlan p;
@@ -566,7 +574,7 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     const bool whole = cfg && cfg->path && cfg->prefetch && cfg->waves_n && cfg->waves_k && cfg->split_k && cfg->m_rows16 && cfg->n_tiles16;
     if (whole) p.m_blocks = 1;                                  // every field comes from the caller
     else if (!cfg && wide_small_groups(a.M, a.g)) wide_plan(a.M, a.N, a.K, a.bits, a.g, &p);
-    else p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0);
+    else p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0, 0, tile_workspace(a, workspace_nbytes));
     if (cfg) {
         if (cfg->path) p.path = cfg->path;
         if (cfg->prefetch) p.prefetch = cfg->prefetch;
@@ -620,6 +628,29 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     }
     *out = p;
     return RTN_OK;
+}
+
+// The one or two launches of a call, in order, with their plans.
+rtn_status linear_launches(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t workspace_nbytes, LinearArgs part[2],
+                           LinearPlan plan[2], int* n) {
+    *n = 1;
+    part[0] = a;
+    rtn_status st = resolve_plan(a, cfg, workspace_nbytes, &plan[0]);
+    if (st != RTN_OK || cfg || plan[0].path != 4) return st;
+    const int64_t rows_first = tile_two_launches(false, a.M, a.N, a.K, tile_workspace(a, workspace_nbytes));
+    if (rows_first == 0) return RTN_OK;
+    rtn_linear_cfg tile_cfg = {};
+    tile_cfg.path = 4;
+    *n = 2;
+    for (int i = 0; i < 2 && st == RTN_OK; ++i) {
+        const int64_t r0 = i == 0 ? 0 : rows_first;
+        part[i] = a;
+        part[i].M = i == 0 ? rows_first : a.M - rows_first;
+        part[i].A = static_cast<const char*>(a.A) + (size_t)r0 * a.K * 2;
+        part[i].C = static_cast<char*>(a.C) + (size_t)r0 * a.N * 2;
+        st = resolve_plan(part[i], &tile_cfg, workspace_nbytes, &plan[i]);
+    }
+    return st;
 }
 
 // ---- split-K partial sums for the entry point that allocates nothing ----------------------------------------------
@@ -689,11 +720,11 @@ size_t rtn_workspace_nbytes(int64_t M, int64_t N, int64_t K, int bits, int group
         const size_t need = ((size_t)M * (size_t)N * sizeof(float) * (size_t)p.split_k + 255) & ~(size_t)255;
         if (need > bound) bound = need;
     }
-    const int64_t rows_first = p.path == 4 ? tile_two_launches(M, N, K) : 0;
+    const int64_t rows_first = p.path == 4 ? tile_two_launches(false, M, N, K, kWorkspaceCapTile) : 0;
     for (int part = 0; rows_first > 0 && part < 2; ++part) {    // and of the two launches rtn_linear would issue
         const int64_t rows = part == 0 ? rows_first : M - rows_first;
         int r16, sk;
-        tile_plan_choose(rows, N, K, &r16, &sk);
+        tile_plan_choose(false, rows, N, K, kWorkspaceCapTile, &r16, &sk);
         const size_t need = sk > 1 ? (((size_t)rows * (size_t)N * sizeof(float) * (size_t)sk + 255) & ~(size_t)255) : 0;
         if (need > bound) bound = need;
     }
@@ -731,27 +762,14 @@ rtn_status rtn_linear_ex(const void* dev_A, int64_t M, const void* dev_qweight, 
     a.A = dev_A; a.qweight = dev_qweight; a.scales = dev_scales; a.C = dev_C;
     a.workspace = static_cast<float*>(dev_workspace);
     a.M = M; a.N = N; a.K = K; a.g = g; a.bits = bits;
-    LinearPlan p;
-    st = resolve_plan(a, cfg, workspace_nbytes, &p);
+    LinearArgs part[2];
+    LinearPlan plan[2];
+    int n;
+    st = linear_launches(a, cfg, workspace_nbytes, part, plan, &n);
     if (st != RTN_OK) return st;
-    const int64_t rows_first = (!cfg && p.path == 4) ? tile_two_launches(M, N, K) : 0;
-    if (rows_first > 0) {
-        rtn_linear_cfg tile_cfg = {};
-        tile_cfg.path = 4;
-        for (int part = 0; part < 2; ++part) {
-            LinearArgs b = a;
-            const int64_t r0 = part == 0 ? 0 : rows_first;
-            b.M = part == 0 ? rows_first : M - rows_first;
-            b.A = static_cast<const char*>(dev_A) + (size_t)r0 * K * 2;
-            b.C = static_cast<char*>(dev_C) + (size_t)r0 * N * 2;
-            st = resolve_plan(b, &tile_cfg, workspace_nbytes, &p);
-            if (st != RTN_OK) return st;
-            if (rtn::launch_linear(b, p, static_cast<hipStream_t>(stream)) != hipSuccess) return RTN_ERR_HIP;
-        }
-        return RTN_OK;
-    }
-    hipError_t e = rtn::launch_linear(a, p, static_cast<hipStream_t>(stream));
-    return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
+    for (int i = 0; i < n; ++i)
+        if (rtn::launch_linear(part[i], plan[i], static_cast<hipStream_t>(stream)) != hipSuccess) return RTN_ERR_HIP;
+    return RTN_OK;
 }
 
 rtn_status rtn_linear(const void* dev_A, int64_t M, const void* dev_qweight, const void* dev_scales,
@@ -897,28 +915,13 @@ rtn_status rtn_quantize_from_host(const void* host_W, int64_t N, int64_t K, int 
     return ok ? RTN_OK : RTN_ERR_HIP;
 }
 
-// The dense GEMM in two launches, as rtn_linear does with the fused tile kernel: the first rows (a multiple of 256) as
-// full rounds, the rest with the K split that fills its round; 0 where one launch is modelled within 7 % of that.
-static int64_t dense_two_launches(int64_t M, int64_t N, int64_t K, size_t workspace_nbytes) {
-    if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
-    int r16, sk;
-    double best = 0.93 * tile_plan_choose(true, M, N, K, workspace_nbytes, &r16, &sk);
-    int64_t rows_first = 0;
-    for (int64_t r1 = 256; r1 < M; r1 += 256) {
-        const double t = tile_plan_choose(true, r1, N, K, workspace_nbytes, &r16, &sk) +
-                         tile_plan_choose(true, M - r1, N, K, workspace_nbytes, &r16, &sk);
-        if (t < best) { best = t; rows_first = r1; }
-    }
-    return rows_first;
-}
-
 rtn_status rtn_gemm_fp16(const void* dev_A, int64_t M, const void* dev_W_fp16, int64_t N, int64_t K, void* dev_C,
                          void* dev_workspace, size_t workspace_nbytes, void* stream) {
     if (!dev_A || !dev_W_fp16 || !dev_C) return RTN_ERR_NULL;
     if (M <= 0 || M > (1 << 20) || N <= 0 || N % 16 != 0 || K <= 0 || K % 128 != 0) return RTN_ERR_SHAPE;
     if ((uint64_t)K * 2 * 128 >= 0x7FFF0000ull) return RTN_ERR_SHAPE;          // one 128-row slab per buffer resource
     if (!aligned16(dev_A) || !aligned16(dev_W_fp16) || !aligned16(dev_C) || !aligned16(dev_workspace)) return RTN_ERR_ALIGN;
-    const int64_t rows_first = dev_workspace ? dense_two_launches(M, N, K, workspace_nbytes) : 0;
+    const int64_t rows_first = dev_workspace ? tile_two_launches(true, M, N, K, workspace_nbytes) : 0;
     for (int part = 0; part < (rows_first > 0 ? 2 : 1); ++part) {
         const int64_t r0 = part == 0 ? 0 : rows_first, rows = rows_first == 0 ? M : part == 0 ? rows_first : M - rows_first;
         int r16, split;
@@ -1135,7 +1138,8 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
     for (int i = 0; i < n_mods; ++i) {
         const LinearArgs& a = args[i];
         // planned as one slice of a launch that streams all the small-batch modules together
-        const LinearPlan h = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, 0, a.M <= 16 ? steps_total : 0);
+        const LinearPlan h = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, 0, a.M <= 16 ? steps_total : 0,
+                                       tile_workspace(a, workspace_nbytes));
         rtn_linear_cfg cfg;
         cfg.path = h.path; cfg.prefetch = h.prefetch; cfg.waves_n = h.waves_n; cfg.waves_k = h.waves_k;
         cfg.split_k = h.split_k; cfg.m_rows16 = h.m_rows16; cfg.n_tiles16 = h.n_tiles16;

@@ -1,0 +1,46 @@
+// Host-only report of the launches behind a call: reads problems from standard input, prints the launches with their
+// plans.  The library's C-ABI translation unit is part of this one, so that its planning functions can be called; no GPU
+// work, nothing is launched.  Built and read by tests/test_host_plans.py.
+#include "../../paper_2505_15909_amd/csrc/rtn_api.hip"
+#include <stdio.h>
+
+static char stand_in[64];                                      // addresses only, nothing is read or written
+
+static LinearArgs problem(int64_t M, int64_t N, int64_t K, int bits, int64_t g, bool workspace) {
+    LinearArgs a;
+    a.A = a.qweight = a.scales = stand_in;
+    a.C = stand_in;
+    a.workspace = workspace ? reinterpret_cast<float*>(stand_in) : nullptr;
+    a.M = M; a.N = N; a.K = K; a.bits = bits; a.g = g;
+    return a;
+}
+
+static void print_plan(const LinearArgs& a, const LinearPlan& p) {
+    printf(" [%ld %d %d %d %d %d %d %d %d]", (long)a.M, p.path, p.prefetch, p.waves_n, p.waves_k, p.split_k, p.m_rows16, p.m_blocks, p.n_tiles16);
+}
+
+int main() {
+    char what[16];
+    while (scanf("%15s", what) == 1) {
+        if (!strcmp(what, "linear")) {                         // M N K bits g workspace -> status, cut and launches
+            long M, N, K, g, ws;
+            int bits;
+            if (scanf("%ld %ld %ld %d %ld %ld", &M, &N, &K, &bits, &g, &ws) != 6) return 1;
+            LinearArgs part[2];
+            LinearPlan plan[2];
+            int n = 0;
+            const rtn_status st = linear_launches(problem(M, N, K, bits, g > 0 ? g : K, ws > 0), nullptr, (size_t)ws, part, plan, &n);
+            printf("%d", (int)st);
+            for (int i = 0; st == RTN_OK && i < n; ++i) print_plan(part[i], plan[i]);
+        } else if (!strcmp(what, "tile")) {                    // M N K rows16 split -> modelled time of a tile-kernel launch
+            long M, N, K;
+            int rows16, split;
+            if (scanf("%ld %ld %ld %d %d", &M, &N, &K, &rows16, &split) != 5) return 1;
+            printf("%.6f", rtn::tile_model_us(false, rows16, M, N, K, split));
+        } else {
+            return 1;
+        }
+        printf("\n");
+    }
+    return 0;
+}

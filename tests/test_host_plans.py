@@ -1,0 +1,83 @@
+"""The plans behind a call, on the CPU: a small host program (tests/host/plan_report_driver.cpp) holds the library's planning
+code and prints, for each problem it reads, the launches the call would issue.  Nothing is launched."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2505_15909_amd")
+FIELDS = ("M", "path", "prefetch", "waves_n", "waves_k", "split_k", "m_rows16", "m_blocks", "n_tiles16")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """ask(lines) -> (first value, [plans]) of each line."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    objs = [os.path.join(PKG, "_build", f) for f in ("rtn_quantize.o", "rtn_linear.o", "rtn_linear_wide.o", "rtn_gemm_tile.o", "rtn_bench.o")]
+    if not all(os.path.exists(o) for o in objs):
+        pytest.skip("library objects not built (run __graft_entry__.build() first)")
+    work = tmp_path_factory.mktemp("plans")
+    obj, exe = str(work / "driver.o"), str(work / "plan_report_driver")
+    subprocess.run([hipcc, "-O1", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-x", "hip", "-c", "-o", obj, os.path.join(ROOT, "tests", "host", "plan_report_driver.cpp")],
+                   check=True, capture_output=True, timeout=600)
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-o", exe, obj, *objs], check=True, capture_output=True, timeout=600)
+
+    def run(lines):
+        r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=600)
+        assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+        out = r.stdout.strip().split("\n")
+        assert len(out) == len(lines)
+        return [(float(o.split()[0]), [dict(zip(FIELDS, map(int, p.split()))) for p in re.findall(r"\[(.*?)\]", o)]) for o in out]
+
+    return run
+
+
+MIB = 1 << 20
+
+
+@pytest.mark.parametrize("workspace", [0, 16 * MIB, 40 * MIB, 256 * MIB])
+def test_tile_plans_are_the_best_within_the_workspace(ask, workspace):
+    """Where a call goes to the tile kernel, no tile height and K split that fit the workspace passed are modelled faster
+    than the launch that goes out (one launch; of two, each for its own rows), and two launches are modelled faster than
+    the best single one."""
+    problems = [(1011, 4608, 5120), (2252, 2176, 5632), (2921, 1792, 5120), (1300, 6144, 4096), (2048, 10240, 8192), (1024, 18432, 16384),
+                (256, 18432, 16384), (700, 4096, 14336), (4096, 28672, 4096), (2048, 4096, 14336)]
+    plans = [p for _, p in ask([f"linear {M} {N} {K} 4 128 {workspace}" for M, N, K in problems])]
+    tile = [(prob, p) for prob, p in zip(problems, plans) if p[0]["path"] == 4]
+    assert len(tile) >= 4 and any(len(p) == 2 for _, p in tile)
+
+    def fitting(M, N, K):
+        return [(M, N, K, h, s) for s in range(1, 9) if s == 1 or (M * N * 4 * s <= workspace and K // 128 // s >= 4)
+                for h in (4, 8) if h == 4 or M > 128]
+
+    lines, index = [], {}
+
+    def want(q):
+        if q not in index:
+            index[q] = len(lines)
+            lines.append("tile %d %d %d %d %d" % q)
+
+    for (M, N, K), launches in tile:
+        assert sum(q["M"] for q in launches) == M
+        for q in launches:
+            assert q["split_k"] == 1 or q["M"] * N * 4 * q["split_k"] <= workspace
+            want((q["M"], N, K, q["m_rows16"], q["split_k"]))
+            for f in fitting(q["M"], N, K):
+                want(f)
+        for f in fitting(M, N, K):
+            want(f)
+    times = [t for t, _ in ask(lines)]
+    for (M, N, K), launches in tile:
+        total = 0.0
+        for q in launches:
+            t = times[index[(q["M"], N, K, q["m_rows16"], q["split_k"])]]
+            best = min(times[index[f]] for f in fitting(q["M"], N, K))
+            assert t <= best * (1 + 1e-9), (M, N, K, q, t, best)
+            total += t
+        if len(launches) == 2:
+            assert total < 0.93 * min(times[index[f]] for f in fitting(M, N, K))
