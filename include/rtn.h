@@ -140,7 +140,8 @@ rtn_status rtn_linear(const void* dev_A, int64_t M, const void* dev_qweight, con
 typedef struct {
     int path;      /* 0 auto, 1 MFMA skinny kernel, 2 vector-ALU dot-product kernel (M <= 4), 3 wide MFMA kernel
                       (group_size a multiple of 128; uses split_k, m_rows16 = 2..4, n_tiles16 and waves_n = 4, 8 or -- with
-                      n_tiles16 = 1 -- 16 wavefronts per workgroup; also m_rows16 = 8 with n_tiles16 = 2 and waves_n = 8:
+                      n_tiles16 = 1 -- 16 wavefronts per workgroup; group_size 32 and 64 with every field given, waves_n = 8
+                      and n_tiles16 = 1 or 2; also m_rows16 = 8 with n_tiles16 = 2 and waves_n = 8:
                       128 rows per workgroup, weights scaled in fp16 before the MFMA as in path 4, chosen automatically
                       for 128 and more rows on large 4-bit matrices below the tile kernel's range), 4 tile kernel: 128 x 256 or
                       256 x 256 output tiles, weights dequantised to fp16 in LDS (group_size a multiple of 128; uses split_k and
@@ -159,9 +160,8 @@ rtn_status rtn_linear_ex(const void* dev_A, int64_t M, const void* dev_qweight, 
                          void* dev_workspace, size_t workspace_nbytes, void* stream,
                          const rtn_linear_cfg* cfg);
 
-/* Reports the configuration rtn_linear would use (host only, launches nothing).  With groups of 32 and 64 columns from 20
- * rows, where rtn_linear takes a form of the wide kernel that no explicit configuration asks for, it is the configuration
- * of the skinny kernel for the same problem. */
+/* Reports the configuration rtn_linear would use with a workspace of rtn_workspace_nbytes() bytes (host only, launches
+ * nothing).  Where rtn_linear issues the tile kernel twice, it is that of the single launch. */
 rtn_status rtn_linear_query(int64_t M, int64_t N, int64_t K, int bits, int group_size, rtn_linear_cfg* out);
 
 /* Host-only checks, nothing is launched and no pointer is needed.  rtn_problem_status: the status every entry point

@@ -102,7 +102,7 @@ double wide_model_us(int64_t M, int64_t N, int64_t K, int bits, int mb, int wv, 
 // kernel still stages a 4096-column slice in one piece and is ahead on the small matrices (8B qkv, group 64: 9.3 us
 // against 11.5 at 19 rows, 15.8 against 11.4 at 20; level on the 70B ones).  Above, it runs 64 rows at a time; the wide
 // kernel takes 27 us against 44 (8B qkv), 83 against 121 (8B gate_up) and 148 against 207 (70B down) at 256 rows, 597
-// against 823 on 8B gate_up at 2048.  An explicit configuration keeps to the skinny kernel on these groups.
+// against 823 on 8B gate_up at 2048.  A partial explicit configuration keeps to the skinny kernel on these groups.
 bool wide_small_groups(int64_t M, int64_t g) { return (g == 64 || g == 32) && M >= 20; }
 
 void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan* p) {
@@ -381,6 +381,10 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
                      int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile) {
     LinearPlan p;
     p.n_tiles16 = 1;
+    if (force_path == 0 && wide_small_groups(M, g)) {
+        wide_plan(M, N, K, bits, g, &p);
+        return p;
+    }
     // more than 16 rows: the wide kernel, except at 17-32 rows on large matrices, where the skinny kernel's pure
     // weight streaming still wins.  4 bit: from 40 MB with rows of 8192 columns and more, 16 wavefronts side by side
     // (6-20 % faster on the 70B and 405B shapes except the 70B o matrix; the wide kernel wins on every 8B shape).
@@ -562,6 +566,14 @@ rules:
     return p;
 }
 
+// The plan as a complete explicit configuration.
+rtn_linear_cfg plan_cfg(const LinearPlan& p) {
+    rtn_linear_cfg c;
+    c.path = p.path; c.prefetch = p.prefetch; c.waves_n = p.waves_n; c.waves_k = p.waves_k;
+    c.split_k = p.split_k; c.m_rows16 = p.m_rows16; c.n_tiles16 = p.n_tiles16;
+    return c;
+}
+
 // Bytes of the workspace passed that the tile kernel's plans may count on.
 size_t tile_workspace(const LinearArgs& a, size_t workspace_nbytes) {
     return a.workspace ? std::min(workspace_nbytes, kWorkspaceCapTile) : 0;
@@ -573,8 +585,10 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     p.n_tiles16 = 1;
     const bool whole = cfg && cfg->path && cfg->prefetch && cfg->waves_n && cfg->waves_k && cfg->split_k && cfg->m_rows16 && cfg->n_tiles16;
     if (whole) p.m_blocks = 1;                                  // every field comes from the caller
-    else if (!cfg && wide_small_groups(a.M, a.g)) wide_plan(a.M, a.N, a.K, a.bits, a.g, &p);
-    else p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg ? cfg->path : 0, 0, tile_workspace(a, workspace_nbytes));
+    else {
+        const int path = !cfg ? 0 : cfg->path == 0 && wide_small_groups(a.M, a.g) ? 1 : cfg->path;
+        p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, path, 0, tile_workspace(a, workspace_nbytes));
+    }
     if (cfg) {
         if (cfg->path) p.path = cfg->path;
         if (cfg->prefetch) p.prefetch = cfg->prefetch;
@@ -602,7 +616,7 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     }
     if (p.path >= 3) {
         bool ok = p.path == 3 ? rtn::wide_plan_valid(a, p) : rtn::tile_plan_valid(a, p);
-        if (p.path == 3 && a.g % 128 != 0 && cfg && !a.zeros) ok = false;     // not for the asking, see wide_small_groups
+        if (p.path == 3 && a.g % 128 != 0 && cfg && !whole) ok = false;       // no defaults to fill in, see wide_small_groups
         if (!ok || p.split_k > kMaxSplitK) return RTN_ERR_CONFIG;
         if ((uint64_t)a.N * a.K * a.bits / 8 >= 0x7FFF0000ull || (uint64_t)a.M * a.K * 2 >= 0x7FFF0000ull)
             return RTN_ERR_SHAPE;                               // 32-bit buffer offsets
@@ -826,9 +840,7 @@ rtn_status rtn_linear_query(int64_t M, int64_t N, int64_t K, int bits, int group
     if ((uint64_t)N * K * bits / 8 >= 0x7FFF0000ull || (uint64_t)M * K * 2 >= 0x7FFF0000ull)
         return RTN_ERR_SHAPE;                                   // what rtn_linear refuses (32-bit buffer offsets)
     LinearPlan p = auto_plan(M, N, K, bits, g, (size_t)device_max_lds());
-    out->path = p.path; out->prefetch = p.prefetch; out->waves_n = p.waves_n;
-    out->waves_k = p.waves_k; out->split_k = p.split_k; out->m_rows16 = p.m_rows16;
-    out->n_tiles16 = p.n_tiles16;
+    *out = plan_cfg(p);
     return RTN_OK;
 }
 
@@ -1137,15 +1149,15 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
     }
     for (int i = 0; i < n_mods; ++i) {
         const LinearArgs& a = args[i];
-        // planned as one slice of a launch that streams all the small-batch modules together
-        const LinearPlan h = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, 0, a.M <= 16 ? steps_total : 0,
-                                       tile_workspace(a, workspace_nbytes));
-        rtn_linear_cfg cfg;
-        cfg.path = h.path; cfg.prefetch = h.prefetch; cfg.waves_n = h.waves_n; cfg.waves_k = h.waves_k;
-        cfg.split_k = h.split_k; cfg.m_rows16 = h.m_rows16; cfg.n_tiles16 = h.n_tiles16;
-        rtn_status st = resolve_plan(a, &cfg, workspace_nbytes, &plans[i]);
-        if (st == RTN_ERR_CONFIG || wide_small_groups(a.M, a.g))
-            st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);                          // the module's own plan
+        rtn_status st = RTN_ERR_CONFIG;
+        if (!wide_small_groups(a.M, a.g)) {
+            // planned as one slice of a launch that streams all the small-batch modules together
+            const LinearPlan h = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, 0, a.M <= 16 ? steps_total : 0,
+                                           tile_workspace(a, workspace_nbytes));
+            const rtn_linear_cfg cfg = plan_cfg(h);
+            st = resolve_plan(a, &cfg, workspace_nbytes, &plans[i]);
+        }
+        if (st == RTN_ERR_CONFIG) st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);    // the module's own plan
         if (st != RTN_OK) return st;
     }
     hipError_t e = rtn::launch_linear_grouped(args.data(), plans.data(), n_mods, static_cast<hipStream_t>(stream));

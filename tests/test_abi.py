@@ -129,7 +129,15 @@ def test_bad_valid_combination_is_not_launched_without_gpu():
         q = rtn.rtn_linear_query(M, 4096, 4096, 4, 128)
         assert q["path"] == 3 and 2 <= q["m_rows16"] <= 4 and q["m_rows16"] * q["n_tiles16"] <= 8
         assert M * 4096 * 4 * q["split_k"] <= 16 << 20 or q["split_k"] == 1
-    assert rtn.rtn_linear_query(64, 4096, 4096, 8, 64)["path"] == 1
+    # groups of 32 and 64 columns too, from 20 rows; what is reported can be asked for, a partial configuration of it cannot
+    for M, path in ((19, 1), (20, 3), (64, 3)):
+        q = rtn.rtn_linear_query(M, 4096, 4096, 8, 64)
+        assert q["path"] == path
+        nbytes = rtn.rtn_workspace_nbytes(M, 4096, 4096, 8, 64)
+        assert rtn.rtn_linear_validate(M, 4096, 4096, 8, 64, nbytes, q) == 0
+        if path == 3:
+            assert rtn.rtn_linear_validate(M, 4096, 4096, 8, 64, nbytes, dict(q, prefetch=0)) == 7
+            assert rtn.rtn_linear_validate(M, 4096, 4096, 8, 64, nbytes, dict(q, waves_n=4)) == 7
     assert rtn.rtn_linear_query(32, 16384, 106496, 4, 128)["path"] == 1     # very large matrix at 32 rows: streaming wins
     # 128-256 rows on a large 4-bit matrix below the tile kernel's range: the wide kernel's 128-row variant, K split to a
     # workgroup per compute unit, and the size helper covers its partial sums

@@ -292,7 +292,9 @@ def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
     if M >= 20:
         C = torch.empty((M, N), dtype=torch.float16, device=DEV)
         outs.append(rtn.rtn_linear(A_t, qw, sc, bits, g, out=C, workspace=torch.empty(16, dtype=torch.uint8, device=DEV)))
+    C = rtn.rtn_linear(A_t, qw, sc, bits, g, cfg=rtn.rtn_linear_query(M, N, K, bits, g))
     torch.cuda.synchronize()
+    assert torch.equal(C, outs[0])                                  # what is reported is what runs
     for C in outs:
         H.assert_linear_close(_to_np(C), ref, f"int{bits} g={g} M={M} N={N} K={K}")
     W = _to_np((synth.normal_weight(N, K, 0.02, seed=M + bits, device=DEV).float() + 0.015).half())

@@ -81,3 +81,22 @@ def test_tile_plans_are_the_best_within_the_workspace(ask, workspace):
             total += t
         if len(launches) == 2:
             assert total < 0.93 * min(times[index[f]] for f in fitting(M, N, K))
+
+
+def test_query_reports_the_plan_that_runs(ask):
+    """rtn_linear_query against the single launch of rtn_linear with the workspace it asks for, every field, over group sizes,
+    rows and shapes; handed back as an explicit configuration it is accepted."""
+    import paper_2505_15909_amd as rtn
+    problems = [(M, N, K, bits, g) for K, N in ((4096, 6144), (14336, 4096), (8192, 57344), (1536, 272), (16384, 18432))
+                for bits, g in ((4, 32), (4, 64), (4, 128), (4, 0), (8, 32), (8, 64), (8, 128), (8, 0))
+                for M in (1, 4, 16, 17, 19, 20, 33, 64, 100, 130, 256, 1000) if not (g and K % g)]
+    nbytes = [rtn.rtn_workspace_nbytes(*p) for p in problems]
+    seen = set()
+    for p, ws, (status, launches) in zip(problems, nbytes, ask([f"linear {' '.join(map(str, p))} {ws}" for p, ws in zip(problems, nbytes)])):
+        assert status == 0
+        if len(launches) == 1:
+            q = rtn.rtn_linear_query(*p)
+            assert {k: launches[0][k] for k in q} == q, (p, launches, q)
+            assert rtn.rtn_linear_validate(*p, ws, q) == 0
+            seen.add((q["path"], p[4] in (32, 64)))
+    assert {(1, False), (1, True), (3, False), (3, True), (4, False)} <= seen
