@@ -228,9 +228,11 @@ typedef struct {
  * instantiation of its own (bits, group_size).  The workspace must cover the largest
  * rtn_workspace_nbytes() of the modules; it is reused, which is safe because the launches
  * are ordered on one stream.  Stops at, and returns, the first error.
- * Small layers (up to 8 rows, one precision and group size, under 256 MB of weights) whose outputs overlap no operand and
- * no output of another module go out as one launch, with a plan of its own: the same result as in order, up to the
- * summation order of a single call. */
+ * Small layers whose outputs overlap no operand and no output of another module go out as one launch: 2 to 16 modules of
+ * one precision and group size, up to 8 rows and 140 KiB of activations each (M K 2 bytes: 5 rows of 14336 columns), under
+ * 256 MB of weights together, where a common plan is not expected to cost more than the launches it saves.  The plan is
+ * the launch's own: the same result as in order, up to the summation order of a single call -- so a module's last bits may
+ * depend on the modules it shares the call with (rtn_linear gives those of the module alone). */
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace,
                              size_t workspace_nbytes, void* stream);
 

@@ -994,17 +994,44 @@ static bool modules_independent(const LinearArgs* a, int n) {
     return true;
 }
 
-// Independent modules of one precision and group size in one launch, up to eight rows and 256 MB of weights: a launch costs
-// 4-5 us of start, ramp and drain around its weight stream, which one grid over all modules pays once.  Plan of the merged
-// modules: a wavefront takes so many k-chunks that there are about 3456 of them in all (6912 from five rows), in
-// workgroups of up to 16 (13) wavefronts, fewer where that leaves compute units without one; two chunks in flight, one at
-// 4 bit from five rows.  From sweeps over 4-16 wavefronts per workgroup and 2-28 chunks per wavefront.  Graph replay over
-// rotating copies, single launches against one: 8B layer int4 30.8 -> 22.5 us at one row, 32.8 -> 23.5 at four, 35.5 ->
-// 30.9 at eight; int8 44.4 -> 37.5, 47.1 -> 38.4, 49.5 -> 43.0; four 2048 x 2048 modules 12.7 -> 4.6, two of 1024 x 4096
-// 7.6 -> 4.3 at one row.  Beyond the line the modules' own plans are better: from nine rows the staged activations want
-// their shapes (8B int4 at 16: 38.5 us against 38.9 at best), 70B and 405B modules lose more by a common shape than they
-// gain (82 -> 86 and 268 -> 297 at two rows), and so do slices that do not fit the LDS at once (28672 columns at four
-// rows, int8: 30 -> 36).
+static int64_t module_blocks(const LinearArgs& a, const LinearPlan& p) { return (a.N / 16 + p.waves_n - 1) / p.waves_n; }
+
+// Whether a merged launch costs more than the launches it saves.  Its workgroups are taken to run one to a compute unit; the
+// few of a last round leave the others idle for the time of the longest of them, at the 6.5 TB/s that the launch streams
+// at (two modules in 258 workgroups, int4 at four rows: 14.3 us apart, 19.3 merged; 5120 x 17408 beside a small module, int8
+// at one to four rows: 22-24 against 24-28).  Drawn from 1048 sets of two to seven modules: all 28 that ran slower merged (up
+// to 1.38 x) lie beyond the line, and ten that gained 6-21 %; of 500 further sets merging slowed 22 by 3-30 %, 20 of them
+// beyond it.  From five rows a matrix of 40 MB beside a module that hardly matters is also better served by its own plan
+// (21 us against 26).
+static bool merge_loses(const LinearArgs* a, const LinearPlan* plans, int n, int64_t rows, int64_t steps, double stream_us) {
+    constexpr int64_t kCus = 256;
+    int64_t blocks = 0, largest = 0, load = 0;
+    for (int i = 0; i < n; ++i) {
+        blocks += module_blocks(a[i], plans[i]);
+        largest = std::max(largest, a[i].N / 16 * (a[i].K / chunk_k(a[i].bits)));
+    }
+    const int64_t last = blocks > kCus ? blocks % kCus : 0;
+    int64_t left = last;
+    for (int i = n - 1; i >= 0 && left > 0; --i) {
+        load = std::max(load, plans[i].waves_n * (a[i].K / chunk_k(a[i].bits)));
+        left -= module_blocks(a[i], plans[i]);
+    }
+    const double idle_us = last == 0 ? 0.0 : (double)((kCus - last) * load) / (double)steps * stream_us;
+    return idle_us > 6.5 * (n - 1) - 2.0 || (n == 2 && rows > 4 && largest > 0.9 * steps && stream_us > 6.0);
+}
+
+// Independent modules of one precision and group size in one launch, up to eight rows, 256 MB of weights and 140 KiB of
+// activations a module (14336 columns at five rows): a launch costs 4-5 us of start, ramp and drain around its weight
+// stream, which one grid over all modules pays once.  Plan of the merged modules: a wavefront takes so many k-chunks that
+// there are about 3456 of them in all (6912 from five rows), in workgroups of up to 16 (13) wavefronts, fewer where that
+// leaves compute units without one; two chunks in flight, one at 4 bit from five rows.  From sweeps over 4-16
+// wavefronts per workgroup and 2-28 chunks per wavefront.  Graph replay over rotating copies, single launches against one:
+// 8B layer int4 30.8 -> 22.6 us at one row, 32.9 -> 23.5 at four, 35.4 -> 29.3 at five; int8 44.0 -> 37.5, 47.0 -> 37.9,
+// 50.1 -> 41.6; the 2048-wide layer int4 17.3 -> 11.1, 18.9 -> 11.6; three modules of 4096 columns and
+// 4096, 1024, 1024 rows 11.8 -> 5.5 at one row, two of 4096 x 1024 6.3 -> 3.6.
+// Beyond the line the modules' own plans are better: from nine rows the staged activations want their shapes (8B int4 at
+// 16: 38.5 us against 38.9 at best), 70B and 405B modules lose more by a common shape than they gain (82 -> 86 and
+// 268 -> 297 at two rows), and so do slices that do not fit the LDS at once (28672 columns at four rows, int8: 30 -> 36).
 static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbytes, LinearPlan* plans) {
     int64_t rows = 0;
     size_t bytes = 0;
@@ -1038,7 +1065,7 @@ static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbyt
         cfg.split_k = 1; cfg.m_rows16 = 1; cfg.n_tiles16 = 1;
         if (resolve_plan(a[i], &cfg, workspace_nbytes, &plans[i]) != RTN_OK) return false;
     }
-    return true;
+    return !merge_loses(a, plans, n, rows, steps, (double)bytes / 6.5e6);
 }
 
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,

@@ -77,3 +77,9 @@ def make_weight(cfg_dist: str, N: int, K: int, seed: int, device):
     if cfg_dist == "heavy":
         return synth.heavy_tail_weight(N, K, 0.02, seed, device)
     raise ValueError(cfg_dist)
+
+
+# Layers (N, K of each module) for the launches that rtn_layer_forward merges: what test_host_plans.py asserts of their plans is
+# what the GPU tests on the same lists rely on.
+LAYER_RAGGED = [(48, 1024), (272, 4096), (16, 1024), (2064, 2048), (80, 14336)]
+LAYER_2048 = [(3072, 2048), (2048, 2048), (16384, 2048), (2048, 8192)]

@@ -37,6 +37,20 @@ int main() {
             int rows16, split;
             if (scanf("%ld %ld %ld %d %d", &M, &N, &K, &rows16, &split) != 5) return 1;
             printf("%.6f", rtn::tile_model_us(false, rows16, M, N, K, split));
+        } else if (!strcmp(what, "layer")) {                   // bits g workspace n, then M N K each -> 1 if one launch, plans
+            long g, ws;
+            int bits, n;
+            if (scanf("%d %ld %ld %d", &bits, &g, &ws, &n) != 4 || n < 1 || n > 16) return 1;
+            LinearArgs a[16];
+            LinearPlan plan[16];
+            for (int i = 0; i < n; ++i) {
+                long M, N, K;
+                if (scanf("%ld %ld %ld", &M, &N, &K) != 3) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
+            }
+            const bool one = merged_layer_plans(a, n, (size_t)ws, plan);
+            printf("%d", one ? 1 : 0);
+            for (int i = 0; one && i < n; ++i) print_plan(a[i], plan[i]);
         } else {
             return 1;
         }

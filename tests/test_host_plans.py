@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from tests import helpers as H
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2505_15909_amd")
 FIELDS = ("M", "path", "prefetch", "waves_n", "waves_k", "split_k", "m_rows16", "m_blocks", "n_tiles16")
@@ -100,3 +102,31 @@ def test_query_reports_the_plan_that_runs(ask):
             assert rtn.rtn_linear_validate(*p, ws, q) == 0
             seen.add((q["path"], p[4] in (32, 64)))
     assert {(1, False), (1, True), (3, False), (3, True), (4, False)} <= seen
+
+
+def _layer(shapes, M, bits, g, workspace=64 * MIB):
+    rows = M if isinstance(M, (list, tuple)) else [M] * len(shapes)
+    return f"layer {bits} {g} {workspace} {len(shapes)} " + " ".join(f"{m} {N} {K}" for m, (N, K) in zip(rows, shapes))
+
+
+LAYER_8B = [(6144, 4096), (4096, 4096), (28672, 4096), (4096, 14336)]
+
+
+def test_which_layers_are_merged(ask):
+    """The range that the documentation states, the layers that the GPU tests rely on, and sets of modules that were measured
+    slower in one launch than apart."""
+    def one(*q):
+        return ask([_layer(*q)])[0][0] == 1
+
+    for bits, g in ((4, 128), (8, 0)):
+        assert [one(LAYER_8B, M, bits, g) for M in range(1, 10)] == [True] * 5 + [False] * 4      # 14336 columns: 140 KiB at five rows
+    assert not one([(10240, 8192), (8192, 8192), (57344, 8192), (8192, 28672)], 1, 4, 128)        # 256 MB and more
+    assert not one(LAYER_8B[:1], 9, 4, 128) and not one(LAYER_8B, [1, 1, 9, 1], 4, 128)
+    # slower merged
+    for bits, g, M, shapes in ((8, 0, 1, [(5120, 17408), (2048, 4096)]), (8, 0, 4, [(5120, 17408), (2048, 4096)]),
+                               (4, 128, 2, [(5120, 17408), (2048, 4096)]), (4, 128, 4, [(7568, 9728), (4640, 2048)]),
+                               (4, 32, 1, [(23680, 3072), (9664, 3072)]), (8, 0, 8, [(22336, 4096), (10976, 4096)]),
+                               (8, 128, 2, [(13728, 13312), (1728, 5120), (20336, 512), (1696, 5120)]),
+                               (8, 0, 6, [(1568, 1024), (12336, 7168)]), (4, 128, 6, [(8960, 10240), (5424, 512)]),
+                               (4, 0, 3, [(9216, 6144), (6144, 6144), (39936, 6144), (6144, 19968)])):
+        assert not one(shapes, M, bits, g), (bits, M, shapes)
