@@ -1024,10 +1024,12 @@ static bool merge_loses(const LinearArgs* a, const LinearPlan* plans, int n, int
 // activations a module (14336 columns at five rows): a launch costs 4-5 us of start, ramp and drain around its weight
 // stream, which one grid over all modules pays once.  Plan of the merged modules: a wavefront takes so many k-chunks that
 // there are about 3456 of them in all (6912 from five rows), in workgroups of up to 16 (13) wavefronts, fewer where that
-// leaves compute units without one; two chunks in flight, one at 4 bit from five rows.  From sweeps over 4-16
+// leaves compute units without one; wavefronts that an even share of the chunks leaves without any are left out (with
+// them a 2048-wide layer, int4 at one row, took 11.1 us instead of 10.4, and its slice of 8192 columns at six rows did not
+// fit the LDS: 20.2 us instead of 15.2); two chunks in flight, one at 4 bit from five rows.  From sweeps over 4-16
 // wavefronts per workgroup and 2-28 chunks per wavefront.  Graph replay over rotating copies, single launches against one:
 // 8B layer int4 30.8 -> 22.6 us at one row, 32.9 -> 23.5 at four, 35.4 -> 29.3 at five; int8 44.0 -> 37.5, 47.0 -> 37.9,
-// 50.1 -> 41.6; the 2048-wide layer int4 17.3 -> 11.1, 18.9 -> 11.6; three modules of 4096 columns and
+// 50.1 -> 41.6; the 2048-wide layer int4 17.3 -> 10.3, 18.9 -> 10.8, 19.9 -> 15.5 at eight; three modules of 4096 columns and
 // 4096, 1024, 1024 rows 11.8 -> 5.5 at one row, two of 4096 x 1024 6.3 -> 3.6.
 // Beyond the line the modules' own plans are better: from nine rows the staged activations want their shapes (8B int4 at
 // 16: 38.5 us against 38.9 at best), 70B and 405B modules lose more by a common shape than they gain (82 -> 86 and
@@ -1062,6 +1064,8 @@ static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbyt
         cfg.path = 1; cfg.prefetch = chunks >= 2 && (rows <= 4 || a[i].bits == 8) ? 2 : 1;
         cfg.waves_k = waves_k(a[i]);
         cfg.waves_n = (int)std::max<int64_t>(1, std::min<int64_t>(width / cfg.waves_k, a[i].N / 16));
+        const int64_t KC = a[i].K / chunk_k(a[i].bits), per = (KC + cfg.waves_k - 1) / cfg.waves_k;
+        cfg.waves_k = (int)((KC + per - 1) / per);
         cfg.split_k = 1; cfg.m_rows16 = 1; cfg.n_tiles16 = 1;
         if (resolve_plan(a[i], &cfg, workspace_nbytes, &plans[i]) != RTN_OK) return false;
     }

@@ -112,6 +112,24 @@ def _layer(shapes, M, bits, g, workspace=64 * MIB):
 LAYER_8B = [(6144, 4096), (4096, 4096), (28672, 4096), (4096, 14336)]
 
 
+def test_merged_layers_leave_no_wavefront_without_work(ask):
+    """Every wavefront of a merged launch has a k-chunk, the staged slice ends within one share of the module's columns,
+    and no workgroup has more than sixteen wavefronts."""
+    layers = [LAYER_8B, H.LAYER_2048, H.LAYER_RAGGED, [(5120, 3072), (3072, 3072), (16384, 3072), (3072, 8192)], [(4096, 8704), (4096, 8704)],
+              [(2560, 2560), (2560, 9728), (9728, 2560)], [(4096, 1024), (4096, 1024)], [(15360, 5120), (5120, 5120), (27648, 5120), (5120, 13824)]]
+    asked = [(s, M, bits, g) for s in layers for M in range(1, 9) for bits, g in ((4, 128), (8, 0), (4, 32))]
+    merged = 0
+    for (shapes, M, bits, g), (one, plans) in zip(asked, ask([_layer(*q) for q in asked])):
+        for (N, K), p in zip(shapes, plans):
+            chunks = K // (512 if bits == 4 else 256)
+            share = -(-chunks // p["waves_k"])
+            assert share * (p["waves_k"] - 1) < chunks, (shapes, M, bits, p)
+            assert 1 <= p["waves_n"] * p["waves_k"] <= 16 and p["waves_n"] <= N // 16 and p["split_k"] == 1
+            assert p["prefetch"] == plans[0]["prefetch"]
+        merged += one == 1
+    assert merged >= 100
+
+
 def test_which_layers_are_merged(ask):
     """The range that the documentation states, the layers that the GPU tests rely on, and sets of modules that were measured
     slower in one launch than apart."""
@@ -120,8 +138,18 @@ def test_which_layers_are_merged(ask):
 
     for bits, g in ((4, 128), (8, 0)):
         assert [one(LAYER_8B, M, bits, g) for M in range(1, 10)] == [True] * 5 + [False] * 4      # 14336 columns: 140 KiB at five rows
+        assert [one(H.LAYER_2048, M, bits, g) for M in range(1, 10)] == [True] * 8 + [False]
     assert not one([(10240, 8192), (8192, 8192), (57344, 8192), (8192, 28672)], 1, 4, 128)        # 256 MB and more
     assert not one(LAYER_8B[:1], 9, 4, 128) and not one(LAYER_8B, [1, 1, 9, 1], 4, 128)
+    # two chunks in flight and several wavefronts along N, in workgroups of different widths
+    for bits, g, M in ((4, 128, 1), (4, 128, 4), (4, 32, 2), (8, 0, 3), (8, 128, 6)):
+        plans = ask([_layer(H.LAYER_2048, M, bits, g)])[0][1]
+        assert {p["prefetch"] for p in plans} == {2} and max(p["waves_n"] for p in plans) >= 3, plans
+        assert len({p["waves_n"] * p["waves_k"] for p in plans}) > 1 and max(p["waves_k"] for p in plans) >= 4, plans
+    # one chunk in flight, a slice that idle wavefronts would not let into the LDS
+    assert all(p["prefetch"] == 1 for p in ask([_layer(H.LAYER_2048, 8, 4, 128)])[0][1])
+    for bits, g in ((4, 128), (4, 32), (8, 0)):
+        assert [one(H.LAYER_RAGGED, [M, max(1, M - 3), M, M, M], bits, g) for M in (1, 4, 5, 8, 9)] == [True] * 3 + [False] * 2
     # slower merged
     for bits, g, M, shapes in ((8, 0, 1, [(5120, 17408), (2048, 4096)]), (8, 0, 4, [(5120, 17408), (2048, 4096)]),
                                (4, 128, 2, [(5120, 17408), (2048, 4096)]), (4, 128, 4, [(7568, 9728), (4640, 2048)]),
