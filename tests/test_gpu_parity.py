@@ -768,11 +768,11 @@ def test_grouped_forward_expert_modules(rtn):
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 32), (8, 0)])
 @pytest.mark.parametrize("M", [1, 4, 5, 8, 9])
 def test_layer_forward_of_independent_and_dependent_modules(rtn, bits, g, M):
-    """Modules of different N and K (workgroups of different widths in one grid, partly filled, several wavefronts along K)
-    with ragged rows: every output against the oracle, also when a graph replays the call.  The same kernel on modules
-    chained through their buffers -- an output that is another's input, an output written twice -- gives what running
+    """Modules of different N and K with ragged rows, some in workgroups of several wavefronts along K, in one launch up to five
+    rows (tests/test_host_plans.py): every output against the oracle, also when a graph replays the call.  The same call on
+    modules chained through their buffers -- an output that is another's input, an output written twice -- gives what running
     them one by one gives, bit for bit."""
-    shapes = [(48, 1024, M), (272, 4096, max(1, M - 3)), (16, 1024, M), (2064, 2048, M), (80, 14336, M)]
+    shapes = [(N, K, max(1, M - 3) if i == 1 else M) for i, (N, K) in enumerate(H.LAYER_RAGGED)]
     mods, refs = [], []
     for i, (N, K, rows) in enumerate(shapes):
         codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=31 + i)
@@ -809,6 +809,31 @@ def test_layer_forward_of_independent_and_dependent_modules(rtn, bits, g, M):
     rtn.rtn_layer_forward(chain)
     torch.cuda.synchronize()
     assert torch.equal(C1, want[1]) and torch.equal(C0, want[2])
+
+
+@pytest.mark.parametrize("bits,g,M", [(4, 128, 1), (4, 128, 4), (4, 32, 2), (8, 0, 3), (8, 128, 6), (4, 128, 8)])
+def test_layer_forward_in_one_launch_at_model_width(rtn, bits, g, M):
+    """A 2048-wide layer, which goes out as one launch with workgroups of several wavefronts along N and along K, of different
+    widths, and (but for the last case) two chunks in flight (tests/test_host_plans.py): every output against the oracle,
+    rows ragged, a second run bit for bit."""
+    mods, refs = [], []
+    for i, (N, K) in enumerate(H.LAYER_2048):
+        rows = max(1, M - i % 2)
+        W = synth.normal_weight(N, K, 0.02, seed=131 + i, device=DEV)
+        qw, sc = rtn.rtn_quantize(W, bits, g)
+        A_t = synth.activation(rows, K, seed=160 + i, device=DEV)
+        mods.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.full((rows, N), float("nan"), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A_t), _to_np(rtn.rtn_unpack(qw, N, K, bits)), _to_np(sc), g or K))
+    plan = rtn.LayerPlan(mods)
+    plan.run()
+    torch.cuda.synchronize()
+    first = [m["C"].clone() for m in mods]
+    for i, m in enumerate(mods):
+        H.assert_linear_close(_to_np(m["C"]), refs[i], f"int{bits} g={g} M={M} module {i}")
+        m["C"].fill_(float("nan"))
+    plan.run()
+    torch.cuda.synchronize()
+    assert all(torch.equal(m["C"], c) for m, c in zip(mods, first))
 
 
 def test_selective_precision_layer(rtn):
