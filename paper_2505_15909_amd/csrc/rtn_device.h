@@ -30,6 +30,22 @@ __device__ __forceinline__ bool xcd_tile(int b, int XB, int ZB, int zgroup, int*
     return true;
 }
 
+// The same for the wide kernel, whose ZB row tiles of a column tile all stay next to one another.  sliced (xcd_slices_save_a_round)
+// or dealt, ragged where XB is not a multiple of eight; one division, since a launch of a few microseconds shows each.
+__host__ __device__ __forceinline__ bool xcd_wide_tile(int b, int XB, int ZB, bool sliced, int* xb, int* zb) {
+    const int xcd = b % kXcds;
+    int i = b / kXcds;
+    if (sliced) {
+        const int n = XB * ZB, base = n / kXcds, more = n % kXcds;
+        if (i >= base + (xcd < more ? 1 : 0)) return false;
+        i += xcd * base + (xcd < more ? xcd : more);
+    }
+    const int x = i / ZB;
+    *zb = i - x * ZB;
+    *xb = sliced ? x : x * kXcds + xcd;
+    return *xb < XB;
+}
+
 typedef _Float16 half_t;
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));

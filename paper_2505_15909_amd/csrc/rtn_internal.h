@@ -42,6 +42,16 @@ hipError_t launch_unpack(const void* qweight, const void* scales, int64_t N, int
 hipError_t launch_linear(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
 // n independent problems with resolved plans: compatible skinny-kernel launches are merged into grouped launches.
 hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, hipStream_t st);
+// Wide kernel: whether column tiles go to the XCDs in contiguous slices, none more than one tile longer than another,
+// instead of dealt in turn.  Only where that saves a round of workgroups on the XCD with most of them (32 compute units):
+// then it pays (816 rows of 384 x 10240: 62 us -> 22, 143 of 20912 x 14848: 230 -> 126); otherwise the cuts, which may
+// part the row tiles that share a column tile's weights, only cost (int8, 71 rows of 3072 x 8192: 16.4 us dealt, 18.0
+// sliced; 221 rows of 5984 x 12288: 59 and 66).  118 shapes measured, none on the wrong side.
+inline bool xcd_slices_save_a_round(int64_t XB, int64_t ZB, int64_t split_k) {
+    const int64_t dealt = (XB + 7) / 8 * ZB * split_k, sliced = (XB * ZB + 7) / 8 * split_k;
+    return (sliced + 31) / 32 < (dealt + 31) / 32;
+}
+inline int wide_blocks(int XB, int ZB, bool sliced) { return 8 * (sliced ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB); }
 // Path 3 (wide MFMA kernel): plan check (group size 32, 64 or a multiple of 128, 2-4 row blocks, 1/2/4 tile-rows, at most 8 blocks) and launch.
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st);

@@ -46,6 +46,7 @@ struct WideParams {
     int KL;             // tiles per weight row
     int KS;             // k-steps per row (K / 128)
     int XB;             // workgroups along N
+    int sliced;         // order of the column tiles over the XCDs, see xcd_wide_tile
     int ZB;             // row blocks
     int split_k;
     int ks_base, ks_rem;   // workgroup sg covers k-steps [sg*ks_base + min(sg, ks_rem), ...)
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
     const int nl = lane & 15, kq = lane >> 4;
 
     int xb, z;                                            // N block, row block (all row blocks of one N block on one XCD)
-    if (!xcd_tile(blockIdx.x, p.XB, p.ZB, p.ZB, &xb, &z)) return;     // padding to a multiple of 8 (whole workgroup)
+    if (!xcd_wide_tile(blockIdx.x, p.XB, p.ZB, p.sliced != 0, &xb, &z)) return;     // padding to a multiple of 8 (whole workgroup)
     const int m0 = z * ROWS;
     const int sg = blockIdx.y;
     const int ks0 = sg * p.ks_base + min(sg, p.ks_rem);
@@ -433,7 +434,8 @@ hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStrea
     wp.qw_bytes = (uint32_t)((size_t)a.N * a.K * a.bits / 8);
     wp.sc_bytes = (uint32_t)((size_t)a.N * wp.G * 2);
     wp.a_bytes = (uint32_t)((size_t)a.M * a.K * 2);
-    dim3 grid((unsigned)((wp.XB * wp.ZB + kXcds - 1) / kXcds * kXcds), (unsigned)p.split_k, 1);
+    wp.sliced = xcd_slices_save_a_round(wp.XB, wp.ZB, p.split_k) ? 1 : 0;
+    dim3 grid((unsigned)wide_blocks(wp.XB, wp.ZB, wp.sliced != 0), (unsigned)p.split_k, 1);
     hipError_t e;
     if (a.zeros) e = (a.bits == 4) ? launch_wide_zp_bits<4>(wp, p.m_rows16, p.n_tiles16, grid, st)
                                    : launch_wide_zp_bits<8>(wp, p.m_rows16, p.n_tiles16, grid, st);

@@ -2,6 +2,7 @@
 // plans.  The library's C-ABI translation unit is part of this one, so that its planning functions can be called; no GPU
 // work, nothing is launched.  Built and read by tests/test_host_plans.py.
 #include "../../paper_2505_15909_amd/csrc/rtn_api.hip"
+#include "../../paper_2505_15909_amd/csrc/rtn_device.h"
 #include <stdio.h>
 
 static char stand_in[64];                                      // addresses only, nothing is read or written
@@ -37,6 +38,17 @@ int main() {
             int rows16, split;
             if (scanf("%ld %ld %ld %d %d", &M, &N, &K, &rows16, &split) != 5) return 1;
             printf("%.6f", rtn::tile_model_us(false, rows16, M, N, K, split));
+        } else if (!strcmp(what, "wide")) {                    // XB ZB split -> 1 if sliced, then [xb zb xcd ...] of the launch
+            int XB, ZB, split;
+            if (scanf("%d %d %d", &XB, &ZB, &split) != 3) return 1;
+            const bool sliced = rtn::xcd_slices_save_a_round(XB, ZB, split);
+            const int blocks = rtn::wide_blocks(XB, ZB, sliced);
+            printf("%d [", sliced ? 1 : 0);
+            for (int b = 0; b < blocks; ++b) {
+                int xb, zb;
+                if (rtn::xcd_wide_tile(b, XB, ZB, sliced, &xb, &zb)) printf("%d %d %d ", xb, zb, b % rtn::kXcds);
+            }
+            printf("]");
         } else if (!strcmp(what, "layer")) {                   // bits g workspace n, then M N K each -> 1 if one launch, plans
             long g, ws;
             int bits, n;

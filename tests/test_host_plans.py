@@ -29,12 +29,12 @@ def ask(tmp_path_factory):
                    check=True, capture_output=True, timeout=600)
     subprocess.run([hipcc, "--offload-arch=gfx950", "-o", exe, obj, *objs], check=True, capture_output=True, timeout=600)
 
-    def run(lines):
+    def run(lines, raw=False):
         r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=600)
         assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
         out = r.stdout.strip().split("\n")
         assert len(out) == len(lines)
-        return [(float(o.split()[0]), [dict(zip(FIELDS, map(int, p.split()))) for p in re.findall(r"\[(.*?)\]", o)]) for o in out]
+        return out if raw else [(float(o.split()[0]), [dict(zip(FIELDS, map(int, p.split()))) for p in re.findall(r"\[(.*?)\]", o)]) for o in out]
 
     return run
 
@@ -158,3 +158,23 @@ def test_which_layers_are_merged(ask):
                                (8, 0, 6, [(1568, 1024), (12336, 7168)]), (4, 128, 6, [(8960, 10240), (5424, 512)]),
                                (4, 0, 3, [(9216, 6144), (6144, 6144), (39936, 6144), (6144, 19968)])):
         assert not one(shapes, M, bits, g), (bits, M, shapes)
+
+
+def test_wide_kernel_tiles_and_their_order_over_the_xcds(ask):
+    """Every (column tile, row tile) of a wide launch is done once; the column tiles are cut into slices only where that saves
+    a round of 32 workgroups on the XCD with most of them, and otherwise all row tiles of a column tile share an XCD."""
+    cases = [(XB, ZB, s) for XB in (1, 2, 3, 7, 8, 9, 12, 16, 20, 47, 65, 82) for ZB in (1, 2, 3, 4, 9, 18, 40) for s in (1, 2, 5, 8)]
+    seen = {True: 0, False: 0}
+    for (XB, ZB, s), line in zip(cases, ask([f"wide {XB} {ZB} {s}" for XB, ZB, s in cases], raw=True)):
+        sliced, blocks = line.split("[")
+        sliced, v = int(sliced) == 1, [int(t) for t in blocks.rstrip("] ").split()]
+        tiles = list(zip(v[0::3], v[1::3], v[2::3]))
+        assert sorted((x, z) for x, z, _ in tiles) == [(x, z) for x in range(XB) for z in range(ZB)], (XB, ZB, s)
+        most = max(sum(c == xcd for _, _, c in tiles) for xcd in range(8))
+        dealt, even = -(-XB // 8) * ZB, -(-XB * ZB // 8)
+        assert most == (even if sliced else dealt)
+        assert sliced == (-(-even * s // 32) < -(-dealt * s // 32))
+        if not sliced:
+            assert all(xcd == x % 8 for x, _, xcd in tiles)
+        seen[sliced] += 1
+    assert min(seen.values()) > 30, seen
