@@ -98,13 +98,6 @@ double wide_model_us(int64_t M, int64_t N, int64_t K, int bits, int mb, int wv, 
     return t * 1e6;
 }
 
-// Groups of 32 and 64 columns from 20 rows up: the wide kernel with several scales per k-step.  Up to 19 rows the skinny
-// kernel still stages a 4096-column slice in one piece and is ahead on the small matrices (8B qkv, group 64: 9.3 us
-// against 11.5 at 19 rows, 15.8 against 11.4 at 20; level on the 70B ones).  Above, it runs 64 rows at a time; the wide
-// kernel takes 27 us against 44 (8B qkv), 83 against 121 (8B gate_up) and 148 against 207 (70B down) at 256 rows, 597
-// against 823 on 8B gate_up at 2048.  A partial explicit configuration keeps to the skinny kernel on these groups.
-bool wide_small_groups(int64_t M, int64_t g) { return (g == 64 || g == 32) && M >= 20; }
-
 void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan* p) {
     p->path = 3;
     p->m_rows16 = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
@@ -373,6 +366,68 @@ bool skinny_plan_from_table(int64_t M, int64_t N, int64_t K, int bits, size_t ld
     return false;
 }
 
+// Groups of 32 and 64 columns from 20 rows up: the wide kernel with several scales per k-step, or the skinny kernel 32 or 64
+// rows at a time (16 with zero points), whichever is modelled faster.  Up to 19 rows the skinny kernel is ahead (8B qkv, group
+// 64: 9.3 us against 11.5 at 19 rows, 15.8 against 11.4 at 20).  Above, the wide kernel leads on large matrices -- 27 us against
+// 44 (8B qkv), 83 against 121 (8B gate_up), 148 against 207 (70B down) at 256 rows -- and the skinny kernel
+//   - where a workgroup's rows fit the LDS in one piece and there are few workgroups: the wide kernel walks K in steps of half a
+//     microsecond and hardly splits so small a matrix.  20 rows of 2048 x 2048: 4.7 us against 11.2 (zero points 3.9 against
+//     13.3), of 3072 x 3072 int4 group 64 12.3 against 16.3, 147 rows of 592 x 1024 6.2 against 9.2;
+//   - up to 32 rows on the matrices it streams (streams_to_32_rows): int4 20 rows of 28672 x 8192 33 us against 41.
+// Both models have the form of wide_model_us (serial time of a workgroup against streamed bytes) and were fitted to both kernels'
+// times on 1018 problems (1015 with zero points) of 128 to 106496 x 512 to 53248 at 20 to 300 rows: 7 % and 10 % rms (8 and
+// 17 %).  The pick is 0.3 % (0.7 %) behind the better kernel on average, more than 10 % on one problem in 93 (42); the wide
+// kernel everywhere would be 9 % (26 %) behind.
+bool small_groups(int64_t M, int64_t g) { return (g == 64 || g == 32) && M >= 20; }
+
+double small_groups_wide_us(const LinearArgs& a, const LinearPlan& p) {
+    struct Fit { double base, split, start, step, rows, tiles, bits8, hbm, l2; };
+    static const Fit kFit = {3.2, 2.87, 0.21, 0.52, 0.22, 0.36, 0.09, 1.09, 0.39}, kFitZp = {0.83, 3.76, 2.02, 0.71, 0.12, 0.39, 0.1, 1.57, 0.31};
+    const Fit& f = a.zeros ? kFitZp : kFit;
+    const int64_t cols = 16 * p.n_tiles16 * p.waves_n, XB = (a.N + cols - 1) / cols;
+    const double wgs = (double)(XB * p.m_blocks * p.split_k), steps = (double)((a.K / 128 + p.split_k - 1) / p.split_k);
+    const double wg_us = f.start + steps * f.step * (1.0 + f.rows * (p.m_rows16 - 2) + f.tiles * (p.n_tiles16 - 1) * p.m_rows16 + (a.bits == 8 ? f.bits8 : 0.0));
+    const double serial = std::max(1.0, wgs / 256.0) * wg_us;
+    const double stream = f.hbm * a.N * a.K * a.bits / 8.0 / 6.5e6 + f.l2 * XB * p.m_blocks * 16.0 * p.m_rows16 * a.K * 2.0 / 1.1e7;
+    double t = f.base + std::cbrt(serial * serial * serial + stream * stream * stream);
+    if (p.split_k > 1) t += f.split + (double)a.M * a.N * p.split_k * 8.0 / 4.5e6;
+    return t;
+}
+
+double small_groups_skinny_us(const LinearArgs& a, const LinearPlan& p) {
+    struct Fit { double base, split, rounds, chunk, rows, bits8, slice, stage, hbm, l2; };
+    static const Fit kFit = {1.83, 3.55, 0.51, 2.14, 0.23, -0.49, 0.96, 0.83, 0.9, 1.54}, kFitZp = {2.49, 0.0, 1.24, 1.42, 0.0, -0.22, 0.41, 0.47, 2.38, 1.24};
+    const Fit& f = a.zeros ? kFitZp : kFit;
+    const rtn::StagePlan s = rtn::linear_stages(a, p);
+    const double wgs = (double)((a.N / 16 + p.waves_n - 1) / p.waves_n * p.split_k * p.m_blocks);
+    const double resident = std::max(1.0, std::min(std::floor(16.0 / (p.waves_n * p.waves_k)), std::floor((double)rtn::kMaxLdsBytes / (double)s.lds)));
+    const double wg_us = s.per * f.chunk * (1.0 + f.rows * (p.m_rows16 - 1) + (a.bits == 8 ? f.bits8 : 0.0)) + f.slice * (double)s.slice / 102400.0 +
+                         (s.nstage > 1 ? f.stage * s.nstage : 0.0);
+    const double serial = std::pow(std::max(1.0, wgs / (256.0 * resident)), f.rounds) * wg_us;
+    const double stream = f.hbm * a.N * a.K * a.bits / 8.0 / 6.5e6 + f.l2 * wgs * (double)s.slice / 1.1e7;
+    double t = f.base + std::cbrt(serial * serial * serial + stream * stream * stream);
+    if (p.split_k > 1) t += f.split + (double)a.M * a.N * p.split_k * 8.0 / 4.5e6;
+    return t;
+}
+
+// more than 16 rows: the wide kernel, except at 17-32 rows on large matrices, where the skinny kernel's pure
+// weight streaming still wins.  4 bit: from 40 MB with rows of 8192 columns and more, 16 wavefronts side by side
+// (6-20 % faster on the 70B and 405B shapes except the 70B o matrix; the wide kernel wins on every 8B shape).
+// 8 bit: above 256 MB, the same 16-wavefront shape (with K split to one round of workgroups it is 15-20 % faster
+// than 8 wavefronts on the 70B gate_up and 405B qkv matrices and level on the 405B gate_up and down matrices).
+bool streams_to_32_rows(int64_t M, int64_t N, int64_t K, int bits) {
+    const size_t packed_bytes = (size_t)N * K * bits / 8;
+    return M <= 32 && ((bits == 4 && packed_bytes >= ((size_t)40 << 20) && K >= 8192) || packed_bytes > ((size_t)256 << 20));
+}
+
+// a: M, N, K, bits, g and whether there are zero points; skinny, wide: the kernels' own plans.
+bool skinny_on_small_groups(const LinearArgs& a, const LinearPlan& skinny, const LinearPlan& wide) {
+    const bool streams = streams_to_32_rows(a.M, a.N, a.K, a.bits) && a.N * a.K * a.bits / 8 > (int64_t)40 << 20;   // (at 40 MiB the models decide)
+    if (!a.zeros && streams) return true;
+    if (a.M > (a.zeros ? 64 : 32) && a.N * a.K >= 8000000) return false;                  // beyond the models' accuracy
+    return small_groups_skinny_us(a, skinny) < (a.zeros ? 0.95 : 1.0) * small_groups_wide_us(a, wide);
+}
+
 // force_path: 0 = choose the path, otherwise the default plan of that path.  workspace: bytes at hand for the tile kernel's
 // partial sums (by default what its best plan may take): kernel, height, split and cut are chosen within it, instead of
 // the unconstrained plan with its split cut down.  Within 16 MiB, cut down against chosen: 1011 rows of 4608 x 5120 104 us
@@ -381,20 +436,18 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
                      int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile) {
     LinearPlan p;
     p.n_tiles16 = 1;
-    if (force_path == 0 && wide_small_groups(M, g)) {
+    if (force_path == 0 && small_groups(M, g)) {
+        LinearArgs a;
+        a.M = M; a.N = N; a.K = K; a.bits = bits; a.g = g;
         wide_plan(M, N, K, bits, g, &p);
-        return p;
+        const LinearPlan skinny = auto_plan(M, N, K, bits, g, lds_limit, 1);
+        // (the wide kernel's split shrinks to the workspace, the skinny kernel's does not)
+        const bool held = skinny.split_k == 1 || (size_t)M * N * sizeof(float) * skinny.split_k <= workspace;
+        return held && skinny_on_small_groups(a, skinny, p) ? skinny : p;
     }
-    // more than 16 rows: the wide kernel, except at 17-32 rows on large matrices, where the skinny kernel's pure
-    // weight streaming still wins.  4 bit: from 40 MB with rows of 8192 columns and more, 16 wavefronts side by side
-    // (6-20 % faster on the 70B and 405B shapes except the 70B o matrix; the wide kernel wins on every 8B shape).
-    // 8 bit: above 256 MB, the same 16-wavefront shape (with K split to one round of workgroups it is 15-20 % faster
-    // than 8 wavefronts on the 70B gate_up and 405B qkv matrices and level on the 405B gate_up and down matrices).
     const size_t packed_bytes = (size_t)N * K * bits / 8;
-    const bool streams16 = M <= 32 && ((bits == 4 && packed_bytes >= ((size_t)40 << 20) && K >= 8192) ||
-                                       packed_bytes > ((size_t)256 << 20));
-    const bool streams_at_32 = streams16;
-    const bool wide_wins = g % 128 == 0 && M > 16 && !streams_at_32;
+    const bool streams16 = streams_to_32_rows(M, N, K, bits);
+    const bool wide_wins = g % 128 == 0 && M > 16 && !streams16;
     const bool tall_wide = wide_wins && bits == 4 && M >= 128 && (M + 127) / 128 * 2 <= (M + 63) / 64 &&
                            packed_bytes >= ((size_t)40 << 20) && K > N;
     // The tile kernel may serve what tile_line admits.  Of that it leaves to the wide kernel what does not give it a full
@@ -586,7 +639,7 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     const bool whole = cfg && cfg->path && cfg->prefetch && cfg->waves_n && cfg->waves_k && cfg->split_k && cfg->m_rows16 && cfg->n_tiles16;
     if (whole) p.m_blocks = 1;                                  // every field comes from the caller
     else {
-        const int path = !cfg ? 0 : cfg->path == 0 && wide_small_groups(a.M, a.g) ? 1 : cfg->path;
+        const int path = !cfg ? 0 : cfg->path == 0 && small_groups(a.M, a.g) ? 1 : cfg->path;
         p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, path, 0, tile_workspace(a, workspace_nbytes));
     }
     if (cfg) {
@@ -616,7 +669,7 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     }
     if (p.path >= 3) {
         bool ok = p.path == 3 ? rtn::wide_plan_valid(a, p) : rtn::tile_plan_valid(a, p);
-        if (p.path == 3 && a.g % 128 != 0 && cfg && !whole) ok = false;       // no defaults to fill in, see wide_small_groups
+        if (p.path == 3 && a.g % 128 != 0 && cfg && !whole) ok = false;       // no defaults to fill in, see small_groups
         if (!ok || p.split_k > kMaxSplitK) return RTN_ERR_CONFIG;
         if ((uint64_t)a.N * a.K * a.bits / 8 >= 0x7FFF0000ull || (uint64_t)a.M * a.K * 2 >= 0x7FFF0000ull)
             return RTN_ERR_SHAPE;                               // 32-bit buffer offsets
@@ -642,6 +695,30 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     }
     *out = p;
     return RTN_OK;
+}
+
+// The asymmetric variant's automatic plan.
+rtn_status resolve_plan_zp(const LinearArgs& a, size_t workspace_nbytes, LinearPlan* p) {
+    // the small-batch kernel, 16 rows per workgroup, planned as for min(M, 16) rows
+    LinearPlan skinny = auto_plan(a.M < 16 ? a.M : 16, a.N, a.K, a.bits, a.g, (size_t)device_max_lds(), 1);
+    skinny.prefetch = 1; skinny.m_rows16 = 1; skinny.n_tiles16 = 1;
+    skinny.m_blocks = (int)((a.M + 15) / 16);
+    if (a.M > 16) skinny.split_k = 1;
+    if (a.M > 16 && (a.g % 128 == 0 || small_groups(a.M, a.g))) {
+        // the wide kernel's zero-point instantiations: 8 wavefronts, at most two tile-rows per wavefront
+        LinearPlan h;
+        wide_plan(a.M, a.N, a.K, a.bits, a.g, &h);
+        h.waves_n = 8; h.n_tiles16 = std::min(h.n_tiles16, 2);
+        if (a.g % 128 == 0 || !skinny_on_small_groups(a, skinny, h)) {
+            // as many of the plan's K splits as the workspace passed can hold
+            const size_t fit = a.workspace ? workspace_nbytes / ((size_t)a.M * a.N * sizeof(float)) : 0;
+            if ((size_t)h.split_k > fit) h.split_k = fit < 1 ? 1 : (int)fit;
+            const rtn_linear_cfg cfg = plan_cfg(h);
+            if (resolve_plan(a, &cfg, workspace_nbytes, p) == RTN_OK) return RTN_OK;
+        }
+    }
+    const rtn_linear_cfg cfg = plan_cfg(skinny);
+    return resolve_plan(a, &cfg, workspace_nbytes, p);
 }
 
 // The one or two launches of a call, in order, with their plans.
@@ -1138,27 +1215,8 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
     a.workspace = static_cast<float*>(dev_workspace);
     a.M = M; a.N = N; a.K = K; a.g = g; a.bits = bits;
     LinearPlan p;
-    rtn_linear_cfg cfg;
-    bool planned = false;
-    if (M > 16 && (g % 128 == 0 || wide_small_groups(M, g))) {
-        // the wide kernel's zero-point instantiations: 8 wavefronts, at most two tile-rows per wavefront
-        LinearPlan h;
-        wide_plan(M, N, K, bits, g, &h);
-        cfg.path = 3; cfg.prefetch = 1; cfg.waves_n = 8; cfg.waves_k = 1; cfg.split_k = h.split_k;
-        // as many of the plan's K splits as the workspace passed can hold
-        const size_t fit = dev_workspace ? workspace_nbytes / ((size_t)M * N * sizeof(float)) : 0;
-        if ((size_t)cfg.split_k > fit) cfg.split_k = fit < 1 ? 1 : (int)fit;
-        cfg.m_rows16 = h.m_rows16; cfg.n_tiles16 = h.n_tiles16 > 2 ? 2 : h.n_tiles16;
-        planned = resolve_plan(a, &cfg, workspace_nbytes, &p) == RTN_OK;
-    }
-    if (!planned) {
-        // the small-batch kernel, 16 rows per workgroup, planned as for min(M, 16) rows
-        LinearPlan h = auto_plan(M < 16 ? M : 16, N, K, bits, g, (size_t)device_max_lds(), 1);
-        cfg.path = 1; cfg.prefetch = 1; cfg.waves_n = h.waves_n; cfg.waves_k = h.waves_k;
-        cfg.split_k = M <= 16 ? h.split_k : 1; cfg.m_rows16 = 1; cfg.n_tiles16 = 1;
-        st = resolve_plan(a, &cfg, workspace_nbytes, &p);
-        if (st != RTN_OK) return st;
-    }
+    st = resolve_plan_zp(a, workspace_nbytes, &p);
+    if (st != RTN_OK) return st;
     hipError_t e = rtn::launch_linear(a, p, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
 }
@@ -1181,7 +1239,7 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
     for (int i = 0; i < n_mods; ++i) {
         const LinearArgs& a = args[i];
         rtn_status st = RTN_ERR_CONFIG;
-        if (!wide_small_groups(a.M, a.g)) {
+        if (!small_groups(a.M, a.g)) {
             // planned as one slice of a launch that streams all the small-batch modules together
             const LinearPlan h = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, 0, a.M <= 16 ? steps_total : 0,
                                            tile_workspace(a, workspace_nbytes));

@@ -31,6 +31,10 @@ struct LinearArgs {
     const void* zeros = nullptr;   // fp16 [N, K/g] integer zero points (asymmetric variant; skinny and wide kernels) or null
 };
 
+// How a skinny-kernel workgroup gets its activations: k-chunks per wavefront, stages, bytes of its whole slice, LDS it takes.
+struct StagePlan { int per, nstage; size_t slice, lds; };
+StagePlan linear_stages(const LinearArgs& a, const LinearPlan& p);
+
 hipError_t launch_quantize(const void* W, int64_t N, int64_t K, int bits, int64_t g, float divisor,
                            void* qweight, void* scales, hipStream_t st);
 // Asymmetric variant: codes, fp16 scales and fp16 integer zero points Z, dequantised weight S (q + Z).

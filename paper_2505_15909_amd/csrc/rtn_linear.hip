@@ -474,7 +474,7 @@ constexpr size_t kMultiStageLdsWide = 72 * 1024;       // more than 16 activatio
 struct StageGeom {
     int per, sc, nstage, rows;
     bool multi, fits;
-    size_t lds, stage_bytes;
+    size_t lds, stage_bytes, slice_bytes;
 };
 
 static StageGeom stage_geometry(const LinearArgs& a, const LinearPlan& p) {
@@ -507,6 +507,7 @@ static StageGeom stage_geometry(const LinearArgs& a, const LinearPlan& p) {
     g.sc = sc;
     g.nstage = g.multi ? (g.per + sc - 1) / sc : 1;
     g.stage_bytes = bytes_of(sc);
+    g.slice_bytes = bytes_of(sc_full);
     const size_t bytes = g.multi ? 2 * g.stage_bytes : g.stage_bytes;
     g.lds = bytes > red ? bytes : red;
     return g;
@@ -516,6 +517,11 @@ bool linear_plan_fits(const LinearArgs& a, const LinearPlan& p, size_t lds_limit
     const StageGeom g = stage_geometry(a, p);
     if (p.path == 2 && g.multi) return false;            // the dot-product variant stages once
     return g.fits && g.lds <= lds_limit;
+}
+
+StagePlan linear_stages(const LinearArgs& a, const LinearPlan& p) {
+    const StageGeom g = stage_geometry(a, p);
+    return {g.per, g.nstage, g.slice_bytes, g.lds};
 }
 
 size_t linear_lds_bytes(const LinearArgs& a, const LinearPlan& p) { return stage_geometry(a, p).lds; }

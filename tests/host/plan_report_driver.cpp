@@ -33,6 +33,16 @@ int main() {
             const rtn_status st = linear_launches(problem(M, N, K, bits, g > 0 ? g : K, ws > 0), nullptr, (size_t)ws, part, plan, &n);
             printf("%d", (int)st);
             for (int i = 0; st == RTN_OK && i < n; ++i) print_plan(part[i], plan[i]);
+        } else if (!strcmp(what, "asym")) {                    // the same with zero points: status and plan
+            long M, N, K, g, ws;
+            int bits;
+            if (scanf("%ld %ld %ld %d %ld %ld", &M, &N, &K, &bits, &g, &ws) != 6) return 1;
+            LinearArgs a = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
+            a.zeros = stand_in;
+            LinearPlan plan;
+            const rtn_status st = resolve_plan_zp(a, (size_t)ws, &plan);
+            printf("%d", (int)st);
+            if (st == RTN_OK) print_plan(a, plan);
         } else if (!strcmp(what, "tile")) {                    // M N K rows16 split -> modelled time of a tile-kernel launch
             long M, N, K;
             int rows16, split;

@@ -178,3 +178,25 @@ def test_wide_kernel_tiles_and_their_order_over_the_xcds(ask):
             assert all(xcd == x % 8 for x, _, xcd in tiles)
         seen[sliced] += 1
     assert min(seen.values()) > 30, seen
+
+
+def test_small_groups_run_on_the_kernel_that_measured_faster(ask):
+    """Groups of 32 and 64 columns from 20 rows: problems on which one kernel was measured at least 15 % ahead go to it, with and
+    without zero points; up to 19 rows they stay on the skinny kernel; without a workspace every call is still accepted."""
+    skinny = [(20, 2048, 2048, 4, 64), (33, 3072, 2048, 8, 32), (38, 384, 2048, 4, 64), (20, 3072, 3072, 4, 64), (147, 592, 1024, 8, 64),
+              (20, 304, 512, 8, 64), (31, 6624, 2048, 8, 64), (24, 16384, 3072, 4, 64), (31, 608, 2560, 8, 64), (52, 6976, 1024, 4, 64),
+              (20, 8192, 28672, 4, 64), (20, 18432, 16384, 4, 64), (32, 106496, 16384, 4, 64), (20, 16384, 53248, 8, 64)]
+    wide = [(20, 6144, 4096, 4, 64), (256, 6144, 4096, 4, 64), (256, 28672, 4096, 4, 64), (256, 8192, 28672, 4, 64), (64, 2048, 2048, 4, 64),
+            (48, 3072, 3072, 4, 64), (33, 18432, 16384, 4, 64), (28, 28032, 1024, 8, 32), (31, 28160, 1536, 4, 64), (20, 2048, 8192, 4, 64),
+            (2048, 28672, 4096, 4, 64), (42, 2640, 1536, 4, 64)]
+    skinny_zp = [(20, 2048, 2048, 4, 64), (24, 2048, 2048, 8, 64), (32, 3072, 3072, 4, 64), (184, 256, 1536, 8, 32), (64, 3072, 2048, 4, 32),
+                 (29, 1040, 4096, 4, 64), (24, 144, 6656, 4, 64), (21, 368, 4608, 4, 64), (51, 480, 3072, 8, 32)]
+    wide_zp = [(256, 6144, 4096, 4, 64), (256, 28672, 4096, 4, 64), (33, 16384, 2048, 8, 64), (64, 5120, 3072, 8, 64), (48, 6144, 4096, 8, 32),
+               (20, 57344, 8192, 8, 64), (192, 8192, 8192, 8, 32)]
+    for kind, problems, path in (("linear", skinny, 1), ("linear", wide, 3), ("asym", skinny_zp, 1), ("asym", wide_zp, 3)):
+        for p, (status, launches) in zip(problems, ask([f"{kind} {' '.join(map(str, p))} {16 * MIB}" for p in problems])):
+            assert status == 0 and [q["path"] for q in launches] == [path], (kind, p, launches)
+        for p, (status, _) in zip(problems, ask([f"{kind} {' '.join(map(str, p))} 0" for p in problems])):
+            assert status == 0, (kind, p)
+        for p, (status, launches) in zip(problems, ask([f"{kind} 19 {' '.join(map(str, p[1:]))} {16 * MIB}" for p in problems])):
+            assert status == 0 and launches[0]["path"] == 1
