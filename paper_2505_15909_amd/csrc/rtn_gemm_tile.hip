@@ -395,7 +395,9 @@ void fill_common(TileParams& tp, const void* A, void* C, float* ws, int64_t M, i
 
 }  // namespace
 
-// One workgroup runs per compute unit, so a launch takes rounds of 256 workgroups.  A 64-column step of a full round takes
+// One workgroup runs per compute unit, so a launch takes rounds of 32 workgroups on each of the eight XCDs; the one with most
+// of the tiles (xcd_tile) counts for all (245 rows of 8208 x 9728: 33 tall tiles in seven splits are 231 workgroups, but 35
+// of them on one XCD: 88 us, against 63 for 66 short tiles in three).  A 64-column step of a full round takes
 // 1.58 us with a 256-row tile and 1.00 with a 128-row one (packed weights; 1.54 and 0.87 dense), of a round that fills half
 // the chip or less 1.26 and 0.82 (1.12 and 0.87): the clock depends on how much of the chip is busy.  A round costs 6 us
 // besides; a split adds the reduce launch and the partial sums' trip through the workspace, mostly cache.  Fitted to 480
@@ -405,7 +407,8 @@ double tile_model_us(bool dense, int rows16, int64_t M, int64_t N, int64_t K, in
     const bool tall = rows16 == 8;
     const double half = tall ? (dense ? 1.12 : 1.26) : (dense ? 0.87 : 0.82);
     const double full = tall ? (dense ? 1.54 : 1.58) : (dense ? 0.87 : 1.00);
-    const int64_t tiles = ((N + kTN - 1) / kTN) * ((M + 32 * rows16 - 1) / (32 * rows16)) * split_k;
+    const int64_t per_xcd = (((N + kTN - 1) / kTN) * ((M + 32 * rows16 - 1) / (32 * rows16)) + kXcds - 1) / kXcds;
+    const int64_t tiles = per_xcd * kXcds * split_k;
     const double steps = (double)((K / kBK + split_k - 1) / split_k), part = (double)(tiles % 256) / 256.0;
     double t = (double)(tiles / 256) * (steps * full + 6.0);
     if (part > 0.0) t += steps * (half + (full - half) * (part > 0.5 ? 2.0 * part - 1.0 : 0.0)) + 6.0;

@@ -200,3 +200,18 @@ def test_small_groups_run_on_the_kernel_that_measured_faster(ask):
             assert status == 0, (kind, p)
         for p, (status, launches) in zip(problems, ask([f"{kind} 19 {' '.join(map(str, p[1:]))} {16 * MIB}" for p in problems])):
             assert status == 0 and launches[0]["path"] == 1
+
+
+def test_tile_launches_count_their_rounds_on_each_xcd(ask):
+    """Tiles that leave one of the eight XCDs with more than its 32 compute units take a second round there, however few there
+    are in all: one tile more than eights costs what seven more cost, and launches that were measured 1.4 x slower for it are
+    not chosen."""
+    t = [v for v, _ in ask([f"tile 245 {N} 9728 8 7" for N in (8192, 8208, 10240)])]
+    assert t[1] > 1.5 * t[0] and abs(t[1] - t[2]) < 0.15 * t[1], t
+    problems = [(245, 8208, 9728), (208, 9184, 9216), (227, 8512, 11264), (226, 9024, 8192)]
+    for (M, N, K), (status, launches) in zip(problems, ask([f"linear {M} {N} {K} 4 128 {256 * MIB}" for M, N, K in problems])):
+        assert status == 0
+        for q in launches:
+            if q["path"] == 4:
+                tiles = -(-N // 256) * -(-q["M"] // (32 * q["m_rows16"]))
+                assert -(-tiles // 8) * q["split_k"] <= 32, (M, N, K, q)
