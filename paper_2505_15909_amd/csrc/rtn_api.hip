@@ -451,9 +451,11 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
     const bool tall_wide = wide_wins && bits == 4 && M >= 128 && (M + 127) / 128 * 2 <= (M + 63) / 64 &&
                            packed_bytes >= ((size_t)40 << 20) && K > N;
     // The tile kernel may serve what tile_line admits.  Of that it leaves to the wide kernel what does not give it a full
-    // round of 128 x 256 tiles and is not below 1.15 x the wide plan's modelled time (in one launch or two; the wide
-    // kernel's model, fitted at 32 to 256 rows, is about that much short of the measured times here): 8B qkv at 1024 rows
-    // 64 us against 68, 4096 x 4096 at 1536 66 against 71.
+    // round of 128 x 256 tiles and where it is not modelled ahead (in one launch or two).  The wide kernel's model, fitted at
+    // 32 to 256 rows, falls short of its times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and 1.30 at 8 bit
+    // (means over 460 problems; the tile kernel's by 1.03), so that 8192 x 8192 int8 group 128 at 622 rows took 152 us instead
+    // of 115, 4096 x 4096 at 1398 rows 78 instead of 63.  Wide ahead of tile: 15760 x 7168 int4 per channel at 382 rows 98
+    // against 106, 5392 x 4096 at 870 rows 56 against 58.
     bool tile_wins = false;
     LinearPlan w;
     if (force_path == 3 || (force_path == 0 && wide_wins)) wide_plan(M, N, K, bits, g, &w);
@@ -466,7 +468,8 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
                 double t_tile = 0, t_wide_fit = t_wide;         // of what resolve_plan leaves of the wide plan's split
                 if (w.split_k > fit) t_wide_fit = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, (int)fit);
                 tile_two_launches(false, M, N, K, workspace, &t_tile);
-                tile_wins = t_tile * 0.87 < t_wide_fit;
+                const double short_of = bits == 4 ? (g == 128 ? 1.26 : 1.20) : (g == 128 ? 1.51 : 1.30);
+                tile_wins = t_tile * 1.03 < t_wide_fit * short_of;
             }
         }
     }

@@ -215,3 +215,14 @@ def test_tile_launches_count_their_rounds_on_each_xcd(ask):
             if q["path"] == 4:
                 tiles = -(-N // 256) * -(-q["M"] // (32 * q["m_rows16"]))
                 assert -(-tiles // 8) * q["split_k"] <= 32, (M, N, K, q)
+
+
+def test_tile_and_wide_kernel_share_their_range_as_measured(ask):
+    """Problems on which the tile kernel was measured at least 15 % ahead of the wide one go to it; some on which the wide kernel was
+    ahead, or the tile kernel may not serve at all, stay on the wide kernel, which does not round the scaled weights."""
+    tile = [(622, 8192, 8192, 8, 128), (1398, 4096, 4096, 8, 128), (3183, 1904, 5632, 8, 128), (1104, 4816, 7168, 8, 128),
+            (2901, 2048, 2048, 8, 128), (1007, 6144, 4096, 8, 128), (2645, 1616, 1536, 8, 128), (2048, 28672, 4096, 4, 128)]
+    wide = [(382, 15760, 7168, 4, 0), (870, 5392, 4096, 4, 0), (619, 7936, 5120, 4, 0), (200, 4096, 4096, 4, 128), (128, 4096, 4096, 8, 128)]
+    for problems, path in ((tile, 4), (wide, 3)):
+        for p, (status, launches) in zip(problems, ask([f"linear {' '.join(map(str, p))} {256 * MIB}" for p in problems])):
+            assert status == 0 and all(q["path"] == path for q in launches), (p, launches)
