@@ -1163,7 +1163,7 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
         bool ok = true;
         for (int i = 0; i < n_mods && ok; ++i) ok = mods[i].M <= 8 && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
         if (ok && modules_independent(args, n_mods) && merged_layer_plans(args, n_mods, workspace_nbytes, plans)) {
-            hipError_t e = rtn::launch_linear_grouped(args, plans, n_mods, static_cast<hipStream_t>(stream));
+            hipError_t e = rtn::launch_linear_grouped(args, plans, n_mods, true, static_cast<hipStream_t>(stream));
             return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
         }
     }
@@ -1224,22 +1224,12 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
     return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
 }
 
-rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
-                               void* stream) {
-    if (!mods) return RTN_ERR_NULL;
-    if (n_mods <= 0) return RTN_ERR_SHAPE;
-    if (!aligned16(dev_workspace)) return RTN_ERR_ALIGN;
+static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans) {
     const size_t lds_limit = (size_t)device_max_lds();
-    std::vector<LinearArgs> args((size_t)n_mods);
-    std::vector<LinearPlan> plans((size_t)n_mods);
     int64_t steps_total = 0;                                   // of the modules the skinny kernel will serve
-    for (int i = 0; i < n_mods; ++i) {
-        const rtn_module& m = mods[i];
-        const rtn_status st = module_args(m, dev_workspace, &args[i]);
-        if (st != RTN_OK) return st;
-        if (m.M <= 16) steps_total += (m.N / 16) * (m.K / chunk_k(m.bits));
-    }
-    for (int i = 0; i < n_mods; ++i) {
+    for (int i = 0; i < n; ++i)
+        if (args[i].M <= 16) steps_total += (args[i].N / 16) * (args[i].K / chunk_k(args[i].bits));
+    for (int i = 0; i < n; ++i) {
         const LinearArgs& a = args[i];
         rtn_status st = RTN_ERR_CONFIG;
         if (!small_groups(a.M, a.g)) {
@@ -1252,7 +1242,23 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
         if (st == RTN_ERR_CONFIG) st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);    // the module's own plan
         if (st != RTN_OK) return st;
     }
-    hipError_t e = rtn::launch_linear_grouped(args.data(), plans.data(), n_mods, static_cast<hipStream_t>(stream));
+    return RTN_OK;
+}
+
+rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
+                               void* stream) {
+    if (!mods) return RTN_ERR_NULL;
+    if (n_mods <= 0) return RTN_ERR_SHAPE;
+    if (!aligned16(dev_workspace)) return RTN_ERR_ALIGN;
+    std::vector<LinearArgs> args((size_t)n_mods);
+    std::vector<LinearPlan> plans((size_t)n_mods);
+    for (int i = 0; i < n_mods; ++i) {
+        const rtn_status st = module_args(mods[i], dev_workspace, &args[i]);
+        if (st != RTN_OK) return st;
+    }
+    const rtn_status st = grouped_plans(args.data(), n_mods, workspace_nbytes, plans.data());
+    if (st != RTN_OK) return st;
+    hipError_t e = rtn::launch_linear_grouped(args.data(), plans.data(), n_mods, false, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
 }
 

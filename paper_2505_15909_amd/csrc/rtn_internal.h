@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <vector>
 
 namespace rtn {
 
@@ -44,8 +45,11 @@ hipError_t launch_quantize_asym(const void* W, int64_t N, int64_t K, int bits, i
 hipError_t launch_unpack(const void* qweight, const void* scales, int64_t N, int64_t K, int bits, int64_t g,
                          bool dequant, void* out, hipStream_t st, const void* zeros = nullptr);
 hipError_t launch_linear(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
-// n independent problems with resolved plans: compatible skinny-kernel launches are merged into grouped launches.
-hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, hipStream_t st);
+// n independent problems with resolved plans: compatible skinny-kernel launches are merged into grouped launches.  common_plan:
+// the plans were made for one launch.
+hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, bool common_plan, hipStream_t st);
+// The launch (0, 1, ...) that each of them goes out with.
+std::vector<int> grouped_launches(const LinearArgs* args, const LinearPlan* plans, int n, bool common_plan);
 // Wide kernel: whether column tiles go to the XCDs in contiguous slices, none more than one tile longer than another,
 // instead of dealt in turn.  Only where that saves a round of workgroups on the XCD with most of them (32 compute units):
 // then it pays (816 rows of 384 x 10240: 62 us -> 22, 143 of 20912 x 14848: 230 -> 126); otherwise the cuts, which may

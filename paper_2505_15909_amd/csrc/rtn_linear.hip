@@ -39,6 +39,7 @@
 // exactly one scale per group (that of its own weight row).
 #include "rtn_device.h"
 #include "rtn_internal.h"
+#include <algorithm>
 #include <vector>
 
 namespace rtn {
@@ -726,48 +727,85 @@ static hipError_t launch_grouped_bits(const GroupedParams& gp, int ngc, bool mul
 // Independent problems: those whose plan is a plain skinny launch (no K split across workgroups, one row block,
 // default prefetch) are bucketed by (bits, groups per chunk, workgroup size, staging mode) and every bucket goes
 // out as grouped launches of up to kMaxGroup problems; the rest are launched one by one.
-hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, hipStream_t st) {
-    std::vector<char> done((size_t)n, 0);
+static bool groupable(const LinearPlan& p) {
+    return p.path == 1 && p.split_k == 1 && p.m_blocks == 1 && p.prefetch <= 2 && p.m_rows16 == 1;
+}
+
+// Every workgroup of a launch gets the LDS of its largest problem (and its wavefronts, of which those without work leave at
+// once).  Problems of different workgroup shapes, unless planned for one launch, are kept apart where that would thin out the
+// workgroups on a compute unit for 64 MB of weights: 4-5 us a launch are not worth it.  8B layer, int4 groups of 32 at four
+// rows, all in one launch because of the down projection's 115 KB slice 37.2 us, the down projection apart 33.3; a 4608-wide
+// layer at two rows 52 and 40.  Under that line one launch wins: a 1024-wide layer 11.4 us apart, 5.4 in one.
+std::vector<int> grouped_launches(const LinearArgs* args, const LinearPlan* plans, int n, bool common_plan) {
+    constexpr size_t kThinnedBytes = (size_t)64 << 20;
+    auto resident = [](const SkinnyLaunch& l, size_t lds) { return std::min((size_t)(1024 / l.block.x), kMaxLdsBytes / std::max<size_t>(lds, 1)); };
+    std::vector<int> launch((size_t)n, -1);
     std::vector<SkinnyLaunch> prep((size_t)n);
-    std::vector<char> eligible((size_t)n, 0);
+    for (int i = 0; i < n; ++i)
+        if (groupable(plans[i])) prep[i] = prepare_skinny(args[i], plans[i]);
+    int launches = 0;
     for (int i = 0; i < n; ++i) {
-        const LinearPlan& p = plans[i];
-        if (p.path != 1 || p.split_k != 1 || p.m_blocks != 1 || p.prefetch > 2 || p.m_rows16 != 1) continue;
-        prep[i] = prepare_skinny(args[i], p);
-        eligible[i] = 1;
+        if (launch[i] >= 0) continue;
+        launch[i] = launches;
+        size_t lds = prep[i].lds;
+        int member[kMaxGroup] = {i}, count = 1;
+        for (int j = i + 1; groupable(plans[i]) && j < n && count < kMaxGroup; ++j) {
+            if (launch[j] >= 0 || !groupable(plans[j]) || args[j].bits != args[i].bits || prep[j].ngc != prep[i].ngc ||
+                plans[j].prefetch != plans[i].prefetch || prep[j].multi != prep[i].multi)
+                continue;
+            const size_t lds_with = std::max(lds, prep[j].lds);
+            member[count] = j;
+            bool one_shape = true;
+            size_t thinned = 0;                              // weights that would stream from fewer workgroups
+            for (int k = 0; k <= count; ++k) {
+                const LinearArgs& a = args[member[k]];
+                const SkinnyLaunch& l = prep[member[k]];
+                one_shape = one_shape && l.block.x == prep[i].block.x;
+                if (resident(l, lds_with) < resident(l, l.lds)) thinned += (size_t)a.N * a.K * a.bits / 8;
+            }
+            if (!common_plan && !one_shape && thinned > kThinnedBytes) continue;
+            lds = lds_with;
+            launch[j] = launches;
+            ++count;
+        }
+        ++launches;
     }
-    for (int i = 0; i < n; ++i) {
-        if (done[i]) continue;
-        if (!eligible[i]) {
-            hipError_t e = launch_linear(args[i], plans[i], st);
+    return launch;
+}
+
+hipError_t launch_linear_grouped(const LinearArgs* args, const LinearPlan* plans, int n, bool common_plan, hipStream_t st) {
+    const std::vector<int> launch = grouped_launches(args, plans, n, common_plan);
+    for (int i = 0, next = 0; i < n; ++i) {
+        if (launch[i] != next) continue;                     // gone out with an earlier one
+        ++next;
+        hipError_t e;
+        if (!groupable(plans[i])) {
+            e = launch_linear(args[i], plans[i], st);
             if (e != hipSuccess) return e;
-            done[i] = 1;
             continue;
         }
+        const SkinnyLaunch first = prepare_skinny(args[i], plans[i]);
         GroupedParams gp;
         gp.n = 0;
         gp.first_block[0] = 0;
         size_t lds = 0;
         unsigned threads = 0;
-        for (int j = i; j < n && gp.n < kMaxGroup; ++j) {
-            if (done[j] || !eligible[j] || args[j].bits != args[i].bits || prep[j].ngc != prep[i].ngc ||
-                plans[j].prefetch != plans[i].prefetch || prep[j].multi != prep[i].multi)
-                continue;
-            gp.p[gp.n] = prep[j].sp;
-            gp.first_block[gp.n + 1] = gp.first_block[gp.n] + (int)prep[j].grid.x;
-            lds = prep[j].lds > lds ? prep[j].lds : lds;
-            threads = prep[j].block.x > threads ? prep[j].block.x : threads;
+        for (int j = i; j < n; ++j) {
+            if (launch[j] != launch[i]) continue;
+            const SkinnyLaunch l = prepare_skinny(args[j], plans[j]);
+            gp.p[gp.n] = l.sp;
+            gp.first_block[gp.n + 1] = gp.first_block[gp.n] + (int)l.grid.x;
+            lds = std::max(lds, l.lds);
+            threads = std::max(threads, (unsigned)l.block.x);
             ++gp.n;
-            done[j] = 1;
         }
         const unsigned blocks = (unsigned)gp.first_block[gp.n];
-        hipError_t e;
         if (plans[i].prefetch == 1) {
-            e = (args[i].bits == 4) ? launch_grouped_bits<4, 1>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st)
-                                    : launch_grouped_bits<8, 1>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st);
+            e = (args[i].bits == 4) ? launch_grouped_bits<4, 1>(gp, first.ngc, first.multi, blocks, threads, lds, st)
+                                    : launch_grouped_bits<8, 1>(gp, first.ngc, first.multi, blocks, threads, lds, st);
         } else {
-            e = (args[i].bits == 4) ? launch_grouped_bits<4, 2>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st)
-                                    : launch_grouped_bits<8, 2>(gp, prep[i].ngc, prep[i].multi, blocks, threads, lds, st);
+            e = (args[i].bits == 4) ? launch_grouped_bits<4, 2>(gp, first.ngc, first.multi, blocks, threads, lds, st)
+                                    : launch_grouped_bits<8, 2>(gp, first.ngc, first.multi, blocks, threads, lds, st);
         }
         if (e != hipSuccess) return e;
     }

@@ -59,7 +59,8 @@ int main() {
                 if (rtn::xcd_wide_tile(b, XB, ZB, sliced, &xb, &zb)) printf("%d %d %d ", xb, zb, b % rtn::kXcds);
             }
             printf("]");
-        } else if (!strcmp(what, "layer")) {                   // bits g workspace n, then M N K each -> 1 if one launch, plans
+        } else if (!strcmp(what, "layer") || !strcmp(what, "grouped")) {   // bits g workspace n, then M N K each
+            // layer -> 1 if one launch, plans; grouped -> status, [launch of each]
             long g, ws;
             int bits, n;
             if (scanf("%d %ld %ld %d", &bits, &g, &ws, &n) != 4 || n < 1 || n > 16) return 1;
@@ -69,6 +70,14 @@ int main() {
                 long M, N, K;
                 if (scanf("%ld %ld %ld", &M, &N, &K) != 3) return 1;
                 a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
+            }
+            if (what[0] == 'g') {
+                const rtn_status st = grouped_plans(a, n, (size_t)ws, plan);
+                printf("%d [", (int)st);
+                if (st == RTN_OK)
+                    for (int l : rtn::grouped_launches(a, plan, n, false)) printf("%d ", l);
+                printf("]\n");
+                continue;
             }
             const bool one = merged_layer_plans(a, n, (size_t)ws, plan);
             printf("%d", one ? 1 : 0);

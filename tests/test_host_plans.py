@@ -226,3 +226,17 @@ def test_tile_and_wide_kernel_share_their_range_as_measured(ask):
     for problems, path in ((tile, 4), (wide, 3)):
         for p, (status, launches) in zip(problems, ask([f"linear {' '.join(map(str, p))} {256 * MIB}" for p in problems])):
             assert status == 0 and all(q["path"] == path for q in launches), (p, launches)
+
+
+def test_grouped_launches_keep_apart_what_one_launch_would_thin_out(ask):
+    """rtn_grouped_forward: modules of one workgroup shape share a launch; of different shapes too, except where the largest staged
+    slice would leave fewer workgroups on a compute unit for much of the weights."""
+    def launches(shapes, M, bits, g):
+        line = ask([_layer(shapes, M, bits, g).replace("layer", "grouped", 1)], raw=True)[0]
+        return [int(t) for t in line.split("[")[1].rstrip("] ").split()]
+
+    assert launches([(2048, 7168)] * 8, [1, 2, 3, 4, 5, 6, 7, 8], 4, 128) == [0] * 8              # experts
+    assert launches([(1536, 1024), (1024, 1024), (8192, 1024), (1024, 4096)], 3, 4, 128) == [0] * 4
+    for g, M in ((32, 3), (32, 4), (128, 3), (0, 4)):                                             # the down projection apart
+        assert launches(LAYER_8B, M, 4, g) == [0, 0, 0, 1]
+    assert len(set(launches([(5760, 4608), (4608, 4608), (35840, 4608), (4608, 17920)], 2, 4, 128))) > 1
