@@ -174,11 +174,11 @@ rtn_status rtn_linear_validate(int64_t M, int64_t N, int64_t K, int bits, int gr
 
 /* rtn_linear for callers that cannot allocate device memory or pass a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation.  Same arguments, results and plan as rtn_linear with a
- * workspace of rtn_workspace_nbytes() bytes, but the split-K partial sums go to a fixed 16 MiB device array inside
- * the library (one copy per GPU, held until the process ends) instead of a caller's buffer; the call allocates and
- * frees nothing.  Problems whose rtn_workspace_nbytes() exceeds 16 MiB (only possible from 64 rows) are refused
- * with RTN_ERR_WORKSPACE: use rtn_linear with a workspace for those --
- * except that from 144 tiles of 128 x 256 outputs the call runs with the K splits that fit.  All calls on one GPU share that array, so
+ * workspace of 16 MiB, but the split-K partial sums go to a fixed 16 MiB device array inside the library (one copy per
+ * GPU, held until the process ends) instead of a caller's buffer; the call allocates and frees nothing.  Where
+ * rtn_workspace_nbytes() exceeds 16 MiB (only possible from 64 rows) that plan is not the one rtn_linear prefers: from
+ * 144 tiles of 128 x 256 outputs, which fill the compute units without a K split, the call runs with it all the same;
+ * below, it is refused with RTN_ERR_WORKSPACE (use rtn_linear with a workspace).  All calls on one GPU share that array, so
  * calls that overlap in time on one GPU (different streams, concurrently replayed graphs) race; calls ordered on a
  * stream are safe.  The first call on a device looks up the array's address (hipGetSymbolAddress); make it before
  * capturing a graph. */
