@@ -8,7 +8,8 @@ Transformer layer (Section 4: QKV 4096->6144, attention output 4096->4096, gate_
 (Sections 1, 5).  Weights ~ N(0, 0.02), activations ~ N(0, 1), seeded, synthetic.
 
 One step = one pass of the hot path over one batch of input: for every M, the layer's four
-modules through rtn_layer_forward (20 fused dequantise-GEMMs).  Every pass streams a different
+modules through rtn_layer_forward (20 fused dequantise-GEMMs; at M = 1, 2, 4 the four independent
+modules go out as one launch, at 8 and 16 one by one).  Every pass streams a different
 copy of the packed layer (enough copies to exceed twice the 256 MB Infinity Cache), as token
 generation does when it walks a model's layers, so the weights come from HBM, not from cache.
 The load-time quantise/pack pass (Section 5) runs once during set-up, is checked to reproduce,
@@ -16,8 +17,8 @@ and its throughput is reported in the "quantize" object; it is not inside the ti
 which measure the metric itself: weight-stream GB/s of the linear layers.
 
 Prints one JSON line: metric, value (GB/s of packed weights and scales streamed, whole job), unit, n_gpus, steps, warmup,
-ms_per_step, dtype, data, config, plus `roofline` (the dominant kernel against the 8 TB/s HBM peak: algorithmic bytes per
-launch over the measured average launch duration, and the HBM traffic per launch from hardware counters), `cpu_baseline`
+ms_per_step, dtype, data, config, plus `roofline` (the step's two kernels against the 8 TB/s HBM peak: algorithmic bytes per
+launch over the measured average launch duration, and the HBM traffic per single launch from hardware counters), `cpu_baseline`
 (the CPU oracle timed on a bounded sample of the same workload) and `quantize` (load-time pass throughput).
 """
 from __future__ import annotations
@@ -34,10 +35,11 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 BATCHES = (1, 2, 4, 8, 16)
+MERGED = (1, 2, 4)                    # batches whose four modules rtn_layer_forward sends as one launch (up to five rows here)
 BITS, GROUP = 4, 128
 CACHE_BYTES = 256e6
-# HBM bytes per launch of the dominant kernel come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this very
-# command, scaled by a copy kernel of known size; the committed summary of those runs carries the figure on a line
+# HBM bytes per single launch of the skinny kernel come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of the layer set,
+# scaled by a copy kernel of known size; the committed summary of those runs carries the figure on a line
 # "traffic_bytes_per_launch: <n>", which is read at run time (null if the summary is not there).
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "skinny_mfma_llama8b_w4a16_hbm_traffic.txt")
 W8_BATCHES = (1, 4, 16, 64)
@@ -568,21 +570,25 @@ def main() -> int:
     value = step_weight_bytes / (ms_per_step * 1e-3) / 1e9
     flops = sum(2.0 * M * N * K for M in BATCHES for _, (K, N) in modules)
 
-    # ---- roofline of the dominant kernel (the int4 skinny MFMA dequantise-GEMM: all 20 launches of a
-    # step).  A pair of HIP events on the launch stream brackets the launches of the same passes issued
-    # back to back (one rtn_linear per launch, direct launches, no graph); the stream is first held busy
-    # so that the host has enqueued everything before the GPU gets there, and the bracket times the GPU.
-    # (Events around every single launch cost several microseconds each on this runtime and were not
-    # usable.)  Average launch duration = bracket / launches; dispatch gaps are inside it.
-    algo_bytes = 0.0
-    calls = []
+    # ---- roofline of the two kernels of a step: the int4 skinny MFMA dequantise-GEMM launched per module (M = 8, 16: half
+    # of the step's time) and the same kernel over the four modules of a layer in one grid (M = 1, 2, 4).  A pair of HIP
+    # events on the launch stream brackets each kind's launches of the same passes, issued back to back (direct launches, no
+    # graph); the stream is first held busy so that the host has enqueued everything before the GPU gets there, and the
+    # bracket times the GPU.  (Events around every single launch cost several microseconds each on this runtime and were
+    # not usable.)  Average launch duration = bracket / launches; dispatch gaps and K-split reductions are inside it.
+    algo_bytes = merged_bytes = 0.0
+    calls, merged = [], []
     for s_i in range(min(args.steps, 20)):
         for j, M in enumerate(BATCHES):
             cp = copies[pass_no[0] % n_copies]
+            nbytes = sum(q.numel() + s.numel() * 2 + 2 * M * K + 2 * M * N for (q, s), (_, (K, N)) in zip(cp, modules))
+            if M in MERGED:
+                merged.append(plans[pass_no[0] % n_copies][j])
+                merged_bytes += nbytes
+            else:
+                calls += [(acts[M][i], cp[i][0], cp[i][1], outs[M][i]) for i in range(len(modules))]
+                algo_bytes += nbytes
             pass_no[0] += 1
-            for i, (_, (K, N)) in enumerate(modules):
-                calls.append((acts[M][i], cp[i][0], cp[i][1], outs[M][i]))
-                algo_bytes += cp[i][0].numel() + cp[i][1].numel() * 2 + 2 * M * K + 2 * M * N
     n_launch = len(calls)
     hold = torch.empty(1 << 30, dtype=torch.uint8, device=dev)
     with torch.cuda.stream(stream):
@@ -595,13 +601,26 @@ def main() -> int:
         ev1.record(stream)
         torch.cuda.synchronize()
         launch_us = ev0.elapsed_time(ev1) * 1e3 / n_launch
+        for _ in range(12):
+            hold.fill_(1)
+        ev0.record(stream)
+        for plan in merged:
+            plan.run()
+        ev1.record(stream)
+        torch.cuda.synchronize()
+        merged_us = ev0.elapsed_time(ev1) * 1e3 / len(merged)
     del hold
     achieved = algo_bytes / n_launch / (launch_us * 1e-6) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": _measured_traffic(),
-                "kernel": "rtn::skinny_mfma_kernel<4,4,1,*,1> (fused int4 g128 dequantise-GEMM; a launch = one rtn_linear)",
+                "kernel": "rtn::skinny_mfma_kernel<4,4,*,*,1> (fused int4 g128 dequantise-GEMM; a launch = one rtn_linear, M = 8 and 16)",
                 "launches": n_launch, "avg_launch_us": round(launch_us, 3),
-                "algorithmic_bytes_per_launch": round(algo_bytes / n_launch, 1)}
+                "algorithmic_bytes_per_launch": round(algo_bytes / n_launch, 1),
+                "merged_layers": {"kernel": "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
+                                  "achieved": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9, 1),
+                                  "frac": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
+                                  "launches": len(merged), "avg_launch_us": round(merged_us, 3),
+                                  "algorithmic_bytes_per_launch": round(merged_bytes / len(merged), 1)}}
 
     # ---- read-stream ceiling: a plain read kernel on buffers of the four matrices' packed sizes, same protocol ----
     read_ceiling_gbs = None
