@@ -229,7 +229,7 @@ typedef struct {
  * rtn_workspace_nbytes() of the modules; it is reused, which is safe because the launches
  * are ordered on one stream.  Stops at, and returns, the first error.
  * Small layers whose outputs overlap no operand and no output of another module go out as one launch: 2 to 16 modules of
- * one precision and group size, up to 8 rows and 140 KiB of activations each (M K 2 bytes: 5 rows of 14336 columns), under
+ * one precision and group size (512 columns and more at 4 bit, 256 at 8 bit count as one), up to 8 rows and 140 KiB of activations each (M K 2 bytes: 5 rows of 14336 columns), under
  * 256 MB of weights together, where a common plan is not expected to cost more than the launches it saves.  The plan is
  * the launch's own: the same result as in order, up to the summation order of a single call -- so a module's last bits may
  * depend on the modules it shares the call with (rtn_linear gives those of the module alone). */

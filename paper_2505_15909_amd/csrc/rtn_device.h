@@ -10,9 +10,9 @@
 
 namespace rtn {
 
-// Workgroups go to the eight XCDs in turn, each XCD has its own L2.  Block b of a grid of XB x ZB tiles rounded up to eights
-// -> column tile and row tile, in an order that keeps the up to zgroup row tiles that share a column tile's weights next to
-// one another on one XCD.  Column tiles in eights are dealt to the XCDs in turn (eight slices of the weights a power of
+// Workgroups go to the eight XCDs in turn, each XCD has its own L2.  The tile kernel's mapping: block b of a grid of XB x ZB
+// tiles rounded up to eights -> column tile and row tile, in an order that keeps the up to zgroup row tiles that share a
+// column tile's weights next to one another on one XCD.  Column tiles in eights are dealt to the XCDs in turn (eight slices of the weights a power of
 // two apart would stream from the same memory channels); otherwise each XCD takes a contiguous slice of the tiles, none
 // more than one tile longer than another (dealing 20 column tiles leaves half of the XCDs a third short: 5120 x 5120 at
 // 1536 rows 146 us against 106).  Returns false for the padding.

@@ -400,8 +400,9 @@ __global__ __launch_bounds__(1024) void skinny_mfma_kernel(const SkinnyParams p)
     skinny_body<BITS, NGC, NB, MULTI, MB, DOT, ZP>(p, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// Grouped launch: up to kMaxGroup independent problems of the same precision, group size and workgroup shape
-// and activation staging mode (e.g. the experts of a mixture-of-experts layer, or modules that do not feed one another) in one grid.
+// Grouped launch: up to kMaxGroup independent problems of the same precision, groups per k-chunk, chunks in flight and
+// activation staging mode (e.g. the experts of a mixture-of-experts layer, or modules that do not feed one another) in one grid;
+// workgroup shapes may differ, within what grouped_launches allows.
 // Workgroup b belongs to the problem g with first_block[g] <= b < first_block[g + 1].
 constexpr int kMaxGroup = 16;
 struct GroupedParams {
@@ -725,8 +726,8 @@ static hipError_t launch_grouped_bits(const GroupedParams& gp, int ngc, bool mul
 }
 
 // Independent problems: those whose plan is a plain skinny launch (no K split across workgroups, one row block,
-// default prefetch) are bucketed by (bits, groups per chunk, workgroup size, staging mode) and every bucket goes
-// out as grouped launches of up to kMaxGroup problems; the rest are launched one by one.
+// one or two chunks in flight) are bucketed by (bits, groups per chunk, chunks in flight, staging mode) and every bucket goes
+// out as grouped launches of up to kMaxGroup problems (grouped_launches); the rest are launched one by one.
 static bool groupable(const LinearPlan& p) {
     return p.path == 1 && p.split_k == 1 && p.m_blocks == 1 && p.prefetch <= 2 && p.m_rows16 == 1;
 }

@@ -273,7 +273,8 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
             if (group_done) scale_row(slot, NBW - 1, gi);
             if constexpr (NG > 1) {
                 // pins this group's sums here: left alone the compiler keeps the partial sums of several groups alive and
-                // adds them up at the end of the step, which spills up to a hundred registers
+                // adds them up at the end of the step, which spills up to a hundred registers (with the pin none do but the
+                // 8-bit form with zero points, 64 rows x 2 tile-rows and groups of 64: 11, 48 bytes of scratch a lane)
 #pragma unroll
                 for (int b = 0; b < MB; ++b)
 #pragma unroll
@@ -369,8 +370,8 @@ hipError_t launch_wide_wv(const WideParams& wp, int wv, dim3 grid, hipStream_t s
     return hipErrorInvalidValue;
 }
 
-// Register tiles of up to 8 accumulator blocks (MB * NBW <= 8) fit 256 registers without spilling; the 128 x 32 tile
-// (16 blocks) does with pre-scaled weights, which need no second accumulator set.
+// Register tiles of up to 8 accumulator blocks (MB * NBW <= 8) fit 256 registers (all but one zero-point form, see the pin
+// in the k-step, without spilling); the 128 x 32 tile (16 blocks) does with pre-scaled weights, which need no second accumulator set.
 template <int BITS>
 hipError_t launch_wide_bits(const WideParams& wp, int mb, int nbw, int wv, dim3 grid, hipStream_t st) {
     if (mb == 8) {
