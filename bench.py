@@ -47,10 +47,10 @@ WARM_MS = float(os.environ.get("RTN_BENCH_WARM_MS", "200"))      # untimed work 
 SETTLE_MS = float(os.environ.get("RTN_BENCH_SETTLE_MS", "300"))  # the step graphs run this long, untimed, before the warm-up steps (clocks)
 
 
-def _measured_traffic():
+def _measured_traffic(key="traffic_bytes_per_launch"):
     try:
         for line in open(TRAFFIC_PROFILE):
-            if line.startswith("traffic_bytes_per_launch:"):
+            if line.startswith(key + ":"):
                 return int(float(line.split(":", 1)[1].split()[0]))
     except OSError:
         pass
@@ -619,6 +619,7 @@ def main() -> int:
                 "merged_layers": {"kernel": "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
                                   "achieved": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9, 1),
                                   "frac": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
+                                  "traffic": _measured_traffic("merged_traffic_bytes_per_launch"),
                                   "launches": len(merged), "avg_launch_us": round(merged_us, 3),
                                   "algorithmic_bytes_per_launch": round(merged_bytes / len(merged), 1)}}
 
