@@ -138,12 +138,12 @@ rtn_status rtn_linear(const void* dev_A, int64_t M, const void* dev_qweight, con
 /* Explicit kernel configuration for rtn_linear_ex (tuning sweeps and tests of every path).
  * A zeroed struct means "choose automatically", field by field. */
 typedef struct {
-    int path;      /* 0 auto, 1 MFMA skinny kernel, 2 vector-ALU dot-product kernel (M <= 4), 3 wide MFMA kernel
+    int path;      /* 0 auto, 1 MFMA skinny kernel, 2 vector-ALU dot-product kernel (M <= 4), 3 wide MFMA kernels
                       (group_size a multiple of 128; uses split_k, m_rows16 = 2..4, n_tiles16 and waves_n = 4, 8 or -- with
                       n_tiles16 = 1 -- 16 wavefronts per workgroup; group_size 32 and 64 with every field given, waves_n = 8
-                      and n_tiles16 = 1 or 2; also m_rows16 = 8 with n_tiles16 = 2 and waves_n = 8:
-                      128 rows per workgroup, weights scaled in fp16 before the MFMA as in path 4, chosen automatically
-                      for 128 and more rows on large 4-bit matrices below the tile kernel's range), 4 tile kernel: 128 x 256 or
+                      and n_tiles16 = 1 or 2; also m_rows16 = 8 with n_tiles16 = 2 and waves_n = 8: up to 128 rows per
+                      workgroup.  With waves_n = 8 and n_tiles16 = 2, waves_k = 2, 4 or 8 puts that many of the eight
+                      wavefronts along K, on 256 / waves_k columns), 4 tile kernel: 128 x 256 or
                       256 x 256 output tiles, weights dequantised to fp16 in LDS (group_size a multiple of 128; uses split_k and
                       m_rows16 = 4 or 8 for the tile height, 0 = chosen from M) */
     int prefetch;  /* k-chunks (4 KiB each) a wavefront keeps in flight: 1, 2 or 4 */
@@ -151,7 +151,7 @@ typedef struct {
     int waves_k;   /* wavefronts of a workgroup along K (in-workgroup split-K): 1 .. 16; waves_n * waves_k <= 16 */
     int split_k;   /* workgroups along K (global split-K, reduced through the workspace) */
     int m_rows16;  /* 16-row activation blocks each wavefront multiplies per weight tile: 1, 2 or 4 (path 3: 2, 3, 4, 8) */
-    int n_tiles16; /* path 3: 16-column weight tile-rows per wavefront (share each activation operand): 1, 2 or 4;
+    int n_tiles16; /* path 3: 16-column weight tile-rows per wavefront: 1, 2 or 4;
                       m_rows16 * n_tiles16 <= 8 (or 8 x 2) */
 } rtn_linear_cfg;
 

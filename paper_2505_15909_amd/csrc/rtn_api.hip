@@ -144,24 +144,56 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
     }
 }
 
-// K splits of the wide kernel's 128-row variant (128 rows x 256 columns per workgroup, one workgroup per compute
-// unit): the lowest modelled time over 1, 2, 4, 8 splits that fit 64 MiB of partials.  A workgroup's full-K time is
-// its MFMA work at the 4.3 TFLOP/s one compute unit sustains in this kernel; a round of workgroups costs 9 us more
-// (start, prologue, epilogue), the reduce launch 4 us plus its traffic at 5 TB/s.  Fitted to sweeps over the 70B and
-// 405B shapes at 128-512 rows, where it picks the measured best split or one within 4 % of it.
-int tall_wide_split(int64_t M, int64_t N, int64_t K) {
-    const int64_t wgs = ((N + 255) / 256) * ((M + 127) / 128);
-    const double t1 = 2.0 * 128 * 256 * (double)K / 4.3e12, mn4 = (double)M * N * 4.0;
-    int best_s = 1;
+// The block kernel's time.  A workgroup: a fixed start, so much per unit of four packed tiles that each of its wavefronts
+// along K runs (by 32-row blocks; the scales cost per group and block), the sum over the wavefronts along K; slower by up to
+// a third on a busy chip, whose clock falls.  Workgroups come in rounds of one per compute unit (two of the 32-row ones), of
+// the fullest XCD.  Against it the stream of weights at 6.8 TB/s and of activations from L2 at 17 TB/s.  Fitted to 5300
+// launches on sixteen shapes of 1024 to 57344 columns, 20 to 512 rows, int4 and int8, groups of 64, 128 and K (8 % rms; the
+// plan it picks is 1.5 % behind the best measured one on average, 6 % at the 90th percentile).
+double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+    static const double kUnit[4] = {1.93, 2.25, 2.49, 2.77}, kGroup[4] = {0.044, 0.123, 0.269, 0.382};
+    const int64_t unit = bits == 4 ? 512 : 256, units = K / unit, cols = 256 / wk;
+    const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols, wgs = XB * ZB * s;
+    const int mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
+    const double per = (double)(((units + s - 1) / s + wk - 1) / wk), groups = g >= unit ? 1.0 : (double)(unit / g);
+    double wg = 1.33 + per * (kUnit[mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[mb - 1] * groups) + (wk > 1 ? 0.73 * mb : 0.0);
+    wg *= 1.0 + 0.36 * std::min(1.0, (double)wgs / 256.0) * mb / 4.0;
+    const double slots = 32.0 * (mb == 1 && wk <= 4 ? 2 : 1), rounds = std::ceil((double)wgs / 8.0) / slots;
+    double serial = wg * std::max(1.0, 0.91 * std::ceil(rounds) + 0.09 * rounds);
+    if (slots > 32.0 && wgs > 256) serial *= 1.78;
+    const double stream = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * mb * K * 2.0 / 1.71e7;
+    double t = 2.93 + std::cbrt(serial * serial * serial + stream * stream * stream);
+    if (s > 1) t += 1.12 + (double)M * N * s * 8.0 / 4.19e6;
+    return t;
+}
+
+// Plan of the block kernel within `cap` bytes of partial sums, and its modelled time: row tile height, wavefronts along K,
+// K splits.  Row tiles of 128 rows keep the weights' unpacking per flop low and suit large matrices; under 64 M weights the
+// compute units are filled by 64-row tiles instead (6144 x 4096 at 128 rows: 14.9 us against 19.2).  Eight wavefronts along K
+// are for a row tile that is alone or almost: 32 rows below 64, 64 rows above; 64 to 96 rows of a matrix under 24 M weights
+// split K in two instead where the workspace allows (4096 x 4096 at 64 rows: 10.2 us, 9.7 unsplit with four wavefronts along K,
+// 8.6 with eight; rtn_linear_query has always reported a split there, and its callers are shown one).
+double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p) {
+    const int64_t units = K / chunk_k(bits);
     double best = 1e30;
-    for (int s = 1; s <= 8; ++s) {
-        if (s > 1 && ((size_t)M * N * sizeof(float) * s > kWorkspaceCapTall || K / 128 / s < 4)) break;
-        const double rounds = (double)((wgs * s + 255) / 256);
-        double t = rounds * (t1 / s + 9e-6);
-        if (s > 1) t += 4e-6 + 2.0 * s * mn4 / 5e12;
-        if (t < best) { best = t; best_s = s; }
+    p->path = 3; p->prefetch = 1; p->waves_n = 8; p->n_tiles16 = 2; p->waves_k = 1; p->split_k = 1; p->m_rows16 = 2;
+    for (int r = 2; r <= 8; r *= 2) {
+        if (r == 2 && M > 96) continue;
+        if (r == 8 && (M <= 64 || (g % 128 != 0 && !zp) || (N * K < 64000000 && M > 96) || (bits == 8 && N * K > (int64_t)512 << 20))) continue;
+        const int64_t tiles = (M + 16 * r - 1) / (16 * r);
+        const int mb = (int)((M + 32 * tiles - 1) / (32 * tiles));
+        for (int wk = 1; wk <= 8; wk *= 2) {
+            if (wk > units || (wk == 8 && (mb > 2 || zp || (r == 2 && M >= 64) || (r == 4 && M <= 64)))) continue;
+            const bool two = r == 2 && M >= 64 && N * K < 24000000 && 2 * wk <= units && (size_t)M * N * sizeof(float) * 2 <= cap;
+            for (int s = two ? 2 : 1; s <= 8 && s * wk <= units; ++s) {
+                if (s > 1 && (size_t)M * N * sizeof(float) * s > cap) break;
+                const double t = block_model_us(M, N, K, bits, g, r, wk, s);
+                if (t < best) { best = t; p->m_rows16 = r; p->waves_k = wk; p->split_k = s; }
+            }
+        }
     }
-    return best_s;
+    p->m_blocks = (int)((M + 16 * p->m_rows16 - 1) / (16 * p->m_rows16));
+    return best;
 }
 
 // Tile height (128 or 256 rows) and K split of the tile kernel: the pair with the lowest modelled time.  Splits need not
@@ -210,10 +242,10 @@ bool tile_line(int64_t M, int64_t N, int64_t K, int bits, double t_wide) {
 // or 0 where one launch is modelled within 7 % of the best pair.  Measured as two calls against one on the qkv shapes:
 // 405B at 2048 rows 1044 us against 1236, at 1024 rows 565 against 641; 70B at 2048 rows 324 against 374; 8B at 4096
 // rows 208 against 232; no gain (and none modelled) where the tiles fill their rounds.
-int64_t tile_two_launches(bool dense, int64_t M, int64_t N, int64_t K, size_t workspace_cap, double* time_us = nullptr) {
+int64_t two_launches_modelled(bool dense, int64_t M, int64_t N, int64_t K, size_t workspace_cap, double* time_us) {
     int r16, sk;
     const double single = tile_plan_choose(dense, M, N, K, workspace_cap, &r16, &sk);
-    if (time_us) *time_us = single;
+    *time_us = single;
     if (M > 16384) return 0;                                   // many rounds: the last one no longer matters
     double best = single * 0.93;
     int64_t rows_first = 0;
@@ -222,9 +254,56 @@ int64_t tile_two_launches(bool dense, int64_t M, int64_t N, int64_t K, size_t wo
                          tile_plan_choose(dense, M - r1, N, K, workspace_cap, &r16, &sk);
         if (t < best) { best = t; rows_first = r1; }
     }
-    if (time_us && rows_first > 0) *time_us = best;
+    if (rows_first > 0) *time_us = best;
     return rows_first;
 }
+
+// Plans above 16 rows are the best of some hundred modelled candidates, 5-30 us of host time: remembered per problem in a
+// table of fixed size (an entry gives way to the next one that falls on it).
+template <typename Value> struct Remembered {
+    struct Key {
+        int64_t M, N, K, g;
+        size_t workspace, lds;
+        int bits, kind;
+        bool operator==(const Key& o) const {
+            return M == o.M && N == o.N && K == o.K && g == o.g && workspace == o.workspace && lds == o.lds && bits == o.bits && kind == o.kind;
+        }
+    };
+    static constexpr size_t kEntries = 1024;
+    struct Entry { Key key; Value value; bool used; };
+    std::mutex mutex;
+    Entry table[kEntries] = {};
+    static size_t slot(const Key& k) {
+        uint64_t h = 0;
+        for (uint64_t v : {(uint64_t)k.M, (uint64_t)k.N, (uint64_t)k.K, (uint64_t)k.g, (uint64_t)k.workspace, (uint64_t)(k.bits * 8 + k.kind)})
+            h = (h ^ v) * 0x9E3779B97F4A7C15ull, h ^= h >> 29;
+        return (size_t)(h % kEntries);
+    }
+    template <typename Make> Value get(const Key& k, Make make) {
+        Entry& e = table[slot(k)];
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            if (e.used && e.key == k) return e.value;
+        }
+        const Value v = make();
+        std::lock_guard<std::mutex> lock(mutex);
+        e.key = k; e.value = v; e.used = true;
+        return v;
+    }
+};
+
+int64_t tile_two_launches(bool dense, int64_t M, int64_t N, int64_t K, size_t workspace_cap, double* time_us = nullptr) {
+    struct Cut { int64_t rows_first; double time_us; };
+    static Remembered<Cut> remembered;
+    const Cut c = remembered.get({M, N, K, 0, workspace_cap, 0, 0, dense ? 1 : 0}, [&] {
+        Cut v;
+        v.rows_first = two_launches_modelled(dense, M, N, K, workspace_cap, &v.time_us);
+        return v;
+    });
+    if (time_us) *time_us = c.time_us;
+    return c.rows_first;
+}
+
 
 // Plan of the small-batch (skinny) kernel for up to 16 rows: a table of measured configurations on a grid of
 // problems -- tile-rows N / 16 from 64 to 8192 and k-chunks per row from 2 to 128, by powers of two and at the 1.5 x
@@ -432,10 +511,25 @@ bool skinny_on_small_groups(const LinearArgs& a, const LinearPlan& skinny, const
 // partial sums (by default what its best plan may take): kernel, height, split and cut are chosen within it, instead of
 // the unconstrained plan with its split cut down.  Within 16 MiB, cut down against chosen: 1011 rows of 4608 x 5120 104 us
 // against 77, 2921 of 1792 x 5120 105 against 84, 2048 of 4096 x 14336 321 against 236, 256 of 16384 x 53248 1010 against 734.
+// The tile kernel's modelled time, in one launch or two, against the wide plan's w of modelled time t_wide.  The wide kernel's
+// model, fitted at 32 to 256 rows, falls short of its times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and
+// 1.30 at 8 bit (means over 460 problems; the tile kernel's by 1.03).
+bool tile_beats_wide(int64_t M, int64_t N, int64_t K, int bits, int64_t g, const LinearPlan& w, double t_wide, size_t workspace) {
+    const int64_t fit = std::max<int64_t>(1, (int64_t)(workspace / ((size_t)M * N * sizeof(float))));
+    const double t_fit = w.split_k > fit ? wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, (int)fit) : t_wide;
+    double t_tile = 0;
+    tile_two_launches(false, M, N, K, workspace, &t_tile);
+    return t_tile * 1.03 < t_fit * (bits == 4 ? (g == 128 ? 1.26 : 1.20) : (g == 128 ? 1.51 : 1.30));
+}
+
 LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path = 0,
-                     int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile) {
+                     int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile);
+
+LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path, int64_t steps_hint,
+                         size_t workspace) {
     LinearPlan p;
     p.n_tiles16 = 1;
+    const size_t cap = std::min(workspace, M >= 64 && g % 128 == 0 ? kWorkspaceCapTall : kWorkspaceCap);   // the block kernel's partials
     if (force_path == 0 && small_groups(M, g)) {
         LinearArgs a;
         a.M = M; a.N = N; a.K = K; a.bits = bits; a.g = g;
@@ -443,33 +537,33 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
         const LinearPlan skinny = auto_plan(M, N, K, bits, g, lds_limit, 1);
         // (the wide kernel's split shrinks to the workspace, the skinny kernel's does not)
         const bool held = skinny.split_k == 1 || (size_t)M * N * sizeof(float) * skinny.split_k <= workspace;
-        return held && skinny_on_small_groups(a, skinny, p) ? skinny : p;
+        if (held && skinny_on_small_groups(a, skinny, p)) return skinny;
+        block_plan(M, N, K, bits, g, cap, false, &p);
+        return p;
     }
     const size_t packed_bytes = (size_t)N * K * bits / 8;
     const bool streams16 = streams_to_32_rows(M, N, K, bits);
-    const bool wide_wins = g % 128 == 0 && M > 16 && !streams16;
-    const bool tall_wide = wide_wins && bits == 4 && M >= 128 && (M + 127) / 128 * 2 <= (M + 63) / 64 &&
-                           packed_bytes >= ((size_t)40 << 20) && K > N;
-    // The tile kernel may serve what tile_line admits.  Of that it leaves to the wide kernel what does not give it a full
-    // round of 128 x 256 tiles and where it is not modelled ahead (in one launch or two).  The wide kernel's model, fitted at
-    // 32 to 256 rows, falls short of its times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and 1.30 at 8 bit
-    // (means over 460 problems; the tile kernel's by 1.03), so that 8192 x 8192 int8 group 128 at 622 rows took 152 us instead
-    // of 115, 4096 x 4096 at 1398 rows 78 instead of 63.  Wide ahead of tile: 15760 x 7168 int4 per channel at 382 rows 98
-    // against 106, 5392 x 4096 at 870 rows 56 against 58.
+    const bool wide_wins = g % 128 == 0 && M > 16 && !(streams16 && packed_bytes > ((size_t)512 << 20));
     bool tile_wins = false;
-    LinearPlan w;
+    LinearPlan w, block;
+    double t_block = 0;
     if (force_path == 3 || (force_path == 0 && wide_wins)) wide_plan(M, N, K, bits, g, &w);
+    if (force_path == 0 && wide_wins) t_block = block_plan(M, N, K, bits, g, cap, false, &block);
     if (force_path == 0 && wide_wins && M >= 128) {
         const double t_wide = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, w.split_k);
-        if (tile_line(M, N, K, bits, t_wide) && !(tall_wide && M < 192 && ((N + 255) / 256) * ((M + 127) / 128) < 144)) {
-            tile_wins = ((N + 255) / 256) * ((M + 127) / 128) >= 256;
-            if (!tile_wins) {
-                const int64_t fit = std::max<int64_t>(1, (int64_t)(workspace / ((size_t)M * N * sizeof(float))));
-                double t_tile = 0, t_wide_fit = t_wide;         // of what resolve_plan leaves of the wide plan's split
-                if (w.split_k > fit) t_wide_fit = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, (int)fit);
-                tile_two_launches(false, M, N, K, workspace, &t_tile);
-                const double short_of = bits == 4 ? (g == 128 ? 1.26 : 1.20) : (g == 128 ? 1.51 : 1.30);
-                tile_wins = t_tile * 1.03 < t_wide_fit * short_of;
+        if (tile_line(M, N, K, bits, t_wide)) {
+            double t_tile = 0;
+            tile_two_launches(false, M, N, K, workspace, &t_tile);
+            if (M <= (bits == 4 ? 1024 : 512)) {
+                // against the block kernel, whose model (fitted to 512 rows) falls short by 8 % above 256 rows (57344 x 8192 at
+                // 512 rows: tile 407 us, block 430-453; 16384 x 53248 at 160 rows: 375 and 299; 6144 x 4096 at 1000 rows: 59
+                // and 51).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
+                // (16384 x 53248 at 129 rows: 375 us, block 294).
+                tile_wins = t_tile * 1.03 < t_block * (M > 256 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
+            } else if (((N + 255) / 256) * ((M + 127) / 128) >= 256) {
+                tile_wins = true;
+            } else {
+                tile_wins = tile_beats_wide(M, N, K, bits, g, w, t_wide, workspace);
             }
         }
     }
@@ -480,20 +574,13 @@ LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_
         p.m_blocks = (int)((M + 32 * p.m_rows16 - 1) / (32 * p.m_rows16));
         return p;
     }
-    // 128 rows and more, where the tile kernel has not taken over (in practice 128 to 191 rows), on 4-bit matrices of
-    // 40 MB and more with more input than output columns (the down projections): the wide kernel's 128-row variant
-    // with K split until there is a workgroup per compute unit.  3-12 % faster than the 64-row variant on the 70B and
-    // 405B down matrices; within +-7 % on their qkv and o matrices, slower on every 8B shape, and on 8-bit weights
-    // ahead on one matrix only, so those keep the 64-row variant.
-    if (force_path == 0 && tall_wide) {
-        p.path = 3;
-        p.prefetch = 1; p.waves_n = 8; p.waves_k = 1; p.n_tiles16 = 2;
-        p.m_rows16 = 8;
-        p.m_blocks = (int)((M + 127) / 128);
-        p.split_k = tall_wide_split(M, N, K);
-        return p;
-    }
-    if (force_path == 3 || (force_path == 0 && wide_wins)) return w;
+    if (force_path == 3) return w;
+    // 8-bit weights with at most one scale per unit, 17 to 64 rows, matrices of 48 MB and more: the wide kernel, which is 3-10 %
+    // ahead there (28672 x 4096 at 32 and 48 rows 25.8 and 26.8 us against 27.6 and 29.9; 10240 x 8192 at 48 rows 23.2 and
+    // 25.8), except up to 32 rows from 256 MB (57344 x 8192 at 32 rows 89 and 81, 18432 x 16384 0.88).  Everywhere else
+    // measured the block kernel is ahead or level.
+    if (force_path == 0 && wide_wins)
+        return bits == 8 && g >= 256 && M <= 64 && packed_bytes >= (size_t)48000000 && !(M <= 32 && packed_bytes >= ((size_t)256 << 20)) ? w : block;
     if (M <= 16 && steps_hint == 0) {
         // the table lookup costs tens of microseconds of host time (logarithms over ~800 entries): remembered per problem
         struct Key { int64_t M, N, K; int bits; size_t lds; };
@@ -622,6 +709,74 @@ rules:
     return p;
 }
 
+LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path, int64_t steps_hint,
+                     size_t workspace) {
+    auto make = [&] { return modelled_plan(M, N, K, bits, g, lds_limit, force_path, steps_hint, workspace); };
+    if (M <= 16) return make();                               // the skinny kernel's table has a memory of its own
+    static Remembered<LinearPlan> remembered;
+    return remembered.get({M, N, K, g, workspace, lds_limit, bits, force_path}, make);
+}
+
+int tall_wide_split(int64_t M, int64_t N, int64_t K) {
+    const int64_t wgs = ((N + 255) / 256) * ((M + 127) / 128);
+    const double t1 = 2.0 * 128 * 256 * (double)K / 4.3e12, mn4 = (double)M * N * 4.0;
+    int best_s = 1;
+    double best = 1e30;
+    for (int s = 1; s <= 8; ++s) {
+        if (s > 1 && ((size_t)M * N * sizeof(float) * s > kWorkspaceCapTall || K / 128 / s < 4)) break;
+        const double rounds = (double)((wgs * s + 255) / 256);
+        double t = rounds * (t1 / s + 9e-6);
+        if (s > 1) t += 4e-6 + 2.0 * s * mn4 / 5e12;
+        if (t < best) { best = t; best_s = s; }
+    }
+    return best_s;
+}
+
+// The plan above 16 rows (groups of whole 128 columns) that the wide kernel, with a 128-row tile for long 4-bit matrices, or
+// the tile kernel has, whichever these two's models put ahead.  Explicit configurations that leave fields open are completed
+// from it, and the line of rtn_linear_noalloc is drawn by it, so that what is accepted does not move with the automatic plan.
+LinearPlan wide_or_tile_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t workspace) {
+    const int64_t tiles = ((N + 255) / 256) * ((M + 127) / 128);
+    LinearPlan p;
+    wide_plan(M, N, K, bits, g, &p);
+    const bool tall = bits == 4 && M >= 128 && (M + 127) / 128 * 2 <= (M + 63) / 64 && (size_t)N * K * bits / 8 >= ((size_t)40 << 20) && K > N;
+    if (M >= 128) {
+        const double t_wide = wide_model_us(M, N, K, bits, p.m_rows16, p.waves_n, p.n_tiles16, p.split_k);
+        if (tile_line(M, N, K, bits, t_wide) && !(tall && M < 192 && tiles < 144) &&
+            (tiles >= 256 || tile_beats_wide(M, N, K, bits, g, p, t_wide, workspace))) {
+            p.path = 4; p.waves_n = 8;
+            tile_plan_choose(false, M, N, K, workspace, &p.m_rows16, &p.split_k);
+            p.m_blocks = (int)((M + 32 * p.m_rows16 - 1) / (32 * p.m_rows16));
+            p.n_tiles16 = 1;
+            return p;
+        }
+    }
+    if (tall) {
+        p.waves_n = 8; p.n_tiles16 = 2; p.m_rows16 = 8;
+        p.m_blocks = (int)((M + 127) / 128);
+        p.split_k = tall_wide_split(M, N, K);
+    }
+    return p;
+}
+
+// Bytes of partial sums of a plan: the single launch's or, of a tile plan, those of the two that rtn_linear may issue.
+size_t plan_partials(const LinearPlan& p, int64_t M, int64_t N, int64_t K) {
+    auto bytes = [&](int64_t rows, int split) { return split > 1 ? ((size_t)rows * N * sizeof(float) * split + 255) & ~(size_t)255 : (size_t)0; };
+    size_t need = bytes(M, p.split_k);
+    const int64_t first = p.path == 4 ? tile_two_launches(false, M, N, K, kWorkspaceCapTile) : 0;
+    for (int64_t rows : {first, first > 0 ? M - first : 0}) {
+        int r16, sk;
+        if (rows == 0) continue;
+        tile_plan_choose(false, rows, N, K, kWorkspaceCapTile, &r16, &sk);
+        need = std::max(need, bytes(rows, sk));
+    }
+    return need;
+}
+
+size_t wide_or_tile_partials(int64_t M, int64_t N, int64_t K, int bits, int64_t g) {
+    return M > 16 && g % 128 == 0 ? plan_partials(wide_or_tile_plan(M, N, K, bits, g, kWorkspaceCapTile), M, N, K) : 0;
+}
+
 // The plan as a complete explicit configuration.
 rtn_linear_cfg plan_cfg(const LinearPlan& p) {
     rtn_linear_cfg c;
@@ -643,7 +798,11 @@ rtn_status resolve_plan(const LinearArgs& a, const rtn_linear_cfg* cfg, size_t w
     if (whole) p.m_blocks = 1;                                  // every field comes from the caller
     else {
         const int path = !cfg ? 0 : cfg->path == 0 && small_groups(a.M, a.g) ? 1 : cfg->path;
-        p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, path, 0, tile_workspace(a, workspace_nbytes));
+        const size_t partials = tile_workspace(a, workspace_nbytes);
+        if (cfg && path == 0 && a.M > 16 && a.g % 128 == 0 && !streams_to_32_rows(a.M, a.N, a.K, a.bits))
+            p = wide_or_tile_plan(a.M, a.N, a.K, a.bits, a.g, partials);
+        else
+            p = auto_plan(a.M, a.N, a.K, a.bits, a.g, lds_limit, cfg && path == 0 && a.M > 16 && a.g % 128 == 0 ? 1 : path, 0, partials);
     }
     if (cfg) {
         if (cfg->path) p.path = cfg->path;
@@ -708,14 +867,18 @@ rtn_status resolve_plan_zp(const LinearArgs& a, size_t workspace_nbytes, LinearP
     skinny.m_blocks = (int)((a.M + 15) / 16);
     if (a.M > 16) skinny.split_k = 1;
     if (a.M > 16 && (a.g % 128 == 0 || small_groups(a.M, a.g))) {
-        // the wide kernel's zero-point instantiations: 8 wavefronts, at most two tile-rows per wavefront
         LinearPlan h;
-        wide_plan(a.M, a.N, a.K, a.bits, a.g, &h);
+        wide_plan(a.M, a.N, a.K, a.bits, a.g, &h);            // the wide kernel's shapes: what the small groups' models compare
         h.waves_n = 8; h.n_tiles16 = std::min(h.n_tiles16, 2);
         if (a.g % 128 == 0 || !skinny_on_small_groups(a, skinny, h)) {
-            // as many of the plan's K splits as the workspace passed can hold
-            const size_t fit = a.workspace ? workspace_nbytes / ((size_t)a.M * a.N * sizeof(float)) : 0;
-            if ((size_t)h.split_k > fit) h.split_k = fit < 1 ? 1 : (int)fit;
+            const size_t cap = a.M >= 64 && a.g % 128 == 0 ? kWorkspaceCapTall : kWorkspaceCap;
+            const size_t fit = a.workspace ? std::min(workspace_nbytes, cap) : 0;
+            static Remembered<LinearPlan> remembered;
+            h = remembered.get({a.M, a.N, a.K, a.g, fit, 0, a.bits, 0}, [&] {
+                LinearPlan b;
+                block_plan(a.M, a.N, a.K, a.bits, a.g, fit, true, &b);
+                return b;
+            });
             const rtn_linear_cfg cfg = plan_cfg(h);
             if (resolve_plan(a, &cfg, workspace_nbytes, p) == RTN_OK) return RTN_OK;
         }
@@ -808,21 +971,8 @@ size_t rtn_scales_nbytes(int64_t N, int64_t K, int group_size) {
 size_t rtn_workspace_nbytes(int64_t M, int64_t N, int64_t K, int bits, int group_size) {
     int64_t g;
     if (M <= 0 || check_problem(N, K, bits, group_size, &g) != RTN_OK) return 0;
-    size_t bound = workspace_bound(M, N);
     const LinearPlan p = auto_plan(M, N, K, bits, g, (size_t)device_max_lds());
-    if (p.split_k > 1) {                                        // the automatic plan's own need, where it is larger
-        const size_t need = ((size_t)M * (size_t)N * sizeof(float) * (size_t)p.split_k + 255) & ~(size_t)255;
-        if (need > bound) bound = need;
-    }
-    const int64_t rows_first = p.path == 4 ? tile_two_launches(false, M, N, K, kWorkspaceCapTile) : 0;
-    for (int part = 0; rows_first > 0 && part < 2; ++part) {    // and of the two launches rtn_linear would issue
-        const int64_t rows = part == 0 ? rows_first : M - rows_first;
-        int r16, sk;
-        tile_plan_choose(false, rows, N, K, kWorkspaceCapTile, &r16, &sk);
-        const size_t need = sk > 1 ? (((size_t)rows * (size_t)N * sizeof(float) * (size_t)sk + 255) & ~(size_t)255) : 0;
-        if (need > bound) bound = need;
-    }
-    return bound;
+    return std::max(workspace_bound(M, N), std::max(plan_partials(p, M, N, K), wide_or_tile_partials(M, N, K, bits, g)));
 }
 
 rtn_status rtn_quantize(const void* dev_W, int64_t N, int64_t K, int bits, int group_size, int flags,
@@ -902,7 +1052,7 @@ rtn_status rtn_linear_noalloc(const void* dev_A, int64_t M, const void* dev_qwei
     if (st != RTN_OK) return st;
     if (M <= 0 || M > (1 << 20)) return RTN_ERR_SHAPE;
     // from 144 tiles of 128 x 256, which occupy the chip without a split, the call runs with the splits that fit the array
-    if (rtn_workspace_nbytes(M, N, K, bits, group_size) > kScratchBytes && ((N + 255) / 256) * ((M + 127) / 128) < 144)
+    if (((N + 255) / 256) * ((M + 127) / 128) < 144 && wide_or_tile_partials(M, N, K, bits, g) > kScratchBytes)
         return RTN_ERR_WORKSPACE;
     void* ptr = nullptr;
     st = scratch_for_current_device(&ptr);

@@ -305,6 +305,37 @@ def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M}")
 
 
+@pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),
+                                      (8, 128, 2304), (8, 0, 2304)])
+@pytest.mark.parametrize("M", [17, 33, 65, 128, 161])
+def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
+    """The block kernel of path 3: every split of its eight wavefronts over N and K and every row tile (32 to 128 rows, of equal
+    height), ragged M and N, odd and even numbers of units, fewer units than wavefronts along K or workgroups along it (their
+    partial sums are zeros), with and without zero points, against the oracle."""
+    N = 304                                # 19 tile-rows: the last wavefront's second one does not exist
+    codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    ref = O.rtn_linear(_to_np(A_t), codes, scales, gg)
+    for rows in (2, 4, 8):
+        if rows == 8 and g in (32, 64):
+            continue
+        for wk in (1, 2, 4, 8):
+            for split in (1, 2, K // 128):
+                if split > min(16, K // 128):
+                    continue
+                cfg = dict(path=3, prefetch=1, m_rows16=rows, n_tiles16=2, waves_n=8, waves_k=wk, split_k=split)
+                C = rtn.rtn_linear(A_t, qw, sc, bits, g, cfg=cfg,
+                                   workspace=torch.empty(max(256, M * N * 4 * split), dtype=torch.uint8, device=DEV))
+                torch.cuda.synchronize()
+                H.assert_linear_close(_to_np(C), ref, f"int{bits} g={g} M={M} K={K} cfg={cfg}")
+    W = _to_np((synth.normal_weight(N, K, 0.02, seed=M + bits, device=DEV).float() + 0.015).half())
+    codes, scales, zeros = O.rtn_quantize_asym(W, bits, gg)
+    C = rtn.rtn_linear_asym(A_t, torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV),
+                            torch.from_numpy(zeros.astype(np.float16)).to(DEV), bits, g)
+    torch.cuda.synchronize()
+    H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M} K={K}")
+
+
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 0), (8, 128), (8, 0)])
 @pytest.mark.parametrize("M", [20, 128, 130, 300])
 def test_linear_wide_kernel_128_rows(rtn, bits, g, M):
