@@ -228,11 +228,13 @@ typedef struct {
  * instantiation of its own (bits, group_size).  The workspace must cover the largest
  * rtn_workspace_nbytes() of the modules; it is reused, which is safe because the launches
  * are ordered on one stream.  Stops at, and returns, the first error.
- * Small layers whose outputs overlap no operand and no output of another module go out as one launch: 2 to 16 modules of
- * one precision and group size (512 columns and more at 4 bit, 256 at 8 bit count as one), up to 8 rows and 140 KiB of activations each (M K 2 bytes: 5 rows of 14336 columns), under
- * 256 MB of weights together, where a common plan is not expected to cost more than the launches it saves.  The plan is
- * the launch's own: the same result as in order, up to the summation order of a single call -- so a module's last bits may
- * depend on the modules it shares the call with (rtn_linear gives those of the module alone). */
+ * 2 to 16 modules whose outputs overlap no operand and no output of another one may share launches, where a common plan is
+ * expected to be faster than the modules' own: up to 8 rows one launch of the small-batch kernel (one precision and group
+ * size -- 512 columns and more at 4 bit, 256 at 8 bit count as one --, 140 KiB of activations each (M K 2 bytes), under 256 MB
+ * of weights together); from 5 to 512 rows one launch of the wide kernels for the modules of each precision and group size, with
+ * their K splits one after another in the workspace.  The plan is the launch's own: the same result as in order, up to the
+ * summation order of a single call -- so a module's last bits may depend on the modules it shares the call with (rtn_linear
+ * gives those of the module alone) -- and with weights that a module alone may round to fp16 after scaling (path 4) not rounded. */
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace,
                              size_t workspace_nbytes, void* stream);
 

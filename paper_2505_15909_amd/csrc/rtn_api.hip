@@ -150,21 +150,35 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
 // the fullest XCD.  Against it the stream of weights at 6.8 TB/s and of activations from L2 at 17 TB/s.  Fitted to 5300
 // launches on sixteen shapes of 1024 to 57344 columns, 20 to 512 rows, int4 and int8, groups of 64, 128 and K (8 % rms; the
 // plan it picks is 1.5 % behind the best measured one on average, 6 % at the 90th percentile).
-double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+struct BlockTimes {
+    int mb;             // row blocks of 32 rows
+    int64_t wgs;        // workgroups
+    double wg_us;       // one workgroup on an idle chip
+    double stream_us;   // its weights and activations at the rates above
+};
+
+BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
     static const double kUnit[4] = {1.93, 2.25, 2.49, 2.77}, kGroup[4] = {0.044, 0.123, 0.269, 0.382};
     const int64_t unit = bits == 4 ? 512 : 256, units = K / unit, cols = 256 / wk;
-    const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols, wgs = XB * ZB * s;
-    const int mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
+    const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols;
+    BlockTimes b;
+    b.mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
+    b.wgs = XB * ZB * s;
     const double per = (double)(((units + s - 1) / s + wk - 1) / wk), groups = g >= unit ? 1.0 : (double)(unit / g);
-    double wg = 1.33 + per * (kUnit[mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[mb - 1] * groups) + (wk > 1 ? 0.73 * mb : 0.0);
-    wg *= 1.0 + 0.36 * std::min(1.0, (double)wgs / 256.0) * mb / 4.0;
-    const double slots = 32.0 * (mb == 1 && wk <= 4 ? 2 : 1), rounds = std::ceil((double)wgs / 8.0) / slots;
+    b.wg_us = 1.33 + per * (kUnit[b.mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[b.mb - 1] * groups) + (wk > 1 ? 0.73 * b.mb : 0.0);
+    b.stream_us = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * b.mb * K * 2.0 / 1.71e7;
+    return b;
+}
+
+double block_split_us(int64_t M, int64_t N, int s) { return s > 1 ? 1.12 + (double)M * N * s * 8.0 / 4.19e6 : 0.0; }
+
+double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+    const BlockTimes b = block_times(M, N, K, bits, g, rows16, wk, s);
+    const double wg = b.wg_us * (1.0 + 0.36 * std::min(1.0, (double)b.wgs / 256.0) * b.mb / 4.0);
+    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), rounds = std::ceil((double)b.wgs / 8.0) / slots;
     double serial = wg * std::max(1.0, 0.91 * std::ceil(rounds) + 0.09 * rounds);
-    if (slots > 32.0 && wgs > 256) serial *= 1.78;
-    const double stream = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * mb * K * 2.0 / 1.71e7;
-    double t = 2.93 + std::cbrt(serial * serial * serial + stream * stream * stream);
-    if (s > 1) t += 1.12 + (double)M * N * s * 8.0 / 4.19e6;
-    return t;
+    if (slots > 32.0 && b.wgs > 256) serial *= 1.78;
+    return 2.93 + std::cbrt(serial * serial * serial + b.stream_us * b.stream_us * b.stream_us) + block_split_us(M, N, s);
 }
 
 // Plan of the block kernel within `cap` bytes of partial sums, and its modelled time: row tile height, wavefronts along K,
@@ -555,11 +569,11 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
             double t_tile = 0;
             tile_two_launches(false, M, N, K, workspace, &t_tile);
             if (M <= (bits == 4 ? 1024 : 512)) {
-                // against the block kernel, whose model (fitted to 512 rows) falls short by 8 % above 256 rows (57344 x 8192 at
-                // 512 rows: tile 407 us, block 430-453; 16384 x 53248 at 160 rows: 375 and 299; 6144 x 4096 at 1000 rows: 59
-                // and 51).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
+                // against the block kernel, whose model falls short by 8 % above 128 rows (57344 x 8192 at 220 and 512 rows: tile 206
+                // and 407 us, block 214 and 430-453; 106496 x 16384 at 200 rows: 780 and 818; 16384 x 53248 at 160 rows: 375 and
+                // 299; 6144 x 4096 at 1000 rows: 59 and 51).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
                 // (16384 x 53248 at 129 rows: 375 us, block 294).
-                tile_wins = t_tile * 1.03 < t_block * (M > 256 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
+                tile_wins = t_tile * 1.03 < t_block * (M > 128 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
             } else if (((N + 255) / 256) * ((M + 127) / 128) >= 256) {
                 tile_wins = true;
             } else {
@@ -1302,6 +1316,201 @@ static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbyt
     return !merge_loses(a, plans, n, rows, steps, (double)bytes / 6.5e6);
 }
 
+// Modelled time of a module's own plan.
+static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t workspace_nbytes) {
+    const double packed = (double)a.N * a.K * a.bits / 8.0;
+    if (p.path == 1) return 4.5 + packed / (a.bits == 8 ? 6.5e6 : a.M <= 16 ? 5.4e6 : 3.9e6);    // the skinny kernel
+    if (p.path == 4) {
+        double t;
+        tile_two_launches(false, a.M, a.N, a.K, tile_workspace(a, workspace_nbytes), &t);
+        return 1.03 * t;
+    }
+    if (p.waves_n == 8 && p.n_tiles16 == 2 && p.m_rows16 != 3)
+        return block_model_us(a.M, a.N, a.K, a.bits, a.g, p.m_rows16, p.waves_k, p.split_k);
+    return 1.1 * block_model_us(a.M, a.N, a.K, a.bits, a.g, 4, 2, 1);
+}
+
+// Independent modules of one precision and number of groups per unit in one launch of the block kernel.  Apart, each fills the
+// chip to a half or three quarters and pays the start, the first data and the last store of a launch; together they fill it and
+// pay once.  Plan: one row tile height and number of wavefronts along K for all (a launch is one kernel), the longest
+// workgroups first, K of the module with the longest split in two or four.  The time is the end of the last workgroup
+// when they are dealt in that order to the compute units of an XCD (32; two of the 32-row ones on each), four fifths of
+// it, and the average load one fifth; against it the streams, as in block_model_us.  Fitted to 408 merged launches of 68
+// layers (6 % rms, the pick 0.4 % behind the best one measured on average).
+struct MergedPlan {
+    double us;                          // modelled time, negative: no such plan
+    int mb, wk;
+    int split[rtn::kMaxBlockGroup];
+};
+
+static double dealt_us(const double* each, const int64_t* count, int n, int64_t slots) {
+    struct Load { double end; int64_t slots; };
+    std::vector<Load> load = {{0.0, slots}};                    // by end
+    int order[rtn::kMaxBlockGroup];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::sort(order, order + n, [&](int x, int y) { return each[x] > each[y]; });
+    double sum = 0.0;
+    for (int k = 0; k < n; ++k) {
+        int64_t left = count[order[k]];
+        const double d = each[order[k]];
+        sum += d * left;
+        if (left > 64 * slots) {                                // many rounds: the load is even to a round
+            for (Load& l : load) l.end += d * (double)(left / slots - 32);
+            left -= (left / slots - 32) * slots;
+        }
+        while (left > 0) {
+            const Load first = load.front();
+            const int64_t k2 = std::min(first.slots, left);
+            if (k2 == first.slots) load.erase(load.begin());
+            else load.front().slots -= k2;
+            size_t at = 0;
+            while (at < load.size() && load[at].end < first.end + d - 1e-9) ++at;
+            if (at < load.size() && load[at].end < first.end + d + 1e-9) load[at].slots += k2;
+            else load.insert(load.begin() + at, {first.end + d, k2});
+            left -= k2;
+        }
+    }
+    return 0.78 * load.back().end + 0.22 * sum / (double)slots;
+}
+
+static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
+    int64_t rows = 0, shortest = INT64_MAX;
+    MergedPlan best;
+    best.us = -1.0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].N >= (1 << 22)) return best;
+        rows = std::max(rows, a[i].M);
+        shortest = std::min(shortest, a[i].K / chunk_k(a[i].bits));
+    }
+    static const double kWaves[9] = {0, 1.076, 1.02, 0, 0.948, 0, 0, 0, 0.908};
+    for (int r = 2; r <= 8; r *= 2) {
+        if ((r == 2 && rows > 96) || (r == 8 && rows <= 64)) continue;
+        const int64_t tiles = (rows + 16 * r - 1) / (16 * r);
+        const int mb = (int)((rows + 32 * tiles - 1) / (32 * tiles));
+        for (int wk = 1; wk <= 8 && wk <= shortest; wk *= 2) {
+            if (wk == 8 && mb > 2) continue;
+            MergedPlan m;
+            m.mb = mb; m.wk = wk;
+            for (int i = 0; i < n; ++i) m.split[i] = 1;
+            for (int cuts = 0; cuts < 4; ++cuts) {
+                double each[rtn::kMaxBlockGroup], stream = 0.0, reduce = 0.0;
+                int64_t count[rtn::kMaxBlockGroup], wgs = 0;
+                size_t partials = 0;
+                int longest = 0;
+                for (int i = 0; i < n; ++i) {
+                    const BlockTimes b = block_times(a[i].M, a[i].N, a[i].K, a[i].bits, a[i].g, 2 * mb, wk, m.split[i]);
+                    each[i] = b.wg_us;
+                    count[i] = (b.wgs + 7) / 8;
+                    wgs += b.wgs;
+                    stream += 0.839 * b.stream_us;
+                    if (each[i] > each[longest]) longest = i;
+                    if (m.split[i] > 1) {
+                        reduce += 1.1 + (double)a[i].M * a[i].N * m.split[i] * 8.0 / 6.53e6;
+                        partials += (((size_t)a[i].M * a[i].N * sizeof(float) * m.split[i]) + 255) & ~(size_t)255;
+                    }
+                }
+                if (partials > workspace) break;
+                const bool two = mb == 1 && wk <= 4;
+                const double slow = (mb == 1 ? 1.081 : 1.02) * (1.0 + 0.36 * std::min(1.0, (double)wgs / 256.0) * mb / 4.0) *
+                                    (two && wgs > 256 ? 1.543 : 1.0) * kWaves[wk];
+                for (int i = 0; i < n; ++i) each[i] *= slow;
+                const double serial = dealt_us(each, count, n, two ? 64 : 32);
+                m.us = 3.7 + std::pow(std::pow(serial, 2.374) + std::pow(stream, 2.374), 1.0 / 2.374) + reduce;
+                if (best.us < 0.0 || m.us < best.us) best = m;
+                if (m.split[longest] >= 4 || 2 * m.split[longest] * wk > a[longest].K / chunk_k(a[longest].bits)) break;
+                m.split[longest] *= 2;
+            }
+        }
+    }
+    return best;
+}
+
+// The same, remembered (some 50 us of host time): a table of fixed size, an entry gives way to the next one that falls on it.
+static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace) {
+    struct Key { int64_t v[4 * rtn::kMaxBlockGroup + 3]; };
+    struct Entry { Key key; MergedPlan plan; bool used; };
+    constexpr size_t kEntries = 128;
+    static std::mutex mutex;
+    static Entry table[kEntries];
+    Key k = {};
+    uint64_t h = 0;
+    k.v[0] = n; k.v[1] = a[0].bits; k.v[2] = a[0].workspace ? (int64_t)workspace : 0;
+    for (int i = 0; i < n; ++i) { k.v[3 + 4 * i] = a[i].M; k.v[4 + 4 * i] = a[i].N; k.v[5 + 4 * i] = a[i].K; k.v[6 + 4 * i] = a[i].g; }
+    for (int64_t v : k.v) h = (h ^ (uint64_t)v) * 0x9E3779B97F4A7C15ull, h ^= h >> 29;
+    Entry& e = table[h % kEntries];
+    {
+        std::lock_guard<std::mutex> lock(mutex);
+        if (e.used && memcmp(&e.key, &k, sizeof(k)) == 0) return e.plan;
+    }
+    const MergedPlan p = merged_blocks(a, n, a[0].workspace ? workspace : 0);
+    std::lock_guard<std::mutex> lock(mutex);
+    e.key = k; e.plan = p; e.used = true;
+    return p;
+}
+
+static rtn_status one_module(const rtn_module& m, void* dev_workspace, size_t workspace_nbytes, void* stream) {
+    return rtn_linear(m.dev_A, m.M, m.dev_qweight, m.dev_scales, m.N, m.K, m.bits, m.group_size, m.dev_C, dev_workspace,
+                      workspace_nbytes, stream);
+}
+
+// A layer of independent modules, 5 to 512 rows: those of one class (precision, groups per unit) together where that is
+// modelled ahead of their own plans' launches, by 3 % up to 256 rows (12 % for two modules up to 16 rows: int8 14336 x 4096 twice at
+// 8 rows 28.5 us together, 26.0 apart) and 15 % above (where the model falls short: 15360-, 5120-,
+// 27648- and 5120-wide modules at 512 rows 310 us together, 300 apart), the others one by one.  8B layer int4 group 128, apart ->
+// together: 9 rows 36.5 -> 29.9 us, 32 rows 48.3 -> 31.2, 64 61.6 -> 38.0, 128 85.1 -> 62.3, 256 125.5 -> 111.6; 70B layer 16 rows
+// 98.8 -> 91.6, 32 110 -> 94, 128 231 -> 212; three modules of 4096 columns and 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.
+// False where a module's own plan does not resolve: the call then runs in order up to that error.
+constexpr int64_t kMaxMergedRows = 512;
+static bool layer_in_blocks(const rtn_module* mods, const LinearArgs* args, int n, void* dev_workspace, size_t workspace_nbytes, void* stream,
+                            rtn_status* status) {
+    constexpr int kMost = 16;
+    double own_us[kMost];
+    for (int i = 0; i < n; ++i) {
+        LinearPlan own;
+        if (resolve_plan(args[i], nullptr, workspace_nbytes, &own) != RTN_OK) return false;
+        own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
+    }
+    auto groups = [](const LinearArgs& x) { const int64_t ck = chunk_k(x.bits); return x.g >= ck ? (int64_t)1 : ck / x.g; };
+    bool done[kMost] = {};
+    for (int i = 0; i < n; ++i) {
+        if (done[i]) continue;
+        LinearArgs set[rtn::kMaxBlockGroup];
+        LinearPlan plans[rtn::kMaxBlockGroup];
+        int member[rtn::kMaxBlockGroup], count = 0;
+        double apart = 0.0;
+        int64_t rows = 0;
+        for (int j = i; j < n && count < rtn::kMaxBlockGroup; ++j) {
+            if (done[j] || args[j].bits != args[i].bits || groups(args[j]) != groups(args[i])) continue;
+            apart += own_us[j];
+            rows = std::max(rows, args[j].M);
+            member[count] = j;
+            set[count++] = args[j];
+        }
+        MergedPlan m;
+        m.us = -1.0;
+        if (count > 1) m = remembered_merge(set, count, workspace_nbytes);
+        if (m.us < 0.0 || m.us > (rows > 256 ? 0.85 : count == 2 && rows <= 16 ? 0.88 : 0.97) * apart) {
+            *status = one_module(mods[i], dev_workspace, workspace_nbytes, stream);
+            if (*status != RTN_OK) return true;
+            done[i] = true;
+            continue;
+        }
+        for (int k = 0; k < count; ++k) {
+            LinearPlan& p = plans[k];
+            p.path = 3; p.prefetch = 1; p.waves_n = 8; p.waves_k = m.wk; p.split_k = m.split[k];
+            p.m_rows16 = 2 * m.mb; p.n_tiles16 = 2;
+            p.m_blocks = (int)((set[k].M + 32 * m.mb - 1) / (32 * m.mb));
+        }
+        if (rtn::launch_linear_blocks(set, plans, count, m.mb, m.wk, static_cast<hipStream_t>(stream)) != hipSuccess) {
+            *status = RTN_ERR_HIP;
+            return true;
+        }
+        for (int k = 0; k < count; ++k) done[member[k]] = true;
+    }
+    *status = RTN_OK;
+    return true;
+}
+
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
                              void* stream) {
     if (!mods) return RTN_ERR_NULL;
@@ -1317,10 +1526,17 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
             return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
         }
     }
+    if (n_mods > 1 && n_mods <= kMerge && aligned16(dev_workspace)) {
+        LinearArgs args[kMerge];
+        bool ok = true;
+        for (int i = 0; i < n_mods && ok; ++i)
+            ok = mods[i].M > 4 && mods[i].M <= kMaxMergedRows && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
+        rtn_status st;
+        if (ok && modules_independent(args, n_mods) && layer_in_blocks(mods, args, n_mods, dev_workspace, workspace_nbytes, stream, &st)) return st;
+    }
     for (int i = 0; i < n_mods; ++i) {
         const rtn_module& m = mods[i];
-        rtn_status st = rtn_linear(m.dev_A, m.M, m.dev_qweight, m.dev_scales, m.N, m.K, m.bits, m.group_size,
-                                   m.dev_C, dev_workspace, workspace_nbytes, stream);
+        rtn_status st = one_module(m, dev_workspace, workspace_nbytes, stream);
         if (st != RTN_OK) return st;
     }
     return RTN_OK;

@@ -63,6 +63,11 @@ inline int wide_blocks(int XB, int ZB, bool sliced) { return 8 * (sliced ? (XB *
 // Path 3 (wide MFMA kernel): plan check (group size 32, 64 or a multiple of 128, 2-4 row blocks, 1/2/4 tile-rows, at most 8 blocks) and launch.
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
+// The block kernel of path 3 on several independent problems at once: one precision and number of groups per unit of four packed
+// tiles, workgroups of one shape (mb row blocks of 32 rows, wk of eight wavefronts along K); partial sums of K splits go to the
+// workspace one problem after another.
+constexpr int kMaxBlockGroup = 8;
+hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, int wk, hipStream_t st);
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st);

@@ -292,7 +292,6 @@ struct BlockParams {
 };
 
 // The problems of one launch: problem i has the workgroups first[i] .. first[i + 1], blocks[i] of them per K split.
-constexpr int kMaxBlockGroup = 8;
 struct BlockGroup {
     int n;
     int first[kMaxBlockGroup + 1], blocks[kMaxBlockGroup];
@@ -742,6 +741,28 @@ static hipError_t launch_linear_block(const LinearArgs& a, const LinearPlan& p, 
     hipError_t e = launch_blocks(&a, &p, 1, block_rows32(a.M, a.N, p.m_rows16), wk, st);
     if (e != hipSuccess) return e;
     if (p.split_k > 1) e = launch_splitk_reduce(a.workspace, static_cast<half_t*>(a.C), a.M * a.N, p.split_k, st);
+    return e;
+}
+
+hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, int wk, hipStream_t st) {
+    // workgroups in order of length: the longest start first
+    const int unit = args[0].bits == 4 ? 512 : 256;
+    LinearArgs a[kMaxBlockGroup];
+    LinearPlan p[kMaxBlockGroup];
+    int order[kMaxBlockGroup];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order, order + n, [&](int x, int y) { return args[x].K / unit / plans[x].split_k > args[y].K / unit / plans[y].split_k; });
+    size_t used = 0;
+    for (int i = 0; i < n; ++i) {
+        a[i] = args[order[i]];
+        p[i] = plans[order[i]];
+        if (p[i].split_k == 1) continue;
+        a[i].workspace = a[i].workspace + used / sizeof(float);
+        used += ((size_t)a[i].M * a[i].N * sizeof(float) * p[i].split_k + 255) & ~(size_t)255;
+    }
+    hipError_t e = launch_blocks(a, p, n, mb, wk, st);
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        if (p[i].split_k > 1) e = launch_splitk_reduce(a[i].workspace, static_cast<half_t*>(a[i].C), a[i].M * a[i].N, p[i].split_k, st);
     return e;
 }
 

@@ -336,6 +336,56 @@ def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M} K={K}")
 
 
+@pytest.mark.parametrize("M", [5, 16, 33, 100, 161, 300])
+def test_layer_of_independent_modules_in_block_launches(rtn, M):
+    """rtn_layer_forward from five rows: modules of one class (precision, groups per unit) share a launch of the block kernel, with K of
+    the longest split where the workspace allows.  Two classes mixed, ragged rows per module and ragged N, K of 2 to 28 units;
+    with the full workspace, with none to speak of, replayed from a graph, and with a module that reads another's output
+    (run one by one), each module against the oracle."""
+    shapes = [(1040, 1024, 4, 128), (304, 2048, 4, 128), (640, 14336, 4, 128), (272, 1536, 8, 0), (528, 2304, 8, 256)]
+    mods, refs = [], []
+    for i, (N, K, bits, g) in enumerate(shapes):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i)
+        m = max(5, M - 3 * i)
+        A_t = synth.activation(m, K, seed=M + i, device=DEV)
+        mods.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.zeros((m, N), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A_t), codes, scales, gg))
+
+    def check(what):
+        torch.cuda.synchronize()
+        for i, (m, ref) in enumerate(zip(mods, refs)):
+            H.assert_linear_close(_to_np(m["C"]), ref, f"{what} M={M} module {i}")
+            m["C"].zero_()
+
+    plan = rtn.LayerPlan(mods)
+    plan.run()
+    check("layer")
+    rtn.LayerPlan(mods, workspace=torch.empty(64 << 20, dtype=torch.uint8, device=DEV)).run()
+    check("64 MiB")
+    if M > 32:                              # (the small-batch kernel's own plans want their workspace)
+        rtn.LayerPlan(mods, workspace=torch.empty(256, dtype=torch.uint8, device=DEV)).run()
+        check("no workspace")
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        plan.run()
+    for _ in range(3):
+        graph.replay()
+        check("graph")
+    # a chain: the second module reads the first one's output
+    N0, K0 = 1536, 1024
+    codes0, scales0, qw0, sc0, _ = _oracle_operands(N0, K0, 4, 128, seed=31)
+    codes1, scales1, qw1, sc1, _ = _oracle_operands(304, N0, 4, 128, seed=32)
+    A_t = synth.activation(M, K0, seed=7, device=DEV) * 0.25
+    C0 = torch.zeros((M, N0), dtype=torch.float16, device=DEV)
+    C1 = torch.zeros((M, 304), dtype=torch.float16, device=DEV)
+    rtn.rtn_layer_forward([dict(A=A_t, qweight=qw0, scales=sc0, bits=4, group_size=128, C=C0),
+                           dict(A=C0, qweight=qw1, scales=sc1, bits=4, group_size=128, C=C1)])
+    torch.cuda.synchronize()
+    H.assert_linear_close(_to_np(C0), O.rtn_linear(_to_np(A_t), codes0, scales0, 128), "chain 0")
+    H.assert_linear_close(_to_np(C1), O.rtn_linear(_to_np(C0), codes1, scales1, 128), "chain 1")
+
+
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 0), (8, 128), (8, 0)])
 @pytest.mark.parametrize("M", [20, 128, 130, 300])
 def test_linear_wide_kernel_128_rows(rtn, bits, g, M):
