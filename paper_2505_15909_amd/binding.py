@@ -110,8 +110,16 @@ def _check(status: int, what: str):
         raise RtnError(status, what)
 
 
+# The current stream's handle without the Stream object that torch.cuda.current_stream() makes: 0.2 us instead of 2 of the
+# 8 us that a small call took on the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _ptr(t):
@@ -119,7 +127,7 @@ def _ptr(t):
 
 
 def _dev_fp16(t: torch.Tensor, name: str):
-    if not (t.is_cuda and t.dtype == torch.float16 and t.is_contiguous() and t.dim() == 2):
+    if not (t.is_cuda and t.dtype is torch.float16 and t.is_contiguous() and t.dim() == 2):
         raise ValueError(f"{name} must be a contiguous fp16 CUDA matrix")
 
 
@@ -179,7 +187,7 @@ def rtn_linear(A: torch.Tensor, qweight: torch.Tensor, scales: torch.Tensor, bit
                                 dtype=torch.uint8, device=A.device)
     c = make_cfg(cfg)
     st = _lib.rtn_linear_ex(A.data_ptr(), M, qweight.data_ptr(), scales.data_ptr(), N, K, bits, group_size,
-                            out.data_ptr(), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+                            out.data_ptr(), workspace.data_ptr(), workspace.nbytes,
                             _stream(), C.byref(c) if c is not None else None)
     _check(st, "rtn_linear")
     return out
@@ -267,7 +275,7 @@ def rtn_gemm_fp16(A: torch.Tensor, W: torch.Tensor, out: torch.Tensor = None, wo
     N = W.shape[0]
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=A.device)
-    wp, wn = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) if workspace is not None else (None, 0)
+    wp, wn = (workspace.data_ptr(), workspace.nbytes) if workspace is not None else (None, 0)
     _check(_lib.rtn_gemm_fp16(A.data_ptr(), M, W.data_ptr(), N, K, out.data_ptr(), wp, wn, _stream()), "rtn_gemm_fp16")
     return out
 
@@ -280,7 +288,7 @@ def rtn_linear_dense(A: torch.Tensor, qweight: torch.Tensor, scales: torch.Tenso
     N = scales.shape[0]
     if out is None:
         out = torch.empty((M, N), dtype=torch.float16, device=A.device)
-    wp, wn = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) if workspace is not None else (None, 0)
+    wp, wn = (workspace.data_ptr(), workspace.nbytes) if workspace is not None else (None, 0)
     _check(_lib.rtn_linear_dense(A.data_ptr(), M, qweight.data_ptr(), scales.data_ptr(), N, K, bits, group_size,
                                  out.data_ptr(), w_tmp.data_ptr(), w_tmp.numel() * w_tmp.element_size(), wp, wn,
                                  _stream()), "rtn_linear_dense")
