@@ -360,6 +360,8 @@ def test_layer_of_independent_modules_in_block_launches(rtn, M):
     plan = rtn.LayerPlan(mods)
     plan.run()
     check("layer")
+    plan.run_grouped()
+    check("grouped")
     rtn.LayerPlan(mods, workspace=torch.empty(64 << 20, dtype=torch.uint8, device=DEV)).run()
     check("64 MiB")
     if M > 32:                              # (the small-batch kernel's own plans want their workspace)
