@@ -571,9 +571,11 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
             if (M <= (bits == 4 ? 1024 : 512)) {
                 // against the block kernel, whose model falls short by 8 % above 128 rows (57344 x 8192 at 220 and 512 rows: tile 206
                 // and 407 us, block 214 and 430-453; 106496 x 16384 at 200 rows: 780 and 818; 16384 x 53248 at 160 rows: 375 and
-                // 299; 6144 x 4096 at 1000 rows: 59 and 51).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
+                // 299; 6144 x 4096 at 1000 rows: 59 and 51), and by 21 % above 512, outside its fit: layers whose matrices are
+                // modelled below that line ran 3-7 % slower on the block kernel (5120-wide layer at 1024 rows 565 us, tile 528;
+                // 16384-wide at 1024 rows 5325, tile 5170), those above it faster (16384-wide at 600 rows 3571, tile 3736).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
                 // (16384 x 53248 at 129 rows: 375 us, block 294).
-                tile_wins = t_tile * 1.03 < t_block * (M > 128 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
+                tile_wins = t_tile * 1.03 < t_block * (M > 512 ? 1.21 : M > 128 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
             } else if (((N + 255) / 256) * ((M + 127) / 128) >= 256) {
                 tile_wins = true;
             } else {
