@@ -232,7 +232,8 @@ typedef struct {
  * expected to be faster than the modules' own: up to 8 rows one launch of the small-batch kernel (one precision and group
  * size -- 512 columns and more at 4 bit, 256 at 8 bit count as one --, 140 KiB of activations each (M K 2 bytes), under 256 MB
  * of weights together); from 5 to 512 rows one launch of the wide kernels for the modules of each precision and group size, with
- * their K splits one after another in the workspace.  The plan is the launch's own: the same result as in order, up to the
+ * their K splits one after another in the workspace; above 512 rows one launch of the tile kernel for the modules of each
+ * precision that it serves.  The plan is the launch's own: the same result as in order, up to the
  * summation order of a single call -- so a module's last bits may depend on the modules it shares the call with (rtn_linear
  * gives those of the module alone) -- and with weights that a module alone may round to fp16 after scaling (path 4) not rounded. */
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace,

@@ -1427,8 +1427,48 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
     return best;
 }
 
+// Independent modules of one precision in one launch of the tile kernel: apart, every one ends in a round that fills the chip in
+// part, or pays a second launch or a reduce pass to fill it.  One tile height for all, the longest workgroups first, K of the module
+// with the longest split in two, four or eight.  Times of a workgroup as in tile_model_us, dealt to the compute units as above.
+static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
+    MergedPlan best;
+    best.us = -1.0;
+    for (int r = 4; r <= 8; r += 4) {
+        const double half = r == 8 ? 1.26 : 0.82, full = r == 8 ? 1.58 : 1.00;
+        MergedPlan m;
+        m.mb = r; m.wk = 0;
+        for (int i = 0; i < n; ++i) m.split[i] = 1;
+        for (;;) {
+            double each[rtn::kMaxBlockGroup], reduce = 0.0;
+            int64_t count[rtn::kMaxBlockGroup], wgs = 0;
+            size_t partials = 0;
+            int longest = 0;
+            for (int i = 0; i < n; ++i) {
+                const int64_t s = m.split[i], mn = a[i].M * a[i].N;
+                count[i] = (((a[i].N + 255) / 256) * ((a[i].M + 32 * r - 1) / (32 * r)) + 7) / 8 * s;
+                wgs += 8 * count[i];
+                each[i] = (double)((a[i].K / 64 + s - 1) / s);
+                if (each[i] > each[longest]) longest = i;
+                if (s > 1) {
+                    reduce += 5.3 + (double)mn * (8.0 * s + 2.0) / 8.0e6;
+                    partials += ((size_t)mn * sizeof(float) * s + 255) & ~(size_t)255;
+                }
+            }
+            if (partials > workspace) break;
+            const double step = half + (full - half) * std::max(0.0, std::min(1.0, (double)wgs / 128.0 - 1.0));
+            const int64_t steps = (int64_t)each[longest];
+            for (int i = 0; i < n; ++i) each[i] = each[i] * step + 6.0;
+            m.us = 1.03 * (dealt_us(each, count, n, 32) + reduce);
+            if (best.us < 0.0 || m.us < best.us) best = m;
+            if (m.split[longest] >= 8 || steps < 16) break;
+            m.split[longest] *= 2;
+        }
+    }
+    return best;
+}
+
 // The same, remembered (some 50 us of host time): a table of fixed size, an entry gives way to the next one that falls on it.
-static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace) {
+static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace, bool tiles = false) {
     struct Key { int64_t v[4 * rtn::kMaxBlockGroup + 3]; };
     struct Entry { Key key; MergedPlan plan; bool used; };
     constexpr size_t kEntries = 128;
@@ -1436,7 +1476,7 @@ static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace)
     static Entry table[kEntries];
     Key k = {};
     uint64_t h = 0;
-    k.v[0] = n; k.v[1] = a[0].bits; k.v[2] = a[0].workspace ? (int64_t)workspace : 0;
+    k.v[0] = n; k.v[1] = a[0].bits + (tiles ? 256 : 0); k.v[2] = a[0].workspace ? (int64_t)workspace : 0;
     for (int i = 0; i < n; ++i) { k.v[3 + 4 * i] = a[i].M; k.v[4 + 4 * i] = a[i].N; k.v[5 + 4 * i] = a[i].K; k.v[6 + 4 * i] = a[i].g; }
     for (int64_t v : k.v) h = (h ^ (uint64_t)v) * 0x9E3779B97F4A7C15ull, h ^= h >> 29;
     Entry& e = table[h % kEntries];
@@ -1444,7 +1484,8 @@ static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace)
         std::lock_guard<std::mutex> lock(mutex);
         if (e.used && memcmp(&e.key, &k, sizeof(k)) == 0) return e.plan;
     }
-    const MergedPlan p = merged_blocks(a, n, a[0].workspace ? workspace : 0);
+    const size_t cap = a[0].workspace ? workspace : 0;
+    const MergedPlan p = tiles ? merged_tiles(a, n, cap) : merged_blocks(a, n, cap);
     std::lock_guard<std::mutex> lock(mutex);
     e.key = k; e.plan = p; e.used = true;
     return p;
@@ -1521,6 +1562,50 @@ static bool layer_in_blocks(const rtn_module* mods, const LinearArgs* args, int 
     return true;
 }
 
+// rtn_layer_forward above 512 rows: modules that the tile kernel serves, of one precision, in one launch of it where that is
+// modelled 3 % ahead (8B layer int4 at 1536 rows 625 -> 553 us, 2048 rows 773 -> 726; 5120-wide layer at 2048 rows
+// 996 -> 900; closer to level it measures within 1 % either way).  Other modules, whose weights are not rounded to fp16, keep their kernel.
+static bool layer_in_tiles(const rtn_module* mods, const LinearArgs* args, int n, void* dev_workspace, size_t workspace_nbytes, void* stream,
+                           rtn_status* status) {
+    constexpr int kMost = 16;
+    double own_us[kMost];
+    bool done[kMost] = {}, tile[kMost];
+    for (int i = 0; i < n; ++i) {
+        LinearPlan own;
+        if (resolve_plan(args[i], nullptr, workspace_nbytes, &own) != RTN_OK) return false;
+        tile[i] = own.path == 4;
+        own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
+    }
+    for (int i = 0; i < n; ++i) {
+        if (done[i]) continue;
+        LinearArgs set[rtn::kMaxTileGroup];
+        int member[rtn::kMaxTileGroup], count = 0;
+        double apart = 0.0;
+        for (int j = i; j < n && count < rtn::kMaxTileGroup; ++j) {
+            if (done[j] || !tile[i] || !tile[j] || args[j].bits != args[i].bits) continue;
+            apart += own_us[j];
+            member[count] = j;
+            set[count++] = args[j];
+        }
+        MergedPlan m;
+        m.us = -1.0;
+        if (count > 1) m = remembered_merge(set, count, std::min(workspace_nbytes, kWorkspaceCapTile), true);
+        if (m.us < 0.0 || m.us > 0.97 * apart) {
+            *status = one_module(mods[i], dev_workspace, workspace_nbytes, stream);
+            if (*status != RTN_OK) return true;
+            done[i] = true;
+            continue;
+        }
+        if (rtn::launch_linear_tiles(set, m.split, count, m.mb, static_cast<hipStream_t>(stream)) != hipSuccess) {
+            *status = RTN_ERR_HIP;
+            return true;
+        }
+        for (int k = 0; k < count; ++k) done[member[k]] = true;
+    }
+    *status = RTN_OK;
+    return true;
+}
+
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
                              void* stream) {
     if (!mods) return RTN_ERR_NULL;
@@ -1543,6 +1628,10 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
             ok = mods[i].M > 4 && mods[i].M <= kMaxMergedRows && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
         rtn_status st;
         if (ok && modules_independent(args, n_mods) && layer_in_blocks(mods, args, n_mods, dev_workspace, workspace_nbytes, stream, &st)) return st;
+        ok = true;
+        for (int i = 0; i < n_mods && ok; ++i)
+            ok = mods[i].M > kMaxMergedRows && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
+        if (ok && modules_independent(args, n_mods) && layer_in_tiles(mods, args, n_mods, dev_workspace, workspace_nbytes, stream, &st)) return st;
     }
     for (int i = 0; i < n_mods; ++i) {
         const rtn_module& m = mods[i];

@@ -28,12 +28,16 @@
 // the chip and 5 % slower on all of it (twice the accumulator traffic per flop); a raised wavefront priority around the
 // MFMAs is 5-8 % slower.
 //
+// A launch takes several independent problems: its workgroups find theirs by a scan over first[], whose order (longest first)
+// lets the short ones fill the last round.  A launch of one problem takes the time it took without the table.
+//
 // Fused dequantisation: a packed tile is unpacked once per workgroup (not once per wavefront), multiplied by
 // its group's scale in fp16 (one rounding per weight, relative error 2^-11, far inside the layer's tolerance)
 // and written to LDS as ordinary fp16, so the inner loop is that of the dense GEMM and carries no
 // per-accumulator scale arithmetic.
 #include "rtn_device.h"
 #include "rtn_internal.h"
+#include <algorithm>
 
 namespace rtn {
 
@@ -64,6 +68,14 @@ struct TileParams {
     uint32_t b_bytes, sc_bytes;   // packed sources only
 };
 
+// The problems of one launch: problem i has the workgroups first[i] .. first[i + 1], blocks[i] of them (a multiple of the XCDs)
+// per K split.
+struct TileGroup {
+    int n;
+    int first[kMaxTileGroup + 1], blocks[kMaxTileGroup];
+    TileParams p[kMaxTileGroup];
+};
+
 __device__ __forceinline__ uint32_t swizzled(int row, int piece) {      // byte offset inside a staged tile
     return (uint32_t)(row * 128 + ((piece ^ (row & 7)) * 16));
 }
@@ -82,7 +94,12 @@ __device__ __forceinline__ void wait_and_barrier() {
 
 // BSRC: 0 = dense fp16 weights, 4 / 8 = packed codes.  MBW: 16-row blocks per wavefront along M (4 or 8).
 template <int BSRC, int MBW>
-__global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams p) {
+__global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup group) {
+    int gi = 0;
+    while (gi + 1 < group.n && (int)blockIdx.x >= group.first[gi + 1]) ++gi;
+    const TileParams p = group.p[gi];                        // by value: read once, not again after each barrier
+    const int local = (int)blockIdx.x - group.first[gi];
+    const int sg = local / group.blocks[gi];                 // K split
     constexpr int TM = 32 * MBW;
     constexpr int A_BYTES = TM * 128, B_BYTES = kTN * 128;
     constexpr int HB = MBW / 4;                              // phases per 32-column slice (four row blocks each)
@@ -105,9 +122,8 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams
     const int nl = lane & 15, kq = lane >> 4;
 
     int xb, zb;                                              // tile along N, along M
-    if (!xcd_tile(blockIdx.x, p.XB, p.ZB, kZGroup, &xb, &zb)) return;
+    if (!xcd_tile(local - sg * group.blocks[gi], p.XB, p.ZB, kZGroup, &xb, &zb)) return;
     const int m0 = zb * TM, n0 = xb * kTN;
-    const int sg = blockIdx.y;
     const int kc0 = sg * p.kc_base + min(sg, p.kc_rem);      // first 128-column chunk
     const int T = 2 * (p.kc_base + (sg < p.kc_rem ? 1 : 0)); // 64-column steps of this workgroup
     const int ks0 = 2 * kc0;
@@ -363,23 +379,35 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileParams
 }
 
 template <int BSRC, int MBW>
-hipError_t launch_tile_inst(const TileParams& tp, dim3 grid, hipStream_t st) {
-    hipLaunchKernelGGL((tile_gemm_kernel<BSRC, MBW>), grid, dim3(kThreads), 0, st, tp);
+hipError_t launch_tile_inst(const TileGroup& group, hipStream_t st) {
+    hipLaunchKernelGGL((tile_gemm_kernel<BSRC, MBW>), dim3((unsigned)group.first[group.n]), dim3(kThreads), 0, st, group);
     return hipGetLastError();
 }
 
+// All problems of a launch in tiles of 128 or (tall) 256 rows.
+hipError_t launch_tiles(TileGroup& group, int bsrc, bool tall, hipStream_t st) {
+    const int tm = tall ? 256 : 128;
+    group.first[0] = 0;
+    for (int i = 0; i < group.n; ++i) {
+        TileParams& tp = group.p[i];
+        tp.XB = (tp.N + kTN - 1) / kTN;
+        tp.ZB = (tp.M + tm - 1) / tm;
+        group.blocks[i] = (tp.XB * tp.ZB + kXcds - 1) / kXcds * kXcds;
+        group.first[i + 1] = group.first[i] + group.blocks[i] * tp.split_k;
+    }
+    if (bsrc == 0) return tall ? launch_tile_inst<0, 8>(group, st) : launch_tile_inst<0, 4>(group, st);
+    if (bsrc == 4) return tall ? launch_tile_inst<4, 8>(group, st) : launch_tile_inst<4, 4>(group, st);
+    return tall ? launch_tile_inst<8, 8>(group, st) : launch_tile_inst<8, 4>(group, st);
+}
+
 // rows16: 16-row blocks per wavefront (4 or 8), 0 = choose.
-hipError_t launch_tile(TileParams& tp, int bsrc, int64_t M, int rows16, hipStream_t st) {
-    const int64_t xb = (tp.N + kTN - 1) / kTN;
+hipError_t launch_tile(const TileParams& tp, int bsrc, int64_t M, int rows16, hipStream_t st) {
     const bool tall = rows16 ? rows16 == 8
                              : M > 128 && tile_model_us(bsrc == 0, 8, M, tp.N, tp.K, tp.split_k) < tile_model_us(bsrc == 0, 4, M, tp.N, tp.K, tp.split_k);
-    const int tm = tall ? 256 : 128;
-    tp.XB = (int)xb;
-    tp.ZB = (int)((M + tm - 1) / tm);
-    dim3 grid((unsigned)((tp.XB * tp.ZB + kXcds - 1) / kXcds * kXcds), (unsigned)tp.split_k, 1);
-    if (bsrc == 0) return tall ? launch_tile_inst<0, 8>(tp, grid, st) : launch_tile_inst<0, 4>(tp, grid, st);
-    if (bsrc == 4) return tall ? launch_tile_inst<4, 8>(tp, grid, st) : launch_tile_inst<4, 4>(tp, grid, st);
-    return tall ? launch_tile_inst<8, 8>(tp, grid, st) : launch_tile_inst<8, 4>(tp, grid, st);
+    TileGroup group;
+    group.n = 1;
+    group.p[0] = tp;
+    return launch_tiles(group, bsrc, tall, st);
 }
 
 void fill_common(TileParams& tp, const void* A, void* C, float* ws, int64_t M, int64_t N, int64_t K, int split_k) {
@@ -421,9 +449,9 @@ bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p) {
     return p.split_k >= 1 && p.split_k <= a.K / kChunkK;
 }
 
-hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st) {
+static TileParams packed_params(const LinearArgs& a, float* workspace, int split_k) {
     TileParams tp;
-    fill_common(tp, a.A, a.C, a.workspace, a.M, a.N, a.K, p.split_k);
+    fill_common(tp, a.A, a.C, workspace, a.M, a.N, a.K, split_k);
     tp.B = a.qweight;
     tp.scales = static_cast<const half_t*>(a.scales);
     tp.G = (int)(a.K / a.g);
@@ -433,9 +461,33 @@ hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStrea
     tp.KL = (int)(a.K / (a.bits == 4 ? 128 : 64));
     tp.b_bytes = (uint32_t)((size_t)a.N * a.K * a.bits / 8);
     tp.sc_bytes = (uint32_t)((size_t)a.N * tp.G * 2);
-    hipError_t e = launch_tile(tp, a.bits, a.M, p.m_rows16 == 4 || p.m_rows16 == 8 ? p.m_rows16 : 0, st);
+    return tp;
+}
+
+hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st) {
+    hipError_t e = launch_tile(packed_params(a, a.workspace, p.split_k), a.bits, a.M, p.m_rows16 == 4 || p.m_rows16 == 8 ? p.m_rows16 : 0, st);
     if (e != hipSuccess) return e;
     if (p.split_k > 1) e = launch_splitk_reduce(a.workspace, a.C, a.M * a.N, p.split_k, st);
+    return e;
+}
+
+hipError_t launch_linear_tiles(const LinearArgs* args, const int* split, int n, int rows16, hipStream_t st) {
+    if (n < 1 || n > kMaxTileGroup) return hipErrorInvalidValue;
+    int order[kMaxTileGroup];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::sort(order, order + n, [&](int x, int y) { return args[x].K / split[x] > args[y].K / split[y]; });   // longest first
+    float* partials[kMaxTileGroup];
+    size_t used = 0;
+    for (int i = 0; i < n; ++i) {
+        partials[i] = split[i] > 1 ? args[i].workspace + used / sizeof(float) : nullptr;
+        if (split[i] > 1) used += ((size_t)args[i].M * args[i].N * sizeof(float) * split[i] + 255) & ~(size_t)255;
+    }
+    TileGroup group;
+    group.n = n;
+    for (int k = 0; k < n; ++k) group.p[k] = packed_params(args[order[k]], partials[order[k]], split[order[k]]);
+    hipError_t e = launch_tiles(group, args[0].bits, rows16 == 8, st);
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        if (split[i] > 1) e = launch_splitk_reduce(partials[i], args[i].C, args[i].M * args[i].N, split[i], st);
     return e;
 }
 

@@ -71,6 +71,10 @@ hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans,
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
+// The tile kernel on several independent problems of one precision at once, in tiles of 16 rows16 x 2 rows (rows16 = 4 or 8); partial
+// sums of K splits go to the workspace one problem after another.
+constexpr int kMaxTileGroup = kMaxBlockGroup;
+hipError_t launch_linear_tiles(const LinearArgs* args, const int* split, int n, int rows16, hipStream_t st);
 // Dense fp16 GEMM C[M,N] = A[M,K] W[N,K]^T with the same tile kernel (K a multiple of 128; rows16 = 4 or 8); split_k > 1 goes
 // through the fp32 workspace [split_k][M][N].
 hipError_t launch_gemm_fp16(const void* A, const void* W, void* C, float* workspace, int64_t M, int64_t N, int64_t K,

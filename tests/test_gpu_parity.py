@@ -1047,3 +1047,40 @@ def test_asym_linear(rtn, bits, g):
     torch.cuda.synchronize()
     ref = _to_np(A_t).astype(np.float64) @ O.rtn_dequantize_asym(codes, scales, zeros, gg).astype(np.float16).astype(np.float64).T
     H.assert_linear_close(_to_np(C), ref, f"asym dual path int{bits} g={g}")
+
+
+@pytest.mark.parametrize("bits,g", [(4, 128), (4, 0), (8, 128)])
+@pytest.mark.parametrize("M", [520, 777, 1041])
+def test_layer_of_independent_modules_in_tile_launches(rtn, bits, g, M):
+    """rtn_layer_forward above 512 rows: modules that the tile kernel serves share a launch of it.  Tile edges ragged in M and N, other
+    rows and K per module, with and without room for a K split, and a module that another kernel serves among them; every
+    module against a float64 product with the oracle's weights (sampled rows), twice from a graph."""
+    shapes = [(6160, 512, M), (4096, 1024, M + 3), (9232, 512, M - 6), (1040, 2048, M), (8208, 2560, M)]
+    mods, refs = [], []
+    for i, (N, K, m) in enumerate(shapes):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i)
+        A_t = synth.activation(m, K, seed=M + i, device=DEV)
+        rows = np.unique(np.concatenate([[0, 127, 128, 255, 256, m - 1], np.arange(i, m, 61)]))
+        mods.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.zeros((m, N), dtype=torch.float16, device=DEV)))
+        refs.append((rows, O.rtn_linear(_to_np(A_t)[rows], codes, scales, gg)))
+
+    def check(what):
+        torch.cuda.synchronize()
+        for i, (m, (rows, ref)) in enumerate(zip(mods, refs)):
+            C = _to_np(m["C"])
+            H.assert_linear_close(C[rows], ref, f"{what} int{bits} g={g} M={M} module {i}")
+            assert (np.abs(C.astype(np.float32)).sum(axis=1) > 0).all(), f"{what}: module {i} has rows not written"
+            m["C"].zero_()
+
+    plan = rtn.LayerPlan(mods)
+    plan.run()
+    check("layer")
+    rtn.LayerPlan(mods, workspace=torch.empty(256, dtype=torch.uint8, device=DEV)).run()
+    check("no workspace")
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        plan.run()
+    for _ in range(2):
+        graph.replay()
+        check("graph")
