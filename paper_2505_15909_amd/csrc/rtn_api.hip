@@ -539,6 +539,8 @@ bool tile_beats_wide(int64_t M, int64_t N, int64_t K, int bits, int64_t g, const
 LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path = 0,
                      int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile);
 
+LinearPlan wide_or_tile_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t workspace);
+
 LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path, int64_t steps_hint,
                          size_t workspace) {
     LinearPlan p;
@@ -563,25 +565,20 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
     double t_block = 0;
     if (force_path == 3 || (force_path == 0 && wide_wins)) wide_plan(M, N, K, bits, g, &w);
     if (force_path == 0 && wide_wins) t_block = block_plan(M, N, K, bits, g, cap, false, &block);
-    if (force_path == 0 && wide_wins && M >= 128) {
-        const double t_wide = wide_model_us(M, N, K, bits, w.m_rows16, w.waves_n, w.n_tiles16, w.split_k);
-        if (tile_line(M, N, K, bits, t_wide)) {
-            double t_tile = 0;
-            tile_two_launches(false, M, N, K, workspace, &t_tile);
-            if (M <= (bits == 4 ? 1024 : 512)) {
-                // against the block kernel, whose model falls short by 8 % above 128 rows (57344 x 8192 at 220 and 512 rows: tile 206
-                // and 407 us, block 214 and 430-453; 106496 x 16384 at 200 rows: 780 and 818; 16384 x 53248 at 160 rows: 375 and
-                // 299; 6144 x 4096 at 1000 rows: 59 and 51), and by 21 % above 512, outside its fit: layers whose matrices are
-                // modelled below that line ran 3-7 % slower on the block kernel (5120-wide layer at 1024 rows 565 us, tile 528;
-                // 16384-wide at 1024 rows 5325, tile 5170), those above it faster (16384-wide at 600 rows 3571, tile 3736).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
-                // (16384 x 53248 at 129 rows: 375 us, block 294).
-                tile_wins = t_tile * 1.03 < t_block * (M > 512 ? 1.21 : M > 128 ? 1.08 : 1.0) || (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
-            } else if (((N + 255) / 256) * ((M + 127) / 128) >= 256) {
-                tile_wins = true;
-            } else {
-                tile_wins = tile_beats_wide(M, N, K, bits, g, w, t_wide, workspace);
-            }
-        }
+    // The tile kernel rounds each scaled weight to fp16, the block kernel does not: it may take a problem from the tile kernel, never
+    // give it one.  (Without the line, 0.4 % of the problems of 129 to 1024 rows lost bits: 749 rows of 5952 x 3072 int4, 362 of
+    // 12176 x 1536 int8; and 16384 x 53248 at 133 rows without a workspace took 697 us on an unsplit tile plan.)
+    if (force_path == 0 && wide_wins && M >= 128 && wide_or_tile_plan(M, N, K, bits, g, workspace).path == 4) {
+        double t_tile = 0;
+        tile_two_launches(false, M, N, K, workspace, &t_tile);
+        // against the block kernel, whose model falls short by 8 % above 128 rows (57344 x 8192 at 220 and 512 rows: tile 206
+        // and 407 us, block 214 and 430-453; 106496 x 16384 at 200 rows: 780 and 818; 16384 x 53248 at 160 rows: 375 and
+        // 299; 6144 x 4096 at 1000 rows: 59 and 51), and by 21 % above 512, outside its fit: layers whose matrices are
+        // modelled below that line ran 3-7 % slower on the block kernel (5120-wide layer at 1024 rows 565 us, tile 528;
+        // 16384-wide at 1024 rows 5325, tile 5170), those above it faster (16384-wide at 600 rows 3571, tile 3736).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
+        // (16384 x 53248 at 129 rows: 375 us, block 294).
+        tile_wins = M > (bits == 4 ? 1024 : 512) || t_tile * 1.03 < t_block * (M > 512 ? 1.21 : M > 128 ? 1.08 : 1.0) ||
+                    (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
     }
     if (force_path == 4 || tile_wins) {
         p.path = 4;

@@ -240,3 +240,15 @@ def test_grouped_launches_keep_apart_what_one_launch_would_thin_out(ask):
     for g, M in ((32, 3), (32, 4), (128, 3), (0, 4)):                                             # the down projection apart
         assert launches(LAYER_8B, M, 4, g) == [0, 0, 0, 1]
     assert len(set(launches([(5760, 4608), (4608, 4608), (35840, 4608), (4608, 17920)], 2, 4, 128))) > 1
+
+
+@pytest.mark.parametrize("workspace", [0, 16 * MIB, 256 * MIB])
+def test_no_problem_goes_from_exact_codes_to_rounded_weights(ask, workspace):
+    """The tile kernel rounds each scaled weight to fp16, so it has the problems that its own line gives it against the wide kernel
+    and no others: where that line says wide, the call stays on exact codes whatever the block kernel's model says."""
+    exact = [(749, 5952, 3072, 4, 128), (892, 6848, 1024, 4, 128), (965, 4624, 3584, 4, 128), (602, 7216, 5632, 4, 128), (609, 8672, 2560, 4, 128),
+             (362, 12176, 1536, 8, 0), (457, 9392, 1024, 8, 0)]
+    if workspace < 64 * MIB:
+        exact += [(130, 16384, 53248, 4, 128), (133, 16384, 53248, 4, 128), (144, 16384, 53248, 4, 0)]
+    for p, (status, launches) in zip(exact, ask([f"linear {' '.join(map(str, p))} {workspace}" for p in exact])):
+        assert status == 0 and all(q["path"] == 3 for q in launches), (p, launches)
