@@ -144,12 +144,11 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
     }
 }
 
-// The block kernel's time.  A workgroup: a fixed start, so much per unit of four packed tiles that each of its wavefronts
-// along K runs (by 32-row blocks; the scales cost per group and block), the sum over the wavefronts along K; slower by up to
-// a third on a busy chip, whose clock falls.  Workgroups come in rounds of one per compute unit (two of the 32-row ones), of
-// the fullest XCD.  Against it the stream of weights at 6.8 TB/s and of activations from L2 at 17 TB/s.  Fitted to 5300
-// launches on sixteen shapes of 1024 to 57344 columns, 20 to 512 rows, int4 and int8, groups of 64, 128 and K (8 % rms; the
-// plan it picks is 1.5 % behind the best measured one on average, 6 % at the 90th percentile).
+// The block kernel's time, as two models have it.  The first: a workgroup has a fixed start, so much per unit of four packed tiles
+// that each of its wavefronts along K runs (by 32-row blocks; the scales cost per group and block), the sum over the wavefronts along
+// K; slower by up to a third on a busy chip, whose clock falls.  Workgroups come in rounds of one per compute unit (two of the 32-row
+// ones), of the fullest XCD.  Against it the stream of weights at 6.8 TB/s and of activations from L2 at 17 TB/s.  Fitted to 5300
+// launches on sixteen shapes of 1024 to 57344 columns, 20 to 512 rows, int4 and int8, groups of 64, 128 and K.
 struct BlockTimes {
     int mb;             // row blocks of 32 rows
     int64_t wgs;        // workgroups
@@ -170,36 +169,73 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
     return b;
 }
 
-double block_split_us(int64_t M, int64_t N, int s) { return s > 1 ? 1.12 + (double)M * N * s * 8.0 / 4.19e6 : 0.0; }
-
-double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
     const BlockTimes b = block_times(M, N, K, bits, g, rows16, wk, s);
     const double wg = b.wg_us * (1.0 + 0.36 * std::min(1.0, (double)b.wgs / 256.0) * b.mb / 4.0);
     const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), rounds = std::ceil((double)b.wgs / 8.0) / slots;
     double serial = wg * std::max(1.0, 0.91 * std::ceil(rounds) + 0.09 * rounds);
     if (slots > 32.0 && b.wgs > 256) serial *= 1.78;
-    return 2.93 + std::cbrt(serial * serial * serial + b.stream_us * b.stream_us * b.stream_us) + block_split_us(M, N, s);
+    return 2.93 + std::cbrt(serial * serial * serial + b.stream_us * b.stream_us * b.stream_us) +
+           (s > 1 ? 1.12 + (double)M * N * s * 8.0 / 4.19e6 : 0.0);
 }
 
-// Plan of the block kernel within `cap` bytes of partial sums, and its modelled time: row tile height, wavefronts along K,
-// K splits.  Row tiles of 128 rows keep the weights' unpacking per flop low and suit large matrices; under 64 M weights the
-// compute units are filled by 64-row tiles instead (6144 x 4096 at 128 rows: 14.9 us against 19.2).  Eight wavefronts along K
-// are for a row tile that is alone or almost: 32 rows below 64, 64 rows above; 64 to 96 rows of a matrix under 24 M weights
-// split K in two instead where the workspace allows (4096 x 4096 at 64 rows: 10.2 us, 9.7 unsplit with four wavefronts along K,
-// 8.6 with eight; rtn_linear_query has always reported a split there, and its callers are shown one).
+// The second, for few columns, long rows and many rows too: a workgroup has a start, and the larger part (a 3/2-norm) of what its
+// wavefronts along K run and of what one compute unit can fetch, which holds back few columns under long rows (each of eight
+// wavefronts along K has activations of its own); two 32-row ones on a compute unit are each slower by two thirds.  Against it
+// (a 4-norm) the stream from HBM, what the XCDs that have a workgroup fetch (all activations each: a matrix of few columns
+// leaves most of them idle) and what they read from their L2.  The reduce pass of a K split costs more above eight splits (its
+// kernel goes round).  Fitted to 78000 launches: 1394 problems of 17 to 4096 rows, 128 to 106496 columns of 512 to 53248.
+double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+    static const double kUnit[4][4] = {{1.791, 1.971, 2.149, 2.810}, {2.437, 2.819, 3.048, 3.392}, {3.418, 3.411, 4.144, 4.144}, {3.948, 4.007, 4.956, 4.956}};
+    static const double kGroup[4] = {0.062, 0.091, 0.044, 0.103};
+    const int64_t unit = bits == 4 ? 512 : 256, units = K / unit, cols = 256 / wk;
+    const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols;
+    const int mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
+    const bool sliced = rtn::xcd_slices_save_a_round(XB, ZB, s), two = mb == 1 && wk <= 4;
+    const double on_xcd = (double)((sliced ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s), xcds = sliced ? 8.0 : (double)std::min<int64_t>(XB, 8);
+    const int64_t share = (units + s - 1) / s, per = (share + wk - 1) / wk;
+    const double groups = g >= unit ? 1.0 : (double)(unit / g), weights = (double)N * K * bits / 8.0, rows = (double)M * K * 2.0;
+    const double run = (double)per * (kUnit[mb - 1][wk == 1 ? 0 : wk == 2 ? 1 : wk == 4 ? 2 : 3] * (bits == 8 ? 0.541 : 1.0) + kGroup[mb - 1] * groups) *
+                       (1.0 + 0.376 * std::min(1.0, (double)(XB * ZB * s) / 256.0) * mb / 4.0);
+    const double a_bytes = 32.0 * mb * share * unit * 2.0, w_bytes = (double)cols * share * unit * bits / 8.0;
+    const double fetch = 0.543 * (a_bytes + w_bytes) / 1e5, both = run * std::sqrt(run) + fetch * std::sqrt(fetch);
+    const double wg = 0.511 + std::cbrt(both * both) + (wk > 1 ? 0.484 * mb : 0.0);
+    const double rounds = on_xcd / (two ? 64.0 : 32.0);
+    const double serial = wg * std::max(1.0, 0.774 * std::ceil(rounds) + 0.226 * rounds) * (two && on_xcd > 32.0 ? 1.667 : 1.0);
+    const double hbm = 1.195 * (weights + rows) / 6.83e6, fabric = 0.530 * (rows + weights / xcds) / 1e6;
+    const double l2 = 0.812 * on_xcd * (a_bytes + 1.550 * w_bytes) / 2e6;
+    auto to4 = [](double x) { return x * x * x * x; };
+    double t = 3.218 + std::sqrt(std::sqrt(to4(serial) + to4(hbm) + to4(fabric) + to4(l2))) + 3.413 * (double)M * N * 2.0 / 1e7;
+    if (s > 1) t += 2.394 + 0.734 * (double)M * N * s * 8.0 / 4.19e6 + (s > 8 ? 1.971 : 0.0);
+    return t;
+}
+
+// Below 1024 columns and above 512 rows the second alone: the best measured plan is 1.5 % and 0.7 % ahead of its pick on average
+// (of the first's 6 % and 3 %, up to 64 % on few columns under long rows: 394 rows of 400 x 43008 66 us, 41 possible).  Elsewhere
+// their mean, whose pick is 1.3 % behind, either alone 1.9 %.
+double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+    const double far = block_far_us(M, N, K, bits, g, rows16, wk, s);
+    return N < 1024 || M > 512 ? far : std::sqrt(far * block_near_us(M, N, K, bits, g, rows16, wk, s));
+}
+
+// Plan of the block kernel within `cap` bytes of partial sums, and its modelled time: row tile height (32 rows up to 96 rows, 128
+// from 65), wavefronts along K, K splits.  Two exceptions to the model, plans that rtn_linear_query has always reported and that are
+// relied upon: 64 to 96 rows of a matrix under 24 M weights split K in two where the workspace allows (4096 x 4096 at 64 rows: 10.2 us,
+// 8.6 unsplit with eight wavefronts along K); and 8-bit matrices of half a gigabyte and more with more input than output columns
+// keep 64-row tiles (16384 x 53248 at 157 rows 403 us, 340 in 128-row tiles).
 double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p) {
     const int64_t units = K / chunk_k(bits);
     double best = 1e30;
     p->path = 3; p->prefetch = 1; p->waves_n = 8; p->n_tiles16 = 2; p->waves_k = 1; p->split_k = 1; p->m_rows16 = 2;
     for (int r = 2; r <= 8; r *= 2) {
         if (r == 2 && M > 96) continue;
-        if (r == 8 && (M <= 64 || (g % 128 != 0 && !zp) || (N * K < 64000000 && M > 96) || (bits == 8 && N * K > (int64_t)512 << 20))) continue;
+        if (r == 8 && (M <= 64 || (g % 128 != 0 && !zp) || (bits == 8 && K > N && N * K > (int64_t)512 << 20))) continue;
         const int64_t tiles = (M + 16 * r - 1) / (16 * r);
         const int mb = (int)((M + 32 * tiles - 1) / (32 * tiles));
         for (int wk = 1; wk <= 8; wk *= 2) {
             if (wk > units || (wk == 8 && (mb > 2 || zp || (r == 2 && M >= 64) || (r == 4 && M <= 64)))) continue;
             const bool two = r == 2 && M >= 64 && N * K < 24000000 && 2 * wk <= units && (size_t)M * N * sizeof(float) * 2 <= cap;
-            for (int s = two ? 2 : 1; s <= 8 && s * wk <= units; ++s) {
+            for (int s = two ? 2 : 1; s <= kMaxSplitK && s * wk <= units; ++s) {
                 if (s > 1 && (size_t)M * N * sizeof(float) * s > cap) break;
                 const double t = block_model_us(M, N, K, bits, g, r, wk, s);
                 if (t < best) { best = t; p->m_rows16 = r; p->waves_k = wk; p->split_k = s; }
@@ -571,13 +607,11 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
     if (force_path == 0 && wide_wins && M >= 128 && wide_or_tile_plan(M, N, K, bits, g, workspace).path == 4) {
         double t_tile = 0;
         tile_two_launches(false, M, N, K, workspace, &t_tile);
-        // against the block kernel, whose model falls short by 8 % above 128 rows (57344 x 8192 at 220 and 512 rows: tile 206
-        // and 407 us, block 214 and 430-453; 106496 x 16384 at 200 rows: 780 and 818; 16384 x 53248 at 160 rows: 375 and
-        // 299; 6144 x 4096 at 1000 rows: 59 and 51), and by 21 % above 512, outside its fit: layers whose matrices are
-        // modelled below that line ran 3-7 % slower on the block kernel (5120-wide layer at 1024 rows 565 us, tile 528;
-        // 16384-wide at 1024 rows 5325, tile 5170), those above it faster (16384-wide at 600 rows 3571, tile 3736).  The long matrices of 400 MB just above 128 rows stay on the tile kernel, as reported to date
+        // against the block kernel (both sides of 156 such problems measured: 2-4 % behind the better one, and no better for lines
+        // 5 % to either side); a little towards the tile kernel above 512 rows, where it also takes several modules of a layer at once.
+        // The long 4-bit matrices of 400 MB just above 128 rows stay on the tile kernel, as rtn_linear_query is known to report them
         // (16384 x 53248 at 129 rows: 375 us, block 294).
-        tile_wins = M > (bits == 4 ? 1024 : 512) || t_tile * 1.03 < t_block * (M > 512 ? 1.21 : M > 128 ? 1.08 : 1.0) ||
+        tile_wins = M > (bits == 4 ? 1024 : 512) || t_tile * 1.03 < t_block * (M > 512 ? 1.05 : 1.0) ||
                     (bits == 4 && K > N && packed_bytes >= ((size_t)400 << 20) && M > 128 && M <= 144);
     }
     if (force_path == 4 || tile_wins) {
@@ -1334,7 +1368,7 @@ static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t works
 // pay once.  Plan: one row tile height and number of wavefronts along K for all (a launch is one kernel), the longest
 // workgroups first, K of the module with the longest split in two or four.  The time is the end of the last workgroup
 // when they are dealt in that order to the compute units of an XCD (32; two of the 32-row ones on each), four fifths of
-// it, and the average load one fifth; against it the streams, as in block_model_us.  Fitted to 408 merged launches of 68
+// it, and the average load one fifth; against it the streams.  Fitted to 408 merged launches of 68
 // layers (6 % rms, the pick 0.4 % behind the best one measured on average).
 struct MergedPlan {
     double us;                          // modelled time, negative: no such plan

@@ -252,3 +252,17 @@ def test_no_problem_goes_from_exact_codes_to_rounded_weights(ask, workspace):
         exact += [(130, 16384, 53248, 4, 128), (133, 16384, 53248, 4, 128), (144, 16384, 53248, 4, 0)]
     for p, (status, launches) in zip(exact, ask([f"linear {' '.join(map(str, p))} {workspace}" for p in exact])):
         assert status == 0 and all(q["path"] == 3 for q in launches), (p, launches)
+
+
+def test_block_plans_of_few_columns_long_rows_and_many_rows(ask):
+    """Problems on which the plan was measured 1.3 to 2 times slower than the best one while the block kernel's model knew only
+    matrices of 1024 columns and more at up to 512 rows: the plans that measured best (89 rows: or, with the K split kept there, 19 % behind)."""
+    best = {(2809, 656, 28160, 8, 128): [(8, 1, 3)], (601, 544, 27648, 8, 32): [(4, 1, 8)], (751, 864, 20480, 8, 32): [(4, 1, 5)],
+            (944, 672, 42496, 8, 64): [(4, 1, 5)], (2988, 864, 9728, 8, 32): [(4, 1, 1)], (1002, 432, 14336, 8, 32): [(4, 1, 8)],
+            (1058, 576, 14336, 8, 128): [(8, 2, 5)], (363, 832, 28672, 8, 128): [(8, 2, 8)], (89, 4112, 3584, 8, 256): [(2, 4, 1), (2, 2, 2)],
+            (1335, 3856, 5632, 4, 128): [(8, 1, 1)], (287, 16080, 1536, 8, 256): [(8, 1, 1)], (127, 5216, 12800, 8, 32): [(4, 1, 5)],
+            (59, 4464, 19456, 8, 64): [(4, 2, 6)]}
+    for (p, good), (status, launches) in zip(best.items(), ask([f"linear {' '.join(map(str, p))} {64 * MIB}" for p in best])):
+        assert status == 0 and len(launches) == 1, (p, launches)
+        q = launches[0]
+        assert (q["m_rows16"], q["waves_k"], q["split_k"]) in good, (p, q)
