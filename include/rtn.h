@@ -23,7 +23,7 @@
  *     GEMM kernels).  group_size g: g == K (or g <= 0) means one scale per output channel;
  *     otherwise g must be 32, 64, 128, 256, 512 or a multiple of 512 dividing K for 4-bit and 32, 64,
  *     128, 256 or a multiple of 256 dividing K for 8-bit (the paper uses 128 and per-channel; the
- *     smaller groups of Section 2.2's discussion run on the skinny and wide kernels at every M).
+ *     smaller groups of Section 2.2's discussion run on the kernels of paths 1 and 3 at every M).
  *   - Size limits of the GEMM entry points (the kernels address each tensor with 32-bit byte offsets): packed
  *     weights N*K*bits/8 and activations M*K*2 must each stay below 0x7FFF0000 bytes (2 GiB - 64 KiB), else
  *     RTN_ERR_SHAPE; M <= 2^20; N <= 2^30; K < 2^23 (group indices come from a multiply-high division that is
@@ -138,12 +138,14 @@ rtn_status rtn_linear(const void* dev_A, int64_t M, const void* dev_qweight, con
 /* Explicit kernel configuration for rtn_linear_ex (tuning sweeps and tests of every path).
  * A zeroed struct means "choose automatically", field by field. */
 typedef struct {
-    int path;      /* 0 auto, 1 MFMA skinny kernel, 2 vector-ALU dot-product kernel (M <= 4), 3 wide MFMA kernels
-                      (group_size a multiple of 128; uses split_k, m_rows16 = 2..4, n_tiles16 and waves_n = 4, 8 or -- with
-                      n_tiles16 = 1 -- 16 wavefronts per workgroup; group_size 32 and 64 with every field given, waves_n = 8
-                      and n_tiles16 = 1 or 2; also m_rows16 = 8 with n_tiles16 = 2 and waves_n = 8: up to 128 rows per
-                      workgroup.  With waves_n = 8 and n_tiles16 = 2, waves_k = 2, 4 or 8 puts that many of the eight
-                      wavefronts along K, on 256 / waves_k columns), 4 tile kernel: 128 x 256 or
+    int path;      /* 0 auto, 1 MFMA skinny kernel, 2 vector-ALU dot-product kernel (M <= 4), 3 MFMA kernels for
+                      more rows, two of them (group_size a multiple of 128; 32 and 64 with every field given, waves_n = 8 and
+                      n_tiles16 = 1 or 2).  waves_n = 8 and n_tiles16 = 1: the wide kernel, 128 columns and 16 m_rows16 rows a
+                      workgroup, m_rows16 = 2..4.  waves_n = 8 and n_tiles16 = 2: the block kernel, up to 16 m_rows16 rows, m_rows16 =
+                      2..4 or 8, with waves_k = 1, 2, 4 or 8 of its eight wavefronts along K, on 256 / waves_k columns.  Any other
+                      accepted shape (waves_n = 4, 8 or -- with n_tiles16 = 1 -- 16, n_tiles16 = 1, 2 or 4) gives only a number of
+                      columns: the block kernel with 64, 128 or 256 of them.  Both use split_k and multiply exact codes, scales
+                      applied in fp32), 4 tile kernel: 128 x 256 or
                       256 x 256 output tiles, weights dequantised to fp16 in LDS (group_size a multiple of 128; uses split_k and
                       m_rows16 = 4 or 8 for the tile height, 0 = chosen from M) */
     int prefetch;  /* k-chunks (4 KiB each) a wavefront keeps in flight: 1, 2 or 4 */
@@ -151,8 +153,7 @@ typedef struct {
     int waves_k;   /* wavefronts of a workgroup along K (in-workgroup split-K): 1 .. 16; waves_n * waves_k <= 16 */
     int split_k;   /* workgroups along K (global split-K, reduced through the workspace) */
     int m_rows16;  /* 16-row activation blocks each wavefront multiplies per weight tile: 1, 2 or 4 (path 3: 2, 3, 4, 8) */
-    int n_tiles16; /* path 3: 16-column weight tile-rows per wavefront: 1, 2 or 4;
-                      m_rows16 * n_tiles16 <= 8 (or 8 x 2) */
+    int n_tiles16; /* path 3, see there: 1, 2 or 4; m_rows16 * n_tiles16 <= 8 (or 8 x 2) */
 } rtn_linear_cfg;
 
 rtn_status rtn_linear_ex(const void* dev_A, int64_t M, const void* dev_qweight, const void* dev_scales,
@@ -231,7 +232,7 @@ typedef struct {
  * 2 to 16 modules whose outputs overlap no operand and no output of another one may share launches, where a common plan is
  * expected to be faster than the modules' own: up to 8 rows one launch of the small-batch kernel (one precision and group
  * size -- 512 columns and more at 4 bit, 256 at 8 bit count as one --, 140 KiB of activations each (M K 2 bytes), under 256 MB
- * of weights together); from 5 to 512 rows one launch of the wide kernels for the modules of each precision and group size, with
+ * of weights together); from 5 to 512 rows one launch of the block kernel for the modules of each precision and group size, with
  * their K splits one after another in the workspace; above 512 rows one launch of the tile kernel for the modules of each
  * precision that it serves.  The plan is the launch's own: the same result as in order, up to the
  * summation order of a single call -- so a module's last bits may depend on the modules it shares the call with (rtn_linear
@@ -250,7 +251,7 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
  * Codes use the same packed layout (rtn_unpack returns q); dev_zeros is fp16 [N, K/g]
  * holding the integers Z; sizes as for the scales (rtn_scales_nbytes).  Group sizes, shapes,
  * alignment and error behaviour as for rtn_quantize / rtn_dequantize / rtn_linear.
- * rtn_linear_asym runs the small-batch kernel up to 16 rows and the wide MFMA kernel above; with groups of 32 and 64
+ * rtn_linear_asym runs the small-batch kernel up to 16 rows and the MFMA kernels of path 3 above; with groups of 32 and 64
  * columns the small-batch kernel up to 19 rows and, above, whichever of the two is modelled faster;
  * for thousands of rows dequantise once with rtn_dequantize_asym and call rtn_gemm_fp16. */
 rtn_status rtn_quantize_asym(const void* dev_W, int64_t N, int64_t K, int bits, int group_size,
@@ -272,7 +273,7 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
  * is unspecified, and modules with M <= 16 and the same (bits, group size) class are merged,
  * up to 16 at a time, into single grids whose workgroups each serve one module, so that one
  * launch streams all their weights; modules of 5 to 512 rows that this leaves to launches of their own share launches of the
- * wide kernels, as in rtn_layer_forward.  No dev_C may overlap any module's dev_A.  Results are
+ * block kernel, as in rtn_layer_forward.  No dev_C may overlap any module's dev_A.  Results are
  * those of rtn_linear with the plan rtn_grouped_forward picks (planned for the summed size),
  * which may differ from the single call's in summation order only. */
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace,

@@ -246,6 +246,50 @@ double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t c
     return best;
 }
 
+// The wide kernel (eight wavefronts of one tile-row: 128 columns a workgroup) in the same terms: a step of 128 columns by 16-row
+// blocks, 64 workgroups a round of an XCD, each slower by 1.84 where two share a compute unit.  Fitted to 11200 launches of 693
+// problems (6.6 % rms, the pick 0.3 % behind the best K split on average).
+double wide16_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int s) {
+    static const double kStep[3] = {0.346, 0.482, 0.527};
+    const int64_t XB = (N + 127) / 128, ZB = (M + 16 * rows16 - 1) / (16 * rows16), steps = (K / 128 + s - 1) / s;
+    const bool sliced = rtn::xcd_slices_save_a_round(XB, ZB, s);
+    const double on_xcd = (double)((sliced ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s), xcds = sliced ? 8.0 : (double)std::min<int64_t>(XB, 8);
+    const double weights = (double)N * K * bits / 8.0, rows = (double)M * K * 2.0, share = 128.0 * steps;
+    const double wg = 0.055 + (double)steps * (kStep[rows16 - 2] * (bits == 8 ? 1.08 : 1.0) + 0.018 * rows16 * 128.0 / (double)g), rounds = on_xcd / 64.0;
+    const double serial = wg * std::max(1.0, 0.357 * std::ceil(rounds) + 0.643 * rounds) * (on_xcd > 32.0 ? 1.844 : 1.0);
+    const double hbm = 0.924 * (weights + rows) / 6.83e6, fabric = 0.330 * (rows + weights / xcds) / 1e6;
+    const double l2 = 0.409 * on_xcd * (16.0 * rows16 * share * 2.0 + 128.0 * share * bits / 8.0) / 2e6;
+    double t = 3.224 + std::sqrt(serial * serial + hbm * hbm + fabric * fabric + l2 * l2) + 3.484 * (double)M * N * 2.0 / 1e7;
+    if (s > 1) t += 2.292 + 0.881 * (double)M * N * s * 8.0 / 4.19e6 + (s > 8 ? 2.033 : 0.0);
+    return t;
+}
+
+// The block kernel's plan, or the wide kernel's where that is modelled ahead: on small problems, where the block kernel's 256 columns
+// and units of 512 (8 bit: 256) leave few workgroups and its first operands come later.  Measured, block against wide kernel:
+// 29 rows of 4448 x 512 int4 6.3 us and 4.6, 32 of 14000 x 1536 10.0 and 7.7, 1885 of 1008 x 1536 g32 17.5 and 13.6; level from about
+// 15 us; 8-bit weights in groups of 256 columns and more at 17 to 64 rows up to 30 us (27648 x 5120 at 41 rows 31.5 and 29.8).
+// Beyond 40 us, where its model was fitted to few problems, the wide kernel is not asked (57344 x 8192 int8 g128 at 29 rows 106 us, block 79).
+// Up to 64 rows the line lies 3 % to its side: of 166 measured problems 20 then run slower than on the better kernel, 24 with the models level.
+// The wide kernel's row blocks: 48 rows above 64 where they save a fifth of the padded rows.  With zero points it is 3 % further
+// behind (a zero point per operand and lane in half the columns).
+double block_or_wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p) {
+    const double t_block = block_plan(M, N, K, bits, g, cap, zp, p);
+    if (t_block > 40.0) return t_block;
+    const bool blocks48 = M > 64 ? ((M + 47) / 48) * 48 * 5 <= ((M + 63) / 64) * 64 * 4 : M > 32 && M <= 48;
+    const int rows16 = M <= 32 ? 2 : blocks48 ? 3 : 4;
+    double best = 1e30;
+    int split = 1;
+    for (int s = 1; s <= kMaxSplitK && (s == 1 || K / 128 / s >= 4); ++s) {
+        if (s > 1 && (size_t)M * N * sizeof(float) * s > cap) break;
+        const double t = (zp ? 1.03 : 1.0) * wide16_model_us(M, N, K, bits, g, rows16, s);
+        if (t < best) { best = t; split = s; }
+    }
+    if (best >= (M <= 64 ? 1.03 : 0.98) * t_block) return t_block;
+    p->waves_n = 8; p->waves_k = 1; p->n_tiles16 = 1; p->m_rows16 = rows16; p->split_k = split;
+    p->m_blocks = (int)((M + 16 * rows16 - 1) / (16 * rows16));
+    return best;
+}
+
 // Tile height (128 or 256 rows) and K split of the tile kernel: the pair with the lowest modelled time.  Splits need not
 // be powers of two: what pays is a split that fills the last round (144 tiles: three splits of 72 tall tiles make one
 // round of 216; 405B qkv at 256 rows: 163 us against 219 with one split).
@@ -557,10 +601,6 @@ bool skinny_on_small_groups(const LinearArgs& a, const LinearPlan& skinny, const
     return small_groups_skinny_us(a, skinny) < (a.zeros ? 0.95 : 1.0) * small_groups_wide_us(a, wide);
 }
 
-// force_path: 0 = choose the path, otherwise the default plan of that path.  workspace: bytes at hand for the tile kernel's
-// partial sums (by default what its best plan may take): kernel, height, split and cut are chosen within it, instead of
-// the unconstrained plan with its split cut down.  Within 16 MiB, cut down against chosen: 1011 rows of 4608 x 5120 104 us
-// against 77, 2921 of 1792 x 5120 105 against 84, 2048 of 4096 x 14336 321 against 236, 256 of 16384 x 53248 1010 against 734.
 // The tile kernel's modelled time, in one launch or two, against the wide plan's w of modelled time t_wide.  The wide kernel's
 // model, fitted at 32 to 256 rows, falls short of its times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and
 // 1.30 at 8 bit (means over 460 problems; the tile kernel's by 1.03).
@@ -572,6 +612,10 @@ bool tile_beats_wide(int64_t M, int64_t N, int64_t K, int bits, int64_t g, const
     return t_tile * 1.03 < t_fit * (bits == 4 ? (g == 128 ? 1.26 : 1.20) : (g == 128 ? 1.51 : 1.30));
 }
 
+// force_path: 0 = choose the path, otherwise the default plan of that path.  workspace: bytes at hand for
+// partial sums (by default what its best plan may take): kernel, height, split and cut are chosen within it, instead of
+// the unconstrained plan with its split cut down.  Within 16 MiB, cut down against chosen: 1011 rows of 4608 x 5120 104 us
+// against 77, 2921 of 1792 x 5120 105 against 84, 2048 of 4096 x 14336 321 against 236, 256 of 16384 x 53248 1010 against 734.
 LinearPlan auto_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t lds_limit, int force_path = 0,
                      int64_t steps_hint = 0, size_t workspace = kWorkspaceCapTile);
 
@@ -590,7 +634,7 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
         // (the wide kernel's split shrinks to the workspace, the skinny kernel's does not)
         const bool held = skinny.split_k == 1 || (size_t)M * N * sizeof(float) * skinny.split_k <= workspace;
         if (held && skinny_on_small_groups(a, skinny, p)) return skinny;
-        block_plan(M, N, K, bits, g, cap, false, &p);
+        block_or_wide_plan(M, N, K, bits, g, cap, false, &p);
         return p;
     }
     const size_t packed_bytes = (size_t)N * K * bits / 8;
@@ -599,8 +643,8 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
     bool tile_wins = false;
     LinearPlan w, block;
     double t_block = 0;
-    if (force_path == 3 || (force_path == 0 && wide_wins)) wide_plan(M, N, K, bits, g, &w);
-    if (force_path == 0 && wide_wins) t_block = block_plan(M, N, K, bits, g, cap, false, &block);
+    if (force_path == 3) wide_plan(M, N, K, bits, g, &w);
+    if (force_path == 0 && wide_wins) t_block = block_or_wide_plan(M, N, K, bits, g, cap, false, &block);
     // The tile kernel rounds each scaled weight to fp16, the block kernel does not: it may take a problem from the tile kernel, never
     // give it one.  (Without the line, 0.4 % of the problems of 129 to 1024 rows lost bits: 749 rows of 5952 x 3072 int4, 362 of
     // 12176 x 1536 int8; and 16384 x 53248 at 133 rows without a workspace took 697 us on an unsplit tile plan.)
@@ -622,12 +666,7 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
         return p;
     }
     if (force_path == 3) return w;
-    // 8-bit weights with at most one scale per unit, 17 to 64 rows, matrices of 48 MB and more: the wide kernel, which is 3-10 %
-    // ahead there (28672 x 4096 at 32 and 48 rows 25.8 and 26.8 us against 27.6 and 29.9; 10240 x 8192 at 48 rows 23.2 and
-    // 25.8), except up to 32 rows from 256 MB (57344 x 8192 at 32 rows 89 and 81, 18432 x 16384 0.88).  Everywhere else
-    // measured the block kernel is ahead or level.
-    if (force_path == 0 && wide_wins)
-        return bits == 8 && g >= 256 && M <= 64 && packed_bytes >= (size_t)48000000 && !(M <= 32 && packed_bytes >= ((size_t)256 << 20)) ? w : block;
+    if (force_path == 0 && wide_wins) return block;
     if (M <= 16 && steps_hint == 0) {
         // the table lookup costs tens of microseconds of host time (logarithms over ~800 entries): remembered per problem
         struct Key { int64_t M, N, K; int bits; size_t lds; };
@@ -923,7 +962,7 @@ rtn_status resolve_plan_zp(const LinearArgs& a, size_t workspace_nbytes, LinearP
             static Remembered<LinearPlan> remembered;
             h = remembered.get({a.M, a.N, a.K, a.g, fit, 0, a.bits, 0}, [&] {
                 LinearPlan b;
-                block_plan(a.M, a.N, a.K, a.bits, a.g, fit, true, &b);
+                block_or_wide_plan(a.M, a.N, a.K, a.bits, a.g, fit, true, &b);
                 return b;
             });
             const rtn_linear_cfg cfg = plan_cfg(h);
@@ -1358,9 +1397,8 @@ static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t works
         tile_two_launches(false, a.M, a.N, a.K, tile_workspace(a, workspace_nbytes), &t);
         return 1.03 * t;
     }
-    if (p.waves_n == 8 && p.n_tiles16 == 2 && p.m_rows16 != 3)
-        return block_model_us(a.M, a.N, a.K, a.bits, a.g, p.m_rows16, p.waves_k, p.split_k);
-    return 1.1 * block_model_us(a.M, a.N, a.K, a.bits, a.g, 4, 2, 1);
+    if (p.n_tiles16 == 1) return wide16_model_us(a.M, a.N, a.K, a.bits, a.g, p.m_rows16, p.split_k);
+    return block_model_us(a.M, a.N, a.K, a.bits, a.g, p.m_rows16, p.waves_k, p.split_k);
 }
 
 // Independent modules of one precision and number of groups per unit in one launch of the block kernel.  Apart, each fills the

@@ -16,24 +16,27 @@
 //   - Scales come once per unit of four packed tiles, two units ahead: per-step loads of two bytes a lane touch 32 cache lines
 //     each, twice as many as the weights (57344 x 8192 int4 at 32 rows 65 us with them, 52 without).
 //   - The WK partial tiles are summed through LDS in a fixed order.
-// What bounds it.  At 128 rows on a full chip, power: with zeros for data the same launch takes 47 us instead of 66.  At 32 to 64 rows
+// What bounds it: at 128 rows on a full chip, power: with zeros for data the same launch takes 47 us instead of 66.  At 32 to 64 rows
 // the weight stream and the vector instructions (unpacking: 9 per 8 weights, for MB MFMAs of 32 cycles each) overlap only
 // partly.  On small matrices the 5-6 us of launch, first data and last store, which is what WK is for: K shared by
 // the wavefronts of a workgroup needs no second launch.  32 x 32 blocks rather than 16 x 16: an MFMA issues every 32 cycles
-// instead of 16 and leaves twice the issue slots to the unpacking.  Measured against the kernel it replaces (16 x 16 blocks,
-// register-staged activations, a barrier a step), graph replay over rotating weights: int4 group 128, 32 rows 106496 x 16384
-// 230 -> 194 us; 64 rows 6144 x 4096 14.0 -> 9.7, 106496 x 16384 315 -> 257; 96 rows 28672 x 4096 37.3 -> 29.2; 160 rows
+// instead of 16 and leaves twice the issue slots to the unpacking.  Measured against the wide kernel in the
+// shapes it had for such sizes (16 x 16 blocks, register-staged activations, a barrier a step), graph replay over rotating weights:
+// int4 group 128, 64 rows 6144 x 4096 14.0 -> 9.7, 106496 x 16384 315 -> 257; 96 rows 28672 x 4096 37.3 -> 29.2; 160 rows
 // 61.6 -> 46.7; group 64 with zero points, 256 rows 28672 x 4096 112 -> 80.  Tried and not kept: eight k-steps of weights in
 // registers (no faster at 32 rows, 2 % slower at 64), a different first k-step per workgroup (no change), loads without the
 // streaming hint (8 % slower).
 //
-// Wide kernel (8-bit weights in groups of 256 columns and more, 17 to 64 rows of matrices of 48 MB and more).  WV (4, 8 or 16)
-// wavefronts side by side along N share the staged activations; every wavefront owns NBW consecutive 16-row weight tile-rows
-// (16 NBW output columns) and all 16 MB activation rows of the workgroup's row block:
+// Wide kernel (small problems: see block_or_wide_plan).  Eight wavefronts side by side along N share the staged activations; every
+// wavefront owns one 16-row weight tile-row and all 16 MB activation rows of the workgroup's row block as v_mfma_f32_16x16x32_f16
+// blocks:
 //   - packed weights go from global memory straight into registers in MFMA operand order, three 128-column k-steps deep;
-//   - the activations of a k-step are staged through LDS by the whole workgroup, double buffered, in 16-byte pieces whose
-//     position inside a row is XOR-swizzled with the row number; one operand read feeds NBW MFMAs.
-// Without zero points or per-step scales it is 3-10 % ahead of the block kernel there (28672 x 4096 at 48 rows: 26.8 us and 29.9).
+//   - the activations of a k-step are staged through registers and LDS by the whole workgroup, double buffered, in 16-byte pieces
+//     whose position inside a row is XOR-swizzled with the row number.
+// What bounds it where it runs is latency: a launch of 5 to 15 us is the start, a chain of a few k-steps of half a microsecond and the
+// last store.  Half the columns per workgroup and steps a quarter as long as the block kernel's units give twice the
+// workgroups and a shorter chain: 4448 x 512 int4 at 29 rows 4.6 us (block kernel 6.3), 14000 x 1536 at 32 rows 7.7 (10.0), 1008 x
+// 1536 g32 at 1885 rows 13.6 (17.5); from 15 us on, with 8-bit weights at up to 64 rows from 30, the block kernel is level or ahead.
 //
 // Row tiles beyond the first are separate workgroups that re-read the weights; the workgroup index is decoded so that the
 // workgroups sharing a weight range are dispatched back to back on the same XCD and the second reader hits that XCD's L2.
@@ -49,34 +52,73 @@ namespace {
 constexpr int kStepK = 128;                     // columns per k-step
 constexpr uint32_t kOutOfRange = 0x7FFF0000u;   // beyond any resource size used here (< 2 GiB)
 constexpr int kBufferFlags = 0x00020000;        // raw buffer, 32-bit data format
+constexpr int kWideThreads = 512;               // wide kernel: eight wavefronts of one tile-row each
 
 struct WideParams {
     const half_t* A;
     const uint8_t* qw;
     const half_t* scales;
+    const half_t* zeros;   // ZP only
     half_t* C;
     float* ws;
     int M, N, K;
     int G;              // groups per row
-    int spg;            // k-steps per group
+    int spg;            // k-steps per group (1 for groups of up to a k-step)
+    int gps;            // groups per k-step: 1, or 2 / 4 for groups of 64 / 32 columns
     int NT;             // N / 16
     int KL;             // tiles per weight row
-    int KS;             // k-steps per row (K / 128)
     int XB;             // workgroups along N
     int sliced;         // order of the column tiles over the XCDs, see xcd_wide_tile
     int ZB;             // row blocks
     int split_k;
     int ks_base, ks_rem;   // workgroup sg covers k-steps [sg*ks_base + min(sg, ks_rem), ...)
-    uint32_t spg_inv;      // floor(2^32 / spg) + 1: k-step -> group by multiply-high
+    uint32_t spg_inv;      // floor(2^32 / spg) + 1 (0 when spg == 1): k-step -> group by multiply-high
     uint32_t qw_bytes, sc_bytes, a_bytes;
 };
 
-// The wide kernel: 8-bit weights in groups of 256 columns and more.  At least two wavefronts per SIMD (256 registers each): the
-// MFMAs then keep their accumulators in ordinary vector registers, where the scale multiply-add can read them directly.
-template <int MB, int NBW, int WV>
-__global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(const WideParams p) {
-    constexpr int MPT = Layout<8>::MFMA_PER_TILE;
-    constexpr int TPS = kStepK / Layout<8>::TK;           // tiles per k-step and tile-row
+// Scales (or zero points) of one weight row: NG consecutive fp16 values, of a k-step or a unit.  A row holds a multiple of NG of
+// them (K is a multiple of a unit's columns), so the loads are aligned.
+template <int NG> struct RowScales { u32x4_t v[NG / 8]; };
+template <> struct RowScales<1> { uint16_t v; };
+template <> struct RowScales<2> { uint32_t v; };
+template <> struct RowScales<4> { u32x2_t v; };
+
+template <int NG>
+__device__ __forceinline__ RowScales<NG> load_row_scales(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff) {
+    RowScales<NG> s;
+    if constexpr (NG == 1) s.v = __builtin_amdgcn_raw_buffer_load_b16(r, off, soff, 0);
+    else if constexpr (NG == 2) s.v = __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+    else if constexpr (NG == 4) s.v = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
+    else {
+#pragma unroll
+        for (int i = 0; i < NG / 8; ++i) s.v[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + i * 16, soff, 0);
+    }
+    return s;
+}
+
+template <int NG>
+__device__ __forceinline__ half_t row_scale(const RowScales<NG>& s, int i) {
+    if constexpr (NG == 1) return __builtin_bit_cast(half_t, s.v);
+    else {
+        uint32_t word;                                    // by value: bit_cast of a vector-element lvalue reads element 0
+        if constexpr (NG == 2) word = s.v;
+        else if constexpr (NG == 4) word = s.v[i >> 1];
+        else word = s.v[i >> 3][(i >> 1) & 3];
+        return __builtin_bit_cast(half2_t, word)[i & 1];
+    }
+}
+
+// The wide kernel.  GPS: groups per k-step -- 1 (group size 128), 2 (64), 4 (32), or 0: a group spans several k-steps.  From 1 up
+// every group starts its partial sums from zero, which its first MFMA takes as a constant operand instead of a cleared register,
+// and is scaled as soon as its last 32-column slice is done.  ZP: the integer zero point of the step's group goes into the unpack
+// (operand = q + Z).  At least two wavefronts per SIMD (256 registers each): the MFMAs then keep their accumulators in ordinary
+// vector registers, where the scale multiply-add can read them directly.
+template <int BITS, int MB, int GPS, bool ZP>
+__global__ __launch_bounds__(kWideThreads, 2) void wide_mfma_kernel(const WideParams p) {
+    constexpr int MPT = Layout<BITS>::MFMA_PER_TILE;
+    constexpr int TPS = kStepK / Layout<BITS>::TK;        // tiles per k-step: 1 / 2
+    constexpr int NG = GPS > 1 ? GPS : 1;                 // scales per k-step
+    constexpr int SPG = 4 / NG;                           // 32-column slices per group, of those in one k-step
     constexpr int ROWS = 16 * MB;
     constexpr int BUF_BYTES = ROWS * kStepK * 2;
     __shared__ __align__(16) uint8_t lds_a[2 * BUF_BYTES];
@@ -96,24 +138,21 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.qw), 0, p.qw_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(p.scales), 0, p.sc_bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(p.A), 0, p.a_bytes, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(ZP ? p.zeros : p.scales), 0, p.sc_bytes, kBufferFlags);
+    (void)rz;
     const uint32_t magic = fp16_magic_vgpr();
 
-    const int nt0 = (xb * WV + wave) * NBW;               // first tile-row of this wavefront
+    const int nt = xb * (kWideThreads / 64) + wave;       // tile-row of this wavefront
+    const bool nt_ok = nt < p.NT;
     // Load addresses: the lane's part goes into the vector offset, fixed for the whole kernel (out of range once and
     // for all for tile-rows and activation rows that do not exist); the k-step's part is wave-uniform and goes into the
     // scalar offset, so a step's loads cost no vector instructions.  Prefetches past the workgroup's last step load
     // that last step again (in bounds, never used).
-    uint32_t w_lane[NBW], s_lane[NBW];
-    bool nt_ok[NBW];
-#pragma unroll
-    for (int r = 0; r < NBW; ++r) {
-        nt_ok[r] = nt0 + r < p.NT;
-        w_lane[r] = nt_ok[r] ? (uint32_t)(nt0 + r) * (uint32_t)p.KL * 1024u + lane * 16 : kOutOfRange;
-        s_lane[r] = nt_ok[r] ? ((uint32_t)(nt0 + r) * 16 + nl) * (uint32_t)p.G * 2u : kOutOfRange;
-    }
+    const uint32_t w_lane = nt_ok ? (uint32_t)nt * (uint32_t)p.KL * 1024u + lane * 16 : kOutOfRange;
+    const uint32_t s_lane = nt_ok ? ((uint32_t)nt * 16 + nl) * (uint32_t)p.G * 2u : kOutOfRange;
 
     // ---- activation staging: thread t moves the 16-byte piece st_p of rows st_row0, st_row0 + RP, ... ----
-    constexpr int RP = 4 * WV;                            // rows covered by one pass of the workgroup's threads
+    constexpr int RP = kWideThreads / 16;                 // rows covered by one pass of the workgroup's threads
     constexpr int NP = (ROWS + RP - 1) / RP;              // passes
     const int st_p = tid & 15, st_row0 = tid >> 4;        // row & 15 == st_row0 & 15 in every pass
     u32x4_t areg[NP];
@@ -138,41 +177,28 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
     };
 
     // ---- weight / scale ring, three k-steps deep ----
-    u32x4_t wbuf[3][NBW][TPS];
-    uint16_t sbuf[3][NBW];
+    u32x4_t wbuf[3][TPS];
+    RowScales<NG> sbuf[3], zbuf[ZP ? 3 : 1];
+    (void)zbuf;
     auto w_load = [&](int slot, int t) {
         const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
-        const uint32_t j = __umulhi(ks, p.spg_inv);
+        const uint32_t j = GPS > 0 ? ks * NG : __umulhi(ks, p.spg_inv);
+        sbuf[slot] = load_row_scales<NG>(rs, s_lane, (int)(j * 2u));
+        if constexpr (ZP) zbuf[slot] = load_row_scales<NG>(rz, s_lane, (int)(j * 2u));
 #pragma unroll
-        for (int r = 0; r < NBW; ++r) {
-            sbuf[slot][r] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[r], (int)(j * 2u), 0);
-#pragma unroll
-            for (int c = 0; c < TPS; ++c)
-                wbuf[slot][r][c] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane[r], (int)((ks * TPS + c) * 1024u), 2 /* nt */);
-        }
+        for (int c = 0; c < TPS; ++c)
+            wbuf[slot][c] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane, (int)((ks * TPS + c) * 1024u), 2 /* nt */);
     };
 
-    float4_t acc[MB][NBW], part[MB][NBW];
+    float4_t acc[MB], part[MB];
 #pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int r = 0; r < NBW; ++r) {
-            acc[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
-            part[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
-        }
+    for (int b = 0; b < MB; ++b) {
+        acc[b] = (float4_t){0.f, 0.f, 0.f, 0.f};
+        part[b] = (float4_t){0.f, 0.f, 0.f, 0.f};
+    }
 
-    auto scale_row = [&](int slot, int r) {
-        const float sc = (float)__builtin_bit_cast(half_t, sbuf[slot][r]);
-#pragma unroll
-        for (int b = 0; b < MB; ++b) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[b][r][e] = fmaf(sc, part[b][r][e], acc[b][r][e]);
-            part[b][r] = (float4_t){0.f, 0.f, 0.f, 0.f};
-        }
-    };
-
-    // steps left in the current group when this workgroup starts
-    int left = p.spg - (int)((uint32_t)ks0 - __umulhi((uint32_t)ks0, p.spg_inv) * (uint32_t)p.spg);
+    // steps left in the current group when this workgroup starts (groups of several k-steps)
+    int left = GPS > 0 ? 1 : p.spg - (int)((uint32_t)ks0 - __umulhi((uint32_t)ks0, p.spg_inv) * (uint32_t)p.spg);
 
     auto step = [&](int slot, int t) {
         a_store((t + 1) & 1);                             // A(t+1), loaded during the previous step
@@ -181,14 +207,13 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
         __builtin_amdgcn_sched_barrier(0);                // keep the prefetch ahead of this step's arithmetic
         const uint8_t* abase = lds_a + (t & 1) * BUF_BYTES + (nl * 16) * 16;
         // the group, or this workgroup's share of it, ends with this step
-        const bool ends = (--left == 0) || (t == T - 1);
+        const bool ends = GPS > 0 ? true : ((--left == 0) || (t == T - 1));
         // the activation operands of a 32-column slice are read one slice ahead of the MFMAs that use them
         half8_t a_next[MB];
 #pragma unroll
         for (int b = 0; b < MB; ++b) a_next[b] = *reinterpret_cast<const half8_t*>(abase + (b * 256 + (kq ^ nl)) * 16);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const bool group_done = i == 3 && ends;
             half8_t a[MB];
 #pragma unroll
             for (int b = 0; b < MB; ++b) a[b] = a_next[b];
@@ -197,14 +222,32 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
                 for (int b = 0; b < MB; ++b)
                     a_next[b] = *reinterpret_cast<const half8_t*>(abase + (b * 256 + (((i + 1) * 4 + kq) ^ nl)) * 16);
             }
+            half8_t bw;
+            if constexpr (ZP) bw = unpack_operand_zp<BITS>(wbuf[slot][i / MPT], i % MPT, magic, (float)row_scale<NG>(zbuf[slot], i / SPG));
+            else bw = unpack_operand<BITS>(wbuf[slot][i / MPT], i % MPT, magic);
 #pragma unroll
-            for (int r = 0; r < NBW; ++r) {
-                const half8_t bw = unpack_operand<8>(wbuf[slot][r][i / MPT], i % MPT, magic);
-#pragma unroll
-                for (int b = 0; b < MB; ++b) part[b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b], bw, part[b][r], 0, 0, 0);
-                if (group_done && r > 0) scale_row(slot, r - 1);     // overlaps the next tile-row's MFMAs
+            for (int b = 0; b < MB; ++b) {
+                const float4_t c_in = (GPS > 0 && i % SPG == 0) ? (float4_t){0.f, 0.f, 0.f, 0.f} : part[b];
+                part[b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b], bw, c_in, 0, 0, 0);
             }
-            if (group_done) scale_row(slot, NBW - 1);
+            if (i % SPG == SPG - 1 && ends) {
+                const float sc = (float)row_scale<NG>(sbuf[slot], i / SPG);
+#pragma unroll
+                for (int b = 0; b < MB; ++b) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[b][e] = fmaf(sc, part[b][e], acc[b][e]);
+                    if constexpr (GPS == 0) part[b] = (float4_t){0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            if constexpr (NG > 1) {
+                // pins this group's sums here: left alone the compiler keeps the partial sums of several groups alive and
+                // adds them up at the end of the step, which spills
+#pragma unroll
+                for (int b = 0; b < MB; ++b) {
+                    if (i % SPG == SPG - 1) asm volatile("" : "+v"(acc[b]));
+                    else asm volatile("" : "+v"(part[b]));
+                }
+            }
             if (i < 3) __builtin_amdgcn_sched_barrier(0);                // keeps the next slice's reads ahead of this slice's MFMAs
         }
         if (ends) left = p.spg;
@@ -231,20 +274,17 @@ __global__ __launch_bounds__(64 * WV, WV <= 8 ? 2 : 4) void wide_mfma_kernel(con
         if (t + 1 < T) step(1, t + 1);
     }
 
-    // ---- store: lane holds rows m = 16 b + 4 kq + e, column n = 16 (nt0 + r) + nl ----
+    // ---- store: lane holds rows m = 16 b + 4 kq + e, column n = 16 nt + nl ----
+    if (!nt_ok) return;
+    const int n = nt * 16 + nl;
 #pragma unroll
-    for (int r = 0; r < NBW; ++r) {
-        if (!nt_ok[r]) continue;
-        const int n = (nt0 + r) * 16 + nl;
+    for (int b = 0; b < MB; ++b) {
 #pragma unroll
-        for (int b = 0; b < MB; ++b) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + b * 16 + kq * 4 + e;
-                if (m < p.M) {
-                    if (p.split_k == 1) p.C[(int64_t)m * p.N + n] = (half_t)acc[b][r][e];
-                    else p.ws[((int64_t)sg * p.M + m) * p.N + n] = acc[b][r][e];
-                }
+        for (int e = 0; e < 4; ++e) {
+            const int m = m0 + b * 16 + kq * 4 + e;
+            if (m < p.M) {
+                if (p.split_k == 1) p.C[(int64_t)m * p.N + n] = (half_t)acc[b][e];
+                else p.ws[((int64_t)sg * p.M + m) * p.N + n] = acc[b][e];
             }
         }
     }
@@ -297,38 +337,6 @@ struct BlockGroup {
     int first[kMaxBlockGroup + 1], blocks[kMaxBlockGroup];
     BlockParams p[kMaxBlockGroup];
 };
-
-// Scales (or zero points) of one weight row for a unit: NG consecutive fp16 values.  A row holds a multiple of NG of them (K is
-// a multiple of a unit's columns), so the loads are aligned.
-template <int NG> struct UnitScales { u32x4_t v[NG / 8]; };
-template <> struct UnitScales<1> { uint16_t v; };
-template <> struct UnitScales<2> { uint32_t v; };
-template <> struct UnitScales<4> { u32x2_t v; };
-
-template <int NG>
-__device__ __forceinline__ UnitScales<NG> load_unit_scales(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff) {
-    UnitScales<NG> s;
-    if constexpr (NG == 1) s.v = __builtin_amdgcn_raw_buffer_load_b16(r, off, soff, 0);
-    else if constexpr (NG == 2) s.v = __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
-    else if constexpr (NG == 4) s.v = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
-    else {
-#pragma unroll
-        for (int i = 0; i < NG / 8; ++i) s.v[i] = __builtin_amdgcn_raw_buffer_load_b128(r, off + i * 16, soff, 0);
-    }
-    return s;
-}
-
-template <int NG>
-__device__ __forceinline__ half_t unit_scale(const UnitScales<NG>& s, int i) {
-    if constexpr (NG == 1) return __builtin_bit_cast(half_t, s.v);
-    else {
-        uint32_t word;                                    // by value: bit_cast of a vector-element lvalue reads element 0
-        if constexpr (NG == 2) word = s.v;
-        else if constexpr (NG == 4) word = s.v[i >> 1];
-        else word = s.v[i >> 3][(i >> 1) & 3];
-        return __builtin_bit_cast(half2_t, word)[i & 1];
-    }
-}
 
 // Stages and depths of a shape of the block kernel.
 template <int BITS, int MB, int WN, int WK>
@@ -415,23 +423,23 @@ __global__ __launch_bounds__(64 * WN * WK, MB == 1 ? 4 : 2) void block_mfma_kern
             for (int q = 0; q < 2; ++q)
                 wbuf[slot][c][q] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane + q * 512, ((u0 * SPU + t) * TPS + c) * 1024, 2 /* nt */);
     };
-    UnitScales<NG> sbuf[2], zbuf[ZP ? 2 : 1];
+    RowScales<NG> sbuf[2], zbuf[ZP ? 2 : 1];
     (void)zbuf;
     auto s_load = [&](int slot, int u) {                  // unit u of this wavefront's share
         const uint32_t unit = (uint32_t)(u0 + u);
         const uint32_t j = NG > 1 ? unit * NG : (p.upg_inv == 0 ? unit : __umulhi(unit, p.upg_inv));
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(p.scales), 0, u < own ? p.sc_bytes : 0u, kBufferFlags);
-        sbuf[slot] = load_unit_scales<NG>(rs, s_lane, (int)(j * 2u));
+        sbuf[slot] = load_row_scales<NG>(rs, s_lane, (int)(j * 2u));
         if constexpr (ZP) {
             const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(p.zeros), 0, u < own ? p.sc_bytes : 0u, kBufferFlags);
-            zbuf[slot] = load_unit_scales<NG>(rz, s_lane, (int)(j * 2u));
+            zbuf[slot] = load_row_scales<NG>(rz, s_lane, (int)(j * 2u));
         }
     };
     // weight operand of slice s of step v (mod UN)
     auto operand = [&](int v, int s) {
         const u32x4_t& chunk = wbuf[v % D][BITS == 4 ? 0 : s >> 2][s & 1];
         const int i = BITS == 4 ? s >> 1 : (s >> 1) & 1;
-        if constexpr (ZP) return unpack_operand_zp<BITS>(chunk, i, magic, (float)unit_scale<NG>(zbuf[v / SPU % 2], ((v % SPU) * 8 + s) / SPG));
+        if constexpr (ZP) return unpack_operand_zp<BITS>(chunk, i, magic, (float)row_scale<NG>(zbuf[v / SPU % 2], ((v % SPU) * 8 + s) / SPG));
         else return unpack_operand<BITS>(chunk, i, magic);
     };
 
@@ -495,7 +503,7 @@ __global__ __launch_bounds__(64 * WN * WK, MB == 1 ? 4 : 2) void block_mfma_kern
             }
             if (us % SPG == SPG - 1) {
                 if (NG > 1 || unit_ends) {
-                    const float sc = (float)unit_scale<NG>(sbuf[v / SPU % 2], us / SPG);
+                    const float sc = (float)row_scale<NG>(sbuf[v / SPU % 2], us / SPG);
 #pragma unroll
                     for (int b = 0; b < MB; ++b) {
 #pragma unroll
@@ -505,7 +513,7 @@ __global__ __launch_bounds__(64 * WN * WK, MB == 1 ? 4 : 2) void block_mfma_kern
                             for (int e = 0; e < 16; ++e) part[b][e] = 0.f;
                     }
                 }
-                // pins the sums here (see the wide kernel)
+                // pins the sums here, as in the wide kernel
 #pragma unroll
                 for (int b = 0; b < MB; ++b) asm volatile("" : "+v"(acc[b]));
             } else if constexpr (SPG < 8) {
@@ -646,28 +654,22 @@ hipError_t launch_block(const BlockGroup& bp, int ng, int mb, int wk, unsigned g
     return hipErrorInvalidValue;
 }
 
-template <int MB, int NBW>
-hipError_t launch_wide_wv(const WideParams& wp, int wv, dim3 grid, hipStream_t st) {
-    if (wv == 4) hipLaunchKernelGGL((wide_mfma_kernel<MB, NBW, 4>), grid, dim3(64 * 4), 0, st, wp);
-    else if (wv == 8) hipLaunchKernelGGL((wide_mfma_kernel<MB, NBW, 8>), grid, dim3(64 * 8), 0, st, wp);
-    else {
-        // sixteen wavefronts leave 128 registers each: only the register tiles with one tile-row per wavefront
-        if constexpr (NBW == 1) hipLaunchKernelGGL((wide_mfma_kernel<MB, NBW, 16>), grid, dim3(64 * 16), 0, st, wp);
-        else return hipErrorInvalidValue;
-    }
+template <int BITS, int MB, bool ZP>
+hipError_t launch_wide_gps(const WideParams& wp, dim3 grid, hipStream_t st) {
+    const dim3 block(kWideThreads);
+    if (wp.gps == 4) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, 4, ZP>), grid, block, 0, st, wp);
+    else if (wp.gps == 2) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, 2, ZP>), grid, block, 0, st, wp);
+    else if (wp.spg == 1) hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, 1, ZP>), grid, block, 0, st, wp);
+    else hipLaunchKernelGGL((wide_mfma_kernel<BITS, MB, 0, ZP>), grid, block, 0, st, wp);
     return hipGetLastError();
 }
 
-// Register tiles of up to 8 accumulator blocks (MB * NBW <= 8) fit 256 registers.
-hipError_t launch_wide(const WideParams& wp, int mb, int nbw, int wv, dim3 grid, hipStream_t st) {
-    switch (mb * 10 + nbw) {
-        case 21: return launch_wide_wv<2, 1>(wp, wv, grid, st);
-        case 22: return launch_wide_wv<2, 2>(wp, wv, grid, st);
-        case 24: return launch_wide_wv<2, 4>(wp, wv, grid, st);
-        case 31: return launch_wide_wv<3, 1>(wp, wv, grid, st);
-        case 32: return launch_wide_wv<3, 2>(wp, wv, grid, st);
-        case 41: return launch_wide_wv<4, 1>(wp, wv, grid, st);
-        case 42: return launch_wide_wv<4, 2>(wp, wv, grid, st);
+template <int BITS>
+hipError_t launch_wide(const WideParams& wp, int mb, dim3 grid, hipStream_t st) {
+    switch (mb) {
+        case 2: return wp.zeros ? launch_wide_gps<BITS, 2, true>(wp, grid, st) : launch_wide_gps<BITS, 2, false>(wp, grid, st);
+        case 3: return wp.zeros ? launch_wide_gps<BITS, 3, true>(wp, grid, st) : launch_wide_gps<BITS, 3, false>(wp, grid, st);
+        case 4: return wp.zeros ? launch_wide_gps<BITS, 4, true>(wp, grid, st) : launch_wide_gps<BITS, 4, false>(wp, grid, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -766,42 +768,42 @@ hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans,
     return e;
 }
 
-// Path 3 is two kernels.  The wide kernel has 8-bit weights in groups of 256 columns and more under the shapes that the automatic
-// plan gives it (any but eight wavefronts of two tile-rows); the block kernel everything else, and a configuration of it
-// means the block kernel's workgroup of as many columns: 64, 128 or 256 (8 wavefronts, 4, 2 or 1 of them along K), or, as eight
-// wavefronts of two tile-rows, with waves_k of the eight along K.
+// Path 3 is two kernels: eight wavefronts of one tile-row are the wide kernel; any other configuration means the block kernel's
+// workgroup of as many columns -- 64, 128 or 256: 8 wavefronts, 4, 2 or 1 of them along K -- or, as eight wavefronts of two
+// tile-rows, with waves_k of the eight along K.
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st) {
-    const bool whole = p.waves_n == 8 && p.n_tiles16 == 2;
-    const int cols = 16 * p.n_tiles16 * p.waves_n;
-    if (a.bits == 4 || a.zeros || a.g < 256 || (whole && p.m_rows16 != 3)) {
-        int wk = whole && (p.waves_k == 2 || p.waves_k == 4 || p.waves_k == 8) ? p.waves_k : std::max(1, 256 / cols);
+    if (p.waves_n != 8 || p.n_tiles16 != 1) {
+        const bool given = p.waves_n == 8 && p.n_tiles16 == 2 && (p.waves_k == 2 || p.waves_k == 4 || p.waves_k == 8);
+        int wk = given ? p.waves_k : std::max(1, 256 / (16 * p.n_tiles16 * p.waves_n));
         if (wk == 8 && (a.zeros || block_rows32(a.M, a.N, p.m_rows16) > 2)) wk = 4;
         return launch_linear_block(a, p, wk, st);
     }
+    constexpr int kCols = kWideThreads / 64 * 16;
     WideParams wp;
     wp.A = static_cast<const half_t*>(a.A);
     wp.qw = static_cast<const uint8_t*>(a.qweight);
     wp.scales = static_cast<const half_t*>(a.scales);
+    wp.zeros = static_cast<const half_t*>(a.zeros);
     wp.C = static_cast<half_t*>(a.C);
     wp.ws = a.workspace;
     wp.M = (int)a.M; wp.N = (int)a.N; wp.K = (int)a.K;
     wp.G = (int)(a.K / a.g);
-    wp.spg = (int)(a.g / kStepK);
-    wp.spg_inv = (uint32_t)(((uint64_t)1 << 32) / (uint32_t)wp.spg) + 1u;
+    wp.gps = a.g < kStepK ? (int)(kStepK / a.g) : 1;
+    wp.spg = a.g < kStepK ? 1 : (int)(a.g / kStepK);
+    wp.spg_inv = wp.spg == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)wp.spg) + 1u;
     wp.NT = (int)(a.N / 16);
-    wp.KL = (int)(a.K / Layout<8>::TK);
-    wp.KS = (int)(a.K / kStepK);
-    wp.XB = (int)((a.N + cols - 1) / cols);
+    wp.KL = (int)(a.K / (a.bits == 4 ? Layout<4>::TK : Layout<8>::TK));
+    wp.XB = (int)((a.N + kCols - 1) / kCols);
     wp.ZB = p.m_blocks;
     wp.split_k = p.split_k;
-    wp.ks_base = wp.KS / p.split_k;
-    wp.ks_rem = wp.KS % p.split_k;
-    wp.qw_bytes = (uint32_t)((size_t)a.N * a.K);
+    wp.ks_base = (int)(a.K / kStepK) / p.split_k;
+    wp.ks_rem = (int)(a.K / kStepK) % p.split_k;
+    wp.qw_bytes = (uint32_t)((size_t)a.N * a.K * a.bits / 8);
     wp.sc_bytes = (uint32_t)((size_t)a.N * wp.G * 2);
     wp.a_bytes = (uint32_t)((size_t)a.M * a.K * 2);
     wp.sliced = xcd_slices_save_a_round(wp.XB, wp.ZB, p.split_k) ? 1 : 0;
     dim3 grid((unsigned)wide_blocks(wp.XB, wp.ZB, wp.sliced != 0), (unsigned)p.split_k, 1);
-    hipError_t e = launch_wide(wp, p.m_rows16, p.n_tiles16, p.waves_n, grid, st);
+    hipError_t e = a.bits == 4 ? launch_wide<4>(wp, p.m_rows16, grid, st) : launch_wide<8>(wp, p.m_rows16, grid, st);
     if (e != hipSuccess) return e;
     if (p.split_k > 1) e = launch_splitk_reduce(a.workspace, static_cast<half_t*>(a.C), a.M * a.N, p.split_k, st);
     return e;

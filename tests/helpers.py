@@ -83,3 +83,9 @@ def make_weight(cfg_dist: str, N: int, K: int, seed: int, device):
 # what the GPU tests on the same lists rely on.
 LAYER_RAGGED = [(48, 1024), (272, 4096), (16, 1024), (2064, 2048), (80, 14336)]
 LAYER_2048 = [(3072, 2048), (2048, 2048), (16384, 2048), (2048, 8192)]
+
+# (M, N, K, bits, g) with zero points that the wide kernel runs: row blocks of 32, 48 and 64 rows, all group sizes, with and without a K split.
+WIDE_ZERO_POINTS = [(17, 304, 512, 4, 0), (21, 304, 1536, 4, 128), (40, 304, 1536, 4, 256), (33, 304, 512, 4, 128), (130, 2576, 1536, 4, 32),
+                    (491, 528, 512, 4, 32), (130, 2576, 1024, 4, 64), (491, 528, 512, 4, 64), (100, 304, 1536, 4, 128), (60, 304, 512, 4, 0),
+                    (17, 304, 256, 8, 0), (130, 528, 2048, 8, 0), (200, 528, 2048, 8, 0), (21, 16400, 256, 8, 32), (33, 16400, 256, 8, 64),
+                    (491, 1040, 256, 8, 32), (200, 2576, 256, 8, 64), (21, 304, 256, 8, 128), (130, 1040, 2048, 8, 128), (60, 304, 256, 8, 128)]

@@ -336,6 +336,37 @@ def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M} K={K}")
 
 
+@pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),
+                                      (8, 128, 2304), (8, 0, 2304)])
+@pytest.mark.parametrize("M", [17, 33, 65, 130])
+def test_linear_wide_kernel_shapes(rtn, bits, g, K, M):
+    """The wide kernel of path 3 (eight wavefronts of one tile-row): row blocks of 32, 48 and 64 rows, ragged M and N, groups that end
+    in, with and after a k-step, one k-step to all of them per workgroup, against the oracle."""
+    N = 304                                # 19 tile-rows: the third workgroup's last five wavefronts have none
+    codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    ref = O.rtn_linear(_to_np(A_t), codes, scales, gg)
+    for rows in (2, 3, 4):
+        for split in sorted({1, 2, min(16, K // 128)}):
+            cfg = dict(path=3, prefetch=1, m_rows16=rows, n_tiles16=1, waves_n=8, waves_k=1, split_k=split)
+            C = rtn.rtn_linear(A_t, qw, sc, bits, g, cfg=cfg, workspace=torch.empty(max(256, M * N * 4 * split), dtype=torch.uint8, device=DEV))
+            torch.cuda.synchronize()
+            H.assert_linear_close(_to_np(C), ref, f"int{bits} g={g} M={M} K={K} cfg={cfg}")
+
+
+@pytest.mark.parametrize("M,N,K,bits,g", H.WIDE_ZERO_POINTS)
+def test_linear_wide_kernel_zero_points(rtn, M, N, K, bits, g):
+    """Zero points on the wide kernel: calls whose plans test_host_plans.py asserts."""
+    W = _to_np((synth.normal_weight(N, K, 0.02, seed=M + bits, device=DEV).float() + 0.015).half())
+    codes, scales, zeros = O.rtn_quantize_asym(W, bits, g if g > 0 else K)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    C = rtn.rtn_linear_asym(A_t, torch.from_numpy(O.pack_gfx950(codes, bits)).to(DEV), torch.from_numpy(scales).to(DEV),
+                            torch.from_numpy(zeros.astype(np.float16)).to(DEV), bits, g,
+                            workspace=torch.empty(64 << 20, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, g if g > 0 else K), f"asym int{bits} g={g} M={M} K={K}")
+
+
 @pytest.mark.parametrize("M", [5, 16, 33, 100, 161, 300])
 def test_layer_of_independent_modules_in_block_launches(rtn, M):
     """rtn_layer_forward from five rows: modules of one class (precision, groups per unit) share a launch of the block kernel, with K of

@@ -256,13 +256,29 @@ def test_no_problem_goes_from_exact_codes_to_rounded_weights(ask, workspace):
 
 def test_block_plans_of_few_columns_long_rows_and_many_rows(ask):
     """Problems on which the plan was measured 1.3 to 2 times slower than the best one while the block kernel's model knew only
-    matrices of 1024 columns and more at up to 512 rows: the plans that measured best (89 rows: or, with the K split kept there, 19 % behind)."""
+    matrices of 1024 columns and more at up to 512 rows: the plans that measured best."""
     best = {(2809, 656, 28160, 8, 128): [(8, 1, 3)], (601, 544, 27648, 8, 32): [(4, 1, 8)], (751, 864, 20480, 8, 32): [(4, 1, 5)],
             (944, 672, 42496, 8, 64): [(4, 1, 5)], (2988, 864, 9728, 8, 32): [(4, 1, 1)], (1002, 432, 14336, 8, 32): [(4, 1, 8)],
-            (1058, 576, 14336, 8, 128): [(8, 2, 5)], (363, 832, 28672, 8, 128): [(8, 2, 8)], (89, 4112, 3584, 8, 256): [(2, 4, 1), (2, 2, 2)],
+            (1058, 576, 14336, 8, 128): [(8, 2, 5)], (363, 832, 28672, 8, 128): [(8, 2, 8)],
             (1335, 3856, 5632, 4, 128): [(8, 1, 1)], (287, 16080, 1536, 8, 256): [(8, 1, 1)], (127, 5216, 12800, 8, 32): [(4, 1, 5)],
             (59, 4464, 19456, 8, 64): [(4, 2, 6)]}
     for (p, good), (status, launches) in zip(best.items(), ask([f"linear {' '.join(map(str, p))} {64 * MIB}" for p in best])):
         assert status == 0 and len(launches) == 1, (p, launches)
         q = launches[0]
         assert (q["m_rows16"], q["waves_k"], q["split_k"]) in good, (p, q)
+
+
+def test_small_problems_run_on_the_wide_kernel(ask):
+    """Problems that measured 15 % and more faster on the wide kernel (eight wavefronts of one tile-row) than on any workgroup of the block
+    kernel go to it, in every format; problems that measured 10 % and more faster on the block kernel to that one."""
+    wide = [(29, 4448, 512, 4, 0), (24, 24048, 512, 4, 32), (32, 14000, 1536, 4, 0), (27, 2480, 512, 4, 128), (649, 448, 512, 4, 0),
+            (149, 2048, 512, 4, 0), (1885, 1008, 1536, 4, 32), (29, 16624, 1024, 8, 256), (1726, 672, 1536, 4, 128), (1619, 384, 512, 4, 128),
+            (368, 3392, 512, 4, 32), (31, 2320, 1024, 4, 0), (1860, 352, 512, 4, 32), (672, 1152, 512, 4, 128)]
+    wide_zp = [(491, 2656, 512, 4, 128), (672, 1152, 512, 4, 128), (1885, 1008, 1536, 4, 32), (32, 14000, 1536, 4, 0)]
+    block = [(96, 28672, 4096, 4, 128), (256, 6144, 4096, 4, 128), (512, 4096, 14336, 8, 0), (64, 28672, 4096, 4, 128), (1335, 3856, 5632, 4, 128),
+             (59, 57344, 8192, 8, 0), (29, 57344, 8192, 8, 128), (28, 18432, 16384, 8, 128)]
+    for kind, problems, shape in (("linear", wide, (8, 1)), ("asym", wide_zp + H.WIDE_ZERO_POINTS, (8, 1)), ("linear", block, (8, 2))):
+        for p, (status, launches) in zip(problems, ask([f"{kind} {' '.join(map(str, p))} {64 * MIB}" for p in problems])):
+            assert status == 0 and len(launches) == 1
+            q = launches[0]
+            assert (q["path"], q["waves_n"], q["n_tiles16"]) == (3, *shape), (kind, p, q)
