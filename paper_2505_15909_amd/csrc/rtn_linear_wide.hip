@@ -203,6 +203,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_mfma_kernel(const WidePa
     auto step = [&](int slot, int t) {
         a_store((t + 1) & 1);                             // A(t+1), loaded during the previous step
         a_load(t + 2);
+        __builtin_amdgcn_sched_barrier(0);                // the store goes first: behind the weights' requests it cost 12 % (14000 x 1536)
         w_load((slot + 2) % 3, t + 2);
         __builtin_amdgcn_sched_barrier(0);                // keep the prefetch ahead of this step's arithmetic
         const uint8_t* abase = lds_a + (t & 1) * BUF_BYTES + (nl * 16) * 16;
@@ -257,9 +258,12 @@ __global__ __launch_bounds__(kWideThreads, 2) void wide_mfma_kernel(const WidePa
     // ---- prologue: the same issue order as in the loop (activations of a step before its weights), so that
     // the loop's waits are counted waits and not waits for everything ----
     a_load(0);
+    __builtin_amdgcn_sched_barrier(0);
     w_load(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
     a_store(0);
     a_load(1);
+    __builtin_amdgcn_sched_barrier(0);
     w_load(1, 1);
     __syncthreads();
 
