@@ -152,6 +152,7 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
 struct BlockTimes {
     int mb;             // row blocks of 32 rows
     int64_t wgs;        // workgroups
+    int64_t on_xcd;     // those of the fullest XCD: each K split deals its column tiles anew
     double wg_us;       // one workgroup on an idle chip
     double stream_us;   // its weights and activations at the rates above
 };
@@ -163,6 +164,7 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
     BlockTimes b;
     b.mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
     b.wgs = XB * ZB * s;
+    b.on_xcd = (rtn::xcd_slices_save_a_round(XB, ZB, s) ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s;
     const double per = (double)(((units + s - 1) / s + wk - 1) / wk), groups = g >= unit ? 1.0 : (double)(unit / g);
     b.wg_us = 1.33 + per * (kUnit[b.mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[b.mb - 1] * groups) + (wk > 1 ? 0.73 * b.mb : 0.0);
     b.stream_us = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * b.mb * K * 2.0 / 1.71e7;
@@ -1405,9 +1407,11 @@ static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t works
 // chip to a half or three quarters and pays the start, the first data and the last store of a launch; together they fill it and
 // pay once.  Plan: one row tile height and number of wavefronts along K for all (a launch is one kernel), the longest
 // workgroups first, K of the module with the longest split in two or four.  The time is the end of the last workgroup
-// when they are dealt in that order to the compute units of an XCD (32; two of the 32-row ones on each), four fifths of
-// it, and the average load one fifth; against it the streams.  Fitted to 408 merged launches of 68
-// layers (6 % rms, the pick 0.4 % behind the best one measured on average).
+// when those of the fullest XCD are dealt in that order to its compute units (32; two of the 32-row ones on each), four fifths of
+// it, and the average load one fifth; against it the streams.  The fullest XCD is counted as the launch deals the tiles, module by
+// module and split by split: 7168-, 5120-, 27648- and 5120-wide modules with K of the last in four are 236 workgroups, but 33 on
+// one XCD, and took 73 us at 12 rows where their own launches take 64.  Fitted to 408 merged launches of 68 layers; of 8534 on 330
+// other sets it picks plans 3.9 % behind the best one on average, 10 % rms.
 struct MergedPlan {
     double us;                          // modelled time, negative: no such plan
     int mb, wk;
@@ -1465,13 +1469,14 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
             for (int i = 0; i < n; ++i) m.split[i] = 1;
             for (int cuts = 0; cuts < 4; ++cuts) {
                 double each[rtn::kMaxBlockGroup], stream = 0.0, reduce = 0.0;
-                int64_t count[rtn::kMaxBlockGroup], wgs = 0;
+                int64_t count[rtn::kMaxBlockGroup], wgs = 0, on_xcd = 0;
                 size_t partials = 0;
                 int longest = 0;
                 for (int i = 0; i < n; ++i) {
                     const BlockTimes b = block_times(a[i].M, a[i].N, a[i].K, a[i].bits, a[i].g, 2 * mb, wk, m.split[i]);
                     each[i] = b.wg_us;
-                    count[i] = (b.wgs + 7) / 8;
+                    count[i] = b.on_xcd;
+                    on_xcd += b.on_xcd;
                     wgs += b.wgs;
                     stream += 0.839 * b.stream_us;
                     if (each[i] > each[longest]) longest = i;
@@ -1483,7 +1488,7 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
                 if (partials > workspace) break;
                 const bool two = mb == 1 && wk <= 4;
                 const double slow = (mb == 1 ? 1.081 : 1.02) * (1.0 + 0.36 * std::min(1.0, (double)wgs / 256.0) * mb / 4.0) *
-                                    (two && wgs > 256 ? 1.543 : 1.0) * kWaves[wk];
+                                    (two && on_xcd > 32 ? 1.543 : 1.0) * kWaves[wk];
                 for (int i = 0; i < n; ++i) each[i] *= slow;
                 const double serial = dealt_us(each, count, n, two ? 64 : 32);
                 m.us = 3.7 + std::pow(std::pow(serial, 2.374) + std::pow(stream, 2.374), 1.0 / 2.374) + reduce;
@@ -1581,98 +1586,75 @@ static rtn_status one_module(const rtn_module& m, void* dev_workspace, size_t wo
                       workspace_nbytes, stream);
 }
 
-// A layer of independent modules, 5 to 512 rows: those of one class (precision, groups per unit) together where that is
-// modelled ahead of their own plans' launches, by 3 % up to 256 rows (12 % for two modules up to 16 rows: int8 14336 x 4096 twice at
-// 8 rows 28.5 us together, 26.0 apart) and 15 % above (where the model falls short: 15360-, 5120-,
-// 27648- and 5120-wide modules at 512 rows 310 us together, 300 apart), the others one by one.  8B layer int4 group 128, apart ->
-// together: 9 rows 36.5 -> 29.9 us, 32 rows 48.3 -> 31.2, 64 61.6 -> 38.0, 128 85.1 -> 62.3, 256 125.5 -> 111.6; 70B layer 16 rows
-// 98.8 -> 91.6, 32 110 -> 94, 128 231 -> 212; three modules of 4096 columns and 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.
-// False where a module's own plan does not resolve: the call then runs in order up to that error.
+// One launch of a layer or a grouped call: a module alone (count 1), or several on the block or the tile kernel.
+struct SharedLaunch {
+    int count;
+    int member[rtn::kMaxBlockGroup];
+    MergedPlan plan;
+};
+static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
+
+// The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
+// (precision, groups per unit; the tile kernel: precision) together where that is modelled 3 % ahead of their own plans' launches
+// (12 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
+// the block kernel that line puts together 293 of 330 measured sets, of which 3 run more than 2 % slower for it, and leaves 14 apart
+// that would gain.  8B layer int4 group 128, apart -> together: 9 rows 36.5 -> 29.9 us, 32 rows 48.3 -> 31.2, 64 61.6 -> 38.0, 128
+// 85.1 -> 62.3, 256 125.5 -> 111.6; 70B layer 16 rows 98.8 -> 91.6, 32 110 -> 94, 128 231 -> 212; three modules of 4096 columns and
+// 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.  Tile kernel: 8B layer int4 at 1536 rows 625 -> 553, 2048 rows 773 -> 726;
+// 5120-wide layer at 2048 rows 996 -> 900; closer to level it measures within 1 % either way.
 constexpr int64_t kMaxMergedRows = 512;
-static bool layer_in_blocks(const rtn_module* mods, const LinearArgs* args, int n, void* dev_workspace, size_t workspace_nbytes, void* stream,
-                            rtn_status* status) {
-    constexpr int kMost = 16;
-    double own_us[kMost];
+enum : char { kOpen, kAlone, kDone };
+static int shared_launches(const LinearArgs* args, const double* own_us, char* state, int n, size_t workspace_nbytes, bool tiles,
+                           SharedLaunch* out) {
+    int launches = 0;
     for (int i = 0; i < n; ++i) {
-        LinearPlan own;
-        if (resolve_plan(args[i], nullptr, workspace_nbytes, &own) != RTN_OK) return false;
-        own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
-    }
-    bool done[kMost] = {};
-    for (int i = 0; i < n; ++i) {
-        if (done[i]) continue;
+        if (state[i] == kDone) continue;
+        SharedLaunch& l = out[launches++];
         LinearArgs set[rtn::kMaxBlockGroup];
-        int member[rtn::kMaxBlockGroup], count = 0;
         double apart = 0.0;
         int64_t rows = 0;
-        for (int j = i; j < n && count < rtn::kMaxBlockGroup; ++j) {
-            if (done[j] || !one_block_class(args[i], args[j])) continue;
+        l.count = 0;
+        for (int j = i; state[i] == kOpen && j < n && l.count < rtn::kMaxBlockGroup; ++j) {
+            if (state[j] != kOpen || !(tiles ? args[i].bits == args[j].bits : one_block_class(args[i], args[j]))) continue;
             apart += own_us[j];
             rows = std::max(rows, args[j].M);
-            member[count] = j;
-            set[count++] = args[j];
+            l.member[l.count] = j;
+            set[l.count++] = args[j];
         }
-        MergedPlan m;
-        m.us = -1.0;
-        if (count > 1) m = remembered_merge(set, count, workspace_nbytes);
-        if (m.us < 0.0 || m.us > (rows > 256 ? 0.85 : count == 2 && rows <= 16 ? 0.88 : 0.97) * apart) {
-            *status = one_module(mods[i], dev_workspace, workspace_nbytes, stream);
-            if (*status != RTN_OK) return true;
-            done[i] = true;
-            continue;
+        if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
+        const double line = !tiles && l.count == 2 && rows <= 16 ? 0.88 : 0.97;
+        if (l.count < 2 || l.plan.us < 0.0 || l.plan.us > line * apart) {
+            l.count = 1;
+            l.member[0] = i;
         }
-        if (launch_merged(set, count, m, stream) != hipSuccess) {
-            *status = RTN_ERR_HIP;
-            return true;
-        }
-        for (int k = 0; k < count; ++k) done[member[k]] = true;
+        for (int k = 0; k < l.count; ++k) state[l.member[k]] = kDone;
     }
-    *status = RTN_OK;
-    return true;
+    return launches;
 }
 
-// rtn_layer_forward above 512 rows: modules that the tile kernel serves, of one precision, in one launch of it where that is
-// modelled 3 % ahead (8B layer int4 at 1536 rows 625 -> 553 us, 2048 rows 773 -> 726; 5120-wide layer at 2048 rows
-// 996 -> 900; closer to level it measures within 1 % either way).  Other modules, whose weights are not rounded to fp16, keep their kernel.
-static bool layer_in_tiles(const rtn_module* mods, const LinearArgs* args, int n, void* dev_workspace, size_t workspace_nbytes, void* stream,
-                           rtn_status* status) {
+// The launches of a layer of independent modules, all of 5 to 512 rows (block kernel) or all above (tile kernel: modules whose
+// own plan is on it; other modules, whose weights are not rounded to fp16, keep their kernel).  -1 where the call runs in order: other
+// rows, or a module whose own plan does not resolve (the call then stops at that error).
+static int layer_launches(const LinearArgs* args, int n, size_t workspace_nbytes, SharedLaunch* out, bool* tiles) {
     constexpr int kMost = 16;
     double own_us[kMost];
-    bool done[kMost] = {}, tile[kMost];
+    char state[kMost];
+    if (n < 2 || n > kMost) return -1;
+    *tiles = args[0].M > kMaxMergedRows;
     for (int i = 0; i < n; ++i) {
         LinearPlan own;
-        if (resolve_plan(args[i], nullptr, workspace_nbytes, &own) != RTN_OK) return false;
-        tile[i] = own.path == 4;
+        if (args[i].M <= 4 || (args[i].M > kMaxMergedRows) != *tiles || resolve_plan(args[i], nullptr, workspace_nbytes, &own) != RTN_OK) return -1;
         own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
+        state[i] = !*tiles || own.path == 4 ? kOpen : kAlone;
     }
-    for (int i = 0; i < n; ++i) {
-        if (done[i]) continue;
-        LinearArgs set[rtn::kMaxTileGroup];
-        int member[rtn::kMaxTileGroup], count = 0;
-        double apart = 0.0;
-        for (int j = i; j < n && count < rtn::kMaxTileGroup; ++j) {
-            if (done[j] || !tile[i] || !tile[j] || args[j].bits != args[i].bits) continue;
-            apart += own_us[j];
-            member[count] = j;
-            set[count++] = args[j];
-        }
-        MergedPlan m;
-        m.us = -1.0;
-        if (count > 1) m = remembered_merge(set, count, std::min(workspace_nbytes, kWorkspaceCapTile), true);
-        if (m.us < 0.0 || m.us > 0.97 * apart) {
-            *status = one_module(mods[i], dev_workspace, workspace_nbytes, stream);
-            if (*status != RTN_OK) return true;
-            done[i] = true;
-            continue;
-        }
-        if (rtn::launch_linear_tiles(set, m.split, count, m.mb, static_cast<hipStream_t>(stream)) != hipSuccess) {
-            *status = RTN_ERR_HIP;
-            return true;
-        }
-        for (int k = 0; k < count; ++k) done[member[k]] = true;
-    }
-    *status = RTN_OK;
-    return true;
+    return shared_launches(args, own_us, state, n, workspace_nbytes, *tiles, out);
+}
+
+static hipError_t launch_shared(const LinearArgs* args, const SharedLaunch& l, bool tiles, void* stream) {
+    LinearArgs set[rtn::kMaxBlockGroup];
+    for (int k = 0; k < l.count; ++k) set[k] = args[l.member[k]];
+    return tiles ? rtn::launch_linear_tiles(set, l.plan.split, l.count, l.plan.mb, static_cast<hipStream_t>(stream))
+                 : launch_merged(set, l.count, l.plan, stream);
 }
 
 rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
@@ -1692,15 +1674,17 @@ rtn_status rtn_layer_forward(const rtn_module* mods, int n_mods, void* dev_works
     }
     if (n_mods > 1 && n_mods <= kMerge && aligned16(dev_workspace)) {
         LinearArgs args[kMerge];
-        bool ok = true;
-        for (int i = 0; i < n_mods && ok; ++i)
-            ok = mods[i].M > 4 && mods[i].M <= kMaxMergedRows && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
-        rtn_status st;
-        if (ok && modules_independent(args, n_mods) && layer_in_blocks(mods, args, n_mods, dev_workspace, workspace_nbytes, stream, &st)) return st;
-        ok = true;
-        for (int i = 0; i < n_mods && ok; ++i)
-            ok = mods[i].M > kMaxMergedRows && module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
-        if (ok && modules_independent(args, n_mods) && layer_in_tiles(mods, args, n_mods, dev_workspace, workspace_nbytes, stream, &st)) return st;
+        SharedLaunch launches[kMerge];
+        bool ok = true, tiles;
+        for (int i = 0; i < n_mods && ok; ++i) ok = module_args(mods[i], dev_workspace, &args[i]) == RTN_OK;
+        const int n = ok && modules_independent(args, n_mods) ? layer_launches(args, n_mods, workspace_nbytes, launches, &tiles) : -1;
+        for (int i = 0; i < n; ++i) {
+            const SharedLaunch& l = launches[i];
+            const rtn_status st = l.count == 1 ? one_module(mods[l.member[0]], dev_workspace, workspace_nbytes, stream)
+                                : launch_shared(args, l, tiles, stream) == hipSuccess ? RTN_OK : RTN_ERR_HIP;
+            if (st != RTN_OK) return st;
+        }
+        if (n >= 0) return RTN_OK;
     }
     for (int i = 0; i < n_mods; ++i) {
         const rtn_module& m = mods[i];
@@ -1779,6 +1763,21 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
     return RTN_OK;
 }
 
+// A grouped call's modules that would each be a launch of their own (more than 16 rows, or K split across workgroups), 5 to 512 rows:
+// together on the block kernel where that is modelled ahead, as in a layer (eight of 2048 x 7168 int8 at 16 rows 71.9 us
+// apart, 23.5 together).  The modules alone in their launch go on to the small-batch kernel's grouped launches.
+static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out) {
+    std::vector<double> own_us((size_t)n, 0.0);
+    std::vector<char> state((size_t)n, kAlone);
+    for (int i = 0; i < n; ++i) {
+        const LinearPlan& p = plans[i];
+        if (args[i].M <= 4 || args[i].M > kMaxMergedRows || (p.path == 1 && p.split_k == 1 && p.m_blocks == 1)) continue;
+        state[i] = kOpen;
+        own_us[i] = own_plan_us(args[i], p, workspace_nbytes);
+    }
+    return shared_launches(args, own_us.data(), state.data(), n, workspace_nbytes, false, out);
+}
+
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
                                void* stream) {
     if (!mods) return RTN_ERR_NULL;
@@ -1792,32 +1791,13 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
     }
     const rtn_status st = grouped_plans(args.data(), n_mods, workspace_nbytes, plans.data());
     if (st != RTN_OK) return st;
-    // Modules that would each be a launch of their own (more than 16 rows, or K split across workgroups), of one class and 5 to 512
-    // rows: up to eight together in one launch of the block kernel where that is modelled ahead, as in rtn_layer_forward (eight
-    // of 2048 x 7168 int8 at 16 rows 71.9 us apart, 23.5 together).
+    std::vector<SharedLaunch> launches((size_t)n_mods);
+    launches.resize((size_t)grouped_blocks(args.data(), plans.data(), n_mods, workspace_nbytes, launches.data()));
     std::vector<char> left((size_t)n_mods, 1);
-    auto alone = [&](int i) {
-        const LinearPlan& p = plans[i];
-        return left[i] && args[i].M > 4 && args[i].M <= kMaxMergedRows && (p.path != 1 || p.split_k != 1 || p.m_blocks != 1);
-    };
-    for (int i = 0; i < n_mods; ++i) {
-        if (!alone(i)) continue;
-        LinearArgs set[rtn::kMaxBlockGroup];
-        int member[rtn::kMaxBlockGroup], count = 0;
-        double apart = 0.0;
-        int64_t rows = 0;
-        for (int j = i; j < n_mods && count < rtn::kMaxBlockGroup; ++j) {
-            if (!alone(j) || !one_block_class(args[i], args[j])) continue;
-            apart += own_plan_us(args[j], plans[j], workspace_nbytes);
-            rows = std::max(rows, args[j].M);
-            member[count] = j;
-            set[count++] = args[j];
-        }
-        if (count < 2) continue;
-        const MergedPlan m = remembered_merge(set, count, workspace_nbytes);
-        if (m.us < 0.0 || m.us > (rows > 256 ? 0.85 : count == 2 && rows <= 16 ? 0.88 : 0.97) * apart) continue;
-        if (launch_merged(set, count, m, stream) != hipSuccess) return RTN_ERR_HIP;
-        for (int k = 0; k < count; ++k) left[member[k]] = 0;
+    for (const SharedLaunch& l : launches) {
+        if (l.count == 1) continue;
+        if (launch_shared(args.data(), l, false, stream) != hipSuccess) return RTN_ERR_HIP;
+        for (int k = 0; k < l.count; ++k) left[l.member[k]] = 0;
     }
     int n = 0;
     for (int i = 0; i < n_mods; ++i)

@@ -89,3 +89,22 @@ WIDE_ZERO_POINTS = [(17, 304, 512, 4, 0), (21, 304, 1536, 4, 128), (40, 304, 153
                     (491, 528, 512, 4, 32), (130, 2576, 1024, 4, 64), (491, 528, 512, 4, 64), (100, 304, 1536, 4, 128), (60, 304, 512, 4, 0),
                     (17, 304, 256, 8, 0), (130, 528, 2048, 8, 0), (200, 528, 2048, 8, 0), (21, 16400, 256, 8, 32), (33, 16400, 256, 8, 64),
                     (491, 1040, 256, 8, 32), (200, 2576, 256, 8, 64), (21, 304, 256, 8, 128), (130, 1040, 2048, 8, 128), (60, 304, 256, 8, 128)]
+
+# Layers whose modules (M, N, K, bits, g) share launches of the block (3) or tile kernel (4) with a workspace of 256 MiB, and how many of
+# them have K split in a shared launch: two splits and more put partial sums behind one another in the workspace.
+SHARED_LAYERS = [(3, 2, [(100, 272, 14336, 4, 128), (101, 288, 14336, 4, 128)]),
+                 (3, 2, [(20, 272, 14336, 8, 0), (21, 288, 14336, 8, 0)]),
+                 (3, 3, [(40, 272, 14336, 4, 32), (41, 288, 14336, 4, 32), (42, 304, 14336, 4, 32)]),
+                 (3, 2, [(200, 272, 14336, 4, 64), (201, 288, 14336, 4, 64)]),
+                 (3, 2, [(100, 272, 8192, 8, 64), (101, 288, 8192, 8, 64)]),
+                 (3, 0, [(33 + i, 272 + 16 * i, 4096, 4, 32) for i in range(11)]),          # eight and three
+                 (4, 2, [(1040, 2064, 14336, 4, 128), (1041, 2080, 14336, 4, 0)]),
+                 (4, 2, [(1100 + i, 4112 + 16 * i, 4096, 8, 128) for i in range(4)])]
+
+# (M, N, K, bits, g) with zero points that the block kernel runs, and its 32-row blocks and wavefronts along K.
+BLOCK_ZERO_POINTS = {(70, 1040, 4096, 4, 128): (1, 1), (33, 304, 1024, 4, 0): (1, 2), (20, 304, 2048, 4, 128): (1, 4), (250, 8208, 1024, 4, 32): (2, 1),
+                     (128, 304, 1024, 4, 128): (2, 2), (250, 304, 2048, 4, 128): (2, 4), (161, 12304, 1024, 4, 32): (3, 2),
+                     (90, 12304, 2048, 4, 32): (3, 4), (230, 16400, 1024, 4, 32): (4, 1), (230, 8208, 4096, 4, 128): (4, 2),
+                     (70, 304, 2048, 8, 128): (1, 1), (20, 304, 1024, 8, 0): (1, 4), (100, 304, 2048, 8, 0): (2, 1), (250, 4112, 1024, 8, 64): (2, 2),
+                     (100, 304, 1024, 8, 128): (2, 4), (161, 12304, 1024, 8, 64): (3, 2), (90, 8208, 2048, 8, 32): (3, 4),
+                     (230, 16400, 1024, 8, 32): (4, 1), (230, 8208, 4096, 8, 0): (4, 2)}

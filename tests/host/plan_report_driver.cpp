@@ -59,6 +59,39 @@ int main() {
                 if (rtn::xcd_wide_tile(b, XB, ZB, sliced, &xb, &zb)) printf("%d %d %d ", xb, zb, b % rtn::kXcds);
             }
             printf("]");
+        } else if (!strcmp(what, "issued") || !strcmp(what, "issued_grouped")) {   // workspace n, then M N K bits g each
+            // the launches of rtn_layer_forward (status 0; 1 = the small-batch kernel's merged launch, -1 = one by one in order) or of the block
+            // kernel in rtn_grouped_forward (those of one module go on): [kernel mb wk, then module and split each]
+            long ws;
+            int n;
+            if (scanf("%ld %d", &ws, &n) != 2 || n < 1 || n > 32) return 1;
+            LinearArgs a[32];
+            LinearPlan plan[32];
+            SharedLaunch l[32];
+            for (int i = 0; i < n; ++i) {
+                long M, N, K, g;
+                int bits;
+                if (scanf("%ld %ld %ld %d %ld", &M, &N, &K, &bits, &g) != 5) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
+            }
+            bool tiles = false;
+            int status = 0, count = 0;
+            if (strlen(what) > 6) {
+                if (grouped_plans(a, n, (size_t)ws, plan) != RTN_OK) return 1;
+                count = grouped_blocks(a, plan, n, (size_t)ws, l);
+            } else if (n > 1 && n <= 16 && merged_layer_plans(a, n, (size_t)ws, plan)) {
+                status = 1;
+            } else {
+                count = layer_launches(a, n, (size_t)ws, l, &tiles);
+                if (count < 0) status = -1;
+            }
+            printf("%d", status);
+            for (int i = 0; i < count; ++i) {
+                const bool alone = l[i].count == 1;
+                printf(" [%d %d %d", alone ? 0 : tiles ? 4 : 3, alone ? 0 : l[i].plan.mb, alone ? 0 : l[i].plan.wk);
+                for (int k = 0; k < l[i].count; ++k) printf(" %d %d", l[i].member[k], alone ? 0 : l[i].plan.split[k]);
+                printf("]");
+            }
         } else if (!strcmp(what, "layer") || !strcmp(what, "grouped")) {   // bits g workspace n, then M N K each
             // layer -> 1 if one launch, plans; grouped -> status, [launch of each]
             long g, ws;

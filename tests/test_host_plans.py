@@ -282,3 +282,66 @@ def test_small_problems_run_on_the_wide_kernel(ask):
             assert status == 0 and len(launches) == 1
             q = launches[0]
             assert (q["path"], q["waves_n"], q["n_tiles16"]) == (3, *shape), (kind, p, q)
+
+
+def _issued(ask, mods, workspace, call="issued"):
+    """(status, [(kernel, mb, wk, [(module, split)])]) of a layer's launches."""
+    out = ask([f"{call} {workspace} {len(mods)} " + " ".join(" ".join(map(str, m)) for m in mods)], raw=True)[0]
+    launches = [list(map(int, g.split())) for g in re.findall(r"\[(.*?)\]", out)]
+    return int(out.split()[0]), [(v[0], v[1], v[2], list(zip(v[3::2], v[4::2]))) for v in launches]
+
+
+@pytest.mark.parametrize("kernel,splits,mods", H.SHARED_LAYERS)
+def test_modules_share_launches_and_their_partial_sums_fit(ask, kernel, splits, mods):
+    """The layers that the GPU tests run: their modules share launches, with the K splits stated, each module in one launch, not more
+    than eight in one, and the partial sums of a launch side by side within the workspace; without one, nothing is split."""
+    for workspace in (256 * MIB, 0):
+        status, launches = _issued(ask, mods, workspace)
+        assert status == 0 and sorted(m for l in launches for m, _ in l[3]) == list(range(len(mods)))
+        assert len(launches) == -(-len(mods) // 8) or not workspace
+        for k, _, wk, members in launches:
+            assert k in (0, kernel) and len(members) <= 8
+            need = sum((mods[m][0] * mods[m][1] * 4 * s + 255) // 256 * 256 for m, s in members if s > 1)
+            assert need <= workspace
+            assert all(s * wk <= mods[m][2] // (512 if mods[m][3] == 4 else 256) for m, s in members if k == 3)
+        assert sum(s > 1 for l in launches for _, s in l[3]) == (splits if workspace else 0)
+    if kernel == 3:
+        _, launches = _issued(ask, mods, 256 * MIB, "issued_grouped")
+        assert any(len(l[3]) > 1 for l in launches)
+
+
+def test_which_modules_share_launches_of_the_block_and_tile_kernels(ask):
+    """Layers of independent modules from five rows: together where that measured ahead, apart where it measured behind or another kernel
+    serves them; and no shared launch of 32-row tiles that gives one XCD more workgroups than its 32 compute units where another plan does not."""
+    def layer(shapes, M, bits, g):
+        return _issued(ask, [(M, N, K, bits, g) for N, K in shapes], 64 * MIB)
+
+    for bits, g in ((4, 128), (4, 32), (4, 64), (8, 0)):
+        for M in (9, 32, 100, 300):
+            status, launches = layer(LAYER_8B, M, bits, g)
+            assert status == 0 and len(launches) == 1 and launches[0][0] == 3, (bits, g, M)
+        status, launches = layer([(4096, 4096), (1024, 4096), (1024, 4096)], 9, bits, g)
+        assert status == 0 and len(launches) == 1 and launches[0][0] == 3
+        assert [l[0] for l in layer([(14336, 4096)] * 2, 9, bits, g)[1]] == [0, 0]             # 28.5 us together, 26.0 apart
+    for M in (1536, 2048):
+        status, launches = layer(LAYER_8B, M, 4, 128)
+        assert status == 0 and len(launches) == 1 and launches[0][0] == 4
+        assert all(l[0] == 0 for l in layer(LAYER_8B, M, 4, 32)[1])                            # groups the tile kernel does not have
+    assert layer(LAYER_8B, 3, 4, 128)[0] == 1 and layer(LAYER_8B, 1, 8, 0)[0] == 1             # the small-batch kernel's launch
+    # 73 us at 12 rows with 33 workgroups on the fullest XCD, 64 apart
+    shapes = [(7168, 5120), (5120, 5120), (27648, 5120), (5120, 13824)]
+    for bits, g in ((8, 128), (8, 0), (4, 64)):
+        for M in (5, 12, 16):
+            status, launches = layer(shapes, M, bits, g)
+            if status == 0 and len(launches) == 1:
+                _, mb, wk, members = launches[0]
+                fullest = sum(-(-(-(-shapes[m][0] // (256 // wk))) // 8) * s for m, s in members)
+                assert mb == 1 and (wk > 1 or fullest <= 32), (bits, g, M, launches)
+
+
+def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
+    """The problems that the GPU tests run with zero points: row blocks and wavefronts along K of their plans."""
+    for (p, want), (status, launches) in zip(H.BLOCK_ZERO_POINTS.items(), ask([f"asym {' '.join(map(str, p))} {64 * MIB}" for p in H.BLOCK_ZERO_POINTS])):
+        q = launches[0]
+        tiles = -(-p[0] // (16 * q["m_rows16"]))
+        assert status == 0 and (q["path"], q["n_tiles16"]) == (3, 2) and (-(-p[0] // (32 * tiles)), q["waves_k"]) == want, (p, q)
