@@ -311,7 +311,7 @@ def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
 def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
     """The block kernel of path 3: every split of its eight wavefronts over N and K and every row tile (32 to 128 rows, of equal
     height), ragged M and N, odd and even numbers of units, fewer units than wavefronts along K or workgroups along it (their
-    partial sums are zeros), with and without zero points, against the oracle."""
+    partial sums are zeros), against the oracle; and the automatic plan of the same problem with zero points."""
     N = 304                                # 19 tile-rows: the last wavefront's second one does not exist
     codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M)
     A_t = synth.activation(M, K, seed=M + 1, device=DEV)
@@ -417,6 +417,48 @@ def test_layer_of_independent_modules_in_block_launches(rtn, M):
     torch.cuda.synchronize()
     H.assert_linear_close(_to_np(C0), O.rtn_linear(_to_np(A_t), codes0, scales0, 128), "chain 0")
     H.assert_linear_close(_to_np(C1), O.rtn_linear(_to_np(C0), codes1, scales1, 128), "chain 1")
+
+
+@pytest.mark.parametrize("M,N,K,bits,g", list(H.BLOCK_ZERO_POINTS))
+def test_linear_block_kernel_zero_points(rtn, M, N, K, bits, g):
+    """Zero points on every workgroup shape of the block kernel, calls whose plans test_host_plans.py asserts: sampled columns, the first
+    and the last tile-row among them, against the oracle."""
+    W_t = (synth.normal_weight(N, K, 0.02, seed=M + bits, device=DEV).float() + 0.015).half()
+    qw, sc, zp = rtn.rtn_quantize_asym(W_t, bits, g)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    C = rtn.rtn_linear_asym(A_t, qw, sc, zp, bits, g, workspace=torch.empty(64 << 20, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    cols = (H.pick_row_tiles(N, 24, seed=M)[:, None] * 16 + np.arange(16)).ravel()
+    gg = g if g > 0 else K
+    codes, scales, zeros = O.rtn_quantize_asym(_to_np(W_t[torch.from_numpy(cols).to(DEV)]), bits, gg)
+    ref = O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg)
+    assert not np.isnan(_to_np(C)).any()
+    H.assert_linear_close(_to_np(C)[:, cols], ref, f"asym int{bits} g={g} M={M} N={N} K={K}")
+
+
+@pytest.mark.parametrize("kernel,splits,mods", H.SHARED_LAYERS)
+def test_layers_whose_modules_share_launches(rtn, kernel, splits, mods):
+    """Layers that test_host_plans.py shows to share launches, with the K splits stated there, so that partial sums lie behind one another
+    in the workspace: every module against a float64 product (sampled rows), outputs and workspace filled with NaN before."""
+    workspace = torch.empty(256 << 20, dtype=torch.uint8, device=DEV)
+    args, refs = [], []
+    for i, (M, N, K, bits, g) in enumerate(mods):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i)
+        A_t = synth.activation(M, K, seed=M + i, device=DEV)
+        rows = np.unique(np.concatenate([[0, M - 1], np.arange(i % M, M, max(1, M // 24))]))
+        args.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.empty((M, N), dtype=torch.float16, device=DEV)))
+        refs.append((rows, O.rtn_linear(_to_np(A_t)[rows], codes, scales, gg)))
+    plan = rtn.LayerPlan(args, workspace=workspace)
+    for what, run in (("layer", plan.run), ("grouped", plan.run_grouped)) if kernel == 3 else (("layer", plan.run),):
+        workspace.fill_(0xFF)
+        for a in args:
+            a["C"].fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        for a, m, (rows, ref) in zip(args, mods, refs):
+            C = _to_np(a["C"])
+            H.assert_linear_close(C[rows], ref, f"{what} {m}")
+            assert not np.isnan(C).any(), (what, m)
 
 
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 0), (8, 128), (8, 0)])
@@ -1084,8 +1126,9 @@ def test_asym_linear(rtn, bits, g):
 @pytest.mark.parametrize("M", [520, 777, 1041])
 def test_layer_of_independent_modules_in_tile_launches(rtn, bits, g, M):
     """rtn_layer_forward above 512 rows: modules that the tile kernel serves share a launch of it.  Tile edges ragged in M and N, other
-    rows and K per module, with and without room for a K split, and a module that another kernel serves among them; every
-    module against a float64 product with the oracle's weights (sampled rows), twice from a graph."""
+    rows and K per module, with and without a workspace, and a module that another kernel serves among them; every
+    module against a float64 product with the oracle's weights (sampled rows), twice from a graph.  (K splits in shared launches: see
+    test_layers_whose_modules_share_launches.)"""
     shapes = [(6160, 512, M), (4096, 1024, M + 3), (9232, 512, M - 6), (1040, 2048, M), (8208, 2560, M)]
     mods, refs = [], []
     for i, (N, K, m) in enumerate(shapes):
