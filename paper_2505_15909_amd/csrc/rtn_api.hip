@@ -1418,10 +1418,13 @@ struct MergedPlan {
     int split[rtn::kMaxBlockGroup];
 };
 
+// No heap: a C entry point has no way to report that it ran out.
+constexpr int64_t kMostSlots = 64;
 static double dealt_us(const double* each, const int64_t* count, int n, int64_t slots) {
     struct Load { double end; int64_t slots; };
-    std::vector<Load> load = {{0.0, slots}};                    // by end
-    int order[rtn::kMaxBlockGroup];
+    Load load[kMostSlots];                                      // by end; each has a slot at least
+    int loads = 1, order[rtn::kMaxBlockGroup];
+    load[0] = {0.0, slots};
     for (int i = 0; i < n; ++i) order[i] = i;
     std::sort(order, order + n, [&](int x, int y) { return each[x] > each[y]; });
     double sum = 0.0;
@@ -1430,22 +1433,27 @@ static double dealt_us(const double* each, const int64_t* count, int n, int64_t 
         const double d = each[order[k]];
         sum += d * left;
         if (left > 64 * slots) {                                // many rounds: the load is even to a round
-            for (Load& l : load) l.end += d * (double)(left / slots - 32);
+            for (int i = 0; i < loads; ++i) load[i].end += d * (double)(left / slots - 32);
             left -= (left / slots - 32) * slots;
         }
         while (left > 0) {
-            const Load first = load.front();
+            const Load first = load[0];
             const int64_t k2 = std::min(first.slots, left);
-            if (k2 == first.slots) load.erase(load.begin());
-            else load.front().slots -= k2;
-            size_t at = 0;
-            while (at < load.size() && load[at].end < first.end + d - 1e-9) ++at;
-            if (at < load.size() && load[at].end < first.end + d + 1e-9) load[at].slots += k2;
-            else load.insert(load.begin() + at, {first.end + d, k2});
+            if (k2 == first.slots) std::copy(load + 1, load + loads--, load);
+            else load[0].slots -= k2;
+            int at = 0;
+            while (at < loads && load[at].end < first.end + d - 1e-9) ++at;
+            if (at < loads && load[at].end < first.end + d + 1e-9) {
+                load[at].slots += k2;
+            } else {
+                std::copy_backward(load + at, load + loads, load + loads + 1);
+                load[at] = {first.end + d, k2};
+                ++loads;
+            }
             left -= k2;
         }
     }
-    return 0.78 * load.back().end + 0.22 * sum / (double)slots;
+    return 0.78 * load[loads - 1].end + 0.22 * sum / (double)slots;
 }
 
 static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {

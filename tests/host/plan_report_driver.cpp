@@ -4,6 +4,16 @@
 #include "../../paper_2505_15909_amd/csrc/rtn_api.hip"
 #include "../../paper_2505_15909_amd/csrc/rtn_device.h"
 #include <stdio.h>
+#include <new>
+
+static long heap_calls = 0;
+void* operator new(size_t n) {
+    ++heap_calls;
+    if (void* p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 static char stand_in[64];                                      // addresses only, nothing is read or written
 
@@ -59,6 +69,19 @@ int main() {
                 if (rtn::xcd_wide_tile(b, XB, ZB, sliced, &xb, &zb)) printf("%d %d %d ", xb, zb, b % rtn::kXcds);
             }
             printf("]");
+        } else if (!strcmp(what, "heap")) {                    // n, then M N K bits g each -> heap allocations of planning a shared launch
+            int n;
+            LinearArgs a[rtn::kMaxBlockGroup];
+            if (scanf("%d", &n) != 1 || n < 1 || n > rtn::kMaxBlockGroup) return 1;
+            for (int i = 0; i < n; ++i) {
+                long M, N, K, g;
+                int bits;
+                if (scanf("%ld %ld %ld %d %ld", &M, &N, &K, &bits, &g) != 5) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, true);
+            }
+            const long before = heap_calls;
+            const MergedPlan blocks = remembered_merge(a, n, (size_t)256 << 20), tiles = remembered_merge(a, n, (size_t)256 << 20, true);
+            printf("%ld %d", heap_calls - before, blocks.us > 0.0 && tiles.us > 0.0 ? 1 : 0);
         } else if (!strcmp(what, "issued") || !strcmp(what, "issued_grouped")) {   // workspace n, then M N K bits g each
             // the launches of rtn_layer_forward (status 0; 1 = the small-batch kernel's merged launch, -1 = one by one in order) or of the block
             // kernel in rtn_grouped_forward (those of one module go on): [kernel mb wk, then module and split each]

@@ -345,3 +345,10 @@ def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
         q = launches[0]
         tiles = -(-p[0] // (16 * q["m_rows16"]))
         assert status == 0 and (q["path"], q["n_tiles16"]) == (3, 2) and (-(-p[0] // (32 * tiles)), q["waves_k"]) == want, (p, q)
+
+
+def test_planning_a_shared_launch_allocates_nothing(ask):
+    """Entry points of a C library: planning the launches of a layer takes no memory that could run out half way."""
+    layers = [[(M, N, K, 4, 128) for N, K in LAYER_8B] for M in (9, 100, 300, 1536)] + [m for _, _, m in H.SHARED_LAYERS if len(m) <= 8 and m[0][4] == m[1][4]]
+    for mods, out in zip(layers, ask([f"heap {len(m)} " + " ".join(" ".join(map(str, x)) for x in m) for m in layers], raw=True)):
+        assert out.split() == ["0", "1"], (mods, out)
