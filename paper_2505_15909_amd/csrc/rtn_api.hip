@@ -16,7 +16,7 @@ using rtn::LinearPlan;
 namespace {
 
 constexpr size_t kWorkspaceCap = (size_t)16 << 20;     // split-K partials never exceed this ...
-constexpr size_t kWorkspaceCapTall = (size_t)64 << 20; // ... except under the wide kernel's plans from 64 rows (and the tile kernel's)
+constexpr size_t kWorkspaceCapTall = (size_t)64 << 20; // ... except under the plans of path 3 from 64 rows (and the tile kernel's)
 constexpr int kMaxSplitK = 16;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -76,12 +76,16 @@ int round_pow2(int64_t v, int lo, int hi) {
 // and K is split inside the workgroup (reduced through LDS).  With more than two activation rows the
 // staged slice grows, so workgroups widen along N (sharing it) and, for long K, K is also split across
 // workgroups so that a slice stays a few chunks long; those partials go through the workspace.
-// Plan of the wide MFMA kernel for more than 16 rows: the candidate (wavefronts per workgroup, tile-rows per
-// wavefront, K splits) with the lowest modelled time.  The model is the larger of three streaming / arithmetic
-// times -- activations re-read from L2 once per workgroup column plus the weights, the weights from HBM, the
-// MFMA work -- derated by how evenly the workgroups fill the compute units, plus fixed per-launch, per-round and
-// split-K reduction costs.  Its constants were fitted to sweeps over the 8B, 70B and 405B shapes at 32-256
-// rows, where its choice is within 2 % of the best measured configuration on average (worst case 15 %).
+// (That is modelled_plan's last part, for the skinny kernel; before it come the models of the other kernels.)
+
+// A fixed shape of path 3 for more than 16 rows: the candidate (wavefronts per workgroup, tile-rows per wavefront, K
+// splits) with the lowest time in a model of a wide kernel that walked K in steps of its own for every shape.  Automatic
+// plans come from block_or_wide_plan below.  This one stands where a caller's program would notice if it moved: it completes
+// explicit configurations that leave fields open, it draws the line up to which a problem keeps its exact codes and
+// what rtn_linear_noalloc accepts (wide_or_tile_plan), and the small groups' models were fitted to its shapes.
+// The model is the larger of three streaming / arithmetic times -- activations re-read from L2 once per workgroup column
+// plus the weights, the weights from HBM, the MFMA work -- derated by how evenly the workgroups fill the compute units, plus
+// fixed per-launch, per-round and split-K reduction costs.
 double wide_model_us(int64_t M, int64_t N, int64_t K, int bits, int mb, int wv, int nbw, int s) {
     const double kL2 = 11.26e12, kHbm = 6.96e12, kMfma = 1.02e15, kSmallTile = 0.767, kFix = 2e-6, kRound = 1.5e-6;
     const double kReduce0 = 2.5e-6, kReduceBw = 4.55e12, kUtilExp = 0.662;
@@ -102,9 +106,8 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
     p->path = 3;
     p->m_rows16 = M <= 32 ? 2 : (M <= 48 ? 3 : 4);
     // 48-row blocks above 64 rows where they save a fifth of the padded rows (65-96 and 129-144 rows: 96 against 128,
-    // 144 against 192): 3-20 % faster there on the 8B, 70B and 405B shapes (a 48-row block is 10-15 % slower per row).
-    // Workgroup shape and K split are still the ones modelled for 64-row blocks: the model's own choice for 48-row
-    // blocks splits K too little (measured: 9-14 % slower on six of the shapes).
+    // 144 against 192).
+    // Workgroup shape and K split are still the ones modelled for 64-row blocks.
     const bool blocks48 = M > 64 && ((M + 47) / 48) * 48 * 5 <= ((M + 63) / 64) * 64 * 4;
     p->m_blocks = (int)((M + 16 * p->m_rows16 - 1) / (16 * p->m_rows16));
     p->prefetch = 1; p->waves_k = 1;
@@ -115,8 +118,7 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
     if (smax > KS / 4) smax = KS / 4;
     if (smax < 1) smax = 1;
     // three splits (they fill the compute units where two leave a third idle and four start a second round) compete
-    // with the powers of two: 19-34 % faster on the 70B and 405B qkv matrices at 48-128 rows.  Other splits are taken
-    // only when the model puts them 5 % ahead: its small preferences for five or six on the 8B shapes cost 2-3 %.
+    // with the powers of two; other splits are taken only when the model puts them 5 % ahead
     double best = 1e30, best_any = 1e30;
     LinearPlan any = *p;
     for (int wv = 4; wv <= 16; wv *= 2)
@@ -541,8 +543,9 @@ bool skinny_plan_from_table(int64_t M, int64_t N, int64_t K, int bits, size_t ld
     return false;
 }
 
-// Groups of 32 and 64 columns from 20 rows up: the wide kernel with several scales per k-step, or the skinny kernel 32 or 64
-// rows at a time (16 with zero points), whichever is modelled faster.  Up to 19 rows the skinny kernel is ahead (8B qkv, group
+// Groups of 32 and 64 columns from 20 rows up: path 3 with several scales per 128 columns (its plan is block_or_wide_plan's), or the
+// skinny kernel 32 or 64 rows at a time (16 with zero points), whichever is modelled faster.  Path 3 is modelled, and was measured
+// for the figures here, on the wide kernel in the shapes that wide_plan picks.  Up to 19 rows the skinny kernel is ahead (8B qkv, group
 // 64: 9.3 us against 11.5 at 19 rows, 15.8 against 11.4 at 20).  Above, the wide kernel leads on large matrices -- 27 us against
 // 44 (8B qkv), 83 against 121 (8B gate_up), 148 against 207 (70B down) at 256 rows -- and the skinny kernel
 //   - where a workgroup's rows fit the LDS in one piece and there are few workgroups: the wide kernel walks K in steps of half a
@@ -603,8 +606,8 @@ bool skinny_on_small_groups(const LinearArgs& a, const LinearPlan& skinny, const
     return small_groups_skinny_us(a, skinny) < (a.zeros ? 0.95 : 1.0) * small_groups_wide_us(a, wide);
 }
 
-// The tile kernel's modelled time, in one launch or two, against the wide plan's w of modelled time t_wide.  The wide kernel's
-// model, fitted at 32 to 256 rows, falls short of its times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and
+// The tile kernel's modelled time, in one launch or two, against the plan w of wide_plan, of modelled time t_wide: where the line of
+// exact codes lies (see wide_or_tile_plan).  wide_plan's model, fitted at 32 to 256 rows, falls short of that kernel's times here: by 1.26 and 1.20 at 4 bit (groups of 128, others), 1.51 and
 // 1.30 at 8 bit (means over 460 problems; the tile kernel's by 1.03).
 bool tile_beats_wide(int64_t M, int64_t N, int64_t K, int bits, int64_t g, const LinearPlan& w, double t_wide, size_t workspace) {
     const int64_t fit = std::max<int64_t>(1, (int64_t)(workspace / ((size_t)M * N * sizeof(float))));
@@ -956,9 +959,13 @@ rtn_status resolve_plan_zp(const LinearArgs& a, size_t workspace_nbytes, LinearP
     if (a.M > 16) skinny.split_k = 1;
     if (a.M > 16 && (a.g % 128 == 0 || small_groups(a.M, a.g))) {
         LinearPlan h;
-        wide_plan(a.M, a.N, a.K, a.bits, a.g, &h);            // the wide kernel's shapes: what the small groups' models compare
-        h.waves_n = 8; h.n_tiles16 = std::min(h.n_tiles16, 2);
-        if (a.g % 128 == 0 || !skinny_on_small_groups(a, skinny, h)) {
+        bool keep = false;
+        if (a.g % 128 != 0) {
+            wide_plan(a.M, a.N, a.K, a.bits, a.g, &h);        // the shapes that the small groups' models compare
+            h.waves_n = 8; h.n_tiles16 = std::min(h.n_tiles16, 2);
+            keep = skinny_on_small_groups(a, skinny, h);
+        }
+        if (!keep) {
             const size_t cap = a.M >= 64 && a.g % 128 == 0 ? kWorkspaceCapTall : kWorkspaceCap;
             const size_t fit = a.workspace ? std::min(workspace_nbytes, cap) : 0;
             static Remembered<LinearPlan> remembered;
@@ -1549,7 +1556,7 @@ static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
     return best;
 }
 
-// The same, remembered (some 50 us of host time): a table of fixed size, an entry gives way to the next one that falls on it.
+// The same, remembered (a few microseconds of host time for four modules): a table of fixed size, an entry gives way to the next one that falls on it.
 static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace, bool tiles = false) {
     struct Key { int64_t v[4 * rtn::kMaxBlockGroup + 3]; };
     struct Entry { Key key; MergedPlan plan; bool used; };

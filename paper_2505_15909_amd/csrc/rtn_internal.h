@@ -10,7 +10,7 @@ constexpr size_t kMaxLdsBytes = 160 * 1024;   // LDS of one gfx950 compute unit,
 
 // Resolved launch configuration of the fused dequantise-GEMM.
 struct LinearPlan {
-    int path;       // 1 = MFMA skinny kernel, 2 = vector-ALU dot kernel, 3 = wide MFMA kernel (larger batches),
+    int path;       // 1 = MFMA skinny kernel, 2 = vector-ALU dot kernel, 3 = wide and block kernels (larger batches),
                     // 4 = tile kernel, 128 or 256 rows x 256 columns per workgroup (matrix-core bound batches)
     int prefetch;   // k-chunks in flight per wavefront (register buffers): 1, 2 or 4
     int waves_n;    // wavefronts along N per workgroup
@@ -60,7 +60,8 @@ inline bool xcd_slices_save_a_round(int64_t XB, int64_t ZB, int64_t split_k) {
     return (sliced + 31) / 32 < (dealt + 31) / 32;
 }
 inline int wide_blocks(int XB, int ZB, bool sliced) { return 8 * (sliced ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB); }
-// Path 3 (wide MFMA kernel): plan check (group size 32, 64 or a multiple of 128, 2-4 row blocks, 1/2/4 tile-rows, at most 8 blocks) and launch.
+// Path 3: plan check (group size 32, 64 or a multiple of 128; m_rows16 x n_tiles16 as the file's header lists them) and launch, on the
+// wide kernel (eight wavefronts of one tile-row) or the block kernel (everything else, by the columns of a workgroup).
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
 // The block kernel of path 3 on several independent problems at once: one precision and number of groups per unit of four packed

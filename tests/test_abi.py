@@ -139,13 +139,12 @@ def test_bad_valid_combination_is_not_launched_without_gpu():
             assert rtn.rtn_linear_validate(M, 4096, 4096, 8, 64, nbytes, dict(q, prefetch=0)) == 7
             assert rtn.rtn_linear_validate(M, 4096, 4096, 8, 64, nbytes, dict(q, waves_n=4)) == 7
     assert rtn.rtn_linear_query(32, 16384, 106496, 4, 128)["path"] == 1     # very large matrix at 32 rows: streaming wins
-    # 128-256 rows on a large 4-bit matrix below the tile kernel's range: the wide kernel's 128-row variant, K split to a
+    # 128-256 rows on a large 4-bit matrix below the tile kernel's range: the block kernel's 128-row tile, K split to a
     # workgroup per compute unit, and the size helper covers its partial sums
     q = rtn.rtn_linear_query(128, 16384, 53248, 4, 128)
     assert (q["path"], q["m_rows16"], q["n_tiles16"], q["waves_n"], q["split_k"]) == (3, 8, 2, 8, 4)
     assert rtn.rtn_workspace_nbytes(128, 16384, 53248, 4, 128) == 128 * 16384 * 4 * 4
-    # one row more: the 128-row variant would pad to 256, and the tile kernel with K in four splits is modelled (and
-    # measured) ahead of the 64-row wide plan
+    # one row more: the 128-row tile would pad to 256, and the long matrices of this size stay on the tile kernel up to 144 rows
     q = rtn.rtn_linear_query(129, 16384, 53248, 4, 128)
     assert (q["path"], q["m_rows16"], q["split_k"]) == (4, 8, 4)
     assert rtn.rtn_linear_query(128, 16384, 53248, 8, 0)["m_rows16"] == 4

@@ -242,8 +242,8 @@ def test_linear_larger_batches(rtn, bits, g, M):
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 512), (4, 0), (8, 128), (8, 256), (8, 0)])
 @pytest.mark.parametrize("M", [5, 17, 33, 48, 64, 100, 130])
 def test_linear_wide_kernel(rtn, bits, g, M):
-    """The wide MFMA kernel (path 3): every register-tile shape, ragged M and N, K split across workgroups
-    inside and across groups, several row blocks."""
+    """Path 3 by explicit configurations, on the wide and the block kernel: every tile shape that the configurations name,
+    ragged M and N, K split across workgroups inside and across groups, several row blocks."""
     N, K = 528, 2560                       # 33 tile-rows: the last workgroup is partly out of range; 20 k-steps
     codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=6)
     A_t = synth.activation(M, K, seed=200 + M, device=DEV)
@@ -282,7 +282,7 @@ def test_linear_wide_kernel(rtn, bits, g, M):
                                         (4, 64, 6160, 512), (8, 32, 6160, 512), (4, 64, 80, 8704)])
 @pytest.mark.parametrize("M", [19, 20, 48, 130])
 def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
-    """Groups of 32 and 64 columns above 16 rows (from 20 rows several groups per 128-column k-step of the wide kernel): the
+    """Groups of 32 and 64 columns above 16 rows (from 20 rows several groups per 128 columns in the wide and block kernels): the
     automatic plan, without a workspace too, and the zero-point variant, against the oracle.  Ragged tile-rows and rows, K
     an odd number of k-chunks, shapes with and without K splits, one and many workgroups."""
     codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M + g)
@@ -464,8 +464,8 @@ def test_layers_whose_modules_share_launches(rtn, kernel, splits, mods):
 @pytest.mark.parametrize("bits,g", [(4, 128), (4, 256), (4, 0), (8, 128), (8, 0)])
 @pytest.mark.parametrize("M", [20, 128, 130, 300])
 def test_linear_wide_kernel_128_rows(rtn, bits, g, M):
-    """The wide kernel's 128-row register tile (explicit configuration only): weights scaled in fp16 before the MFMA,
-    row blocks in two halves; ragged M and N, K split with uneven shares."""
+    """The block kernel's 128-row tile (its automatic plans have it too): exact codes, scales on the accumulators; ragged M and N,
+    K split with uneven shares."""
     N, K = 400, 2560
     codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=9)
     A_t = synth.activation(M, K, seed=400 + M, device=DEV)
@@ -706,8 +706,8 @@ def test_linear_tile_kernel_in_two_launches(rtn, M):
 
 
 def test_linear_automatic_plans_on_large_random_shapes(rtn):
-    """What rtn_linear chooses by itself from 48 rows up on matrices large enough for every branch of its plan (wide
-    kernel with 1-8 K splits, its 128-row variant, tile kernel of either height with and without splits), with the
+    """What rtn_linear chooses by itself from 48 rows up on matrices large enough for every branch of its plan (block
+    kernel with 1-8 K splits and tiles of 32 to 128 rows, tile kernel of either height with and without splits), with the
     workspace rtn_workspace_nbytes asks for: a stripe of output columns (first and last tile-row, 96 random ones)
     against the oracle on the unpacked codes."""
     rng = np.random.default_rng(5)

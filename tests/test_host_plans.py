@@ -131,8 +131,9 @@ def test_merged_layers_leave_no_wavefront_without_work(ask):
 
 
 def test_which_layers_are_merged(ask):
-    """The range that the documentation states, the layers that the GPU tests rely on, and sets of modules that were measured
-    slower in one launch than apart."""
+    """The small-batch kernel's merge alone (shared launches of the block and tile kernels are below): the range that the
+    documentation states, the layers that the GPU tests rely on, and sets of modules that were measured slower in one launch than
+    apart."""
     def one(*q):
         return ask([_layer(*q)])[0][0] == 1
 
