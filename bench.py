@@ -8,8 +8,8 @@ Transformer layer (Section 4: QKV 4096->6144, attention output 4096->4096, gate_
 (Sections 1, 5).  Weights ~ N(0, 0.02), activations ~ N(0, 1), seeded, synthetic.
 
 One step = one pass of the hot path over one batch of input: for every M, the layer's four
-modules through rtn_layer_forward (20 fused dequantise-GEMMs; at M = 1, 2, 4 the four independent
-modules go out as one launch, at 8 and 16 one by one).  Every pass streams a different
+modules through rtn_layer_forward (20 fused dequantise-GEMMs; the four independent modules go out as one
+launch, of the small-batch kernel at M = 1, 2, 4 and of the block kernel, with a reduce launch, at 8 and 16).  Every pass streams a different
 copy of the packed layer (enough copies to exceed twice the 256 MB Infinity Cache), as token
 generation does when it walks a model's layers, so the weights come from HBM, not from cache.
 The load-time quantise/pack pass (Section 5) runs once during set-up, is checked to reproduce,
@@ -18,7 +18,7 @@ which measure the metric itself: weight-stream GB/s of the linear layers.
 
 Prints one JSON line: metric, value (GB/s of packed weights and scales streamed, whole job), unit, n_gpus, steps, warmup,
 ms_per_step, dtype, data, config, plus `roofline` (the step's two kernels against the 8 TB/s HBM peak: algorithmic bytes per
-launch over the measured average launch duration, and the HBM traffic per single launch from hardware counters), `cpu_baseline`
+layer over its measured average duration, and the HBM traffic per layer from hardware counters), `cpu_baseline`
 (the CPU oracle timed on a bounded sample of the same workload) and `quantize` (load-time pass throughput).
 """
 from __future__ import annotations
@@ -35,13 +35,13 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 BATCHES = (1, 2, 4, 8, 16)
-MERGED = (1, 2, 4)                    # batches whose four modules rtn_layer_forward sends as one launch (up to five rows here)
+SMALL = (1, 2, 4)                     # batches whose four modules go out as one launch of the small-batch kernel (up to five rows here)
 BITS, GROUP = 4, 128
 CACHE_BYTES = 256e6
-# HBM bytes per single launch of the skinny kernel come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of the layer set,
-# scaled by a copy kernel of known size; the committed summary of those runs carries the figure on a line
-# "traffic_bytes_per_launch: <n>", which is read at run time (null if the summary is not there).
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "skinny_mfma_llama8b_w4a16_hbm_traffic.txt")
+# HBM bytes per layer come from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of the layer set,
+# scaled by a copy kernel of known size; the committed summary of those runs carries the figures on lines
+# "traffic_bytes_per_launch: <n>" (block kernel) and "merged_traffic_bytes_per_launch: <n>" (small-batch kernel), which are read at run time (null if the summary is not there).
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "layer_llama8b_w4a16_hbm_traffic.txt")
 W8_BATCHES = (1, 4, 16, 64)
 WARM_MS = float(os.environ.get("RTN_BENCH_WARM_MS", "200"))      # untimed work before each event-bracketed measurement
 SETTLE_MS = float(os.environ.get("RTN_BENCH_SETTLE_MS", "300"))  # the step graphs run this long, untimed, before the warm-up steps (clocks)
@@ -207,7 +207,9 @@ def report(args, rtn, synth, torch, np, dev) -> int:
             line = (f"{name:8s} {'int' + str(bits) if args.selective else '':4s} {K:6d}->{N:6d} M={M:3d}  {t:8.2f} us  {nbytes / t / 1e3:7.0f} GB/s  "
                     f"{nbytes / t / 80e3:5.1f} %  {2.0 * M * N * K / t / 1e6:7.2f} TFLOP/s  ")
             if plan["path"] == 3:
-                line += (f"wide {plan['waves_n']} waves x {16 * plan['m_rows16']}x{16 * plan['n_tiles16']} split {plan['split_k']}")
+                wide = (plan["waves_n"], plan["n_tiles16"]) == (8, 1)
+                line += (f"{'wide' if wide else 'block'} kernel {16 * plan['m_rows16']} rows x {128 if wide else 256 // plan['waves_k']} columns "
+                         f"split {plan['split_k']}")
             elif plan["path"] == 4:
                 line += f"tile kernel (128 or 256 rows x 256 columns per workgroup) split {plan['split_k']}"
             else:
@@ -570,58 +572,47 @@ def main() -> int:
     value = step_weight_bytes / (ms_per_step * 1e-3) / 1e9
     flops = sum(2.0 * M * N * K for M in BATCHES for _, (K, N) in modules)
 
-    # ---- roofline of the two kernels of a step: the int4 skinny MFMA dequantise-GEMM launched per module (M = 8, 16: half
-    # of the step's time) and the same kernel over the four modules of a layer in one grid (M = 1, 2, 4).  A pair of HIP
-    # events on the launch stream brackets each kind's launches of the same passes, issued back to back (direct launches, no
-    # graph); the stream is first held busy so that the host has enqueued everything before the GPU gets there, and the
-    # bracket times the GPU.  (Events around every single launch cost several microseconds each on this runtime and were
-    # not usable.)  Average launch duration = bracket / launches; dispatch gaps and K-split reductions are inside it.
-    algo_bytes = merged_bytes = 0.0
-    calls, merged = [], []
+    # ---- roofline of the two kernels of a step: the int4 block kernel over the four modules of a layer in one grid (M = 8, 16:
+    # half of the step's time, its reduce launch for the K split of the down projection included) and the small-batch kernel
+    # over the same (M = 1, 2, 4).  A pair of HIP events on the launch stream brackets each kind's passes, issued back to back
+    # (direct launches, no graph); the stream is first held busy so that the host has enqueued everything before the GPU gets
+    # there, and the bracket times the GPU.  (Events around every single launch cost several microseconds each on this runtime
+    # and were not usable.)  Average duration = bracket / layers; dispatch gaps and K-split reductions are inside it.
+    layers = {True: [], False: []}
+    layer_algo_bytes = {True: 0.0, False: 0.0}
     for s_i in range(min(args.steps, 20)):
         for j, M in enumerate(BATCHES):
             cp = copies[pass_no[0] % n_copies]
-            nbytes = sum(q.numel() + s.numel() * 2 + 2 * M * K + 2 * M * N for (q, s), (_, (K, N)) in zip(cp, modules))
-            if M in MERGED:
-                merged.append(plans[pass_no[0] % n_copies][j])
-                merged_bytes += nbytes
-            else:
-                calls += [(acts[M][i], cp[i][0], cp[i][1], outs[M][i]) for i in range(len(modules))]
-                algo_bytes += nbytes
+            layer_algo_bytes[M in SMALL] += sum(q.numel() + s.numel() * 2 + 2 * M * K + 2 * M * N for (q, s), (_, (K, N)) in zip(cp, modules))
+            layers[M in SMALL].append(plans[pass_no[0] % n_copies][j])
             pass_no[0] += 1
-    n_launch = len(calls)
     hold = torch.empty(1 << 30, dtype=torch.uint8, device=dev)
+    layer_us = {}
     with torch.cuda.stream(stream):
         ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        for _ in range(12):
-            hold.fill_(1)                                   # a few milliseconds of head start for the host
-        ev0.record(stream)
-        for A_, q_, s_, o_ in calls:
-            rtn.rtn_linear(A_, q_, s_, BITS, GROUP, out=o_, workspace=ws)
-        ev1.record(stream)
-        torch.cuda.synchronize()
-        launch_us = ev0.elapsed_time(ev1) * 1e3 / n_launch
-        for _ in range(12):
-            hold.fill_(1)
-        ev0.record(stream)
-        for plan in merged:
-            plan.run()
-        ev1.record(stream)
-        torch.cuda.synchronize()
-        merged_us = ev0.elapsed_time(ev1) * 1e3 / len(merged)
+        for small, kind in layers.items():
+            for _ in range(12):
+                hold.fill_(1)                               # a few milliseconds of head start for the host
+            ev0.record(stream)
+            for plan in kind:
+                plan.run()
+            ev1.record(stream)
+            torch.cuda.synchronize()
+            layer_us[small] = ev0.elapsed_time(ev1) * 1e3 / len(kind)
     del hold
-    achieved = algo_bytes / n_launch / (launch_us * 1e-6) / 1e9
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": _measured_traffic(),
-                "kernel": "rtn::skinny_mfma_kernel<4,4,*,*,1> (fused int4 g128 dequantise-GEMM; a launch = one rtn_linear, M = 8 and 16)",
-                "launches": n_launch, "avg_launch_us": round(launch_us, 3),
-                "algorithmic_bytes_per_launch": round(algo_bytes / n_launch, 1),
-                "merged_layers": {"kernel": "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
-                                  "achieved": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9, 1),
-                                  "frac": round(merged_bytes / len(merged) / (merged_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
-                                  "traffic": _measured_traffic("merged_traffic_bytes_per_launch"),
-                                  "launches": len(merged), "avg_launch_us": round(merged_us, 3),
-                                  "algorithmic_bytes_per_launch": round(merged_bytes / len(merged), 1)}}
+
+    def kernel_roofline(small, kernel, traffic):
+        per_layer = layer_algo_bytes[small] / len(layers[small])
+        achieved = per_layer / (layer_us[small] * 1e-6) / 1e9
+        return {"kernel": kernel, "achieved": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBS, 4),
+                "traffic": _measured_traffic(traffic), "launches": len(layers[small]), "avg_launch_us": round(layer_us[small], 3),
+                "algorithmic_bytes_per_launch": round(per_layer, 1)}
+
+    roofline = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                **kernel_roofline(False, "rtn::block_mfma_kernel<4,1,4,8,1,false> (fused int4 g128 dequantise-GEMM, the four modules of a layer "
+                                         "in one launch, M = 8 and 16; its reduce launch included)", "traffic_bytes_per_launch"),
+                "merged_layers": kernel_roofline(True, "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
+                                                 "merged_traffic_bytes_per_launch")}
 
     # ---- read-stream ceiling: a plain read kernel on buffers of the four matrices' packed sizes, same protocol ----
     read_ceiling_gbs = None
