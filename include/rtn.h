@@ -84,7 +84,9 @@ int rtn_layout_version(void);
  * fp32 split-K partial sums; an upper bound over every configuration the library may
  * choose for this problem; never more than 16 MiB up to 63 rows.  From 64 rows the
  * chosen plan may split K further to fill the compute units (never more than 64 MiB up
- * to 127 rows, 256 MiB above). */
+ * to 127 rows, 256 MiB above).  The kernels above 16 rows make do with less, or none (fewer
+ * splits, slower); the small-batch kernel's own plans, up to 16 rows and on a few larger calls
+ * (RTN_ERR_WORKSPACE), do not.  Sizes are those of this build's plans: ask, do not store them. */
 size_t rtn_qweight_nbytes(int64_t N, int64_t K, int bits);
 size_t rtn_scales_nbytes(int64_t N, int64_t K, int group_size);
 size_t rtn_workspace_nbytes(int64_t M, int64_t N, int64_t K, int bits, int group_size);
