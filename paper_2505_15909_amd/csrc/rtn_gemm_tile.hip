@@ -48,6 +48,7 @@ constexpr int kBK = 64;                         // columns of K per step
 constexpr int kChunkK = 128;                    // packed weights are fetched in 128-column chunks (two steps)
 constexpr int kThreads = 512;
 constexpr int kBufferFlags = 0x00020000;
+constexpr uint32_t kNoRow = 0x80000000u;        // beyond a resource of 2 GiB; in a larger one, data of rows that are never stored
 constexpr int kZGroup = 4;                      // row tiles in a group (1, 2, 8: within 1 %; 16: 1-2 % slower)
 
 struct TileParams {
@@ -129,8 +130,9 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     const int ks0 = 2 * kc0;
 
     // Row-major fp16 operands are addressed through a resource that starts at this workgroup's first row (no 32-bit
-    // limit on the whole matrix).  Rows past M or N read the last valid row, steps past the last one the last step:
-    // every load is in bounds, and those rows are never stored, those steps never used.
+    // limit on the whole matrix).  Rows past M or N read zeros (an offset beyond the resource; they are multiplied like the others and
+    // draw less power than copies of a row), steps past the last one the last step; those rows are never stored, those
+    // steps never used.
     const int a_rows = min(TM, p.M - m0), b_rows = min(kTN, p.N - n0);
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<half_t*>(p.A) + (int64_t)m0 * p.K, 0, (uint32_t)a_rows * (uint32_t)p.K * 2u, kBufferFlags);
@@ -148,10 +150,10 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     const int st_row = lane >> 3, st_piece = (lane & 7) ^ (lane >> 3);
 #pragma unroll
     for (int i = 0; i < NA; ++i)
-        a_lane[i] = ((uint32_t)min((wave * NA + i) * 8 + st_row, a_rows - 1) * (uint32_t)p.K + st_piece * 8) * 2u;
+        a_lane[i] = (wave * NA + i) * 8 + st_row < a_rows ? ((uint32_t)((wave * NA + i) * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u : kNoRow;
 #pragma unroll
     for (int i = 0; i < NB; ++i)
-        b_lane[i] = ((uint32_t)min((wave * NB + i) * 8 + st_row, b_rows - 1) * (uint32_t)p.K + st_piece * 8) * 2u;
+        b_lane[i] = (wave * NB + i) * 8 + st_row < b_rows ? ((uint32_t)((wave * NB + i) * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u : kNoRow;
     auto a_dma = [&](int stage, int t, int i) {
         load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, a_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
     };

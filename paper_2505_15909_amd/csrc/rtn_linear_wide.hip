@@ -405,11 +405,13 @@ __global__ __launch_bounds__(64 * WN * WK, MB == 1 ? 4 : 2) void block_mfma_kern
     const uint32_t w_lane = nt_ok ? (uint32_t)nt * (uint32_t)p.KL * 1024u + (h * 16 + (lane & 15)) * 16 : kOutOfRange;
     const uint32_t s_lane = nt_ok ? ((uint32_t)nt * 16 + (lane & 15)) * (uint32_t)p.G * 2u : kOutOfRange;
 
+    // Rows past M are zeros, not copies of the last row: they are multiplied all the same, and zeros draw less power (8B layer at
+    // 200 rows, 256 multiplied: 118.9 -> 113.6 us).
     uint32_t a_lane[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int r = (wn * NA + i) * RPI + lane / PIECES;
-        a_lane[i] = (uint32_t)min(r, a_rows - 1) * (uint32_t)p.K * 2u + (uint32_t)(((lane % PIECES) ^ ((r / SWZ) % PIECES)) * 16);
+        a_lane[i] = r < a_rows ? (uint32_t)r * (uint32_t)p.K * 2u + (uint32_t)(((lane % PIECES) ^ ((r / SWZ) % PIECES)) * 16) : kOutOfRange;
     }
     // steps past the last one request nothing: their resource is empty (zeros arrive)
     auto a_load = [&](int st, int q) {                    // stage q of this wavefront's share
