@@ -7,7 +7,10 @@ import subprocess
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "librtn_gfx950.so")
-SOURCES = ["rtn_api.hip", "rtn_quantize.hip", "rtn_linear.hip", "rtn_linear_wide.hip", "rtn_gemm_tile.hip", "rtn_bench.hip"]
+SOURCES = ["rtn_api.hip", "rtn_quantize.hip", "rtn_linear.hip", "rtn_linear_wide.hip", "rtn_linear_block4.hip", "rtn_linear_block4z.hip",
+           "rtn_linear_block8.hip", "rtn_linear_block8z.hip", "rtn_gemm_tile.hip", "rtn_bench.hip"]
+# objects of several translation units, which compile side by side
+JOINED = {"rtn_linear_wide.o": ["rtn_linear_wide.o", "rtn_linear_block4.o", "rtn_linear_block4z.o", "rtn_linear_block8.o", "rtn_linear_block8z.o"]}
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
     # no packed-fp32 instruction selection: some packed fp32 forms have given wrong results on this platform
@@ -34,6 +37,11 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
 
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
         objs = list(pool.map(compile_one, SOURCES))
+    for name, parts in JOINED.items():
+        whole, parts = os.path.join(obj_dir, name), [os.path.join(obj_dir, p) for p in parts]
+        subprocess.run(["ld", "-r", "-o", whole + ".joined", *parts], check=True)
+        os.replace(whole + ".joined", whole)
+        objs = [o for o in objs if o not in parts] + [whole]
     link = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB_PATH, *objs]
     if verbose:
         print(" ".join(link), flush=True)

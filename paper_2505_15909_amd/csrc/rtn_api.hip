@@ -159,16 +159,27 @@ struct BlockTimes {
     double stream_us;   // its weights and activations at the rates above
 };
 
-BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+double block_wg_us(int mb, int64_t K, int bits, int64_t g, int wk, int s) {
     static const double kUnit[4] = {1.93, 2.25, 2.49, 2.77}, kGroup[4] = {0.044, 0.123, 0.269, 0.382};
-    const int64_t unit = bits == 4 ? 512 : 256, units = K / unit, cols = 256 / wk;
+    const int64_t unit = bits == 4 ? 512 : 256, units = K / unit;
+    const double per = (double)(((units + s - 1) / s + wk - 1) / wk), groups = g >= unit ? 1.0 : (double)(unit / g);
+    return 1.33 + per * (kUnit[mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[mb - 1] * groups) + (wk > 1 ? 0.73 * mb : 0.0);
+}
+
+// Workgroups of ZB row tiles on the fullest XCD.
+int64_t block_on_xcd(int64_t N, int64_t ZB, int wk, int s) {
+    const int64_t XB = (N + 256 / wk - 1) / (256 / wk);
+    return (rtn::xcd_slices_save_a_round(XB, ZB, s) ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s;
+}
+
+BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
+    const int64_t cols = 256 / wk;
     const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols;
     BlockTimes b;
     b.mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
     b.wgs = XB * ZB * s;
-    b.on_xcd = (rtn::xcd_slices_save_a_round(XB, ZB, s) ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s;
-    const double per = (double)(((units + s - 1) / s + wk - 1) / wk), groups = g >= unit ? 1.0 : (double)(unit / g);
-    b.wg_us = 1.33 + per * (kUnit[b.mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[b.mb - 1] * groups) + (wk > 1 ? 0.73 * b.mb : 0.0);
+    b.on_xcd = block_on_xcd(N, ZB, wk, s);
+    b.wg_us = block_wg_us(b.mb, K, bits, g, wk, s);
     b.stream_us = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * b.mb * K * 2.0 / 1.71e7;
     return b;
 }
@@ -1412,25 +1423,25 @@ static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t works
 
 // Independent modules of one precision and number of groups per unit in one launch of the block kernel.  Apart, each fills the
 // chip to a half or three quarters and pays the start, the first data and the last store of a launch; together they fill it and
-// pay once.  Plan: one row tile height and number of wavefronts along K for all (a launch is one kernel), the longest
-// workgroups first, K of the module with the longest split in two or four.  The time is the end of the last workgroup
-// when those of the fullest XCD are dealt in that order to its compute units (32; two of the 32-row ones on each), four fifths of
-// it, and the average load one fifth; against it the streams.  The fullest XCD is counted as the launch deals the tiles, module by
-// module and split by split: 7168-, 5120-, 27648- and 5120-wide modules with K of the last in four are 236 workgroups, but 33 on
-// one XCD, and took 73 us at 12 rows where their own launches take 64.  Fitted to 408 merged launches of 68 layers; of 8534 on 330
-// other sets it picks plans 3.9 % behind the best one on average, 10 % rms.
+// pay once.  Plan: one height of the tallest row tiles for all (a launch is one kernel), wavefronts along K by module, the longest
+// workgroups first, K of the modules with the longest split in up to six.  The time is about the mean of the end of the last workgroup,
+// when those of the fullest XCD are dealt in that order to its compute units (32; two of the 32-row ones on each), and the
+// average load (the clock is higher while part of the chip is idle); against it the streams.  The fullest XCD is counted as the launch
+// deals the tiles, module by module and split by split: 7168-, 5120-, 27648- and 5120-wide modules with K of the last in four are 236
+// workgroups, but 33 on one XCD, and took 73 us at 12 rows where their own launches take 64.
 struct MergedPlan {
     double us;                          // modelled time, negative: no such plan
-    int mb, wk;
+    int mb, wk;                         // row blocks of 32 rows (the tile kernel: 16-row blocks per wavefront), least wavefronts along K
+    int waves[rtn::kMaxBlockGroup];     // wavefronts along K of each
     int split[rtn::kMaxBlockGroup];
 };
 
 // No heap: a C entry point has no way to report that it ran out.
 constexpr int64_t kMostSlots = 64;
-static double dealt_us(const double* each, const int64_t* count, int n, int64_t slots) {
+static double dealt_us(const double* each, const int64_t* count, int n, int64_t slots, double last) {
     struct Load { double end; int64_t slots; };
     Load load[kMostSlots];                                      // by end; each has a slot at least
-    int loads = 1, order[rtn::kMaxBlockGroup];
+    int loads = 1, order[2 * rtn::kMaxBlockGroup];
     load[0] = {0.0, slots};
     for (int i = 0; i < n; ++i) order[i] = i;
     std::sort(order, order + n, [&](int x, int y) { return each[x] > each[y]; });
@@ -1460,56 +1471,109 @@ static double dealt_us(const double* each, const int64_t* count, int n, int64_t 
             left -= k2;
         }
     }
-    return 0.78 * load[loads - 1].end + 0.22 * sum / (double)slots;
+    return last * load[loads - 1].end + (1.0 - last) * sum / (double)slots;
 }
 
+// What the time of a launch is made of, fitted for launches of up to 16 rows, of which a workgroup stages no more, and for others.
+struct BlockCosts {
+    double start, unit[4], group[4], int8;     // a workgroup: its start, a unit of four packed tiles by row blocks, a scale group in it, an 8-bit unit
+    double waves[4][3];                        // a unit with 2, 4, 8 wavefronts along K, by row blocks
+    double rows, sum;                          // staging 32 rows for a unit, the sum over the wavefronts along K per row block
+    double busy, shared, one;                  // slower on a full chip, two on a compute unit, 32-row workgroups
+    double stream, norm, reduce, reduce_bw, launch, last;
+};
+static const BlockCosts kBlockCosts = {0.38, {2.607, 2.141, 2.770, 2.750}, {0.043, 0.168, 0.159, 0.280}, 0.739,
+                                       {{1.031, 0.874, 1.120}, {0.956, 0.731, 0.908}, {0.909, 0.861, 1.0}, {0.796, 0.615, 1.0}}, 0.238, 0.226,
+                                       0.353, 1.543, 0.955, 0.614, 1.890, 1.558, 6.906e6, 5.003, 0.519};
+static const BlockCosts kBlockCosts16 = {0.636, {1.923, 0.0, 0.0, 0.0}, {0.063, 0.0, 0.0, 0.0}, 0.879,
+                                         {{0.980, 0.801, 0.495}}, 0.021, 0.624, 0.322, 1.617, 0.967, 0.539, 1.495, 1.621, 6.083e6, 4.197, 0.780};
+
+// Modelled time of m, negative where its partial sums do not fit; the module with the longest workgroups.  The workgroups of a part (row
+// tiles of one height) are dealt longest first, as launch_blocks orders them, to the compute units of the fullest XCD.  Fitted to
+// 2600 launches: the 8B, 70B and 405B layers in five formats at 5 to 512 rows, two to eight modules of 1024 to 8192 columns at 1 to 16
+// rows (4 % rms; the pick is 0.9 % behind the best of 10 to 80 plans measured for each).
+static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, size_t workspace, int* longest) {
+    int64_t most = 0;
+    for (int i = 0; i < n; ++i) most = std::max(most, a[i].M);
+    const BlockCosts& c = most <= 16 && m.mb == 1 ? kBlockCosts16 : kBlockCosts;
+    double each[2 * rtn::kMaxBlockGroup], length = 0.0, stream = 0.0, reduce = 0.0;
+    int64_t count[2 * rtn::kMaxBlockGroup], wgs = 0, on_xcd = 0;
+    size_t partials = 0;
+    int parts = 0;
+    for (int i = 0; i < n; ++i) {
+        const int s = m.split[i], wk = m.waves[i], tiles = (int)((a[i].M + 32 * m.mb - 1) / (32 * m.mb)), tall = rtn::tall_row_tiles(a[i].M, m.mb);
+        const int64_t unit = chunk_k(a[i].bits), cols = 256 / wk, XB = (a[i].N + cols - 1) / cols;
+        const double per = (double)(((a[i].K / unit + s - 1) / s + wk - 1) / wk), groups = a[i].g >= unit ? 1.0 : (double)(unit / a[i].g);
+        const double waves = wk == 1 ? 1.0 : c.waves[m.mb - 1][wk == 2 ? 0 : wk == 4 ? 1 : 2];
+        for (int h = 0; h < 2; ++h) {                       // the row tiles of 32 mb rows, those of 32 rows less
+            const int tiles_h = h == 0 ? tall : tiles - tall, mb = m.mb - h;
+            if (tiles_h == 0) continue;
+            const double rows = (double)wk * std::min((double)a[i].M, 32.0 * mb) / 32.0;
+            each[parts] = c.start + per * (c.unit[mb - 1] * (a[i].bits == 8 ? c.int8 : 1.0) * waves + c.group[mb - 1] * groups +
+                                           c.rows * rows * (a[i].bits == 8 ? 0.5 : 1.0)) + (wk > 1 ? c.sum * mb : 0.0);
+            count[parts] = block_on_xcd(a[i].N, tiles_h, wk, s);
+            on_xcd += count[parts];
+            if (each[parts] > length) { length = each[parts]; *longest = i; }
+            ++parts;
+        }
+        wgs += XB * tiles * s;
+        stream += c.stream * ((double)a[i].N * a[i].K * a[i].bits / 8.0 / 6.83e6 +
+                              (double)XB * std::min<int64_t>((int64_t)tiles * 32 * m.mb, (a[i].M + 31) / 32 * 32) * a[i].K * 2.0 / 1.71e7);
+        if (s > 1) {
+            reduce += c.reduce + (double)a[i].M * a[i].N * s * 8.0 / c.reduce_bw;
+            partials += (((size_t)a[i].M * a[i].N * sizeof(float) * s) + 255) & ~(size_t)255;
+        }
+    }
+    if (partials > workspace) return -1.0;
+    const bool two = m.mb == 1;
+    const double slow = (two ? c.one : 1.02) * (1.0 + c.busy * std::min(1.0, (double)wgs / 256.0) * m.mb / 4.0) * (two && on_xcd > 32 ? c.shared : 1.0);
+    for (int i = 0; i < parts; ++i) each[i] *= slow;
+    const double serial = dealt_us(each, count, parts, two ? 64 : 32, c.last);
+    return c.launch + std::pow(std::pow(serial, c.norm) + std::pow(stream, c.norm), 1.0 / c.norm) + reduce;
+}
+
+// The plan with the lowest modelled time: row tile height (32 rows up to 96 rows, 128 from 65), wavefronts along K, and then the longest
+// workgroups shorter step by step, K shared by more workgroups, before that in further passes by two wavefronts (up to 64 rows only
+// where that is modelled 3 % ahead), and up to 8 rows by four: with more rows those are staged too late for the weights that four have in
+// flight (8B layer with four for the down projection against one and four splits: 8 rows 26.6 us and 26.9, 16 rows 29.3 and 28.2, 32 rows
+// 33.2 and 29.6).
 static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
     int64_t rows = 0, shortest = INT64_MAX;
     MergedPlan best;
     best.us = -1.0;
+    double best_line = 0.0;
     for (int i = 0; i < n; ++i) {
         if (a[i].N >= (1 << 22)) return best;
         rows = std::max(rows, a[i].M);
         shortest = std::min(shortest, a[i].K / chunk_k(a[i].bits));
     }
-    static const double kWaves[9] = {0, 1.076, 1.02, 0, 0.948, 0, 0, 0, 0.908};
     for (int r = 2; r <= 8; r *= 2) {
         if ((r == 2 && rows > 96) || (r == 8 && rows <= 64)) continue;
         const int64_t tiles = (rows + 16 * r - 1) / (16 * r);
         const int mb = (int)((rows + 32 * tiles - 1) / (32 * tiles));
         for (int wk = 1; wk <= 8 && wk <= shortest; wk *= 2) {
             if (wk == 8 && mb > 2) continue;
-            MergedPlan m;
-            m.mb = mb; m.wk = wk;
-            for (int i = 0; i < n; ++i) m.split[i] = 1;
-            for (int cuts = 0; cuts < 4; ++cuts) {
-                double each[rtn::kMaxBlockGroup], stream = 0.0, reduce = 0.0;
-                int64_t count[rtn::kMaxBlockGroup], wgs = 0, on_xcd = 0;
-                size_t partials = 0;
-                int longest = 0;
-                for (int i = 0; i < n; ++i) {
-                    const BlockTimes b = block_times(a[i].M, a[i].N, a[i].K, a[i].bits, a[i].g, 2 * mb, wk, m.split[i]);
-                    each[i] = b.wg_us;
-                    count[i] = b.on_xcd;
-                    on_xcd += b.on_xcd;
-                    wgs += b.wgs;
-                    stream += 0.839 * b.stream_us;
-                    if (each[i] > each[longest]) longest = i;
-                    if (m.split[i] > 1) {
-                        reduce += 1.1 + (double)a[i].M * a[i].N * m.split[i] * 8.0 / 6.53e6;
-                        partials += (((size_t)a[i].M * a[i].N * sizeof(float) * m.split[i]) + 255) & ~(size_t)255;
+            for (int deepen = 1; deepen <= (wk > 1 ? 1 : rows <= 8 ? 4 : 2); deepen *= 2) {
+                MergedPlan m;
+                m.mb = mb; m.wk = wk;
+                for (int i = 0; i < n; ++i) { m.waves[i] = wk; m.split[i] = 1; }
+                bool deep = false;
+                for (int cuts = 0; cuts < 6; ++cuts) {
+                    int longest = 0;
+                    m.us = merged_blocks_us(a, n, m, workspace, &longest);
+                    if (m.us < 0.0) break;
+                    const double line = m.us * (deep && mb <= 2 ? 1.03 : 1.0);    
+                    if (best.us < 0.0 || line < best_line) { best = m; best_line = line; }
+                    const int s = m.split[longest];
+                    const int64_t units = a[longest].K / chunk_k(a[longest].bits);
+                    if (m.waves[longest] < deepen && deepen * s <= units) {
+                        m.waves[longest] = deepen;
+                        deep = deepen == 2;
+                        continue;
                     }
+                    m.split[longest] = s == 4 ? 6 : s + 1;
+                    if (s >= 6 || (int64_t)m.split[longest] * m.waves[longest] > units) break;
                 }
-                if (partials > workspace) break;
-                const bool two = mb == 1 && wk <= 4;
-                const double slow = (mb == 1 ? 1.081 : 1.02) * (1.0 + 0.36 * std::min(1.0, (double)wgs / 256.0) * mb / 4.0) *
-                                    (two && on_xcd > 32 ? 1.543 : 1.0) * kWaves[wk];
-                for (int i = 0; i < n; ++i) each[i] *= slow;
-                const double serial = dealt_us(each, count, n, two ? 64 : 32);
-                m.us = 3.7 + std::pow(std::pow(serial, 2.374) + std::pow(stream, 2.374), 1.0 / 2.374) + reduce;
-                if (best.us < 0.0 || m.us < best.us) best = m;
-                if (m.split[longest] >= 4 || 2 * m.split[longest] * wk > a[longest].K / chunk_k(a[longest].bits)) break;
-                m.split[longest] *= 2;
             }
         }
     }
@@ -1526,7 +1590,7 @@ static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
         const double half = r == 8 ? 1.26 : 0.82, full = r == 8 ? 1.58 : 1.00;
         MergedPlan m;
         m.mb = r; m.wk = 0;
-        for (int i = 0; i < n; ++i) m.split[i] = 1;
+        for (int i = 0; i < n; ++i) { m.waves[i] = 0; m.split[i] = 1; }
         for (;;) {
             double each[rtn::kMaxBlockGroup], reduce = 0.0;
             int64_t count[rtn::kMaxBlockGroup], wgs = 0;
@@ -1547,7 +1611,7 @@ static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
             const double step = half + (full - half) * std::max(0.0, std::min(1.0, (double)wgs / 128.0 - 1.0));
             const int64_t steps = (int64_t)each[longest];
             for (int i = 0; i < n; ++i) each[i] = each[i] * step + 6.0;
-            m.us = 1.03 * (dealt_us(each, count, n, 32) + reduce);
+            m.us = 1.03 * (dealt_us(each, count, n, 32, 0.78) + reduce);
             if (best.us < 0.0 || m.us < best.us) best = m;
             if (m.split[longest] >= 8 || steps < 16) break;
             m.split[longest] *= 2;
@@ -1560,7 +1624,7 @@ static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
 static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace, bool tiles = false) {
     struct Key { int64_t v[4 * rtn::kMaxBlockGroup + 3]; };
     struct Entry { Key key; MergedPlan plan; bool used; };
-    constexpr size_t kEntries = 128;
+    constexpr size_t kEntries = 512;
     static std::mutex mutex;
     static Entry table[kEntries];
     Key k = {};
@@ -1589,11 +1653,11 @@ static hipError_t launch_merged(const LinearArgs* set, int count, const MergedPl
     LinearPlan plans[rtn::kMaxBlockGroup];
     for (int k = 0; k < count; ++k) {
         LinearPlan& p = plans[k];
-        p.path = 3; p.prefetch = 1; p.waves_n = 8; p.waves_k = m.wk; p.split_k = m.split[k];
+        p.path = 3; p.prefetch = 1; p.waves_n = 8; p.waves_k = m.waves[k]; p.split_k = m.split[k];
         p.m_rows16 = 2 * m.mb; p.n_tiles16 = 2;
         p.m_blocks = (int)((set[k].M + 32 * m.mb - 1) / (32 * m.mb));
     }
-    return rtn::launch_linear_blocks(set, plans, count, m.mb, m.wk, static_cast<hipStream_t>(stream));
+    return rtn::launch_linear_blocks(set, plans, count, m.mb, static_cast<hipStream_t>(stream));
 }
 
 static rtn_status one_module(const rtn_module& m, void* dev_workspace, size_t workspace_nbytes, void* stream) {
@@ -1611,14 +1675,15 @@ static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
 
 // The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
 // (precision, groups per unit; the tile kernel: precision) together where that is modelled 3 % ahead of their own plans' launches
-// (12 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
+// (20 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
 // the block kernel that line puts together 293 of 330 measured sets, of which 3 run more than 2 % slower for it, and leaves 14 apart
 // that would gain.  8B layer int4 group 128, apart -> together: 9 rows 36.5 -> 29.9 us, 32 rows 48.3 -> 31.2, 64 61.6 -> 38.0, 128
 // 85.1 -> 62.3, 256 125.5 -> 111.6; 70B layer 16 rows 98.8 -> 91.6, 32 110 -> 94, 128 231 -> 212; three modules of 4096 columns and
 // 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.  Tile kernel: 8B layer int4 at 1536 rows 625 -> 553, 2048 rows 773 -> 726;
 // 5120-wide layer at 2048 rows 996 -> 900; closer to level it measures within 1 % either way.
 constexpr int64_t kMaxMergedRows = 512;
-enum : char { kOpen, kAlone, kDone };
+// kTogether: open, but alone if the first set that it is in is not put together (the other sets of a call's modules are not tried).
+enum : char { kOpen, kTogether, kAlone, kDone };
 static int shared_launches(const LinearArgs* args, const double* own_us, char* state, int n, size_t workspace_nbytes, bool tiles,
                            SharedLaunch* out) {
     int launches = 0;
@@ -1629,16 +1694,18 @@ static int shared_launches(const LinearArgs* args, const double* own_us, char* s
         double apart = 0.0;
         int64_t rows = 0;
         l.count = 0;
-        for (int j = i; state[i] == kOpen && j < n && l.count < rtn::kMaxBlockGroup; ++j) {
-            if (state[j] != kOpen || !(tiles ? args[i].bits == args[j].bits : one_block_class(args[i], args[j]))) continue;
+        for (int j = i; state[i] < kAlone && j < n && l.count < rtn::kMaxBlockGroup; ++j) {
+            if (state[j] >= kAlone || !(tiles ? args[i].bits == args[j].bits : one_block_class(args[i], args[j]))) continue;
             apart += own_us[j];
             rows = std::max(rows, args[j].M);
             l.member[l.count] = j;
             set[l.count++] = args[j];
         }
         if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
-        const double line = !tiles && l.count == 2 && rows <= 16 ? 0.88 : 0.97;
+        const double line = !tiles && l.count == 2 && rows <= 16 ? 0.80 : 0.97;
         if (l.count < 2 || l.plan.us < 0.0 || l.plan.us > line * apart) {
+            for (int k = 0; k < l.count; ++k)
+                if (state[l.member[k]] == kTogether) state[l.member[k]] = kAlone;
             l.count = 1;
             l.member[0] = i;
         }
@@ -1778,17 +1845,32 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
     return RTN_OK;
 }
 
-// A grouped call's modules that would each be a launch of their own (more than 16 rows, or K split across workgroups), 5 to 512 rows:
-// together on the block kernel where that is modelled ahead, as in a layer (eight of 2048 x 7168 int8 at 16 rows 71.9 us
-// apart, 23.5 together).  The modules alone in their launch go on to the small-batch kernel's grouped launches.
+// Modelled time of a module's share of a grouped launch of the small-batch kernel: its bytes and a part of the start.  A workgroup
+// stages all its rows' columns: from 100 KiB one fits a compute unit, from 150 it goes through them in stages.  Medians of 66
+// measured launches of two to eight modules, 1024 to 8192 columns of 2048 to 7168, 1 to 16 rows.
+static double grouped_share_us(const LinearArgs& a, int n) {
+    const double bytes = (double)a.N * a.K * a.bits / 8.0 + (double)a.N * (a.K / a.g) * 2.0 + 2.0 * a.M * (a.K + a.N);
+    const int64_t slice = a.M * a.K * 2;
+    return (3.0 / n + bytes / (a.bits == 8 ? 6.4e6 : 5.8e6)) * (slice < 50 << 10 ? 1.0 : slice < 100 << 10 ? 1.08 : slice < 150 << 10 ? 1.30 : 2.2);
+}
+
+// A grouped call's modules of up to 512 rows: together on the block kernel where that is modelled ahead of the small-batch kernel's grouped
+// launches or of launches of their own, as in a layer.  Eight of 2048 x 7168, int4 group 128, 1 to 8 rows 17.4 us on the small-batch
+// kernel, 15.1 here, 2 to 16 rows 30.5 and 15.9; int8 31.0 and 22.4; small modules stay (8 of 1024 x 2048 5.6, 7.4 here).  The modules
+// alone in their launch go on to the small-batch kernel's grouped launches.
 static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out) {
     std::vector<double> own_us((size_t)n, 0.0);
     std::vector<char> state((size_t)n, kAlone);
+    int small = 0;
+    double bytes = 0.0;
+    auto grouped = [&](int i) { return plans[i].path == 1 && plans[i].split_k == 1 && plans[i].m_blocks == 1; };
+    for (int i = 0; i < n; ++i)
+        if (grouped(i)) { ++small; bytes += (double)args[i].N * args[i].K * args[i].bits / 8.0; }
     for (int i = 0; i < n; ++i) {
-        const LinearPlan& p = plans[i];
-        if (args[i].M <= 4 || args[i].M > kMaxMergedRows || (p.path == 1 && p.split_k == 1 && p.m_blocks == 1)) continue;
-        state[i] = kOpen;
-        own_us[i] = own_plan_us(args[i], p, workspace_nbytes);
+        if (args[i].M > kMaxMergedRows || (args[i].M <= 4 && !grouped(i))) continue;
+        if (grouped(i) && bytes < 24e6 && args[i].M * args[i].K * 2 < 100 << 10) continue;      // none of these was ahead
+        state[i] = grouped(i) ? kTogether : kOpen;
+        own_us[i] = grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
     }
     return shared_launches(args, own_us.data(), state.data(), n, workspace_nbytes, false, out);
 }

@@ -65,10 +65,17 @@ inline int wide_blocks(int XB, int ZB, bool sliced) { return 8 * (sliced ? (XB *
 bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_wide(const LinearArgs& a, const LinearPlan& p, hipStream_t st);
 // The block kernel of path 3 on several independent problems at once: one precision and number of groups per unit of four packed
-// tiles, workgroups of one shape (mb row blocks of 32 rows, wk of eight wavefronts along K); partial sums of K splits go to the
-// workspace one problem after another.
+// tiles, row tiles of up to mb blocks of 32 rows, waves_k of each problem's plan of eight wavefronts along K; partial sums of K
+// splits go to the workspace one problem after another.
 constexpr int kMaxBlockGroup = 8;
-hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, int wk, hipStream_t st);
+// Whether a shape (mb row blocks, wk wavefronts along K) has a kernel of its own: such a launch has it for all its problems.
+constexpr bool block_shape_alone(int bits, int mb, int wk) { return mb * wk > 8 || (bits == 8 && wk == 8); }
+// Row tiles of the block kernel: ceil(M / 32 mb) of them, the first tall_row_tiles(M, mb) of 32 mb rows, the others of 32 rows less.
+inline int tall_row_tiles(int64_t M, int mb) {
+    const int64_t tiles = (M + 32 * mb - 1) / (32 * mb), tall = (M + 31) / 32 - tiles * (mb - 1);
+    return (int)(mb == 1 ? tiles : tall > 0 ? tall : 0);
+}
+hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, hipStream_t st);
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p);
 hipError_t launch_linear_tile(const LinearArgs& a, const LinearPlan& p, hipStream_t st);

@@ -101,6 +101,12 @@ SHARED_LAYERS = [(3, 2, [(100, 272, 14336, 4, 128), (101, 288, 14336, 4, 128)]),
                  (4, 2, [(1040, 2064, 14336, 4, 128), (1041, 2080, 14336, 4, 0)]),
                  (4, 2, [(1100 + i, 4112 + 16 * i, 4096, 8, 128) for i in range(4)])]
 
+# Grouped calls of modules of up to 16 rows that share a launch of the block kernel instead of the small-batch kernel's, and the modules
+# that do: (members, [(M, N, K, bits, g)]).
+GROUPED_ON_BLOCKS = [([0, 1, 2, 3], [(16, 528, 7168, 4, 64), (9, 528, 7168, 4, 64), (12, 512, 7168, 4, 64), (16, 544, 7168, 4, 64)]),
+                     ([0, 2, 3], [(16, 528, 14336, 8, 0), (1, 512, 14336, 8, 0), (9, 544, 14336, 8, 0), (12, 528, 14336, 8, 0)]),
+                     ([], [(4, 1024, 2048, 4, 128)] * 4)]
+
 # (M, N, K, bits, g) with zero points that the block kernel runs, and its 32-row blocks and wavefronts along K.
 BLOCK_ZERO_POINTS = {(70, 1040, 4096, 4, 128): (1, 1), (33, 304, 1024, 4, 0): (1, 2), (20, 304, 2048, 4, 128): (1, 4), (250, 8208, 1024, 4, 32): (2, 1),
                      (128, 304, 1024, 4, 128): (2, 2), (250, 304, 2048, 4, 128): (2, 4), (161, 12304, 1024, 4, 32): (3, 2),

@@ -336,6 +336,49 @@ def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M} K={K}")
 
 
+@pytest.mark.parametrize("bits,g,K", [(4, 128, 4608), (4, 32, 1536), (4, 0, 4096), (8, 64, 1280), (8, 128, 2304), (8, 0, 2304)])
+@pytest.mark.parametrize("M", [1, 9, 16, 129, 200, 300])
+def test_linear_block_kernel_few_rows_and_row_tiles_of_two_heights(rtn, bits, g, K, M):
+    """The block kernel where a workgroup stages 16 rows (the other 16 of its MFMAs read a row of zeros), and where row tiles have two
+    heights (129 rows: 96 and 64, 200: 128 and 96, 300: 128, 96 and 96), ragged N, every number of wavefronts along K, with and
+    without a K split."""
+    N = 304
+    codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    ref = O.rtn_linear(_to_np(A_t), codes, scales, gg)
+    for rows in (2, 4, 8) if g % 128 == 0 else (2, 4):
+        for wk in (1, 2, 4, 8):
+            for split in (1, 3):
+                cfg = dict(path=3, prefetch=1, m_rows16=rows, n_tiles16=2, waves_n=8, waves_k=wk, split_k=split)
+                C = rtn.rtn_linear(A_t, qw, sc, bits, g, cfg=cfg,
+                                   workspace=torch.empty(max(256, M * N * 4 * split), dtype=torch.uint8, device=DEV))
+                torch.cuda.synchronize()
+                H.assert_linear_close(_to_np(C), ref, f"int{bits} g={g} M={M} K={K} cfg={cfg}")
+
+
+@pytest.mark.parametrize("mods", [m for _, m in H.GROUPED_ON_BLOCKS])
+def test_grouped_modules_of_few_rows_on_the_block_kernel(rtn, mods):
+    """Grouped calls whose modules of up to 16 rows share a launch of the block kernel (tests/test_host_plans.py says which), from a graph
+    too, each against the oracle."""
+    plan_mods, refs = [], []
+    for i, (M, N, K, bits, g) in enumerate(mods):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i)
+        A_t = synth.activation(M, K, seed=50 + i, device=DEV)
+        plan_mods.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.zeros((M, N), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A_t), codes, scales, gg))
+    plan = rtn.LayerPlan(plan_mods)
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        plan.run_grouped()
+    for run in (plan.run_grouped, graph.replay, graph.replay):
+        run()
+        torch.cuda.synchronize()
+        for i, (m, ref) in enumerate(zip(plan_mods, refs)):
+            H.assert_linear_close(_to_np(m["C"]), ref, f"module {i} {mods[i]}")
+            m["C"].zero_()
+
+
 @pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),
                                       (8, 128, 2304), (8, 0, 2304)])
 @pytest.mark.parametrize("M", [17, 33, 65, 130])

@@ -340,6 +340,26 @@ def test_which_modules_share_launches_of_the_block_and_tile_kernels(ask):
                 assert mb == 1 and (wk > 1 or fullest <= 32), (bits, g, M, launches)
 
 
+def test_row_tiles_of_two_heights_are_planned_as_they_are_launched(ask):
+    """8B layer: rows that leave a row tile of 32 rows less than the others cost less than the next full height (200 rows: 128 + 96), in
+    one launch, with partial sums within the workspace."""
+    for M in (150, 200, 300, 400):
+        status, launches = _issued(ask, [(M, N, K, 4, 128) for N, K in LAYER_8B], 16 * MIB)
+        assert status == 0 and len(launches) == 1 and launches[0][0] == 3
+        _, mb, wk, members = launches[0]
+        tiles = -(-M // (32 * mb))
+        assert mb == -(-M // (32 * tiles)) and sum(M * LAYER_8B[m][0] * 4 * s for m, s in members if s > 1) <= 16 * MIB
+        assert wk == 1
+
+
+def test_grouped_calls_of_few_rows_on_the_block_kernel(ask):
+    """Modules of up to 16 rows whose activations do not fit a compute unit beside one another (100 KiB and more) go to the block kernel;
+    small modules stay on the small-batch kernel's grouped launch."""
+    for members, mods in H.GROUPED_ON_BLOCKS:
+        _, launches = _issued(ask, mods, 16 * MIB, "issued_grouped")
+        assert [m for l in launches if l[0] == 3 for m, _ in l[3]] == members, (mods, launches)
+
+
 def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
     """The problems that the GPU tests run with zero points: row blocks and wavefronts along K of their plans."""
     for (p, want), (status, launches) in zip(H.BLOCK_ZERO_POINTS.items(), ask([f"asym {' '.join(map(str, p))} {64 * MIB}" for p in H.BLOCK_ZERO_POINTS])):
