@@ -184,11 +184,29 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
     return b;
 }
 
+// Rounds of workgroups (slots of them on the fullest XCD at once) in times of the tallest ones, of mb blocks; those of a block less take
+// `low` of that and start last: whole rounds and the mean.  As if all were tall 28672 x 4096 at 300 rows, 128 + 96 + 96, went out in
+// 64-row tiles: 88 us, 83 this way; 20000 x 5120 at 400 rows 108 and 93, 57344 x 8192 at 200 rows 215 and 193.
+void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, double low, double* whole, double* mean) {
+    const int64_t tiles = (M + 32 * mb - 1) / (32 * mb), tall = rtn::tall_row_tiles(M, mb);
+    if ((N + 256 / wk - 1) / (256 / wk) * tiles * s <= 256) {             // launched together (launch_blocks)
+        *mean = (double)block_on_xcd(N, tiles, wk, s) / slots;
+        *whole = std::ceil(*mean);
+        return;
+    }
+    const double t = tall > 0 ? (double)block_on_xcd(N, tall, wk, s) : 0.0, l = tiles > tall ? (double)block_on_xcd(N, tiles - tall, wk, s) : 0.0;
+    const double of_tall = std::ceil(t / slots);
+    *whole = of_tall + (std::ceil((t + l) / slots) - of_tall) * low;
+    *mean = (t + l * low) / slots;
+}
+
 double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
     const BlockTimes b = block_times(M, N, K, bits, g, rows16, wk, s);
     const double wg = b.wg_us * (1.0 + 0.36 * std::min(1.0, (double)b.wgs / 256.0) * b.mb / 4.0);
-    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), rounds = std::ceil((double)b.wgs / 8.0) / slots;
-    double serial = wg * std::max(1.0, 0.91 * std::ceil(rounds) + 0.09 * rounds);
+    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), low = b.mb == 1 ? 1.0 : block_wg_us(b.mb - 1, K, bits, g, wk, s) / b.wg_us;
+    double whole, mean;
+    block_rounds(M, N, b.mb, wk, s, slots, low, &whole, &mean);
+    double serial = wg * std::max(1.0, 0.91 * whole + 0.09 * mean);
     if (slots > 32.0 && b.wgs > 256) serial *= 1.78;
     return 2.93 + std::cbrt(serial * serial * serial + b.stream_us * b.stream_us * b.stream_us) +
            (s > 1 ? 1.12 + (double)M * N * s * 8.0 / 4.19e6 : 0.0);
@@ -215,8 +233,11 @@ double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int ro
     const double a_bytes = 32.0 * mb * share * unit * 2.0, w_bytes = (double)cols * share * unit * bits / 8.0;
     const double fetch = 0.543 * (a_bytes + w_bytes) / 1e5, both = run * std::sqrt(run) + fetch * std::sqrt(fetch);
     const double wg = 0.511 + std::cbrt(both * both) + (wk > 1 ? 0.484 * mb : 0.0);
-    const double rounds = on_xcd / (two ? 64.0 : 32.0);
-    const double serial = wg * std::max(1.0, 0.774 * std::ceil(rounds) + 0.226 * rounds) * (two && on_xcd > 32.0 ? 1.667 : 1.0);
+    double whole, mean;
+    const int w = wk == 1 ? 0 : wk == 2 ? 1 : wk == 4 ? 2 : 3;
+    const double low = mb == 1 ? 1.0 : kUnit[mb - 2][w] / kUnit[mb - 1][w];
+    block_rounds(M, N, mb, wk, s, two ? 64.0 : 32.0, low, &whole, &mean);
+    const double serial = wg * std::max(1.0, 0.774 * whole + 0.226 * mean) * (two && on_xcd > 32.0 ? 1.667 : 1.0);
     const double hbm = 1.195 * (weights + rows) / 6.83e6, fabric = 0.530 * (rows + weights / xcds) / 1e6;
     const double l2 = 0.812 * on_xcd * (a_bytes + 1.550 * w_bytes) / 2e6;
     auto to4 = [](double x) { return x * x * x * x; };

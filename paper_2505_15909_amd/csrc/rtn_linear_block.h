@@ -18,9 +18,10 @@
 // weights are in flight than the staged rows lead by.  Up to 16 rows only those are staged, which with several wavefronts along K doubles
 // the lead, and the MFMAs' other 16 rows read zeros (eight modules of 2048 x 7168 at one row 15.8 -> 14.7 us; with copies of the rows, which
 // draw more power, 8 % slower at 16 rows than 32 staged ones).
-// A launch consists of parts, a problem's row tiles of one height, longest workgroups first: 200 rows are 128 + 96, and the short
-// tiles fill the last round (8B layer int4 112 -> 100 us; inside one part, tall and short in turn, it stayed at 107).  Every part has its
-// own number of wavefronts along K.
+// A launch of more than a round consists of parts, a problem's row tiles of one height, longest workgroups first: 200 rows are 128 + 96, and
+// the short tiles fill the last round (8B layer int4 112 -> 100 us; inside one part, tall and short in turn, it stayed at 107).  Within
+// one round they stay together, so that those of one column read its weights at once (4096 x 14336 int8 at 140 rows 36 us, 43 apart).
+// Every problem has its own number of wavefronts along K.
 // What bounds it: at 128 rows on a full chip, power: with zeros for data the same launch takes 47 us instead of 66.  At 32 to 64 rows
 // the weight stream and the vector instructions (unpacking: 9 per 8 weights, for MB MFMAs of 32 cycles each) overlap only
 // partly.  On small matrices the 5-6 us of launch, first data and last store, which is what WK is for: K shared by
@@ -378,7 +379,6 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
     BlockPart part;
     if (!block_part(group, &part, &xb, &z, &sg)) return;
     const BlockProblem& p = group.p[part.info >> 20];
-    const bool low = (part.info >> 16 & 1) != 0;
     const int wk = (int)(p.groups >> 24);
     auto run = [&](auto height, int m0) {
         constexpr int H = decltype(height)::value;
@@ -401,12 +401,12 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
         }
     };
     if constexpr (MB > 1) {
-        if (low) {
-            run(std::integral_constant<int, MB - 1>{}, part.row0 + z * (32 * (MB - 1)));
+        if (z >= part.tall) {
+            run(std::integral_constant<int, MB - 1>{}, part.row0 + part.tall * 32 + z * (32 * (MB - 1)));
             return;
         }
     }
-    run(std::integral_constant<int, MB>{}, z * (32 * MB));
+    run(std::integral_constant<int, MB>{}, part.row0 + z * (32 * MB));
 }
 
 // The shapes whose stages do not fit the kernel above: every part of the launch has them.
@@ -420,14 +420,13 @@ __global__ __launch_bounds__(kBlockThreads, 2) void block_mfma_deep_kernel(const
     BlockPart part;
     if (!block_part(group, &part, &xb, &z, &sg)) return;
     const BlockProblem& p = group.p[part.info >> 20];
-    const bool low = (part.info >> 16 & 1) != 0;
     if constexpr (MB > 1) {
-        if (low) {
-            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP>(p, xb, part.row0 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
+        if (z >= part.tall) {
+            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP>(p, xb, part.row0 + part.tall * 32 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
             return;
         }
     }
-    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP>(p, xb, z * (32 * MB), sg, lds0, lds1, lds2, lds3);
+    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP>(p, xb, part.row0 + z * (32 * MB), sg, lds0, lds1, lds2, lds3);
 }
 
 }  // namespace

@@ -21,10 +21,10 @@ struct BlockProblem {
     uint32_t groups;       // units per group (1 where a unit holds several) | K splits << 16 | wavefronts along K << 24
     uint32_t upg_inv;      // floor(2^32 / units per group) + 1 (0 when that is 1)
 };
-// A problem's row tiles of one height: workgroups from first on, blocks of them per K split; the first row; row tiles | low << 16 | sliced << 17 |
-// problem << 20.  low: the tiles are of 32 rows less than the launch's tallest; sliced: their order over the XCDs (xcd_wide_tile).
+// Row tiles of a problem: workgroups from first on, blocks of them per K split; the first row; how many are as tall as the launch's tallest,
+// the ones after them have 32 rows less; row tiles | sliced << 17 | problem << 20.  sliced: their order over the XCDs (xcd_wide_tile).
 struct BlockPart {
-    int first, blocks, row0;
+    int first, blocks, row0, tall;
     uint32_t info;
 };
 constexpr int kMaxBlockParts = 2 * kMaxBlockGroup;

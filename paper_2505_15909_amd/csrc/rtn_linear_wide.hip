@@ -283,14 +283,22 @@ static int block_rows32(int64_t M, int64_t N, int m_rows16) {
 // for each, 8 / wk along N.  The longest workgroups start first: by units of K and by height.
 static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, const int* wk, hipStream_t st) {
     const int unit = args[0].bits == 4 ? 512 : 256;       // columns of four packed tiles
-    struct Part { int problem, row0, tiles, low; int64_t length; };
+    struct Part { int problem, row0, tiles, tall; int64_t length; };
     Part parts[kMaxBlockParts];
     int count = 0;
+    int64_t workgroups = 0;
+    for (int i = 0; i < n; ++i)
+        workgroups += (args[i].N + 256 / wk[i] - 1) / (256 / wk[i]) * ((args[i].M + 32 * mb - 1) / (32 * mb)) * plans[i].split_k;
+    const bool together = workgroups <= 256;              // at most a round
     for (int i = 0; i < n; ++i) {
         const int tiles = (int)((args[i].M + 32 * mb - 1) / (32 * mb)), tall = tall_row_tiles(args[i].M, mb);
         const int64_t units = (args[i].K / unit + plans[i].split_k * wk[i] - 1) / (plans[i].split_k * wk[i]);
-        if (tall > 0) parts[count++] = {i, 0, tall, 0, units * mb};
-        if (tall < tiles) parts[count++] = {i, tall * 32 * mb, tiles - tall, 1, units * (mb - 1)};
+        if (together) {
+            parts[count++] = {i, 0, tiles, tall, units * (tall > 0 ? mb : mb - 1)};
+            continue;
+        }
+        if (tall > 0) parts[count++] = {i, 0, tall, tall, units * mb};
+        if (tall < tiles) parts[count++] = {i, tall * 32 * mb, tiles - tall, 0, units * (mb - 1)};
     }
     std::stable_sort(parts, parts + count, [](const Part& x, const Part& y) { return x.length > y.length; });
     BlockGroup g = {};
@@ -321,7 +329,8 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
         part.first = (int)first;
         part.blocks = wide_blocks(XB, parts[i].tiles, sliced);
         part.row0 = parts[i].row0;
-        part.info = (uint32_t)parts[i].tiles | (uint32_t)parts[i].low << 16 | (sliced ? 1u << 17 : 0u) | (uint32_t)k << 20;   // (M <= 2^20: at most 2^15 tiles)
+        part.tall = parts[i].tall;
+        part.info = (uint32_t)parts[i].tiles | (sliced ? 1u << 17 : 0u) | (uint32_t)k << 20;   // (M <= 2^20: at most 2^15 tiles)
         first += (int64_t)part.blocks * plans[k].split_k;
     }
     if (first >= (int64_t)1 << 31) return hipErrorInvalidValue;
