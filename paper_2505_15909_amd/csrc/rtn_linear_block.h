@@ -20,7 +20,8 @@
 // draw more power, 8 % slower at 16 rows than 32 staged ones).
 // A launch of more than a round consists of parts, a problem's row tiles of one height, longest workgroups first: 200 rows are 128 + 96, and
 // the short tiles fill the last round (8B layer int4 112 -> 100 us; inside one part, tall and short in turn, it stayed at 107).  Within
-// one round they stay together, so that those of one column read its weights at once (4096 x 14336 int8 at 140 rows 36 us, 43 apart).
+// one round all are tall and the tiles of a column next to one another: in step they read its weights once (4096 x 14336 int8 at 140 rows
+// 33 us, with two heights 37, and 43 in two parts).
 // Every problem has its own number of wavefronts along K.
 // What bounds it: at 128 rows on a full chip, power: with zeros for data the same launch takes 47 us instead of 66.  At 32 to 64 rows
 // the weight stream and the vector instructions (unpacking: 9 per 8 weights, for MB MFMAs of 32 cycles each) overlap only

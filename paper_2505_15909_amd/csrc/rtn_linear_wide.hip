@@ -289,12 +289,12 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
     int64_t workgroups = 0;
     for (int i = 0; i < n; ++i)
         workgroups += (args[i].N + 256 / wk[i] - 1) / (256 / wk[i]) * ((args[i].M + 32 * mb - 1) / (32 * mb)) * plans[i].split_k;
-    const bool together = workgroups <= 256;              // at most a round
+    const bool together = workgroups <= 256;              // at most a round: of one height, which keeps those of a column in step on its weights
     for (int i = 0; i < n; ++i) {
         const int tiles = (int)((args[i].M + 32 * mb - 1) / (32 * mb)), tall = tall_row_tiles(args[i].M, mb);
         const int64_t units = (args[i].K / unit + plans[i].split_k * wk[i] - 1) / (plans[i].split_k * wk[i]);
         if (together) {
-            parts[count++] = {i, 0, tiles, tall, units * (tall > 0 ? mb : mb - 1)};
+            parts[count++] = {i, 0, tiles, tall > 0 ? tiles : 0, units * (tall > 0 ? mb : mb - 1)};
             continue;
         }
         if (tall > 0) parts[count++] = {i, 0, tall, tall, units * mb};
