@@ -609,8 +609,8 @@ def main() -> int:
                 "algorithmic_bytes_per_launch": round(per_layer, 1)}
 
     roofline = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                **kernel_roofline(False, "rtn::block_mfma_kernel<4,1,4,8,1,false> (fused int4 g128 dequantise-GEMM, the four modules of a layer "
-                                         "in one launch, M = 8 and 16; its reduce launch included)", "traffic_bytes_per_launch"),
+                **kernel_roofline(False, "rtn::block_mfma_kernel<4,1,4,false> (fused int4 g128 dequantise-GEMM, the four modules of a layer "
+                                         "in one launch, M = 8 and 16; the reduce launch of M = 16 included)", "traffic_bytes_per_launch"),
                 "merged_layers": kernel_roofline(True, "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
                                                  "merged_traffic_bytes_per_launch")}
 
