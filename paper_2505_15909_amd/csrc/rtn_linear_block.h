@@ -67,7 +67,8 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 // with one block): one kernel has all shapes that fit, and a launch may give every problem its own.  The others have a kernel of their
 // own: most wavefronts along K on two blocks and more, with two stages of 64 columns (four of 32: 4 % slower at 128 rows), and eight on 8-bit
 // weights, with four of 64 columns (of 32: 6144 x 4096 at 32 rows 11.1 us instead of 10.3; 4-bit weights the other way, 7.5 instead of 8.1).
-template <int BITS, int MB, int WN, int WK, bool HALF = false>
+// FIT: stages no larger than the shape needs, for a kernel that has no other shape.
+template <int BITS, int MB, int WN, int WK, bool HALF = false, bool FIT = false>
 struct BlockShape {
     static constexpr bool ALONE = !HALF && block_shape_alone(BITS, MB, WK);
     static constexpr int KA = WK == 1 || (WK == 2 && MB <= 2) || (HALF && WK == 4) ? kStepK : WK == 8 && !ALONE && !HALF ? 32 : 64;   // columns of an activation stage, per wavefront along K
@@ -76,7 +77,7 @@ struct BlockShape {
     static constexpr int D = BITS == 4 ? 4 : 2;     // k-steps of weights in registers
     static constexpr int SPU = BITS == 4 ? 4 : 2;                   // k-steps per unit
     static constexpr int UN = D > 2 * SPU ? D : 2 * SPU;            // k-steps per turn of the loop: every buffer index is a literal
-    static constexpr int STAGE = ALONE ? WK * 32 * MB * KA * 2 : MB == 1 ? 16384 : MB == 3 ? 24576 : 32768;
+    static constexpr int STAGE = ALONE || FIT ? WK * 32 * MB * KA * 2 : MB == 1 ? 16384 : MB == 3 ? 24576 : 32768;
     static_assert(UN % D == 0 && UN % (2 * SPU) == 0 && UN * R % S == 0 && WK * (HALF ? 16 : 32 * MB) * KA * 2 <= STAGE && S * STAGE <= 150 * 1024, "");
 };
 
@@ -86,7 +87,7 @@ constexpr int kZeroRow = 256;
 // of the stages.  HALF: at most 16 rows; the MFMAs' other 16 read a row of zeros.
 template <int BITS, int MB, int TALL, int NG, int WN, int WK, bool ZP, bool HALF = false>
 __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0, int sg, uint8_t* lds0, uint8_t* lds1, uint8_t* lds2, uint8_t* lds3) {
-    typedef BlockShape<BITS, TALL, WN, WK, HALF> Shape;
+    typedef BlockShape<BITS, TALL, WN, WK, HALF, ZP> Shape;
     constexpr int TPS = kStepK / Layout<BITS>::TK;        // packed tiles per k-step: 1 / 2
     constexpr int SPU = Shape::SPU, UN = Shape::UN;
     constexpr int SPG = 8 * SPU / NG;                     // 16-column slices per group, of those in a unit (8 in a k-step)
@@ -371,7 +372,7 @@ __device__ __forceinline__ bool block_part(const BlockGroup& group, BlockPart* p
 }
 
 // Row tiles of two heights, MB blocks and one less, as many of each as M takes: 200 rows are 128 + 96, not twice 128.
-template <int BITS, int MB, int NG, bool ZP>
+template <int BITS, int MB, int NG>
 __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_kernel(const BlockGroup group) {
     constexpr int STAGE = BlockShape<BITS, MB, 8, 1>::STAGE;
     constexpr int BYTES = STAGE + (MB == 1 ? kZeroRow : 0);
@@ -385,20 +386,18 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
         constexpr int H = decltype(height)::value;
         if constexpr (MB == 1) {
             if (p.M <= 16 && wk > 1) {
-                if (wk == 2) block_tile<BITS, 1, 1, NG, 4, 2, ZP, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-                else if (wk == 4) block_tile<BITS, 1, 1, NG, 2, 4, ZP, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-                else if constexpr (!ZP) block_tile<BITS, 1, 1, NG, 1, 8, ZP, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+                if (wk == 2) block_tile<BITS, 1, 1, NG, 4, 2, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+                else if (wk == 4) block_tile<BITS, 1, 1, NG, 2, 4, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+                else block_tile<BITS, 1, 1, NG, 1, 8, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
                 return;
             }
         }
-        if (wk == 1) block_tile<BITS, H, MB, NG, 8, 1, ZP>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-        else if (MB > 2 || wk == 2) block_tile<BITS, H, MB, NG, 4, 2, ZP>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+        if (wk == 1) block_tile<BITS, H, MB, NG, 8, 1, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+        else if (MB > 2 || wk == 2) block_tile<BITS, H, MB, NG, 4, 2, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
         if constexpr (MB <= 2) {
-            if (wk == 4) block_tile<BITS, H, MB, NG, 2, 4, ZP>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-            if constexpr (MB == 1 && !ZP) {
-                if constexpr (!block_shape_alone(BITS, 1, 8))
-                    if (wk == 8) block_tile<BITS, H, MB, NG, 1, 8, ZP>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-            }
+            if (wk == 4) block_tile<BITS, H, MB, NG, 2, 4, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+            if constexpr (MB == 1 && !block_shape_alone(BITS, 1, 8))
+                if (wk == 8) block_tile<BITS, H, MB, NG, 1, 8, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
         }
     };
     if constexpr (MB > 1) {
@@ -410,11 +409,14 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
     run(std::integral_constant<int, MB>{}, part.row0 + z * (32 * MB));
 }
 
-// The shapes whose stages do not fit the kernel above: every part of the launch has them.
+// One shape, which every part of the launch has: those whose stages do not fit the kernel above, and all with zero points.  A launch with
+// zero points is one problem, so there is nothing to share, and the common kernel cost it: with groups of 32 columns on 32-row tiles eight
+// registers went to scratch memory (6144 x 4096 at 24 rows 11.8 us, 11.3 here), and with stages of 32 KiB where 16 do, half of them lie
+// beyond the offset that an LDS read holds and every read takes an addition (4096 x 14336 group 64 at 256 rows 43.9 us, 43.1).
 template <int BITS, int MB, int NG, int WK, bool ZP>
-__global__ __launch_bounds__(kBlockThreads, 2) void block_mfma_deep_kernel(const BlockGroup group) {
-    typedef BlockShape<BITS, MB, 8 / WK, WK> Shape;
-    static_assert(Shape::ALONE, "");
+__global__ __launch_bounds__(kBlockThreads, MB == 1 && WK < 8 ? 4 : 2) void block_mfma_alone_kernel(const BlockGroup group) {
+    typedef BlockShape<BITS, MB, 8 / WK, WK, false, ZP> Shape;
+    static_assert(ZP || Shape::ALONE, "");
     constexpr int LAST = Shape::S > 2 ? Shape::STAGE : 16;
     __shared__ __align__(16) uint8_t lds0[Shape::STAGE], lds1[Shape::STAGE], lds2[LAST], lds3[LAST];
     int xb, z, sg;
@@ -436,20 +438,29 @@ template <int BITS, bool ZP>
 hipError_t launch_block(const BlockGroup& g, int ng, int mb, unsigned grid, hipStream_t st) {
     auto with_groups = [&](auto blocks, auto groups) {
         constexpr int MB = decltype(blocks)::value, NG = decltype(groups)::value, DEEP = MB <= 2 ? 8 : 4;
-        bool alone = block_shape_alone(BITS, mb, (int)(g.p[0].groups >> 24));
-        if (MB == 1 && alone) {                           // 16 rows and less are staged as such by the common kernel
-            alone = false;
-            for (int i = 0; i < g.n; ++i) alone = alone || g.p[g.part[i].info >> 20].M > 16;
-        }
-        if (!alone) {
-            hipLaunchKernelGGL((block_mfma_kernel<BITS, MB, NG, ZP>), dim3(grid), dim3(kBlockThreads), 0, st, g);
+        const int wk = (int)(g.p[0].groups >> 24);
+        auto alone_kernel = [&](auto waves) {
+            hipLaunchKernelGGL((block_mfma_alone_kernel<BITS, MB, NG, decltype(waves)::value, ZP>), dim3(grid), dim3(kBlockThreads), 0, st, g);
             return hipGetLastError();
-        }
-        if constexpr ((MB > 2 || !ZP) && block_shape_alone(BITS, MB, DEEP)) {
-            if ((int)(g.p[0].groups >> 24) == DEEP) {
-                hipLaunchKernelGGL((block_mfma_deep_kernel<BITS, MB, NG, DEEP, ZP>), dim3(grid), dim3(kBlockThreads), 0, st, g);
+        };
+        if constexpr (ZP) {                               // no shape with eight wavefronts along K
+            switch (wk) {
+                case 1: return alone_kernel(std::integral_constant<int, 1>{});
+                case 2: return alone_kernel(std::integral_constant<int, 2>{});
+                case 4: return alone_kernel(std::integral_constant<int, 4>{});
+            }
+        } else {
+            bool alone = block_shape_alone(BITS, mb, wk);
+            if (MB == 1 && alone) {                       // 16 rows and less are staged as such by the common kernel
+                alone = false;
+                for (int i = 0; i < g.n; ++i) alone = alone || g.p[g.part[i].info >> 20].M > 16;
+            }
+            if (!alone) {
+                hipLaunchKernelGGL((block_mfma_kernel<BITS, MB, NG>), dim3(grid), dim3(kBlockThreads), 0, st, g);
                 return hipGetLastError();
             }
+            if constexpr (block_shape_alone(BITS, MB, DEEP))
+                if (wk == DEEP) return alone_kernel(std::integral_constant<int, DEEP>{});
         }
         return hipErrorInvalidValue;
     };

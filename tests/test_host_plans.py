@@ -2,6 +2,7 @@
 code and prints, for each problem it reads, the launches the call would issue.  Nothing is launched."""
 import os
 import re
+import shutil
 import subprocess
 
 import pytest
@@ -373,3 +374,24 @@ def test_planning_a_shared_launch_allocates_nothing(ask):
     layers = [[(M, N, K, 4, 128) for N, K in LAYER_8B] for M in (9, 100, 300, 1536)] + [m for _, _, m in H.SHARED_LAYERS if len(m) <= 8 and m[0][4] == m[1][4]]
     for mods, out in zip(layers, ask([f"heap {len(m)} " + " ".join(" ".join(map(str, x)) for x in m) for m in layers], raw=True)):
         assert out.split() == ["0", "1"], (mods, out)
+
+
+def test_no_kernel_of_the_linear_path_uses_scratch_memory(tmp_path):
+    """Registers that do not fit go to scratch memory, an access to it per use: none of the wide, block and tile kernels has any, by the
+    metadata of the built library's code objects."""
+    tools = "/opt/rocm/llvm/bin"
+    lib = os.path.join(PKG, "librtn_gfx950.so")
+    if not os.path.exists(os.path.join(tools, "llvm-objdump")) or not os.path.exists(lib):
+        pytest.skip("no llvm-objdump or no built library")
+    copy = str(tmp_path / "lib.so")
+    shutil.copy(lib, copy)
+    subprocess.run([os.path.join(tools, "llvm-objdump"), "--offloading", copy], check=True, capture_output=True, timeout=120)
+    sizes = {}
+    for name in os.listdir(tmp_path):
+        if "gfx950" not in name:
+            continue
+        notes = subprocess.run([os.path.join(tools, "llvm-readelf"), "--notes", str(tmp_path / name)], check=True, capture_output=True,
+                               text=True, timeout=120).stdout
+        sizes.update(re.findall(r"\.name:\s+(\S+)\n\s+\.private_segment_fixed_size:\s+(\d+)", notes))
+    kernels = {k: int(v) for k, v in sizes.items() if re.search("wide_mfma|block_mfma|tile_gemm", k)}
+    assert len(kernels) > 50 and not {k: v for k, v in kernels.items() if v}
