@@ -29,7 +29,7 @@ struct BlockPart {
 };
 constexpr int kMaxBlockParts = 2 * kMaxBlockGroup;
 struct BlockGroup {
-    int n;                 // parts
+    int n;                 // parts; the first one is of the first problem
     BlockPart part[kMaxBlockParts];
     BlockProblem p[kMaxBlockGroup];
 };

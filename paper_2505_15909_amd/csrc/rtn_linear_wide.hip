@@ -303,9 +303,14 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
     std::stable_sort(parts, parts + count, [](const Part& x, const Part& y) { return x.length > y.length; });
     BlockGroup g = {};
     g.n = count;
-    for (int i = 0; i < n; ++i) {
+    int slot[kMaxBlockGroup], filled = 0;                 // problems in the order of their first parts (block_part)
+    std::fill(slot, slot + n, -1);
+    for (int part = 0; part < count; ++part) {
+        const int i = parts[part].problem;
+        if (slot[i] >= 0) continue;
+        slot[i] = filled;
         const LinearArgs& a = args[i];
-        BlockProblem& bp = g.p[i];
+        BlockProblem& bp = g.p[filled++];
         bp.A = static_cast<const half_t*>(a.A);
         bp.qw = static_cast<const uint8_t*>(a.qweight);
         bp.scales = static_cast<const half_t*>(a.scales);
@@ -323,14 +328,14 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
     }
     int64_t first = 0;
     for (int i = 0; i < count; ++i) {
-        const int k = parts[i].problem, XB = g.p[k].XB;
+        const int k = parts[i].problem, XB = g.p[slot[k]].XB;
         const bool sliced = xcd_slices_save_a_round(XB, parts[i].tiles, plans[k].split_k);
         BlockPart& part = g.part[i];
         part.first = (int)first;
         part.blocks = wide_blocks(XB, parts[i].tiles, sliced);
         part.row0 = parts[i].row0;
         part.tall = parts[i].tall;
-        part.info = (uint32_t)parts[i].tiles | (sliced ? 1u << 17 : 0u) | (uint32_t)k << 20;   // (M <= 2^20: at most 2^15 tiles)
+        part.info = (uint32_t)parts[i].tiles | (sliced ? 1u << 17 : 0u) | (uint32_t)slot[k] << 20;   // (M <= 2^20: at most 2^15 tiles)
         first += (int64_t)part.blocks * plans[k].split_k;
     }
     if (first >= (int64_t)1 << 31) return hipErrorInvalidValue;
