@@ -197,15 +197,15 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
         for (int b = 0; b < MB; ++b) aop[s % (PD + 1)][b] = *reinterpret_cast<const half8_t*>(stage(st) + o + b * (32 * KA * 2));
     };
 
-    // 8-bit weights, of which two steps are in registers, are requested before those of the next step are unpacked, which has to wait for
-    // them (37504 x 5632 group 128 at 32 rows 51.8 us, 49.3 this way).  That puts them before the activations requested in that slice, which
-    // then wait for them: with more row blocks, wavefronts along K, or 4-bit weights, four steps of them, it is 1-4 % slower.
-    constexpr bool EARLY = BITS == 8 && TALL == 1 && WK == 1;
+    // 8-bit weights, of which two steps are in registers, are requested before the next step's first ones are unpacked, which has to wait for
+    // them: 67 rows of 8128 x 3072 group 128 14.2 -> 13.7 us, 9216 x 5632 at 91 rows 26.0 -> 25.5.  (4-bit weights, four steps of
+    // them, do not mind.)
+    constexpr bool LATE = BITS == 8;
     // Weight loads requested since the stage after stage rr of a step (those of older steps have been used).  Scales are not
     // counted: a unit's wait is for a load more than it need be.
     auto weights_since = [](int rr) {
         int n = 0;
-        const int from = rr + (EARLY ? 2 : 1) - S;
+        const int from = rr + 1 - S;
         for (int j = from > rr - D * R ? from : rr - D * R; j < rr; ++j) n += (j + 64 * R) % R == R - 1 ? 2 * TPS : 0;
         return n;
     };
@@ -229,12 +229,7 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
             }
             a_read((v * R + (s + PD) / SPS) % S, (s + PD) % 8);
             const half8_t b_now = bw;
-            if (EARLY && s == 7 && !tail) {
-                __builtin_amdgcn_sched_barrier(0);
-                w_load(v % D, t + D);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            bw = s == 7 ? operand((v + 1) % UN, 0) : operand(v, s + 1);
+            if (!LATE || s < 7) bw = s == 7 ? operand((v + 1) % UN, 0) : operand(v, s + 1);
 #pragma unroll
             for (int b = 0; b < MB; ++b) {
                 float16_t c_in;
@@ -270,10 +265,14 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
             }
             if (s == 7 && !tail) {
                 __builtin_amdgcn_sched_barrier(0);
-                if (!EARLY) w_load(v % D, t + D);
+                w_load(v % D, t + D);
                 if (v % SPU == SPU - 1) s_load(v / SPU % 2, t / SPU + 2);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (LATE && s == 7) {
+                bw = operand((v + 1) % UN, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         if (NG == 1 && unit_ends) left = upg;
     };
@@ -285,11 +284,9 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
 #pragma unroll
     for (int q = -AHEAD; q < 0; ++q) {
         __builtin_amdgcn_sched_barrier(0);
-        if (!EARLY && q >= -S) a_load(q + S, q + S);
+        if (q >= -S) a_load(q + S, q + S);
         __builtin_amdgcn_sched_barrier(0);
         if (q >= -D * R && (q + AHEAD * R) % R == R - 1) w_load((q + D * R) / R, (q + D * R) / R);
-        __builtin_amdgcn_sched_barrier(0);
-        if (EARLY && q >= -S) a_load(q + S, q + S);
         __builtin_amdgcn_sched_barrier(0);
     }
     wait_stage((S - 1) * NA + weights_since(0));
