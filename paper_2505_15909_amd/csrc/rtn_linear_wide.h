@@ -69,10 +69,7 @@ __device__ __forceinline__ half_t row_scale(const RowScales<NG>& s, int i) {
     if constexpr (NG == 1) return __builtin_bit_cast(half_t, s.v);
     else {
         uint32_t word;                                    // by value: bit_cast of a vector-element lvalue reads element 0
-        if constexpr (NG == 2) {
-            word = s.v;
-            asm volatile("" : "+v"(word));                // taken apart where it is used, not where it is loaded, which would wait for it there
-        }
+        if constexpr (NG == 2) word = s.v;
         else if constexpr (NG == 4) word = s.v[i >> 1];
         else word = s.v[i >> 3][(i >> 1) & 3];
         return __builtin_bit_cast(half2_t, word)[i & 1];
