@@ -85,9 +85,9 @@ constexpr int kZeroRow = 256;
 
 // One row tile of MB blocks: column tile xb, rows from m0, part sg of K.  TALL: blocks of the launch's tallest tiles, which give the shape
 // of the stages.  HALF: at most 16 rows; the MFMAs' other 16 read a row of zeros.
-template <int BITS, int MB, int TALL, int NG, int WN, int WK, bool ZP, bool HALF = false>
+template <int BITS, int MB, int TALL, int NG, int WN, int WK, bool ZP, bool HALF = false, bool FIT = false>
 __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0, int sg, uint8_t* lds0, uint8_t* lds1, uint8_t* lds2, uint8_t* lds3) {
-    typedef BlockShape<BITS, TALL, WN, WK, HALF, ZP> Shape;
+    typedef BlockShape<BITS, TALL, WN, WK, HALF, FIT> Shape;
     constexpr int TPS = kStepK / Layout<BITS>::TK;        // packed tiles per k-step: 1 / 2
     constexpr int SPU = Shape::SPU, UN = Shape::UN;
     constexpr int SPG = 8 * SPU / NG;                     // 16-column slices per group, of those in a unit (8 in a k-step)
@@ -441,14 +441,16 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
     run(std::integral_constant<int, MB>{}, part.row0 + z * (32 * MB));
 }
 
-// One shape, which every part of the launch has: those whose stages do not fit the kernel above, and all with zero points.  A launch with
+// One shape, which every part of the launch has: those whose stages do not fit the kernel above, 64-row tiles without wavefronts along K,
+// and all with zero points.  A launch with
 // zero points is one problem, so there is nothing to share, and the common kernel cost it: with groups of 32 columns on 32-row tiles eight
 // registers went to scratch memory (6144 x 4096 at 24 rows 11.8 us, 11.3 here), and with stages of 32 KiB where 16 do, half of them lie
-// beyond the offset that an LDS read holds and every read takes an addition (4096 x 14336 group 64 at 256 rows 43.9 us, 43.1).
+// beyond the offset that an LDS read holds and every read takes an addition (4096 x 14336 group 64 at 256 rows 43.9 us, 43.1; without
+// zero points 28672 x 4096 group 128 at 117 rows 38.1 and 37.3, group 64 at 256 rows 73.9 and 71.8).
 template <int BITS, int MB, int NG, int WK, bool ZP>
 __global__ __launch_bounds__(kBlockThreads, MB == 1 && WK < 8 ? 4 : 2) void block_mfma_alone_kernel(const BlockGroup group) {
-    typedef BlockShape<BITS, MB, 8 / WK, WK, false, ZP> Shape;
-    static_assert(ZP || Shape::ALONE, "");
+    typedef BlockShape<BITS, MB, 8 / WK, WK, false, true> Shape;
+    static_assert(ZP || Shape::ALONE || (MB == 2 && WK == 1), "");
     constexpr int LAST = Shape::S > 2 ? Shape::STAGE : 16;
     __shared__ __align__(16) uint8_t lds0[Shape::STAGE], lds1[Shape::STAGE], lds2[LAST], lds3[LAST];
     int xb, z, sg;
@@ -457,11 +459,11 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 && WK < 8 ? 4 : 2) void bloc
     if (!block_part(group, &part, &p, &xb, &z, &sg)) return;
     if constexpr (MB > 1) {
         if (z >= part.tall) {
-            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP>(p, xb, part.row0 + part.tall * 32 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
+            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP, false, true>(p, xb, part.row0 + part.tall * 32 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
             return;
         }
     }
-    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP>(p, xb, part.row0 + z * (32 * MB), sg, lds0, lds1, lds2, lds3);
+    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP, false, true>(p, xb, part.row0 + z * (32 * MB), sg, lds0, lds1, lds2, lds3);
 }
 
 }  // namespace
@@ -482,6 +484,11 @@ hipError_t launch_block(const BlockGroup& g, int ng, int mb, unsigned grid, hipS
                 case 4: return alone_kernel(std::integral_constant<int, 4>{});
             }
         } else {
+            if constexpr (MB == 2) {
+                bool one = true;
+                for (int i = 0; i < g.n; ++i) one = one && g.p[g.part[i].info >> 20].groups >> 24 == 1;
+                if (one) return alone_kernel(std::integral_constant<int, 1>{});
+            }
             bool alone = block_shape_alone(BITS, mb, wk);
             if (MB == 1 && alone) {                       // 16 rows and less are staged as such by the common kernel
                 alone = false;
