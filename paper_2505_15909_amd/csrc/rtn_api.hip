@@ -154,7 +154,6 @@ void wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, LinearPlan*
 struct BlockTimes {
     int mb;             // row blocks of 32 rows
     int64_t wgs;        // workgroups
-    int64_t on_xcd;     // those of the fullest XCD: each K split deals its column tiles anew
     double wg_us;       // one workgroup on an idle chip
     double stream_us;   // its weights and activations at the rates above
 };
@@ -166,19 +165,12 @@ double block_wg_us(int mb, int64_t K, int bits, int64_t g, int wk, int s) {
     return 1.33 + per * (kUnit[mb - 1] * (bits == 8 ? 0.675 : 1.0) + kGroup[mb - 1] * groups) + (wk > 1 ? 0.73 * mb : 0.0);
 }
 
-// Workgroups of ZB row tiles on the fullest XCD.
-int64_t block_on_xcd(int64_t N, int64_t ZB, int wk, int s) {
-    const int64_t XB = (N + 256 / wk - 1) / (256 / wk);
-    return (rtn::xcd_slices_save_a_round(XB, ZB, s) ? (XB * ZB + 7) / 8 : (XB + 7) / 8 * ZB) * s;
-}
-
 BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
     const int64_t cols = 256 / wk;
     const int64_t ZB = (M + 16 * rows16 - 1) / (16 * rows16), XB = (N + cols - 1) / cols;
     BlockTimes b;
     b.mb = (int)((M + 32 * ZB - 1) / (32 * ZB));
     b.wgs = XB * ZB * s;
-    b.on_xcd = block_on_xcd(N, ZB, wk, s);
     b.wg_us = block_wg_us(b.mb, K, bits, g, wk, s);
     b.stream_us = (double)N * K * bits / 8.0 / 6.83e6 + (double)XB * ZB * 32 * b.mb * K * 2.0 / 1.71e7;
     return b;
@@ -188,13 +180,9 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
 // `low` of that and start last: whole rounds and the mean.  As if all were tall 28672 x 4096 at 300 rows, 128 + 96 + 96, went out in
 // 64-row tiles: 88 us, 83 this way; 20000 x 5120 at 400 rows 108 and 93, 57344 x 8192 at 200 rows 215 and 193.
 void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, double low, double* whole, double* mean) {
-    const int64_t tiles = (M + 32 * mb - 1) / (32 * mb), tall = rtn::tall_row_tiles(M, mb);
-    if ((N + 256 / wk - 1) / (256 / wk) * tiles * s <= 256) {             // launched together (launch_blocks)
-        *mean = (double)block_on_xcd(N, tiles, wk, s) / slots;
-        *whole = std::ceil(*mean);
-        return;
-    }
-    const double t = tall > 0 ? (double)block_on_xcd(N, tall, wk, s) : 0.0, l = tiles > tall ? (double)block_on_xcd(N, tiles - tall, wk, s) : 0.0;
+    const rtn::BlockTiles tiles = rtn::block_tiles(M, N, mb, wk, s);
+    const rtn::BlockParts p = rtn::block_parts(tiles, mb, tiles.workgroups() <= 256);
+    const double t = (double)p.part[0].on_xcd, l = (double)p.part[1].on_xcd;      // (none in a part that is not there)
     const double of_tall = std::ceil(t / slots);
     *whole = of_tall + (std::ceil((t + l) / slots) - of_tall) * low;
     *mean = (t + l * low) / slots;
@@ -1521,25 +1509,29 @@ static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, 
     int64_t count[2 * rtn::kMaxBlockGroup], wgs = 0, on_xcd = 0;
     size_t partials = 0;
     int parts = 0;
+    rtn::BlockTiles tiles[rtn::kMaxBlockGroup];
     for (int i = 0; i < n; ++i) {
-        const int s = m.split[i], wk = m.waves[i], tiles = (int)((a[i].M + 32 * m.mb - 1) / (32 * m.mb)), tall = rtn::tall_row_tiles(a[i].M, m.mb);
-        const int64_t unit = chunk_k(a[i].bits), cols = 256 / wk, XB = (a[i].N + cols - 1) / cols;
+        tiles[i] = rtn::block_tiles(a[i].M, a[i].N, m.mb, m.waves[i], m.split[i]);
+        wgs += tiles[i].workgroups();
+    }
+    for (int i = 0; i < n; ++i) {
+        const int s = m.split[i], wk = m.waves[i];
+        const int64_t unit = chunk_k(a[i].bits);
         const double per = (double)(((a[i].K / unit + s - 1) / s + wk - 1) / wk), groups = a[i].g >= unit ? 1.0 : (double)(unit / a[i].g);
         const double waves = wk == 1 ? 1.0 : c.waves[m.mb - 1][wk == 2 ? 0 : wk == 4 ? 1 : 2];
-        for (int h = 0; h < 2; ++h) {                       // the row tiles of 32 mb rows, those of 32 rows less
-            const int tiles_h = h == 0 ? tall : tiles - tall, mb = m.mb - h;
-            if (tiles_h == 0) continue;
+        const rtn::BlockParts p = rtn::block_parts(tiles[i], m.mb, false);
+        for (int h = 0; h < p.n; ++h) {                     // the row tiles of 32 mb rows, those of 32 rows less
+            const int mb = p.part[h].tall > 0 ? m.mb : m.mb - 1;
             const double rows = (double)wk * std::min((double)a[i].M, 32.0 * mb) / 32.0;
             each[parts] = c.start + per * (c.unit[mb - 1] * (a[i].bits == 8 ? c.int8 : 1.0) * waves + c.group[mb - 1] * groups +
                                            c.rows * rows * (a[i].bits == 8 ? 0.5 : 1.0)) + (wk > 1 ? c.sum * mb : 0.0);
-            count[parts] = block_on_xcd(a[i].N, tiles_h, wk, s);
+            count[parts] = p.part[h].on_xcd;
             on_xcd += count[parts];
             if (each[parts] > length) { length = each[parts]; *longest = i; }
             ++parts;
         }
-        wgs += XB * tiles * s;
         stream += c.stream * ((double)a[i].N * a[i].K * a[i].bits / 8.0 / 6.83e6 +
-                              (double)XB * std::min<int64_t>((int64_t)tiles * 32 * m.mb, (a[i].M + 31) / 32 * 32) * a[i].K * 2.0 / 1.71e7);
+                              (double)tiles[i].columns * std::min<int64_t>((int64_t)tiles[i].rows * 32 * m.mb, (a[i].M + 31) / 32 * 32) * a[i].K * 2.0 / 1.71e7);
         if (s > 1) {
             reduce += c.reduce + (double)a[i].M * a[i].N * s * 8.0 / c.reduce_bw;
             partials += (((size_t)a[i].M * a[i].N * sizeof(float) * s) + 255) & ~(size_t)255;

@@ -75,6 +75,43 @@ inline int tall_row_tiles(int64_t M, int mb) {
     const int64_t tiles = (M + 32 * mb - 1) / (32 * mb), tall = (M + 31) / 32 - tiles * (mb - 1);
     return (int)(mb == 1 ? tiles : tall > 0 ? tall : 0);
 }
+// The workgroups of a problem in a launch of the block kernel: column tiles (256 / wavefronts along K columns), row tiles, K splits.
+struct BlockTiles {
+    int64_t columns;
+    int rows, tall, split;
+    int64_t workgroups() const { return columns * rows * split; }
+};
+inline BlockTiles block_tiles(int64_t M, int64_t N, int mb, int wk, int split) {
+    return {(N + 256 / wk - 1) / (256 / wk), (int)((M + 32 * mb - 1) / (32 * mb)), tall_row_tiles(M, mb), split};
+}
+// Its parts: a launch of at most a round of workgroups (256, of all its problems) has tiles of one height, which keeps those of a column in
+// step on its weights; a larger one has the tall tiles and the low ones apart.  sliced: the order over the XCDs, as above, one
+// for both parts -- each by itself may save no round where both together do (3232 x 3584 int4 group 64 at 605 rows 38 us, 30
+// this way; 25856 x 4608 int8 at 278 rows 110 and 92).
+struct BlockParts {
+    int n;
+    bool sliced;
+    struct { int row0, rows, tall; int64_t on_xcd; } part[2];      // first row, row tiles, tall ones of them; workgroups on the fullest XCD
+};
+inline BlockParts block_parts(const BlockTiles& t, int mb, bool one_round) {
+    BlockParts p = {};
+    if (one_round || t.tall == 0 || t.tall == t.rows) {
+        p.n = 1;
+        p.part[0] = {0, t.rows, t.tall > 0 ? t.rows : 0, 0};
+    } else {
+        p.n = 2;
+        p.part[0] = {0, t.tall, t.tall, 0};
+        p.part[1] = {t.tall * 32 * mb, t.rows - t.tall, 0, 0};
+    }
+    int64_t dealt[2] = {}, sliced[2] = {};
+    for (int i = 0; i < p.n; ++i) {
+        dealt[i] = (t.columns + 7) / 8 * p.part[i].rows * t.split;
+        sliced[i] = (t.columns * p.part[i].rows + 7) / 8 * t.split;
+    }
+    p.sliced = (sliced[0] + sliced[1] + 31) / 32 < (dealt[0] + dealt[1] + 31) / 32;
+    for (int i = 0; i < p.n; ++i) p.part[i].on_xcd = p.sliced ? sliced[i] : dealt[i];
+    return p;
+}
 hipError_t launch_linear_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, hipStream_t st);
 // Path 4 (tile kernel, weights dequantised into LDS): plan check (group size a multiple of 128) and launch.
 bool tile_plan_valid(const LinearArgs& a, const LinearPlan& p);

@@ -283,22 +283,21 @@ static int block_rows32(int64_t M, int64_t N, int m_rows16) {
 // for each, 8 / wk along N.  The longest workgroups start first: by units of K and by height.
 static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans, int n, int mb, const int* wk, hipStream_t st) {
     const int unit = args[0].bits == 4 ? 512 : 256;       // columns of four packed tiles
-    struct Part { int problem, row0, tiles, tall; int64_t length; };
+    struct Part { int problem, row0, rows, tall, blocks; bool sliced; int64_t length; };
     Part parts[kMaxBlockParts];
+    BlockTiles tiles[kMaxBlockGroup];
     int count = 0;
     int64_t workgroups = 0;
-    for (int i = 0; i < n; ++i)
-        workgroups += (args[i].N + 256 / wk[i] - 1) / (256 / wk[i]) * ((args[i].M + 32 * mb - 1) / (32 * mb)) * plans[i].split_k;
-    const bool together = workgroups <= 256;              // at most a round: of one height, which keeps those of a column in step on its weights
     for (int i = 0; i < n; ++i) {
-        const int tiles = (int)((args[i].M + 32 * mb - 1) / (32 * mb)), tall = tall_row_tiles(args[i].M, mb);
+        tiles[i] = block_tiles(args[i].M, args[i].N, mb, wk[i], plans[i].split_k);
+        workgroups += tiles[i].workgroups();
+    }
+    for (int i = 0; i < n; ++i) {
+        const BlockParts p = block_parts(tiles[i], mb, workgroups <= 256);
         const int64_t units = (args[i].K / unit + plans[i].split_k * wk[i] - 1) / (plans[i].split_k * wk[i]);
-        if (together) {
-            parts[count++] = {i, 0, tiles, tall > 0 ? tiles : 0, units * (tall > 0 ? mb : mb - 1)};
-            continue;
-        }
-        if (tall > 0) parts[count++] = {i, 0, tall, tall, units * mb};
-        if (tall < tiles) parts[count++] = {i, tall * 32 * mb, tiles - tall, 0, units * (mb - 1)};
+        for (int k = 0; k < p.n; ++k)
+            parts[count++] = {i, p.part[k].row0, p.part[k].rows, p.part[k].tall, wide_blocks((int)tiles[i].columns, p.part[k].rows, p.sliced),
+                              p.sliced, units * (p.part[k].tall > 0 ? mb : mb - 1)};
     }
     std::stable_sort(parts, parts + count, [](const Part& x, const Part& y) { return x.length > y.length; });
     BlockGroup g = {};
@@ -319,8 +318,7 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
         bp.ws = a.workspace;
         bp.M = (int)a.M; bp.N = (int)a.N; bp.K = (int)a.K;
         bp.G = (int)(a.K / a.g);
-        const int cols = 256 / wk[i];
-        bp.XB = (int)((a.N + cols - 1) / cols);
+        bp.XB = (int)tiles[i].columns;
         const uint32_t units = (uint32_t)(a.K / unit), split = (uint32_t)plans[i].split_k, upg = a.g >= unit ? (uint32_t)(a.g / unit) : 1u;
         bp.u_share = units / split | (units % split) << 16;      // (K < 2^23: both under 2^15)
         bp.groups = upg | split << 16 | (uint32_t)wk[i] << 24;
@@ -328,15 +326,13 @@ static hipError_t launch_blocks(const LinearArgs* args, const LinearPlan* plans,
     }
     int64_t first = 0;
     for (int i = 0; i < count; ++i) {
-        const int k = parts[i].problem, XB = g.p[slot[k]].XB;
-        const bool sliced = xcd_slices_save_a_round(XB, parts[i].tiles, plans[k].split_k);
         BlockPart& part = g.part[i];
         part.first = (int)first;
-        part.blocks = wide_blocks(XB, parts[i].tiles, sliced);
+        part.blocks = parts[i].blocks;
         part.row0 = parts[i].row0;
         part.tall = parts[i].tall;
-        part.info = (uint32_t)parts[i].tiles | (sliced ? 1u << 17 : 0u) | (uint32_t)slot[k] << 20;   // (M <= 2^20: at most 2^15 tiles)
-        first += (int64_t)part.blocks * plans[k].split_k;
+        part.info = (uint32_t)parts[i].rows | (parts[i].sliced ? 1u << 17 : 0u) | (uint32_t)slot[parts[i].problem] << 20;   // (M <= 2^20: at most 2^15 tiles)
+        first += (int64_t)part.blocks * plans[parts[i].problem].split_k;
     }
     if (first >= (int64_t)1 << 31) return hipErrorInvalidValue;
     const int ng = args[0].g >= unit ? 1 : (int)(unit / args[0].g);

@@ -69,6 +69,31 @@ int main() {
                 if (rtn::xcd_wide_tile(b, XB, ZB, sliced, &xb, &zb)) printf("%d %d %d ", xb, zb, b % rtn::kXcds);
             }
             printf("]");
+        } else if (!strcmp(what, "parts")) {                   // mb n, then M N wk split each -> 1 if one round, then a launch's [problem row0 rows tall on_xcd]
+            int mb, n;                                         // and of each part [columns, then xb zb xcd of its workgroups]
+            if (scanf("%d %d", &mb, &n) != 2 || n < 1 || n > rtn::kMaxBlockGroup) return 1;
+            rtn::BlockTiles t[rtn::kMaxBlockGroup];
+            int64_t workgroups = 0;
+            for (int i = 0; i < n; ++i) {
+                long M, N;
+                int wk, split;
+                if (scanf("%ld %ld %d %d", &M, &N, &wk, &split) != 4) return 1;
+                t[i] = rtn::block_tiles(M, N, mb, wk, split);
+                workgroups += t[i].workgroups();
+            }
+            printf("%d", workgroups <= 256 ? 1 : 0);
+            for (int i = 0; i < n; ++i) {
+                const rtn::BlockParts p = rtn::block_parts(t[i], mb, workgroups <= 256);
+                for (int k = 0; k < p.n; ++k) {
+                    printf(" [%d %d %d %d %ld] [%ld", i, p.part[k].row0, p.part[k].rows, p.part[k].tall, (long)p.part[k].on_xcd, (long)t[i].columns);
+                    const int blocks = rtn::wide_blocks((int)t[i].columns, p.part[k].rows, p.sliced);
+                    for (int b = 0; b < blocks; ++b) {
+                        int xb, zb;
+                        if (rtn::xcd_wide_tile(b, (int)t[i].columns, p.part[k].rows, p.sliced, &xb, &zb)) printf(" %d %d %d", xb, zb, b % rtn::kXcds);
+                    }
+                    printf("]");
+                }
+            }
         } else if (!strcmp(what, "heap")) {                    // n, then M N K bits g each -> heap allocations of planning a shared launch
             int n;
             LinearArgs a[rtn::kMaxBlockGroup];

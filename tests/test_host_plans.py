@@ -353,6 +353,38 @@ def test_row_tiles_of_two_heights_are_planned_as_they_are_launched(ask):
         assert wk == 1
 
 
+def test_parts_of_a_launch_of_the_block_kernel(ask):
+    """The parts that a launch is made of: every row and column tile once, tall and low tiles apart above 256 workgroups, one height
+    within; and where the column tiles do not divide evenly over the XCDs, two heights take no round more on the fullest one than the
+    same tiles of one height (605 rows of 3232 columns on four wavefronts along K: 63 and 7 workgroups dealt, 58 and 7 in slices)."""
+    asked = [(mb, [(M, N, wk, s)]) for mb in (2, 3, 4) for M, N in ((605, 3232), (278, 25856), (647, 11520), (194, 10288), (200, 8208), (129, 33040), (300, 272))
+             for wk in (1, 2, 4) for s in (1, 3)]
+    asked += [(4, [(200, 6144, 1, 1), (200, 4096, 1, 1), (200, 28672, 1, 1), (200, 4096, 2, 1)]), (3, [(150, 8208, 2, 2), (33, 4096, 1, 1), (300, 4112, 4, 1)])]
+    lines = [f"parts {mb} {len(ps)} " + " ".join(f"{M} {N} {wk} {s}" for M, N, wk, s in ps) for mb, ps in asked]
+    two, fewer = 0, 0
+    for (mb, ps), raw in zip(asked, ask(lines, raw=True)):
+        one_round = int(raw.split()[0])
+        blocks = [list(map(int, b.split())) for b in re.findall(r"\[(.*?)\]", raw)]
+        launch = list(zip(blocks[::2], blocks[1::2]))
+        assert one_round == (sum(-(-N // (256 // wk)) * -(-M // (32 * mb)) * s for M, N, wk, s in ps) <= 256)
+        for i, (M, N, wk, s) in enumerate(ps):
+            parts = [(p, t) for p, t in launch if p[0] == i]
+            columns, row, dealt = -(-N // (256 // wk)), 0, 0
+            for (_, row0, rows, tall, on_xcd), (cols, *tiles) in parts:
+                assert cols == columns and row0 == row and (tall in (0, rows))
+                row += rows * 32 * (mb if tall else mb - 1)
+                at = list(zip(tiles[::3], tiles[1::3], tiles[2::3]))
+                assert sorted((x, z) for x, z, _ in at) == [(x, z) for x in range(columns) for z in range(rows)]
+                assert on_xcd == s * max(sum(x == c for *_, x in at) for c in range(8))
+                dealt += -(-columns // 8) * rows * s
+            assert row - 32 * mb < M <= row and len(parts) <= (1 if one_round else 2)
+            two += len(parts) == 2
+            rounds = -(-sum(p[4] for p, _ in parts) // 32)
+            assert rounds <= -(-dealt // 32) and rounds <= -(-(-(-columns * -(-M // (32 * mb)) // 8) * s + s) // 32)
+            fewer += rounds < -(-dealt // 32)
+    assert two >= 20 and fewer >= 10
+
+
 def test_grouped_calls_of_few_rows_on_the_block_kernel(ask):
     """Modules of up to 16 rows whose activations do not fit a compute unit beside one another (100 KiB and more) go to the block kernel;
     small modules stay on the small-batch kernel's grouped launch."""
