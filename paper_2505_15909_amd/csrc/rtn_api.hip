@@ -1519,7 +1519,7 @@ static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, 
         const int64_t unit = chunk_k(a[i].bits);
         const double per = (double)(((a[i].K / unit + s - 1) / s + wk - 1) / wk), groups = a[i].g >= unit ? 1.0 : (double)(unit / a[i].g);
         const double waves = wk == 1 ? 1.0 : c.waves[m.mb - 1][wk == 2 ? 0 : wk == 4 ? 1 : 2];
-        const rtn::BlockParts p = rtn::block_parts(tiles[i], m.mb, false);
+        const rtn::BlockParts p = rtn::block_parts(tiles[i], m.mb, wgs <= 256);
         for (int h = 0; h < p.n; ++h) {                     // the row tiles of 32 mb rows, those of 32 rows less
             const int mb = p.part[h].tall > 0 ? m.mb : m.mb - 1;
             const double rows = (double)wk * std::min((double)a[i].M, 32.0 * mb) / 32.0;

@@ -94,6 +94,18 @@ int main() {
                     printf("]");
                 }
             }
+        } else if (!strcmp(what, "merged")) {                  // mb n, then M N K bits g wk split each -> modelled time of that shared launch
+            MergedPlan m = {};
+            int n, longest;
+            LinearArgs a[rtn::kMaxBlockGroup];
+            if (scanf("%d %d", &m.mb, &n) != 2 || n < 1 || n > rtn::kMaxBlockGroup) return 1;
+            for (int i = 0; i < n; ++i) {
+                long M, N, K, g;
+                int bits;
+                if (scanf("%ld %ld %ld %d %ld %d %d", &M, &N, &K, &bits, &g, &m.waves[i], &m.split[i]) != 7) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, true);
+            }
+            printf("%.6f", merged_blocks_us(a, n, m, (size_t)1 << 40, &longest));
         } else if (!strcmp(what, "heap")) {                    // n, then M N K bits g each -> heap allocations of planning a shared launch
             int n;
             LinearArgs a[rtn::kMaxBlockGroup];

@@ -385,6 +385,17 @@ def test_parts_of_a_launch_of_the_block_kernel(ask):
     assert two >= 20 and fewer >= 10
 
 
+def test_shared_launches_of_one_round_are_modelled_with_tiles_of_one_height(ask):
+    """160 rows in tiles of up to 96 are 96 and 64 above a round of workgroups, twice 96 within one: then they cost what 192 rows do but for
+    the rows read."""
+    def us(M, N, modules):
+        return ask([f"merged 3 {modules} " + " ".join([f"{M} {N} 4096 4 128 1 1"] * modules)])[0][0]
+
+    for N, modules in ((4096, 2), (4096, 8), (2048, 8)):
+        assert 0.97 * us(192, N, modules) <= us(160, N, modules) <= us(192, N, modules), (N, modules)
+    assert us(160, 16384, 8) < 0.95 * us(192, 16384, 8)
+
+
 def test_grouped_calls_of_few_rows_on_the_block_kernel(ask):
     """Modules of up to 16 rows whose activations do not fit a compute unit beside one another (100 KiB and more) go to the block kernel;
     small modules stay on the small-batch kernel's grouped launch."""
