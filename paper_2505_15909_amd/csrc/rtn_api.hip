@@ -178,7 +178,11 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
 
 // Rounds of workgroups (slots of them on the fullest XCD at once) in times of the tallest ones, of mb blocks; those of a block less take
 // `low` of that and start last: whole rounds and the mean.  As if all were tall 28672 x 4096 at 300 rows, 128 + 96 + 96, went out in
-// 64-row tiles: 88 us, 83 this way; 20000 x 5120 at 400 rows 108 and 93, 57344 x 8192 at 200 rows 215 and 193.
+// 64-row tiles: 88 us, 83 this way; 20000 x 5120 at 400 rows 108 and 93, 57344 x 8192 at 200 rows 215 and 193.  A 32-row tile is taken as
+// long as a 64-row one: it unpacks as much, and where the model had it shorter a round that low tiles began looked cheap (16384 x 16384
+// int8 group 64 at 160 rows in 384 workgroups 172 us, in 192 of twice the length 142; 8192 x 8192 int4 at 521 rows 97 and 84).
+// Of 250 plans that two heights change in 12000 drawn problems 111 are more than 2 % faster than the plan for one, 4 more than 2 %
+// slower (5 % at most); with the models' own ratio 67 were, up to 22 %.
 void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, double low, double* whole, double* mean) {
     const rtn::BlockTiles tiles = rtn::block_tiles(M, N, mb, wk, s);
     const rtn::BlockParts p = rtn::block_parts(tiles, mb, tiles.workgroups() <= 256);
@@ -191,7 +195,7 @@ void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, dou
 double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s) {
     const BlockTimes b = block_times(M, N, K, bits, g, rows16, wk, s);
     const double wg = b.wg_us * (1.0 + 0.36 * std::min(1.0, (double)b.wgs / 256.0) * b.mb / 4.0);
-    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), low = b.mb == 1 ? 1.0 : block_wg_us(b.mb - 1, K, bits, g, wk, s) / b.wg_us;
+    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), low = b.mb <= 2 ? 1.0 : block_wg_us(b.mb - 1, K, bits, g, wk, s) / b.wg_us;
     double whole, mean;
     block_rounds(M, N, b.mb, wk, s, slots, low, &whole, &mean);
     double serial = wg * std::max(1.0, 0.91 * whole + 0.09 * mean);
@@ -223,7 +227,9 @@ double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int ro
     const double wg = 0.511 + std::cbrt(both * both) + (wk > 1 ? 0.484 * mb : 0.0);
     double whole, mean;
     const int w = wk == 1 ? 0 : wk == 2 ? 1 : wk == 4 ? 2 : 3;
-    const double low = mb == 1 ? 1.0 : kUnit[mb - 2][w] / kUnit[mb - 1][w];
+    // (8 bit: no less than the other model has it, which the measurements agree with: 16480 x 10752 at 147 rows 100 us split in three, 84 unsplit)
+    const double other = bits == 8 && mb > 2 ? block_wg_us(mb - 1, K, bits, g, wk, s) / block_wg_us(mb, K, bits, g, wk, s) : 0.0;
+    const double low = mb <= 2 ? 1.0 : std::max(kUnit[mb - 2][w] / kUnit[mb - 1][w], other);
     block_rounds(M, N, mb, wk, s, two ? 64.0 : 32.0, low, &whole, &mean);
     const double serial = wg * std::max(1.0, 0.774 * whole + 0.226 * mean) * (two && on_xcd > 32.0 ? 1.667 : 1.0);
     const double hbm = 1.195 * (weights + rows) / 6.83e6, fabric = 0.530 * (rows + weights / xcds) / 1e6;

@@ -385,6 +385,17 @@ def test_parts_of_a_launch_of_the_block_kernel(ask):
     assert two >= 20 and fewer >= 10
 
 
+def test_row_tiles_of_two_heights_are_planned_where_they_measured_faster(ask):
+    """Row tiles, wavefronts along K and K splits of problems measured with the plans for one height and for two: 32-row tiles save
+    nothing beside 64-row ones (the first five), 96-row tiles beside 128-row ones do."""
+    want = {(521, 8192, 8192, 4, 0): (8, 1, 1), (160, 16384, 16384, 8, 64): (4, 1, 1), (147, 16480, 10752, 8, 0): (4, 1, 1),
+            (151, 13296, 10752, 8, 64): (4, 1, 1), (651, 6144, 4096, 4, 256): (8, 1, 1),
+            (300, 28672, 4096, 4, 128): (8, 2, 1), (397, 57344, 8192, 4, 128): (8, 1, 1), (513, 18432, 16384, 4, 128): (8, 2, 1)}
+    for (p, (rows, wk, split)), (status, plans) in zip(want.items(), ask([f"linear {' '.join(map(str, p))} {256 * MIB}" for p in want])):
+        got = plans[0]
+        assert status == 0 and len(plans) == 1 and (got["path"], got["m_rows16"], got["waves_k"], got["split_k"]) == (3, rows, wk, split), (p, got)
+
+
 def test_shared_launches_of_one_round_are_modelled_with_tiles_of_one_height(ask):
     """160 rows in tiles of up to 96 are 96 and 64 above a round of workgroups, twice 96 within one: then they cost what 192 rows do but for
     the rows read."""
