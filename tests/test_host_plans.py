@@ -256,6 +256,16 @@ def test_no_problem_goes_from_exact_codes_to_rounded_weights(ask, workspace):
         assert status == 0 and all(q["path"] == 3 for q in launches), (p, launches)
 
 
+def test_exact_codes_do_not_depend_on_how_row_tiles_are_modelled(ask):
+    """Problems with workspaces that ran on exact codes while the block kernel's model had row tiles of one height, and went to the
+    tile kernel, which rounds each scaled weight, when it got two."""
+    exact = [(608, 19520, 24576, 4, 128, 256), (852, 13584, 5120, 4, 256, 256), (718, 53408, 5632, 4, 128, 0), (520, 20496, 3072, 4, 128, 16),
+             (593, 25952, 1536, 4, 128, 0), (731, 21520, 14848, 4, 0, 40), (774, 29312, 4096, 4, 128, 0), (391, 26800, 1024, 4, 128, 256),
+             (486, 19616, 8192, 8, 0, 40), (664, 12528, 3072, 4, 128, 0), (978, 16832, 2560, 4, 128, 256)]
+    for p, (status, launches) in zip(exact, ask([f"linear {' '.join(map(str, p[:5]))} {p[5] * MIB}" for p in exact])):
+        assert status == 0 and all(q["path"] == 3 for q in launches), (p, launches)
+
+
 def test_block_plans_of_few_columns_long_rows_and_many_rows(ask):
     """Problems on which the plan was measured 1.3 to 2 times slower than the best one while the block kernel's model knew only
     matrices of 1024 columns and more at up to 512 rows: the plans that measured best."""
