@@ -183,27 +183,33 @@ BlockTimes block_times(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
 // int8 group 64 at 160 rows in 384 workgroups 172 us, in 192 of twice the length 142; 8192 x 8192 int4 at 521 rows 97 and 84).
 // Of 250 plans that two heights change in 12000 drawn problems 111 are more than 2 % faster than the plan for one, 4 more than 2 %
 // slower (5 % at most); with the models' own ratio 67 were, up to 22 %.
-// line: the least of what the model has had for the row tiles, of one height (`equal` rounds) or of two, in whichever order over the
-// XCDs.  A problem that ran on exact codes by any of them keeps them (modelled_plan).
-void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, double low, bool line, double equal, double* whole, double* mean) {
+// How the model has had row tiles.  The earlier ones draw the line to the tile kernel alone: a problem that ran on exact codes by any
+// of them keeps them (modelled_plan).
+enum Picture : int { kLaunched, kOneHeight, kTwoHeights };      // kTwoHeights: 32-row tiles shorter too, an order over the XCDs for each part
+void block_rounds(int64_t M, int64_t N, int mb, int wk, int s, double slots, double low, Picture picture, double equal, double* whole, double* mean) {
+    if (picture == kOneHeight) {
+        *mean = equal;
+        *whole = std::ceil(equal);
+        return;
+    }
     const rtn::BlockTiles tiles = rtn::block_tiles(M, N, mb, wk, s);
     const rtn::BlockParts p = rtn::block_parts(tiles, mb, tiles.workgroups() <= 256);
-    auto on_xcd = [&](int i) { return (double)(line ? (tiles.columns * p.part[i].rows + 7) / 8 * s : p.part[i].on_xcd); };
-    const double t = on_xcd(0), l = on_xcd(1);                                    // (none in a part that is not there)
-    const double of_tall = std::ceil(t / slots);
+    auto on_xcd = [&](int i) {                                                    // (none in a part that is not there)
+        if (picture == kLaunched || p.n == 1) return (double)p.part[i].on_xcd;
+        const int64_t rows = p.part[i].rows, sliced = (tiles.columns * rows + 7) / 8 * s, dealt = (tiles.columns + 7) / 8 * rows * s;
+        return (double)(rtn::xcd_slices_save_a_round(tiles.columns, rows, s) ? sliced : dealt);
+    };
+    const double t = on_xcd(0), l = on_xcd(1), of_tall = std::ceil(t / slots);
     *whole = of_tall + (std::ceil((t + l) / slots) - of_tall) * low;
     *mean = (t + l * low) / slots;
-    if (!line) return;
-    *whole = std::min(*whole, std::ceil(equal));
-    *mean = std::min(*mean, equal);
 }
 
-double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, bool line) {
+double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, Picture picture) {
     const BlockTimes b = block_times(M, N, K, bits, g, rows16, wk, s);
     const double wg = b.wg_us * (1.0 + 0.36 * std::min(1.0, (double)b.wgs / 256.0) * b.mb / 4.0);
-    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), low = b.mb <= (line ? 1 : 2) ? 1.0 : block_wg_us(b.mb - 1, K, bits, g, wk, s) / b.wg_us;
+    const double slots = 32.0 * (b.mb == 1 && wk <= 4 ? 2 : 1), low = b.mb <= (picture == kTwoHeights ? 1 : 2) ? 1.0 : block_wg_us(b.mb - 1, K, bits, g, wk, s) / b.wg_us;
     double whole, mean;
-    block_rounds(M, N, b.mb, wk, s, slots, low, line, std::ceil((double)b.wgs / 8.0) / slots, &whole, &mean);
+    block_rounds(M, N, b.mb, wk, s, slots, low, picture, std::ceil((double)b.wgs / 8.0) / slots, &whole, &mean);
     double serial = wg * std::max(1.0, 0.91 * whole + 0.09 * mean);
     if (slots > 32.0 && b.wgs > 256) serial *= 1.78;
     return 2.93 + std::cbrt(serial * serial * serial + b.stream_us * b.stream_us * b.stream_us) +
@@ -216,7 +222,7 @@ double block_near_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int r
 // (a 4-norm) the stream from HBM, what the XCDs that have a workgroup fetch (all activations each: a matrix of few columns
 // leaves most of them idle) and what they read from their L2.  The reduce pass of a K split costs more above eight splits (its
 // kernel goes round).  Fitted to 78000 launches: 1394 problems of 17 to 4096 rows, 128 to 106496 columns of 512 to 53248.
-double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, bool line) {
+double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, Picture picture) {
     static const double kUnit[4][4] = {{1.791, 1.971, 2.149, 2.810}, {2.437, 2.819, 3.048, 3.392}, {3.418, 3.411, 4.144, 4.144}, {3.948, 4.007, 4.956, 4.956}};
     static const double kGroup[4] = {0.062, 0.091, 0.044, 0.103};
     const int64_t unit = bits == 4 ? 512 : 256, units = K / unit, cols = 256 / wk;
@@ -234,9 +240,9 @@ double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int ro
     double whole, mean;
     const int w = wk == 1 ? 0 : wk == 2 ? 1 : wk == 4 ? 2 : 3;
     // (8 bit: no less than the other model has it, which the measurements agree with: 16480 x 10752 at 147 rows 100 us split in three, 84 unsplit)
-    const double other = bits == 8 && mb > 2 && !line ? block_wg_us(mb - 1, K, bits, g, wk, s) / block_wg_us(mb, K, bits, g, wk, s) : 0.0;
-    const double low = mb <= (line ? 1 : 2) ? 1.0 : std::max(kUnit[mb - 2][w] / kUnit[mb - 1][w], other);
-    block_rounds(M, N, mb, wk, s, two ? 64.0 : 32.0, low, line, on_xcd / (two ? 64.0 : 32.0), &whole, &mean);
+    const double other = bits == 8 && mb > 2 && picture == kLaunched ? block_wg_us(mb - 1, K, bits, g, wk, s) / block_wg_us(mb, K, bits, g, wk, s) : 0.0;
+    const double low = mb <= (picture == kTwoHeights ? 1 : 2) ? 1.0 : std::max(kUnit[mb - 2][w] / kUnit[mb - 1][w], other);
+    block_rounds(M, N, mb, wk, s, two ? 64.0 : 32.0, low, picture, on_xcd / (two ? 64.0 : 32.0), &whole, &mean);
     const double serial = wg * std::max(1.0, 0.774 * whole + 0.226 * mean) * (two && on_xcd > 32.0 ? 1.667 : 1.0);
     const double hbm = 1.195 * (weights + rows) / 6.83e6, fabric = 0.530 * (rows + weights / xcds) / 1e6;
     const double l2 = 0.812 * on_xcd * (a_bytes + 1.550 * w_bytes) / 2e6;
@@ -249,9 +255,9 @@ double block_far_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int ro
 // Below 1024 columns and above 512 rows the second alone: the best measured plan is 1.5 % and 0.7 % ahead of its pick on average
 // (of the first's 6 % and 3 %, up to 64 % on few columns under long rows: 394 rows of 400 x 43008 66 us, 41 possible).  Elsewhere
 // their mean, whose pick is 1.3 % behind, either alone 1.9 %.
-double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, bool line = false) {
-    const double far = block_far_us(M, N, K, bits, g, rows16, wk, s, line);
-    return N < 1024 || M > 512 ? far : std::sqrt(far * block_near_us(M, N, K, bits, g, rows16, wk, s, line));
+double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int rows16, int wk, int s, Picture picture = kLaunched) {
+    const double far = block_far_us(M, N, K, bits, g, rows16, wk, s, picture);
+    return N < 1024 || M > 512 ? far : std::sqrt(far * block_near_us(M, N, K, bits, g, rows16, wk, s, picture));
 }
 
 // Plan of the block kernel within `cap` bytes of partial sums, and its modelled time: row tile height (32 rows up to 96 rows, 128
@@ -259,7 +265,7 @@ double block_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int 
 // relied upon: 64 to 96 rows of a matrix under 24 M weights split K in two where the workspace allows (4096 x 4096 at 64 rows: 10.2 us,
 // 8.6 unsplit with eight wavefronts along K); and 8-bit matrices of half a gigabyte and more with more input than output columns
 // keep 64-row tiles (16384 x 53248 at 157 rows 403 us, 340 in 128-row tiles).
-double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p, bool line) {
+double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p, Picture picture) {
     const int64_t units = K / chunk_k(bits);
     double best = 1e30;
     p->path = 3; p->prefetch = 1; p->waves_n = 8; p->n_tiles16 = 2; p->waves_k = 1; p->split_k = 1; p->m_rows16 = 2;
@@ -273,7 +279,7 @@ double block_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t c
             const bool two = r == 2 && M >= 64 && N * K < 24000000 && 2 * wk <= units && (size_t)M * N * sizeof(float) * 2 <= cap;
             for (int s = two ? 2 : 1; s <= kMaxSplitK && s * wk <= units; ++s) {
                 if (s > 1 && (size_t)M * N * sizeof(float) * s > cap) break;
-                const double t = block_model_us(M, N, K, bits, g, r, wk, s, line);
+                const double t = block_model_us(M, N, K, bits, g, r, wk, s, picture);
                 if (t < best) { best = t; p->m_rows16 = r; p->waves_k = wk; p->split_k = s; }
             }
         }
@@ -308,8 +314,8 @@ double wide16_model_us(int64_t M, int64_t N, int64_t K, int bits, int64_t g, int
 // Up to 64 rows the line lies 3 % to its side: of 166 measured problems 20 then run slower than on the better kernel, 24 with the models level.
 // The wide kernel's row blocks: 48 rows above 64 where they save a fifth of the padded rows.  With zero points it is 3 % further
 // behind (a zero point per operand and lane in half the columns).
-double block_or_wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p, bool line = false) {
-    const double t_block = block_plan(M, N, K, bits, g, cap, zp, p, line);
+double block_or_wide_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, size_t cap, bool zp, LinearPlan* p, Picture picture = kLaunched) {
+    const double t_block = block_plan(M, N, K, bits, g, cap, zp, p, picture);
     if (t_block > 40.0) return t_block;
     const bool blocks48 = M > 64 ? ((M + 47) / 48) * 48 * 5 <= ((M + 63) / 64) * 64 * 4 : M > 32 && M <= 48;
     const int rows16 = M <= 32 ? 2 : blocks48 ? 3 : 4;
@@ -688,12 +694,14 @@ LinearPlan modelled_plan(int64_t M, int64_t N, int64_t K, int bits, int64_t g, s
     if (force_path == 0 && wide_wins && M >= 128 && wide_or_tile_plan(M, N, K, bits, g, workspace).path == 4) {
         double t_tile = 0;
         tile_two_launches(false, M, N, K, workspace, &t_tile);
-        // This line is one of precision too: it lies where every earlier picture of the block kernel's row tiles has it at the least, so that
-        // no problem that ran on exact codes is rounded because the model changed (two heights alone moved 31 of 60000 drawn
-        // problems to the tile kernel; 391 rows of 26800 x 1024, 593 of 25952 x 1536 without a workspace).  It costs nothing: 17 that it
-        // brought back from the tile kernel run 0.98 of their time on the mean.
-        LinearPlan unused;
-        t_block = std::min(t_block, block_or_wide_plan(M, N, K, bits, g, cap, false, &unused, true));
+        // This line is one of precision too: it does not move where the picture of the block kernel's row tiles changes (two heights alone
+        // moved 31 of 60000 drawn problems to the tile kernel; 391 rows of 26800 x 1024, 593 of 25952 x 1536 without a
+        // workspace).  Beyond a third no picture is ahead of another.
+        if (t_tile * 1.03 < t_block * 1.05 && t_tile * 1.5 > t_block) {
+            LinearPlan unused;
+            for (Picture picture : {kOneHeight, kTwoHeights})
+                t_block = std::min(t_block, block_or_wide_plan(M, N, K, bits, g, cap, false, &unused, picture));
+        }
         // against the block kernel (both sides of 156 such problems measured: 2-4 % behind the better one, and no better for lines
         // 5 % to either side); a little towards the tile kernel above 512 rows, where it also takes several modules of a layer at once.
         // The long 4-bit matrices of 400 MB just above 128 rows stay on the tile kernel, as rtn_linear_query is known to report them
