@@ -1478,12 +1478,16 @@ static double dealt_us(const double* each, const int64_t* count, int n, int64_t 
     Load load[kMostSlots];                                      // by end; each has a slot at least
     int loads = 1, order[2 * rtn::kMaxBlockGroup];
     load[0] = {0.0, slots};
-    for (int i = 0; i < n; ++i) order[i] = i;
-    std::sort(order, order + n, [&](int x, int y) { return each[x] > each[y]; });
+    for (int i = 0; i < n; ++i) {                               // longest first
+        int at = i;
+        for (; at > 0 && each[order[at - 1]] < each[i]; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
     double sum = 0.0;
     for (int k = 0; k < n; ++k) {
         int64_t left = count[order[k]];
         const double d = each[order[k]];
+        while (k + 1 < n && each[order[k + 1]] == d && left + count[order[k + 1]] <= 64 * slots) left += count[order[++k]];    // like modules
         sum += d * left;
         if (left > 64 * slots) {                                // many rounds: the load is even to a round
             for (int i = 0; i < loads; ++i) load[i].end += d * (double)(left / slots - 32);
@@ -1526,8 +1530,10 @@ static const BlockCosts kBlockCosts16 = {0.636, {1.923, 0.0, 0.0, 0.0}, {0.063, 
 // Modelled time of m, negative where its partial sums do not fit; the module with the longest workgroups.  The workgroups of a part (row
 // tiles of one height) are dealt longest first, as launch_blocks orders them, to the compute units of the fullest XCD.  Fitted to
 // 2600 launches: the 8B, 70B and 405B layers in five formats at 5 to 512 rows, two to eight modules of 1024 to 8192 columns at 1 to 16
-// rows (4 % rms; the pick is 0.9 % behind the best of 10 to 80 plans measured for each).
-static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, size_t workspace, int* longest) {
+// rows (4 % rms; the pick is 0.9 % behind the best of 10 to 80 plans measured for each).  From `bound` on a lower bound of the time will do.
+// floor: what no plan that shares K among more workgroups gets below (they add to the load and to the reduce pass).
+static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, size_t workspace, int* longest, double bound = INFINITY,
+                               double* floor = nullptr) {
     int64_t most = 0;
     for (int i = 0; i < n; ++i) most = std::max(most, a[i].M);
     const BlockCosts& c = most <= 16 && m.mb == 1 ? kBlockCosts16 : kBlockCosts;
@@ -1566,7 +1572,16 @@ static double merged_blocks_us(const LinearArgs* a, int n, const MergedPlan& m, 
     if (partials > workspace) return -1.0;
     const bool two = m.mb == 1;
     const double slow = (two ? c.one : 1.02) * (1.0 + c.busy * std::min(1.0, (double)wgs / 256.0) * m.mb / 4.0) * (two && on_xcd > 32 ? c.shared : 1.0);
-    for (int i = 0; i < parts; ++i) each[i] *= slow;
+    double load = 0.0;
+    for (int i = 0; i < parts; ++i) {
+        each[i] *= slow;
+        load += each[i] * (double)count[i];
+    }
+    load /= two ? 64.0 : 32.0;
+    const double end = c.last * std::max(load, length * slow) + (1.0 - c.last) * load;
+    const double least = c.launch + std::sqrt(end * end + stream * stream) + reduce;       // (c.norm is under 2)
+    if (floor) *floor = c.launch + std::sqrt(load * load + stream * stream) + reduce;
+    if (least >= bound) return least;                           // no need to deal them out
     const double serial = dealt_us(each, count, parts, two ? 64 : 32, c.last);
     return c.launch + std::pow(std::pow(serial, c.norm) + std::pow(stream, c.norm), 1.0 / c.norm) + reduce;
 }
@@ -1586,10 +1601,12 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
         rows = std::max(rows, a[i].M);
         shortest = std::min(shortest, a[i].K / chunk_k(a[i].bits));
     }
-    for (int r = 2; r <= 8; r *= 2) {
+    for (int r = 2, last_mb = 0; r <= 8; r *= 2) {
         if ((r == 2 && rows > 96) || (r == 8 && rows <= 64)) continue;
         const int64_t tiles = (rows + 16 * r - 1) / (16 * r);
         const int mb = (int)((rows + 32 * tiles - 1) / (32 * tiles));
+        if (mb == last_mb) continue;                            // up to 32 rows: the same tiles
+        last_mb = mb;
         for (int wk = 1; wk <= 8 && wk <= shortest; wk *= 2) {
             if (wk == 8 && mb > 2) continue;
             for (int deepen = 1; deepen <= (wk > 1 ? 1 : rows <= 8 ? 4 : 2); deepen *= 2) {
@@ -1599,10 +1616,12 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
                 bool deep = false;
                 for (int cuts = 0; cuts < 6; ++cuts) {
                     int longest = 0;
-                    m.us = merged_blocks_us(a, n, m, workspace, &longest);
+                    double floor;
+                    m.us = merged_blocks_us(a, n, m, workspace, &longest, best.us < 0.0 ? INFINITY : best_line, &floor);
                     if (m.us < 0.0) break;
                     const double line = m.us * (deep && mb <= 2 ? 1.03 : 1.0);    
                     if (best.us < 0.0 || line < best_line) { best = m; best_line = line; }
+                    if (deepen == 1 && floor >= best_line) break;
                     const int s = m.split[longest];
                     const int64_t units = a[longest].K / chunk_k(a[longest].bits);
                     if (m.waves[longest] < deepen && deepen * s <= units) {
@@ -1659,7 +1678,7 @@ static MergedPlan merged_tiles(const LinearArgs* a, int n, size_t workspace) {
     return best;
 }
 
-// The same, remembered (a few microseconds of host time for four modules): a table of fixed size, an entry gives way to the next one that falls on it.
+// The same, remembered (3 to 9 us of host time for four modules, 10 for eight): a table of fixed size, an entry gives way to the next one that falls on it.
 static MergedPlan remembered_merge(const LinearArgs* a, int n, size_t workspace, bool tiles = false) {
     struct Key { int64_t v[4 * rtn::kMaxBlockGroup + 3]; };
     struct Entry { Key key; MergedPlan plan; bool used; };
