@@ -66,12 +66,14 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 // Stages and depths of a shape of the block kernel: row tiles of up to MB blocks of 32 rows.  Four activation stages of up to 32 KiB (16
 // with one block): one kernel has all shapes that fit, and a launch may give every problem its own.  The others have a kernel of their
 // own: most wavefronts along K on two blocks and more, with two stages of 64 columns (four of 32: 4 % slower at 128 rows), and eight on 8-bit
-// weights, with four of 64 columns (of 32: 6144 x 4096 at 32 rows 11.1 us instead of 10.3; 4-bit weights the other way, 7.5 instead of 8.1).
+// weights, with four of 64 columns (of 32: 6144 x 4096 at 32 rows 11.1 us instead of 10.3).  4-bit weights have both: of 32 columns where
+// a wavefront has one unit (4096 columns and less: 6144 x 4096 7.5 us instead of 8.1), of 64 from two, where the weights are asked for as far
+// ahead as the rows are (4096 x 7168 at 32 rows 14.6 us with 32, 13.0 with 64; 4096 x 14336 at 28 rows 25.3 and 21.0).
 // FIT: stages no larger than the shape needs, for a kernel that has no other shape.
 template <int BITS, int MB, int WN, int WK, bool HALF = false, bool FIT = false>
 struct BlockShape {
     static constexpr bool ALONE = !HALF && block_shape_alone(BITS, MB, WK);
-    static constexpr int KA = WK == 1 || (WK == 2 && MB <= 2) || (HALF && WK == 4) ? kStepK : WK == 8 && !ALONE && !HALF ? 32 : 64;   // columns of an activation stage, per wavefront along K
+    static constexpr int KA = WK == 1 || (WK == 2 && MB <= 2) || (HALF && WK == 4) ? kStepK : WK == 8 && !ALONE && !HALF && !FIT ? 32 : 64;   // columns of an activation stage, per wavefront along K
     static constexpr int R = kStepK / KA;                           // stages per k-step
     static constexpr int S = ALONE && MB > 1 ? 2 : 4;               // activation stages
     static constexpr int D = BITS == 4 ? 4 : 2;     // k-steps of weights in registers
@@ -441,8 +443,8 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
     run(std::integral_constant<int, MB>{}, part.row0 + z * (32 * MB));
 }
 
-// One shape, which every part of the launch has: those whose stages do not fit the kernel above, 64-row tiles without wavefronts along K,
-// and all with zero points.  A launch with
+// One shape, which every part of the launch has: those whose stages do not fit the kernel above or are not its own, 64-row tiles without
+// wavefronts along K, and all with zero points.  A launch with
 // zero points is one problem, so there is nothing to share, and the common kernel cost it: with groups of 32 columns on 32-row tiles eight
 // registers went to scratch memory (6144 x 4096 at 24 rows 11.8 us, 11.3 here), and with stages of 32 KiB where 16 do, half of them lie
 // beyond the offset that an LDS read holds and every read takes an addition (4096 x 14336 group 64 at 256 rows 43.9 us, 43.1; without
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
 template <int BITS, int MB, int NG, int WK, bool ZP>
 __global__ __launch_bounds__(kBlockThreads, MB == 1 && WK < 8 ? 4 : 2) void block_mfma_alone_kernel(const BlockGroup group) {
     typedef BlockShape<BITS, MB, 8 / WK, WK, false, true> Shape;
-    static_assert(ZP || Shape::ALONE || (MB == 2 && WK == 1), "");
+    static_assert(ZP || Shape::ALONE || (MB == 2 && WK == 1) || (MB == 1 && WK == 8), "");
     constexpr int LAST = Shape::S > 2 ? Shape::STAGE : 16;
     __shared__ __align__(16) uint8_t lds0[Shape::STAGE], lds1[Shape::STAGE], lds2[LAST], lds3[LAST];
     int xb, z, sg;
@@ -490,6 +492,8 @@ hipError_t launch_block(const BlockGroup& g, int ng, int mb, unsigned grid, hipS
                 if (one) return alone_kernel(std::integral_constant<int, 1>{});
             }
             bool alone = block_shape_alone(BITS, mb, wk);
+            if (MB == 1 && wk == 8)                       // several units for a wavefront (BlockShape)
+                for (int i = 0; i < g.n; ++i) alone = alone || (g.p[g.part[i].info >> 20].u_share & 0xFFFFu) + (g.p[g.part[i].info >> 20].u_share >> 16 ? 1 : 0) > 8;
             if (MB == 1 && alone) {                       // 16 rows and less are staged as such by the common kernel
                 alone = false;
                 for (int i = 0; i < g.n; ++i) alone = alone || g.p[g.part[i].info >> 20].M > 16;
@@ -498,7 +502,7 @@ hipError_t launch_block(const BlockGroup& g, int ng, int mb, unsigned grid, hipS
                 hipLaunchKernelGGL((block_mfma_kernel<BITS, MB, NG>), dim3(grid), dim3(kBlockThreads), 0, st, g);
                 return hipGetLastError();
             }
-            if constexpr (block_shape_alone(BITS, MB, DEEP))
+            if constexpr (block_shape_alone(BITS, MB, DEEP) || MB == 1)
                 if (wk == DEEP) return alone_kernel(std::integral_constant<int, DEEP>{});
         }
         return hipErrorInvalidValue;
