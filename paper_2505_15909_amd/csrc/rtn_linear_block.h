@@ -86,9 +86,9 @@ struct BlockShape {
 constexpr int kZeroRow = 256;
 
 // One row tile of MB blocks: column tile xb, rows from m0, part sg of K.  TALL: blocks of the launch's tallest tiles, which give the shape
-// of the stages.  HALF: at most 16 rows; the MFMAs' other 16 read a row of zeros.
+// of the stages.  args: where p came from, for what is needed at the end.  HALF: at most 16 rows; the MFMAs' other 16 read a row of zeros.
 template <int BITS, int MB, int TALL, int NG, int WN, int WK, bool ZP, bool HALF = false, bool FIT = false>
-__device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0, int sg, uint8_t* lds0, uint8_t* lds1, uint8_t* lds2, uint8_t* lds3) {
+__device__ __forceinline__ void block_tile(const BlockProblem& p, const BlockProblem& args, int xb, int m0, int sg, uint8_t* lds0, uint8_t* lds1, uint8_t* lds2, uint8_t* lds3) {
     typedef BlockShape<BITS, TALL, WN, WK, HALF, FIT> Shape;
     constexpr int TPS = kStepK / Layout<BITS>::TK;        // packed tiles per k-step: 1 / 2
     constexpr int SPU = Shape::SPU, UN = Shape::UN;
@@ -113,12 +113,14 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
     const int u_base = (int)(p.u_share & 0xFFFFu), u_rem = (int)(p.u_share >> 16), upg = (int)(p.groups & 0xFFFFu);
     const int u_wg = sg * u_base + min(sg, u_rem);                 // units of this workgroup: u_wg .. u_wg + n_wg
     const int n_wg = u_base + (sg < u_rem ? 1 : 0);
-    const uint32_t qw_bytes = (uint32_t)p.N * ((uint32_t)p.K / 8u) * BITS, sc_bytes = (uint32_t)p.N * (uint32_t)p.G * 2u;
+    // (what several shapes of a kernel have in common the compiler may put into vector registers, and loop over the lanes at each load)
+    const uint32_t qw_bytes = __builtin_amdgcn_readfirstlane((uint32_t)p.N * ((uint32_t)p.K / 8u) * BITS);
+    const uint32_t sc_bytes = __builtin_amdgcn_readfirstlane((uint32_t)p.N * (uint32_t)p.G * 2u);
     const int TU = (n_wg + WK - 1) / WK;                           // units every wavefront runs; those beyond its share add zeros
     const int u0 = u_wg + wk * TU;
     const int own = max(0, min(TU, n_wg - wk * TU));
 
-    const int a_rows = min(ROWS, p.M - m0);
+    const int a_rows = __builtin_amdgcn_readfirstlane(min(ROWS, p.M - m0));
     half_t* a0 = const_cast<half_t*>(p.A) + (int64_t)m0 * p.K;
     // held in scalar registers: left alone the compiler reads the pointers again after each barrier, and waits for them with every LDS read
     uint8_t* qw = const_cast<uint8_t*>(p.qw);
@@ -196,7 +198,12 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
 
     half8_t aop[PD + 1][MB];
     // piece 2 s + h of a row stands at slot (2 s + h) ^ (row's swizzle): one exclusive-or per slice on the lane's own address
-    const uint32_t rd = HALF && row >= 16 ? STAGE + h * 16 : wk * SLICE_BYTES + row * (KA * 2) + ((h ^ ((row / SWZ) % PIECES)) * 16);
+    uint32_t rd = wk * SLICE_BYTES + row * (KA * 2) + ((h ^ ((row / SWZ) % PIECES)) * 16);
+    if constexpr (HALF) {                                 // both addresses first: with a branch the compiler has values of its sides in vector registers
+        uint32_t zero = STAGE + h * 16;
+        asm volatile("" : "+v"(rd), "+v"(zero));
+        rd = row >= 16 ? zero : rd;
+    }
     if constexpr (HALF) {                                 // a row of zeros behind each stage; every wavefront writes it for itself
 #pragma unroll
         for (int i = 0; i < S; ++i) *reinterpret_cast<uint32_t*>(stage(i) + STAGE + lane * 4) = 0;
@@ -336,10 +343,10 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
     // past N are outside the resource and dropped by the hardware (a row tile of results is under 2 GiB, see the launch).
     auto finish = [&](auto partial) {
         constexpr uint32_t BYTES = partial.value ? 4 : 2;
-        const uint32_t row_bytes = (uint32_t)p.N * BYTES;
+        const uint32_t row_bytes = (uint32_t)args.N * BYTES;
         const __amdgpu_buffer_rsrc_t rc = partial.value
-            ? __builtin_amdgcn_make_buffer_rsrc(p.ws + ((int64_t)sg * p.M + m0) * p.N, 0, (uint32_t)a_rows * row_bytes, kBufferFlags)
-            : __builtin_amdgcn_make_buffer_rsrc(p.C + (int64_t)m0 * p.N, 0, (uint32_t)a_rows * row_bytes, kBufferFlags);
+            ? __builtin_amdgcn_make_buffer_rsrc(args.ws + ((int64_t)sg * args.M + m0) * args.N, 0, (uint32_t)a_rows * row_bytes, kBufferFlags)
+            : __builtin_amdgcn_make_buffer_rsrc(args.C + (int64_t)m0 * args.N, 0, (uint32_t)a_rows * row_bytes, kBufferFlags);
         const uint32_t c_lane = nt_ok ? h * 4 * row_bytes + (uint32_t)(nt * 16 + (lane & 15)) * BYTES : 0x80000000u;
         auto store = [&](int b, int e, float v) {
             const uint32_t off = c_lane + (uint32_t)(b * 32 + (e >> 2) * 8 + (e & 3)) * row_bytes;
@@ -379,7 +386,7 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
                 }
         }
     };
-    if (((p.groups >> 16) & 0xFFu) == 1) finish(std::false_type{});
+    if (((args.groups >> 16) & 0xFFu) == 1) finish(std::false_type{});
     else finish(std::true_type{});
 }
 
@@ -387,18 +394,20 @@ __device__ __forceinline__ void block_tile(const BlockProblem& p, int xb, int m0
 // the first one, are read before it is known whether they are the right ones: the arguments come from memory, and to read the number of
 // parts, then the part, then the problem, each after the other has arrived, put 0.2-0.4 us before the first request for data (int8,
 // 18192 x 2560 at 64 rows 18.5 us, 18.1 this way; 67 rows of 8128 x 3072 13.8 and 13.4).
-__device__ __forceinline__ bool block_part(const BlockGroup& group, BlockPart* part, BlockProblem* p, int* xb, int* z, int* sg) {
+__device__ __forceinline__ bool block_part(const BlockGroup& group, BlockPart* part, int* problem, BlockProblem* p, int* xb, int* z, int* sg) {
     *part = group.part[0];
     *p = group.p[0];
+    *problem = 0;
     // values from here on: left alone the compiler picks the address first and reads once, after it
     asm volatile("" : "+s"(part->first), "+s"(part->blocks), "+s"(part->row0), "+s"(part->tall), "+s"(part->info));
-    asm volatile("" : "+s"(p->A), "+s"(p->qw), "+s"(p->scales), "+s"(p->zeros), "+s"(p->C), "+s"(p->ws));
+    asm volatile("" : "+s"(p->A), "+s"(p->qw), "+s"(p->scales), "+s"(p->zeros));
     asm volatile("" : "+s"(p->M), "+s"(p->N), "+s"(p->K), "+s"(p->G), "+s"(p->XB), "+s"(p->u_share), "+s"(p->groups), "+s"(p->upg_inv));
     if (group.n > 1 && (int)blockIdx.x >= group.part[1].first) {
         int gi = 1;
         while (gi + 1 < group.n && (int)blockIdx.x >= group.part[gi + 1].first) ++gi;
         *part = group.part[gi];
-        *p = group.p[part->info >> 20];
+        *problem = (int)(part->info >> 20);
+        *p = group.p[*problem];
     }
     const int local = (int)blockIdx.x - part->first;
     *sg = local / part->blocks;
@@ -411,27 +420,27 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 ? 4 : 2) void block_mfma_ker
     constexpr int STAGE = BlockShape<BITS, MB, 8, 1>::STAGE;
     constexpr int BYTES = STAGE + (MB == 1 ? kZeroRow : 0);
     __shared__ __align__(256) uint8_t lds0[BYTES], lds1[BYTES], lds2[BYTES], lds3[BYTES];
-    int xb, z, sg;
+    int problem, xb, z, sg;
     BlockPart part;
     BlockProblem p;
-    if (!block_part(group, &part, &p, &xb, &z, &sg)) return;
+    if (!block_part(group, &part, &problem, &p, &xb, &z, &sg)) return;
     const int wk = (int)(p.groups >> 24);
     auto run = [&](auto height, int m0) {
         constexpr int H = decltype(height)::value;
         if constexpr (MB == 1) {
             if (p.M <= 16 && wk > 1) {
-                if (wk == 2) block_tile<BITS, 1, 1, NG, 4, 2, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-                else if (wk == 4) block_tile<BITS, 1, 1, NG, 2, 4, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-                else block_tile<BITS, 1, 1, NG, 1, 8, false, true>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+                if (wk == 2) block_tile<BITS, 1, 1, NG, 4, 2, false, true>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
+                else if (wk == 4) block_tile<BITS, 1, 1, NG, 2, 4, false, true>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
+                else block_tile<BITS, 1, 1, NG, 1, 8, false, true>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
                 return;
             }
         }
-        if (wk == 1) block_tile<BITS, H, MB, NG, 8, 1, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
-        else if (MB > 2 || wk == 2) block_tile<BITS, H, MB, NG, 4, 2, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+        if (wk == 1) block_tile<BITS, H, MB, NG, 8, 1, false>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
+        else if (MB > 2 || wk == 2) block_tile<BITS, H, MB, NG, 4, 2, false>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
         if constexpr (MB <= 2) {
-            if (wk == 4) block_tile<BITS, H, MB, NG, 2, 4, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+            if (wk == 4) block_tile<BITS, H, MB, NG, 2, 4, false>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
             if constexpr (MB == 1 && !block_shape_alone(BITS, 1, 8))
-                if (wk == 8) block_tile<BITS, H, MB, NG, 1, 8, false>(p, xb, m0, sg, lds0, lds1, lds2, lds3);
+                if (wk == 8) block_tile<BITS, H, MB, NG, 1, 8, false>(p, group.p[problem], xb, m0, sg, lds0, lds1, lds2, lds3);
         }
     };
     if constexpr (MB > 1) {
@@ -455,17 +464,17 @@ __global__ __launch_bounds__(kBlockThreads, MB == 1 && WK < 8 ? 4 : 2) void bloc
     static_assert(ZP || Shape::ALONE || (MB == 2 && WK == 1) || (MB == 1 && WK == 8), "");
     constexpr int LAST = Shape::S > 2 ? Shape::STAGE : 16;
     __shared__ __align__(16) uint8_t lds0[Shape::STAGE], lds1[Shape::STAGE], lds2[LAST], lds3[LAST];
-    int xb, z, sg;
+    int problem, xb, z, sg;
     BlockPart part;
     BlockProblem p;
-    if (!block_part(group, &part, &p, &xb, &z, &sg)) return;
+    if (!block_part(group, &part, &problem, &p, &xb, &z, &sg)) return;
     if constexpr (MB > 1) {
         if (z >= part.tall) {
-            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP, false, true>(p, xb, part.row0 + part.tall * 32 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
+            block_tile<BITS, MB - 1, MB, NG, 8 / WK, WK, ZP, false, true>(p, group.p[problem], xb, part.row0 + part.tall * 32 + z * (32 * (MB - 1)), sg, lds0, lds1, lds2, lds3);
             return;
         }
     }
-    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP, false, true>(p, xb, part.row0 + z * (32 * MB), sg, lds0, lds1, lds2, lds3);
+    block_tile<BITS, MB, MB, NG, 8 / WK, WK, ZP, false, true>(p, group.p[problem], xb, part.row0 + z * (32 * MB), sg, lds0, lds1, lds2, lds3);
 }
 
 }  // namespace

@@ -440,9 +440,8 @@ def test_planning_a_shared_launch_allocates_nothing(ask):
         assert out.split() == ["0", "1"], (mods, out)
 
 
-def test_no_kernel_of_the_linear_path_uses_scratch_memory(tmp_path):
-    """Registers that do not fit go to scratch memory, an access to it per use: none of the wide, block and tile kernels has any, by the
-    metadata of the built library's code objects."""
+def _code_objects(tmp_path):
+    """The gfx950 code objects of the built library, as files."""
     tools = "/opt/rocm/llvm/bin"
     lib = os.path.join(PKG, "librtn_gfx950.so")
     if not os.path.exists(os.path.join(tools, "llvm-objdump")) or not os.path.exists(lib):
@@ -450,12 +449,25 @@ def test_no_kernel_of_the_linear_path_uses_scratch_memory(tmp_path):
     copy = str(tmp_path / "lib.so")
     shutil.copy(lib, copy)
     subprocess.run([os.path.join(tools, "llvm-objdump"), "--offloading", copy], check=True, capture_output=True, timeout=120)
+    return tools, [str(tmp_path / f) for f in os.listdir(tmp_path) if "gfx950" in f]
+
+
+def test_buffer_resources_are_scalar(tmp_path):
+    """A buffer resource in vector registers is a loop over the lanes around each of its loads (v_cmp_eq_u64 against a lane's): no kernel
+    has any."""
+    tools, objects = _code_objects(tmp_path)
+    for o in objects:
+        r = subprocess.run(f"{tools}/llvm-objdump -d --no-show-raw-insn {o} | grep -c v_cmp_eq_u64", shell=True, capture_output=True, text=True, timeout=300)
+        assert r.stdout.strip() == "0", (o, r.stdout, r.stderr[-500:])
+
+
+def test_no_kernel_of_the_linear_path_uses_scratch_memory(tmp_path):
+    """Registers that do not fit go to scratch memory, an access to it per use: none of the wide, block and tile kernels has any, by the
+    metadata of the built library's code objects."""
+    tools, objects = _code_objects(tmp_path)
     sizes = {}
-    for name in os.listdir(tmp_path):
-        if "gfx950" not in name:
-            continue
-        notes = subprocess.run([os.path.join(tools, "llvm-readelf"), "--notes", str(tmp_path / name)], check=True, capture_output=True,
-                               text=True, timeout=120).stdout
+    for o in objects:
+        notes = subprocess.run([os.path.join(tools, "llvm-readelf"), "--notes", o], check=True, capture_output=True, text=True, timeout=120).stdout
         sizes.update(re.findall(r"\.name:\s+(\S+)\n\s+\.private_segment_fixed_size:\s+(\d+)", notes))
     kernels = {k: int(v) for k, v in sizes.items() if re.search("wide_mfma|block_mfma|tile_gemm", k)}
     assert len(kernels) > 50 and not {k: v for k, v in kernels.items() if v}
