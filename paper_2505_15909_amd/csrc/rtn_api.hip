@@ -1731,6 +1731,44 @@ struct SharedLaunch {
 };
 static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
 
+// A set of a grouped call's modules on the block kernel.  In a mixture-of-experts model their rows change with every call, so a plan is
+// made, and remembered, for classes of rows, up to 8 or 16 and then by 32, in an order of its own: all lists of up to 16 rows of like modules
+// share two plans (eight experts with rows drawn anew each call 0.4 us of host time, 25 for a plan of their own).  With more than 16 rows in
+// the set its time is that of the rows themselves.
+static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) {
+    int64_t most = 0;
+    for (int k = 0; k < l->count; ++k) most = std::max(most, args[l->member[k]].M);
+    auto row_class = [&](int j) { return args[j].M > 16 ? (args[j].M + 31) / 32 * 32 : most <= 8 ? (int64_t)8 : (int64_t)16; };
+    auto before = [&](int x, int y) {
+        const LinearArgs &a = args[x], &b = args[y];
+        if (a.N != b.N) return a.N > b.N;
+        if (a.K != b.K) return a.K > b.K;
+        if (a.g != b.g) return a.g > b.g;
+        return row_class(x) > row_class(y);
+    };
+    int order[rtn::kMaxBlockGroup];
+    for (int k = 0; k < l->count; ++k) {
+        int at = k;
+        for (; at > 0 && before(l->member[k], l->member[order[at - 1]]); --at) order[at] = order[at - 1];
+        order[at] = k;
+    }
+    LinearArgs set[rtn::kMaxBlockGroup];
+    for (int k = 0; k < l->count; ++k) {
+        set[k] = args[l->member[order[k]]];
+        set[k].M = row_class(l->member[order[k]]);
+    }
+    const MergedPlan p = remembered_merge(set, l->count, workspace);
+    l->plan = p;
+    if (p.us < 0.0) return;
+    for (int k = 0; k < l->count; ++k) {
+        l->plan.waves[order[k]] = p.waves[k];
+        l->plan.split[order[k]] = p.split[k];
+        set[k].M = args[l->member[order[k]]].M;
+    }
+    int longest;
+    if (most > 16) l->plan.us = merged_blocks_us(set, l->count, p, args[0].workspace ? workspace : 0, &longest);
+}
+
 // The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
 // (precision, groups per unit; the tile kernel: precision) together where that is modelled 3 % ahead of their own plans' launches
 // (20 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
@@ -1743,7 +1781,7 @@ constexpr int64_t kMaxMergedRows = 512;
 // kTogether: open, but alone if the first set that it is in is not put together (the other sets of a call's modules are not tried).
 enum : char { kOpen, kTogether, kAlone, kDone };
 static int shared_launches(const LinearArgs* args, const double* own_us, char* state, int n, size_t workspace_nbytes, bool tiles,
-                           SharedLaunch* out) {
+                           bool classes, SharedLaunch* out) {
     int launches = 0;
     for (int i = 0; i < n; ++i) {
         if (state[i] == kDone) continue;
@@ -1759,7 +1797,8 @@ static int shared_launches(const LinearArgs* args, const double* own_us, char* s
             l.member[l.count] = j;
             set[l.count++] = args[j];
         }
-        if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
+        if (l.count > 1 && classes) plan_set(args, &l, workspace_nbytes);
+        else if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
         const double line = !tiles && l.count == 2 && rows <= 16 ? 0.80 : 0.97;
         if (l.count < 2 || l.plan.us < 0.0 || l.plan.us > line * apart) {
             for (int k = 0; k < l.count; ++k)
@@ -1787,7 +1826,7 @@ static int layer_launches(const LinearArgs* args, int n, size_t workspace_nbytes
         own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
         state[i] = !*tiles || own.path == 4 ? kOpen : kAlone;
     }
-    return shared_launches(args, own_us, state, n, workspace_nbytes, *tiles, out);
+    return shared_launches(args, own_us, state, n, workspace_nbytes, *tiles, false, out);
 }
 
 static hipError_t launch_shared(const LinearArgs* args, const SharedLaunch& l, bool tiles, void* stream) {
@@ -1930,7 +1969,7 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         state[i] = grouped(i) ? kTogether : kOpen;
         own_us[i] = grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
     }
-    return shared_launches(args, own_us.data(), state.data(), n, workspace_nbytes, false, out);
+    return shared_launches(args, own_us.data(), state.data(), n, workspace_nbytes, false, true, out);
 }
 
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,

@@ -305,6 +305,26 @@ def test_linear_small_groups_above_sixteen_rows(rtn, bits, g, N, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M}")
 
 
+@pytest.mark.parametrize("bits,g,K", [(4, 64, 7168), (8, 0, 14336)])
+def test_grouped_calls_with_rows_of_their_own_each_time(rtn, bits, g, K):
+    """The weights of ten modules, as many calls with other rows each, as routing gives them: up to 8, up to 16, more in some, so that modules
+    change between the small-batch kernel's launches and shared ones of the block kernel and their sets change size."""
+    # (activations of other seeds than the weights', whose rows they would repeat: then outputs have a deviation of 0.02 sqrt(K) = 2.4 at most
+    # and stay under 16, where fp16 rounds by 2^-8 at most, as the common bound of 1e-2 supposes)
+    N = [528, 512, 544, 528, 512, 528, 560, 512, 528, 544]
+    weights = [_oracle_operands(n, K, bits, g, seed=i) for i, n in enumerate(N)]
+    for call, rows in enumerate(([1, 8, 3, 2, 5, 1, 4, 7, 2, 6], [16, 9, 12, 16, 1, 3, 11, 16, 10, 2], [16, 24, 12, 16, 33, 3, 11, 16, 10, 2],
+                                 [2, 16, 100, 9, 1, 40, 12, 3, 16, 17], [16, 16, 12, 16, 16, 9, 13, 16, 10, 12])):
+        mods = []
+        for i, (M, (_, _, qw, sc, _)) in enumerate(zip(rows, weights)):
+            mods.append(dict(A=synth.activation(M, K, seed=1000 + 100 * call + i, device=DEV), qweight=qw, scales=sc, bits=bits, group_size=g,
+                             C=torch.full((M, N[i]), float("nan"), dtype=torch.float16, device=DEV)))
+        rtn.LayerPlan(mods).run_grouped()
+        torch.cuda.synchronize()
+        for i, (m, (codes, scales, _, _, gg)) in enumerate(zip(mods, weights)):
+            H.assert_linear_close(_to_np(m["C"]), O.rtn_linear(_to_np(m["A"]), codes, scales, gg), f"call {call} module {i} of {rows[i]} rows")
+
+
 @pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),
                                       (8, 128, 2304), (8, 0, 2304)])
 @pytest.mark.parametrize("M", [17, 33, 65, 128, 161])

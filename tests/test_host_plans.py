@@ -425,6 +425,27 @@ def test_grouped_calls_of_few_rows_on_the_block_kernel(ask):
         assert [m for l in launches if l[0] == 3 for m, _ in l[3]] == members, (mods, launches)
 
 
+def _grouped(ask, mods, workspace=16 * MIB):
+    """Sets of modules that share launches of the block kernel in a grouped call, with their K splits."""
+    _, launches = _issued(ask, mods, workspace, "issued_grouped")
+    return [l[3] for l in launches if l[0] == 3]
+
+
+def test_grouped_plans_are_made_for_classes_of_rows(ask):
+    """Rows routed anew each call: all lists of up to 8 rows, and of up to 16, have the same sets, wavefronts along K and splits, and partial
+    sums of the rows themselves fit the workspace."""
+    for bits, g in ((8, 0), (4, 128)):
+        for lists in ([[16, 9, 12, 16, 13, 10, 11, 9], [9, 10, 16, 16, 12, 13, 14, 15], [12, 16, 16, 12, 12, 16, 10, 11]],
+                      [[17, 20, 32, 30, 18, 25, 22, 19], [32, 31, 30, 29, 28, 27, 26, 25]]):
+            calls = [f"issued_grouped {16 * MIB} 8 " + " ".join(f"{M} 2048 7168 {bits} {g}" for M in rows) for rows in lists]
+            out = ask(calls, raw=True)
+            assert len(set(out)) == 1 and "[3 " in out[0], (lists, out)
+    for workspace in (1 * MIB, 4 * MIB, 16 * MIB):
+        for rows in ([5] * 8, [16] * 8, [33] * 8, [17, 3, 2, 16, 40, 1, 9, 12]):
+            for s in _grouped(ask, [(M, 1024, 14336, 4, 128) for M in rows], workspace):
+                assert sum(rows[m] * 1024 * 4 * k for m, k in s if k > 1) <= workspace, (rows, workspace, s)
+
+
 def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
     """The problems that the GPU tests run with zero points: row blocks and wavefronts along K of their plans."""
     for (p, want), (status, launches) in zip(H.BLOCK_ZERO_POINTS.items(), ask([f"asym {' '.join(map(str, p))} {64 * MIB}" for p in H.BLOCK_ZERO_POINTS])):
