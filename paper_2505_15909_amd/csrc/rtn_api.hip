@@ -1731,44 +1731,6 @@ struct SharedLaunch {
 };
 static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
 
-// A set of a grouped call's modules on the block kernel.  In a mixture-of-experts model their rows change with every call, so a plan is
-// made, and remembered, for classes of rows, up to 8 or 16 and then by 32, in an order of its own: all lists of up to 16 rows of like modules
-// share two plans (eight experts with rows drawn anew each call 0.4 us of host time, 25 for a plan of their own).  With more than 16 rows in
-// the set its time is that of the rows themselves.
-static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) {
-    int64_t most = 0;
-    for (int k = 0; k < l->count; ++k) most = std::max(most, args[l->member[k]].M);
-    auto row_class = [&](int j) { return args[j].M > 16 ? (args[j].M + 31) / 32 * 32 : most <= 8 ? (int64_t)8 : (int64_t)16; };
-    auto before = [&](int x, int y) {
-        const LinearArgs &a = args[x], &b = args[y];
-        if (a.N != b.N) return a.N > b.N;
-        if (a.K != b.K) return a.K > b.K;
-        if (a.g != b.g) return a.g > b.g;
-        return row_class(x) > row_class(y);
-    };
-    int order[rtn::kMaxBlockGroup];
-    for (int k = 0; k < l->count; ++k) {
-        int at = k;
-        for (; at > 0 && before(l->member[k], l->member[order[at - 1]]); --at) order[at] = order[at - 1];
-        order[at] = k;
-    }
-    LinearArgs set[rtn::kMaxBlockGroup];
-    for (int k = 0; k < l->count; ++k) {
-        set[k] = args[l->member[order[k]]];
-        set[k].M = row_class(l->member[order[k]]);
-    }
-    const MergedPlan p = remembered_merge(set, l->count, workspace);
-    l->plan = p;
-    if (p.us < 0.0) return;
-    for (int k = 0; k < l->count; ++k) {
-        l->plan.waves[order[k]] = p.waves[k];
-        l->plan.split[order[k]] = p.split[k];
-        set[k].M = args[l->member[order[k]]].M;
-    }
-    int longest;
-    if (most > 16) l->plan.us = merged_blocks_us(set, l->count, p, args[0].workspace ? workspace : 0, &longest);
-}
-
 // The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
 // (precision, groups per unit; the tile kernel: precision) together where that is modelled 3 % ahead of their own plans' launches
 // (20 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
@@ -1778,10 +1740,10 @@ static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) 
 // 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.  Tile kernel: 8B layer int4 at 1536 rows 625 -> 553, 2048 rows 773 -> 726;
 // 5120-wide layer at 2048 rows 996 -> 900; closer to level it measures within 1 % either way.
 constexpr int64_t kMaxMergedRows = 512;
-// kTogether: open, but alone if the first set that it is in is not put together (the other sets of a call's modules are not tried).
-enum : char { kOpen, kTogether, kAlone, kDone };
+enum : char { kOpen, kSmall, kAlone, kDone };                   // kSmall: see grouped_blocks
+constexpr double kTogetherLine = 0.97, kTwoTogetherLine = 0.80;
 static int shared_launches(const LinearArgs* args, const double* own_us, char* state, int n, size_t workspace_nbytes, bool tiles,
-                           bool classes, SharedLaunch* out) {
+                           SharedLaunch* out) {
     int launches = 0;
     for (int i = 0; i < n; ++i) {
         if (state[i] == kDone) continue;
@@ -1790,19 +1752,16 @@ static int shared_launches(const LinearArgs* args, const double* own_us, char* s
         double apart = 0.0;
         int64_t rows = 0;
         l.count = 0;
-        for (int j = i; state[i] < kAlone && j < n && l.count < rtn::kMaxBlockGroup; ++j) {
-            if (state[j] >= kAlone || !(tiles ? args[i].bits == args[j].bits : one_block_class(args[i], args[j]))) continue;
+        for (int j = i; state[i] == kOpen && j < n && l.count < rtn::kMaxBlockGroup; ++j) {
+            if (state[j] != kOpen || !(tiles ? args[i].bits == args[j].bits : one_block_class(args[i], args[j]))) continue;
             apart += own_us[j];
             rows = std::max(rows, args[j].M);
             l.member[l.count] = j;
             set[l.count++] = args[j];
         }
-        if (l.count > 1 && classes) plan_set(args, &l, workspace_nbytes);
-        else if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
-        const double line = !tiles && l.count == 2 && rows <= 16 ? 0.80 : 0.97;
+        if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
+        const double line = !tiles && l.count == 2 && rows <= 16 ? kTwoTogetherLine : kTogetherLine;
         if (l.count < 2 || l.plan.us < 0.0 || l.plan.us > line * apart) {
-            for (int k = 0; k < l.count; ++k)
-                if (state[l.member[k]] == kTogether) state[l.member[k]] = kAlone;
             l.count = 1;
             l.member[0] = i;
         }
@@ -1826,7 +1785,7 @@ static int layer_launches(const LinearArgs* args, int n, size_t workspace_nbytes
         own_us[i] = own_plan_us(args[i], own, workspace_nbytes);
         state[i] = !*tiles || own.path == 4 ? kOpen : kAlone;
     }
-    return shared_launches(args, own_us, state, n, workspace_nbytes, *tiles, false, out);
+    return shared_launches(args, own_us, state, n, workspace_nbytes, *tiles, out);
 }
 
 static hipError_t launch_shared(const LinearArgs* args, const SharedLaunch& l, bool tiles, void* stream) {
@@ -1951,10 +1910,51 @@ static double grouped_share_us(const LinearArgs& a, int n) {
     return (3.0 / n + bytes / (a.bits == 8 ? 6.4e6 : 5.8e6)) * (slice < 50 << 10 ? 1.0 : slice < 100 << 10 ? 1.08 : slice < 150 << 10 ? 1.30 : 2.2);
 }
 
-// A grouped call's modules of up to 512 rows: together on the block kernel where that is modelled ahead of the small-batch kernel's grouped
-// launches or of launches of their own, as in a layer.  Eight of 2048 x 7168, int4 group 128, 1 to 8 rows 17.4 us on the small-batch
-// kernel, 15.1 here, 2 to 16 rows 30.5 and 15.9; int8 31.0 and 22.4; small modules stay (8 of 1024 x 2048 5.6, 7.4 here).  The modules
-// alone in their launch go on to the small-batch kernel's grouped launches.
+// A set of a grouped call's modules on the block kernel.  In a mixture-of-experts model their rows change with every call, so a plan is
+// made, and remembered, for classes of rows, up to 8 or 16 and then by 32, in an order of its own: all lists of up to 16 rows of like modules
+// share two plans (eight experts with rows drawn anew each call 0.4 us of host time, 25 for a plan of their own).  With more than 16 rows in
+// the set its time is that of the rows themselves.
+static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) {
+    int64_t most = 0;
+    for (int k = 0; k < l->count; ++k) most = std::max(most, args[l->member[k]].M);
+    auto row_class = [&](int j) { return args[j].M > 16 ? (args[j].M + 31) / 32 * 32 : most <= 8 ? (int64_t)8 : (int64_t)16; };
+    auto before = [&](int x, int y) {
+        const LinearArgs &a = args[x], &b = args[y];
+        if (a.N != b.N) return a.N > b.N;
+        if (a.K != b.K) return a.K > b.K;
+        if (a.g != b.g) return a.g > b.g;
+        return row_class(x) > row_class(y);
+    };
+    int order[rtn::kMaxBlockGroup];
+    for (int k = 0; k < l->count; ++k) {
+        int at = k;
+        for (; at > 0 && before(l->member[k], l->member[order[at - 1]]); --at) order[at] = order[at - 1];
+        order[at] = k;
+    }
+    LinearArgs set[rtn::kMaxBlockGroup];
+    for (int k = 0; k < l->count; ++k) {
+        set[k] = args[l->member[order[k]]];
+        set[k].M = row_class(l->member[order[k]]);
+    }
+    const MergedPlan p = remembered_merge(set, l->count, workspace);
+    l->plan = p;
+    if (p.us < 0.0) return;
+    for (int k = 0; k < l->count; ++k) {
+        l->plan.waves[order[k]] = p.waves[k];
+        l->plan.split[order[k]] = p.split[k];
+        set[k].M = args[l->member[order[k]]].M;
+    }
+    int longest;
+    if (most > 16) l->plan.us = merged_blocks_us(set, l->count, p, args[0].workspace ? workspace : 0, &longest);
+}
+
+// A grouped call's modules of up to 512 rows: together on the block kernel where that is modelled ahead of the launches that go out
+// otherwise.  Modules with a launch of their own (kOpen) make up the sets, in order; the small ones, which the small-batch kernel's
+// grouped launches serve, fill the places left where that is modelled level (200, 100 and six times 1 to 6 rows of 4096 x 4096: 0.98,
+// measured 30.0 and 34.2 us), and then make sets of their own.  Measured against the small-batch kernel, int4 group
+// 128: eight of 2048 x 7168 at 2 to 16 rows 30.5 us and 15.9, int8 31.0 and 22.4, 5280 x 6144 37.2 and 30.9; small modules
+// stay there (eight of 1024 x 2048 5.6, 7.4 here), as do few rows (2048 x 7168 at 1 to 8).  The modules alone in their launch go on
+// to the small-batch kernel's grouped launches.
 static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out) {
     std::vector<double> own_us((size_t)n, 0.0);
     std::vector<char> state((size_t)n, kAlone);
@@ -1966,10 +1966,64 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
     for (int i = 0; i < n; ++i) {
         if (args[i].M > kMaxMergedRows || (args[i].M <= 4 && !grouped(i))) continue;
         if (grouped(i) && bytes < 24e6 && args[i].M * args[i].K * 2 < 100 << 10) continue;      // none of these was ahead
-        state[i] = grouped(i) ? kTogether : kOpen;
+        state[i] = grouped(i) ? kSmall : kOpen;
         own_us[i] = grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
     }
-    return shared_launches(args, own_us.data(), state.data(), n, workspace_nbytes, false, true, out);
+    int launches = 0;
+    // up to eight modules of i's class from i on that are in `wanted`, after those in l; their time apart
+    auto gather = [&](SharedLaunch* l, int i, int from, char wanted) {
+        double apart = 0.0;
+        for (int j = from; j < n && l->count < rtn::kMaxBlockGroup; ++j) {
+            if (state[j] != wanted || !one_block_class(args[i], args[j])) continue;
+            apart += own_us[j];
+            l->member[l->count++] = j;
+        }
+        return apart;
+    };
+    auto ahead = [&](SharedLaunch* l, double apart, bool more_of_a_launch) {
+        if (l->count < 2) return false;
+        plan_set(args, l, workspace_nbytes);
+        int64_t rows = 0;
+        for (int k = 0; k < l->count; ++k) rows = std::max(rows, args[l->member[k]].M);
+        const double line = more_of_a_launch ? 1.0 : l->count == 2 && rows <= 16 ? kTwoTogetherLine : kTogetherLine;
+        return l->plan.us >= 0.0 && l->plan.us <= line * apart;
+    };
+    auto take = [&](const SharedLaunch& l) {
+        for (int k = 0; k < l.count; ++k) state[l.member[k]] = kDone;
+        out[launches++] = l;
+    };
+    for (char kind : {kOpen, kSmall})
+        for (int i = 0; i < n; ++i) {
+            if (state[i] != kind) continue;
+            SharedLaunch set, filled;
+            set.count = 0;
+            double apart = gather(&set, i, i, kind);
+            const bool together = ahead(&set, apart, false);
+            if (kind == kOpen) {
+                if (together) apart = set.plan.us;
+                filled = set;
+                apart += gather(&filled, i, 0, kSmall);
+                if (filled.count > set.count && ahead(&filled, apart, true)) {
+                    take(filled);
+                    continue;
+                }
+            }
+            if (together) {
+                take(set);
+            } else if (kind == kOpen) {
+                set.count = 1;
+                set.member[0] = i;
+                take(set);
+            } else {
+                for (int k = 0; k < set.count; ++k) state[set.member[k]] = kAlone;
+            }
+        }
+    for (int i = 0; i < n; ++i)
+        if (state[i] == kAlone) {
+            out[launches].count = 1;
+            out[launches++].member[0] = i;
+        }
+    return launches;
 }
 
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,

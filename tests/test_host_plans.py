@@ -431,6 +431,18 @@ def _grouped(ask, mods, workspace=16 * MIB):
     return [l[3] for l in launches if l[0] == 3]
 
 
+def test_small_modules_leave_the_larger_ones_of_a_grouped_call_together(ask):
+    """Modules of more than 16 rows make up sets first, wherever they stand; small ones join them where that is modelled level with the
+    launches that go out otherwise, and modules refused with them still share one."""
+    rows = [24, 15, 2, 7, 12, 11, 10, 2, 1, 1, 3, 100]
+    assert [[m for m, _ in s] for s in _grouped(ask, [(M, 4096, 2048, 4, 128) for M in rows])] == [[0, 11]]
+    assert [[m for m, _ in s] for s in _grouped(ask, [(M, 4096, 4096, 4, 128) for M in (200, 100, 2, 5, 1, 3, 1, 4)])] == [list(range(8))]
+    for lists in ([2, 200, 3, 1, 4, 100, 5, 2, 6, 2, 3, 180], [16] * 7 + [30, 31], [5, 19, 3, 9, 4, 16, 15, 16, 21, 13, 7, 4, 16, 1, 13, 14]):
+        sets = _grouped(ask, [(M, 4096, 2048, 4, 128) for M in lists])
+        large = [m for m, M in enumerate(lists) if M > 16]
+        assert set(large) <= {m for m, _ in sets[0]}, (lists, sets)
+
+
 def test_grouped_plans_are_made_for_classes_of_rows(ask):
     """Rows routed anew each call: all lists of up to 8 rows, and of up to 16, have the same sets, wavefronts along K and splits, and partial
     sums of the rows themselves fit the workspace."""
