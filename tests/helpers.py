@@ -101,6 +101,16 @@ SHARED_LAYERS = [(3, 2, [(100, 272, 14336, 4, 128), (101, 288, 14336, 4, 128)]),
                  (4, 2, [(1040, 2064, 14336, 4, 128), (1041, 2080, 14336, 4, 0)]),
                  (4, 2, [(1100 + i, 4112 + 16 * i, 4096, 8, 128) for i in range(4)])]
 
+# Launches of the block kernel with row tiles of two heights, which have more than 256 workgroups: explicit configurations (M, N, K, bits, g):
+# (m_rows16, wavefronts along K, K splits); automatic plans with zero points; and layers whose modules share the launch.
+TWO_HEIGHTS = {(129, 33040, 512, 4, 128): (8, 1, 1), (200, 33040, 512, 4, 128): (8, 1, 1), (200, 33040, 512, 8, 0): (8, 1, 1),
+               (200, 16528, 1024, 8, 128): (8, 2, 1), (129, 16528, 1536, 4, 256): (8, 2, 1), (300, 8272, 2048, 4, 128): (8, 4, 1), (300, 11296, 1536, 4, 0): (8, 1, 2),
+               (270, 13328, 1024, 4, 32): (4, 1, 1), (270, 6672, 1024, 8, 64): (4, 2, 1), (270, 3344, 2048, 4, 64): (4, 4, 1),
+               (80, 4176, 4096, 4, 128): (4, 8, 1), (80, 4176, 2304, 8, 32): (4, 8, 1)}
+TWO_HEIGHTS_ZP = [(129, 33040, 512, 4, 128), (129, 33040, 512, 4, 32), (200, 33040, 512, 8, 128), (200, 33040, 512, 4, 128), (300, 41232, 512, 4, 64)]
+TWO_HEIGHTS_LAYERS = [[(M + i, N, K, bits, g) for i, (N, K) in enumerate([(4112, 1024), (8208, 1024), (16400, 1024), (4112, 2048)])]
+                      for M, bits, g in ((129, 4, 128), (200, 4, 64), (300, 4, 128), (300, 8, 128))]
+
 # Grouped calls of modules of up to 16 rows that share a launch of the block kernel instead of the small-batch kernel's, and the modules
 # that do: (members, [(M, N, K, bits, g)]).
 GROUPED_ON_BLOCKS = [([0, 1, 2, 3], [(16, 528, 7168, 4, 64), (9, 528, 7168, 4, 64), (12, 512, 7168, 4, 64), (16, 544, 7168, 4, 64)]),

@@ -356,12 +356,77 @@ def test_linear_block_kernel_shapes(rtn, bits, g, K, M):
     H.assert_linear_close(_to_np(C), O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym int{bits} g={g} M={M} K={K}")
 
 
+def _some_columns(N, seed):
+    return np.unique(np.concatenate([np.arange(0, 16), np.arange(N - 16, N), np.random.default_rng(seed).integers(0, N, 96)]))
+
+
+@pytest.mark.parametrize("problem", list(H.TWO_HEIGHTS))
+def test_linear_row_tiles_of_two_heights(rtn, problem):
+    """Launches of more than a round, whose row tiles are of two heights in parts of their own (tests/test_host_plans.py): ragged N, each
+    number of wavefronts along K, a K split; a stripe of output columns against the oracle on the unpacked codes, nothing unwritten."""
+    M, N, K, bits, g = problem
+    rows, wk, split = H.TWO_HEIGHTS[problem]
+    qw, sc = rtn.rtn_quantize(synth.normal_weight(N, K, 0.02, seed=M, device=DEV), bits, g)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    C = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    workspace = torch.full((max(256, M * N * split),), float("nan"), dtype=torch.float32, device=DEV).view(torch.uint8)
+    rtn.rtn_linear(A_t, qw, sc, bits, g, out=C, workspace=workspace,
+                   cfg=dict(path=3, prefetch=1, m_rows16=rows, n_tiles16=2, waves_n=8, waves_k=wk, split_k=split))
+    torch.cuda.synchronize()
+    sel = _some_columns(N, M)
+    ref = O.rtn_linear(_to_np(A_t), _to_np(rtn.rtn_unpack(qw, N, K, bits))[sel], _to_np(sc)[sel], K if g == 0 else g)
+    H.assert_linear_close(_to_np(C)[:, sel], ref, f"{problem}")
+    assert not torch.isnan(C).any()
+
+
+@pytest.mark.parametrize("problem", H.TWO_HEIGHTS_ZP)
+def test_linear_asym_row_tiles_of_two_heights(rtn, problem):
+    """The same with zero points, by the plans that rtn_linear_asym makes."""
+    M, N, K, bits, g = problem
+    W = (synth.normal_weight(N, K, 0.02, seed=M, device=DEV).float() + 0.015).half()
+    qw, sc, zp = rtn.rtn_quantize_asym(W, bits, g)
+    A_t = synth.activation(M, K, seed=M + 1, device=DEV)
+    C = torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)
+    rtn.rtn_linear_asym(A_t, qw, sc, zp, bits, g, out=C, workspace=torch.empty(64 << 20, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    sel = _some_columns(N, M)
+    gg = K if g == 0 else g
+    codes, scales, zeros = O.rtn_quantize_asym(_to_np(W)[sel], bits, gg)
+    H.assert_linear_close(_to_np(C)[:, sel], O.rtn_linear_asym(_to_np(A_t), codes, scales, zeros, gg), f"asym {problem}")
+    assert not torch.isnan(C).any()
+
+
+@pytest.mark.parametrize("mods", H.TWO_HEIGHTS_LAYERS)
+def test_layer_row_tiles_of_two_heights(rtn, mods):
+    """The same with several modules in the launch, from a graph too."""
+    args, refs = [], []
+    for i, (M, N, K, bits, g) in enumerate(mods):
+        qw, sc = rtn.rtn_quantize(synth.normal_weight(N, K, 0.02, seed=i, device=DEV), bits, g)
+        A_t = synth.activation(M, K, seed=50 + i, device=DEV)
+        sel = _some_columns(N, i)
+        refs.append((sel, O.rtn_linear(_to_np(A_t), _to_np(rtn.rtn_unpack(qw, N, K, bits))[sel], _to_np(sc)[sel], K if g == 0 else g)))
+        args.append(dict(A=A_t, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.empty((M, N), dtype=torch.float16, device=DEV)))
+    plan = rtn.LayerPlan(args, workspace=torch.empty(16 << 20, dtype=torch.uint8, device=DEV))
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        plan.run()
+    for run in (plan.run, graph.replay, graph.replay):
+        for a in args:
+            a["C"].fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        for a, m, (sel, ref) in zip(args, mods, refs):
+            H.assert_linear_close(_to_np(a["C"])[:, sel], ref, f"{m}")
+            assert not torch.isnan(a["C"]).any(), m
+
+
 @pytest.mark.parametrize("bits,g,K", [(4, 128, 4608), (4, 32, 1536), (4, 0, 4096), (8, 64, 1280), (8, 128, 2304), (8, 0, 2304)])
 @pytest.mark.parametrize("M", [1, 9, 16, 129, 200, 300])
 def test_linear_block_kernel_few_rows_and_row_tiles_of_two_heights(rtn, bits, g, K, M):
-    """The block kernel where a workgroup stages 16 rows (the other 16 of its MFMAs read a row of zeros), and where row tiles have two
-    heights (129 rows: 96 and 64, 200: 128 and 96, 300: 128, 96 and 96), ragged N, every number of wavefronts along K, with and
-    without a K split."""
+    """The block kernel where a workgroup stages 16 rows (the other 16 of its MFMAs read a row of zeros), and where the last row tile is
+    only partly filled (all tiles are of one height: these launches are less than a round), ragged N, every number of wavefronts along K,
+    with and without a K split."""
     N = 304
     codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=M)
     A_t = synth.activation(M, K, seed=M + 1, device=DEV)

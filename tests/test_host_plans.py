@@ -351,16 +351,39 @@ def test_which_modules_share_launches_of_the_block_and_tile_kernels(ask):
                 assert mb == 1 and (wk > 1 or fullest <= 32), (bits, g, M, launches)
 
 
+def _heights(ask, mb, problems):
+    """Heights, in blocks of 32 rows, of the parts of a launch: problems are (M, N, wavefronts along K, splits)."""
+    raw = ask([f"parts {mb} {len(problems)} " + " ".join("%d %d %d %d" % p for p in problems)], raw=True)[0]
+    return [(i, mb if tall else mb - 1) for i, _, _, tall, _ in (map(int, b.split()) for b in re.findall(r"\[(.*?)\]", raw)[::2])]
+
+
 def test_row_tiles_of_two_heights_are_planned_as_they_are_launched(ask):
-    """8B layer: rows that leave a row tile of 32 rows less than the others cost less than the next full height (200 rows: 128 + 96), in
-    one launch, with partial sums within the workspace."""
-    for M in (150, 200, 300, 400):
+    """The problems that the GPU tests run for it are launched with tall and low row tiles; and on the 8B layer rows that leave a tile 32
+    rows less than the others cost less than the next full height (200 rows: 128 + 96), in one launch."""
+    for (M, N, K, bits, g), (rows16, wk, split) in H.TWO_HEIGHTS.items():
+        tiles = -(-M // (16 * rows16))
+        mb = -(-M // (32 * tiles))
+        assert _heights(ask, mb, [(M, N, wk, split)]) == [(0, mb), (0, mb - 1)], (M, N, K)
+    for (M, N, K, bits, g), (status, plans) in zip(H.TWO_HEIGHTS_ZP, ask([f"asym {' '.join(map(str, p))} {64 * MIB}" for p in H.TWO_HEIGHTS_ZP])):
+        p = plans[0]
+        tiles = -(-M // (16 * p["m_rows16"]))
+        mb = -(-M // (32 * tiles))
+        assert status == 0 and p["path"] == 3 and p["n_tiles16"] == 2
+        assert _heights(ask, mb, [(M, N, p["waves_k"], p["split_k"])]) == [(0, mb), (0, mb - 1)], (M, N, p)
+    for mods in H.TWO_HEIGHTS_LAYERS:
+        status, launches = _issued(ask, mods, 16 * MIB)
+        assert status == 0 and len(launches) == 1 and launches[0][0] == 3 and len(launches[0][3]) == len(mods)
+        _, mb, wk, members = launches[0]                    # (wk: the least of them, which has the fewest workgroups)
+        heights = _heights(ask, mb, [(mods[m][0], mods[m][1], wk, s) for m, s in members])
+        assert {h for _, h in heights} == {mb, mb - 1} and len(heights) > len(mods), (mods, heights)
+    for M, full in ((150, 192), (200, 256), (300, 384), (400, 512)):
         status, launches = _issued(ask, [(M, N, K, 4, 128) for N, K in LAYER_8B], 16 * MIB)
         assert status == 0 and len(launches) == 1 and launches[0][0] == 3
         _, mb, wk, members = launches[0]
-        tiles = -(-M // (32 * mb))
-        assert mb == -(-M // (32 * tiles)) and sum(M * LAYER_8B[m][0] * 4 * s for m, s in members if s > 1) <= 16 * MIB
-        assert wk == 1
+        assert {h for _, h in _heights(ask, mb, [(M, LAYER_8B[m][0], wk, s) for m, s in members])} == {mb, mb - 1}
+        low, high = (ask([f"merged {mb} 4 " + " ".join(f"{rows} {LAYER_8B[m][0]} {LAYER_8B[m][1]} 4 128 {wk} {s}" for m, s in members)])[0][0]
+                     for rows in (M, full))
+        assert low < 0.985 * high, (M, low, high)
 
 
 def test_parts_of_a_launch_of_the_block_kernel(ask):
