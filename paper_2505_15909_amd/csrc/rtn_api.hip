@@ -1732,16 +1732,19 @@ struct SharedLaunch {
 static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
 
 // The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
-// (precision, groups per unit; the tile kernel: precision) together where that is modelled 3 % ahead of their own plans' launches
-// (20 % for two modules up to 16 rows: int8 14336 x 4096 twice at 8 rows 28.5 us together, 26.0 apart), the others one by one.  On
-// the block kernel that line puts together 293 of 330 measured sets, of which 3 run more than 2 % slower for it, and leaves 14 apart
-// that would gain.  8B layer int4 group 128, apart -> together: 9 rows 36.5 -> 29.9 us, 32 rows 48.3 -> 31.2, 64 61.6 -> 38.0, 128
-// 85.1 -> 62.3, 256 125.5 -> 111.6; 70B layer 16 rows 98.8 -> 91.6, 32 110 -> 94, 128 231 -> 212; three modules of 4096 columns and
-// 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.  Tile kernel: 8B layer int4 at 1536 rows 625 -> 553, 2048 rows 773 -> 726;
-// 5120-wide layer at 2048 rows 996 -> 900; closer to level it measures within 1 % either way.
+// (precision, groups per unit; the tile kernel: precision) together where that is modelled ahead of their own plans' launches, the others
+// one by one.  How far ahead (together_line): up to 16 rows 3 %, two modules 20 % (int8 14336 x 4096 twice at 8 rows 28.5 us together,
+// 26.0 apart); above 16 rows not at all, since the models have launches apart too fast there: of 63 drawn sets and 40 layers that
+// they put between 0.97 and 1.066 two ran more than 2 % slower together (7 %), and they take 0.92 of the time on the mean (5120-wide layer
+// int8 at 257 rows 243 us apart, 207; 70B layer int4 group 64 at 50 rows 161 and 137); from there to 1.08 every second set did.
+// 8B layer int4 group 128, apart -> together: 9 rows 36.5 -> 28.4 us, 32 rows 48.3 -> 31.9, 64 61.6 -> 40.6, 128 85.1 -> 62.8; 70B layer
+// 16 rows 98.8 -> 88.5, 32 110 -> 94; three modules of 4096 columns and 4096, 1024, 1024 rows at 32 rows 23.6 -> 9.2.  Tile kernel, 3 %:
+// 8B layer int4 at 1536 rows 625 -> 553, 2048 rows 773 -> 726; 5120-wide layer at 2048 rows 996 -> 900; closer to level it measures
+// within 1 % either way.
 constexpr int64_t kMaxMergedRows = 512;
 enum : char { kOpen, kSmall, kAlone, kDone };                   // kSmall: see grouped_blocks
-constexpr double kTogetherLine = 0.97, kTwoTogetherLine = 0.80;
+// The line for sets of modules with that many rows at most: time together against time apart.
+static double together_line(int count, int64_t rows, bool tiles) { return tiles ? 0.97 : rows > 16 ? 1.066 : count == 2 ? 0.80 : 0.97; }
 static int shared_launches(const LinearArgs* args, const double* own_us, char* state, int n, size_t workspace_nbytes, bool tiles,
                            SharedLaunch* out) {
     int launches = 0;
@@ -1760,7 +1763,7 @@ static int shared_launches(const LinearArgs* args, const double* own_us, char* s
             set[l.count++] = args[j];
         }
         if (l.count > 1) l.plan = remembered_merge(set, l.count, tiles ? std::min(workspace_nbytes, kWorkspaceCapTile) : workspace_nbytes, tiles);
-        const double line = !tiles && l.count == 2 && rows <= 16 ? kTwoTogetherLine : kTogetherLine;
+        const double line = together_line(l.count, rows, tiles);
         if (l.count < 2 || l.plan.us < 0.0 || l.plan.us > line * apart) {
             l.count = 1;
             l.member[0] = i;
@@ -1985,7 +1988,7 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         plan_set(args, l, workspace_nbytes);
         int64_t rows = 0;
         for (int k = 0; k < l->count; ++k) rows = std::max(rows, args[l->member[k]].M);
-        const double line = more_of_a_launch ? 1.0 : l->count == 2 && rows <= 16 ? kTwoTogetherLine : kTogetherLine;
+        const double line = more_of_a_launch ? 1.0 : together_line(l->count, rows, false);
         return l->plan.us >= 0.0 && l->plan.us <= line * apart;
     };
     auto take = [&](const SharedLaunch& l) {

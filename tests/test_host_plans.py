@@ -357,6 +357,17 @@ def _heights(ask, mb, problems):
     return [(i, mb if tall else mb - 1) for i, _, _, tall, _ in (map(int, b.split()) for b in re.findall(r"\[(.*?)\]", raw)[::2])]
 
 
+def test_layers_that_measured_faster_together_share_a_launch(ask):
+    """Layers of more than 16 rows that the models put within 7 % of their modules' own launches either way, and that measured 2 to 14 %
+    faster in one."""
+    layers = {5120: [(15360, 5120), (5120, 5120), (27648, 5120), (5120, 13824)], 2560: [(2560, 2560), (2560, 9728), (9728, 2560)],
+              8192: [(10240, 8192), (8192, 8192), (57344, 8192), (8192, 28672)], 4096: LAYER_8B}
+    for width, M, bits, g in ((5120, 257, 8, 128), (5120, 161, 8, 128), (5120, 433, 4, 128), (2560, 273, 8, 128), (2560, 337, 4, 64), (8192, 257, 8, 128),
+                              (8192, 369, 8, 0), (8192, 50, 4, 64), (8192, 512, 4, 128), (4096, 512, 8, 0), (4096, 470, 8, 0)):
+        status, launches = _issued(ask, [(M, N, K, bits, g) for N, K in layers[width]], 64 * MIB)
+        assert status == 0 and len(launches) == 1 and launches[0][0] == 3, (width, M, bits, g, launches)
+
+
 def test_row_tiles_of_two_heights_are_planned_as_they_are_launched(ask):
     """The problems that the GPU tests run for it are launched with tall and low row tiles; and on the 8B layer rows that leave a tile 32
     rows less than the others cost less than the next full height (200 rows: 128 + 96), in one launch."""
