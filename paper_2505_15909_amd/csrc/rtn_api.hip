@@ -1446,7 +1446,8 @@ static bool merged_layer_plans(const LinearArgs* a, int n, size_t workspace_nbyt
 // Modelled time of a module's own plan.
 static double own_plan_us(const LinearArgs& a, const LinearPlan& p, size_t workspace_nbytes) {
     const double packed = (double)a.N * a.K * a.bits / 8.0;
-    if (p.path == 1) return 4.5 + packed / (a.bits == 8 ? 6.5e6 : a.M <= 16 ? 5.4e6 : 3.9e6);    // the skinny kernel
+    if (p.path == 1)                                               // the skinny kernel, and the reduce pass of a K split, a launch of its own
+        return 4.5 + packed / (a.bits == 8 ? 6.5e6 : a.M <= 16 ? 5.4e6 : 3.9e6) + (p.split_k > 1 ? 2.4 + (double)a.M * a.N * p.split_k * 8.0 / 4.2e6 : 0.0);
     if (p.path == 4) {
         double t;
         tile_two_launches(false, a.M, a.N, a.K, tile_workspace(a, workspace_nbytes), &t);
@@ -1733,8 +1734,8 @@ static_assert(rtn::kMaxTileGroup == rtn::kMaxBlockGroup, "");
 
 // The launches of n independent modules, in order of their first module: of those whose state is kOpen, modules of one class
 // (precision, groups per unit; the tile kernel: precision) together where that is modelled ahead of their own plans' launches, the others
-// one by one.  How far ahead (together_line): up to 16 rows 3 %, two modules 20 % (int8 14336 x 4096 twice at 8 rows 28.5 us together,
-// 26.0 apart); above 16 rows not at all, since the models have launches apart too fast there: of 63 drawn sets and 40 layers that
+// one by one.  How far ahead (together_line): up to 16 rows 3 %, two modules 20 % (a plan that rtn_layer_forward has always had; of 36 pairs
+// between 0.80 and 0.95 one measured more than 2 % slower together, and 0.94 on the mean); above 16 rows not at all, since the models have launches apart too fast there: of 63 drawn sets and 40 layers that
 // they put between 0.97 and 1.066 two ran more than 2 % slower together (7 %), and they take 0.92 of the time on the mean (5120-wide layer
 // int8 at 257 rows 243 us apart, 207; 70B layer int4 group 64 at 50 rows 161 and 137); from there to 1.08 every second set did.
 // 8B layer int4 group 128, apart -> together: 9 rows 36.5 -> 28.4 us, 32 rows 48.3 -> 31.9, 64 61.6 -> 40.6, 128 85.1 -> 62.8; 70B layer
