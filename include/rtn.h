@@ -274,8 +274,9 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
  * rtn_layer_forward, but nothing is launched unless every module passes, the launch order
  * is unspecified, and modules with M <= 16 and the same (bits, group size) class are merged,
  * up to 16 at a time, into single grids whose workgroups each serve one module, so that one
- * launch streams all their weights; modules of up to 512 rows that this leaves to launches of their own, or that are expected
- * to be faster there (activations of 100 KiB and more, long rows), share launches of the block kernel, as in rtn_layer_forward.  No dev_C may overlap any module's dev_A.  Results are
+ * launch streams all their weights; modules of up to 512 rows that this leaves to launches of their own share launches of
+ * the block kernel, as in rtn_layer_forward, and so do modules of M <= 16 where that is expected to be faster (considered from
+ * 24 MB of packed weights in the merged modules, or 100 KiB of activations in one).  No dev_C may overlap any module's dev_A.  Results are
  * those of rtn_linear with the plan rtn_grouped_forward picks (planned for the summed size),
  * which may differ from the single call's in summation order only. */
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace,

@@ -9,7 +9,9 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "librtn_gfx950.so")
 SOURCES = ["rtn_api.hip", "rtn_quantize.hip", "rtn_linear.hip", "rtn_linear_wide.hip", "rtn_linear_block4.hip", "rtn_linear_block4z.hip",
            "rtn_linear_block8.hip", "rtn_linear_block8z.hip", "rtn_gemm_tile.hip", "rtn_bench.hip"]
-# objects of several translation units, which compile side by side
+# The block kernel's instantiations are translation units of their own so that they compile side by side (one unit takes minutes).  They
+# are joined with the unit that launches them into one object: the host tests link the library's objects by name around a driver of
+# their own, and an object that refers to the others would have to be listed with them everywhere.
 JOINED = {"rtn_linear_wide.o": ["rtn_linear_wide.o", "rtn_linear_block4.o", "rtn_linear_block4z.o", "rtn_linear_block8.o", "rtn_linear_block8z.o"]}
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

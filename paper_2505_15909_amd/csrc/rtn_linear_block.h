@@ -1,4 +1,4 @@
-// Fused dequantise-GEMM from 17 rows (shared launches from 5): the block kernel, one translation unit per precision and variant
+// Fused dequantise-GEMM from 17 rows (shared launches of a layer from 5, of a grouped call from one): the block kernel, one translation unit per precision and variant
 // (rtn_linear_block4.hip, ...).  Exact integer codes in the MFMAs, the fp16 scale applied in fp32 to the partial sum of each group (or of
 // the part of a group that lies in a share of K: scaling is linear, so groups may straddle splits).
 //

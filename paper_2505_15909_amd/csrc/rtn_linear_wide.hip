@@ -272,7 +272,8 @@ bool wide_plan_valid(const LinearArgs& a, const LinearPlan& p) {
     return true;
 }
 
-// Row blocks of 32 rows per workgroup: row tiles of up to 16 m_rows16 rows, as many as that takes, of equal height.
+// Row blocks of 32 rows of the tallest row tile: as many tiles as up to 16 m_rows16 rows each take, of this height or one block less
+// (tall_row_tiles), of one height within a round (block_parts).
 static int block_rows32(int64_t M, int64_t N, int m_rows16) {
     const int64_t tiles = (M + 16 * m_rows16 - 1) / (16 * m_rows16);
     const int mb = (int)((M + 32 * tiles - 1) / (32 * tiles));
