@@ -9,7 +9,7 @@ Transformer layer (Section 4: QKV 4096->6144, attention output 4096->4096, gate_
 
 One step = one pass of the hot path over one batch of input: for every M, the layer's four
 modules through rtn_layer_forward (20 fused dequantise-GEMMs; the four independent modules go out as one
-launch, of the small-batch kernel at M = 1, 2, 4 and of the block kernel, with a reduce launch, at 8 and 16).  Every pass streams a different
+launch, of the small-batch kernel at M = 1, 2, 4 and of the block kernel at 8 and 16, there with a reduce launch).  Every pass streams a different
 copy of the packed layer (enough copies to exceed twice the 256 MB Infinity Cache), as token
 generation does when it walks a model's layers, so the weights come from HBM, not from cache.
 The load-time quantise/pack pass (Section 5) runs once during set-up, is checked to reproduce,
@@ -573,7 +573,7 @@ def main() -> int:
     flops = sum(2.0 * M * N * K for M in BATCHES for _, (K, N) in modules)
 
     # ---- roofline of the two kernels of a step: the int4 block kernel over the four modules of a layer in one grid (M = 8, 16:
-    # half of the step's time, its reduce launch for the K split of the down projection included) and the small-batch kernel
+    # half of the step's time, the reduce launch for the K split of the down projection at M = 16 included) and the small-batch kernel
     # over the same (M = 1, 2, 4).  A pair of HIP events on the launch stream brackets each kind's passes, issued back to back
     # (direct launches, no graph); the stream is first held busy so that the host has enqueued everything before the GPU gets
     # there, and the bracket times the GPU.  (Events around every single launch cost several microseconds each on this runtime
@@ -609,7 +609,7 @@ def main() -> int:
                 "algorithmic_bytes_per_launch": round(per_layer, 1)}
 
     roofline = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                **kernel_roofline(False, "rtn::block_mfma_kernel<4,1,4,false> (fused int4 g128 dequantise-GEMM, the four modules of a layer "
+                **kernel_roofline(False, "rtn::block_mfma_kernel<4,1,4> (fused int4 g128 dequantise-GEMM, the four modules of a layer "
                                          "in one launch, M = 8 and 16; the reduce launch of M = 16 included)", "traffic_bytes_per_launch"),
                 "merged_layers": kernel_roofline(True, "rtn::skinny_grouped_kernel<4,4,2,*> (the four modules of a layer in one launch, M = 1, 2, 4)",
                                                  "merged_traffic_bytes_per_launch")}
