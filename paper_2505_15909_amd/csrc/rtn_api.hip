@@ -1620,7 +1620,7 @@ static MergedPlan merged_blocks(const LinearArgs* a, int n, size_t workspace) {
                     double floor;
                     m.us = merged_blocks_us(a, n, m, workspace, &longest, best.us < 0.0 ? INFINITY : best_line, &floor);
                     if (m.us < 0.0) break;
-                    const double line = m.us * (deep && mb <= 2 ? 1.03 : 1.0);    
+                    const double line = m.us * (deep && mb <= 2 ? 1.03 : 1.0);
                     if (best.us < 0.0 || line < best_line) { best = m; best_line = line; }
                     if (deepen == 1 && floor >= best_line) break;
                     const int s = m.split[longest];
