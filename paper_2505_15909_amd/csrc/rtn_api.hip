@@ -1884,7 +1884,71 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
     return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
 }
 
-static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans) {
+// One launch of the small-batch kernel for alike modules (N, K, precision and groups; up to sixteen of 1 to 16 rows): one workgroup shape for
+// all of them.  A plan of each module's own leaves out that its workgroups share compute units with the others': every one gets the LDS of
+// the largest slice, so eight modules of 2048 x 7168 with 1 to 8 rows were 224 workgroups of 4 x 4 wavefronts and, for the one-row module,
+// 128 of 1 x 7, one a compute unit: a second round for 96 of them (16.7 us; as 256 of 4 x 3 13.9).  Modelled time: a start, 0.77 us for every
+// further round, the weights at 7.2 TB/s (8 bit: 9.2) by what the fullest compute unit streams over the mean, what the wavefronts in
+// flight can request, the staged rows at 11.4 TB/s, 0.15 us per thousand wavefronts; slices that take several stages are a launch of their
+// own.  Fitted to 5979 launches of 110 sets (1024 to 8192 columns, K 2048 to 7168, 2 to 16 modules of 1 to 16 rows, groups of 64, 128 and
+// a row): 8 % rms near the best; the pick is 3 % behind the best measured shape on the mean, 19 at most (plans of their own: 18 and 65).
+struct ModuleSetPlan { int wn, wk, nb; double us; };
+constexpr int kRowClasses[] = {1, 2, 3, 4, 6, 8, 10, 12, 14, 16};
+constexpr int kRowClassCount = sizeof(kRowClasses) / sizeof(kRowClasses[0]);
+// rows: modules of each class.  own: the plan that they would all have by themselves, or null: kept where the best is not 6 % ahead.
+static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, const LinearPlan* own) {
+    const int64_t NT = like.N / 16, KC = like.K / chunk_k(like.bits);
+    const double stream = like.bits == 8 ? 9.2e6 : 7.23e6;
+    LinearArgs a = like;
+    a.M = 1;
+    LinearPlan p = {};
+    p.path = 1; p.prefetch = p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
+    ModuleSetPlan best = {0, 0, 0, 0.0}, kept = best;
+    for (int wn : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16})
+        for (int wk : {1, 2, 3, 4, 5, 7, 8}) {
+            if (wn > NT || wk > KC || wn * wk < 4 || wn * wk > 16) continue;
+            const int64_t per = (KC + wk - 1) / wk, each = (NT + wn - 1) / wn;
+            p.waves_n = wn; p.waves_k = wk;
+            const size_t row = rtn::linear_stages(a, p).slice, sums = wk > 1 ? (size_t)(wk - 1) * wn * 1024 : 0;
+            // modules whose slice is staged at once, and those that take it in stages
+            int count[2] = {};
+            size_t staged[2] = {}, lds[2] = {sums, (size_t)66 << 10};
+            for (int c = 0; c < kRowClassCount; ++c) {
+                if (rows[c] == 0) continue;
+                const size_t slice = row * kRowClasses[c];
+                const int kind = slice > (size_t)150 << 10;
+                count[kind] += rows[c];
+                staged[kind] += slice * rows[c];
+                if (kind == 0) lds[0] = std::max(lds[0], slice);
+            }
+            for (int nb = 1; nb <= (per > 1 ? 2 : 1); ++nb) {
+                double us = 0.0;
+                for (int kind = 0; kind < 2; ++kind) {
+                    if (count[kind] == 0) continue;
+                    const double n = (double)(count[kind] * each), bytes = (double)count[kind] * NT * KC * 4096.0;
+                    const double resident = (double)std::max<size_t>(1, std::min((size_t)(32 / (wn * wk)), rtn::kMaxLdsBytes / std::max<size_t>(lds[kind], 1)));
+                    const double fullest = std::max(1.0, std::ceil(n / 256.0) * 256.0 * wn * KC * 4096.0 / bytes);
+                    const double flight = std::min(n / 256.0, resident) * wn * wk * nb * 4096.0 * 256.0;
+                    const double t = 2.9 + 0.774 * (std::ceil(n / (256.0 * resident)) - 1.0) + bytes / stream * std::pow(fullest, 0.703) + bytes * 0.33 / flight +
+                                     (double)staged[kind] * each / 11.4e6 + 0.152e-3 * n * wn * wk;
+                    us += kind == 0 ? t : 0.88 * t + (count[0] > 0 ? 3.7 : 0.0);
+                }
+                us *= 1.0 + 0.033 * (std::log2((double)wn) - 1.5) + 0.034 * (std::log2((double)wk) - 1.0) + 0.057 * (nb - 1.5);
+                if (best.wn == 0 || us < best.us) best = {wn, wk, nb, us};
+                if (own && own->waves_n == wn && own->waves_k == wk && own->prefetch == nb) kept = {wn, wk, nb, us};
+            }
+        }
+    if (kept.wn > 0 && best.us > 0.94 * kept.us) best = kept;
+    p.waves_n = best.wn; p.waves_k = best.wk; p.prefetch = best.nb;
+    for (int c = 0; c < kRowClassCount && best.wn > 0; ++c) {
+        a.M = kRowClasses[c];
+        if (rows[c] > 0 && !rtn::linear_plan_fits(a, p, (size_t)device_max_lds())) best.wn = 0;
+    }
+    return best;
+}
+
+// share_us: a module's part of the modelled time of its set, 0 for a module in none.
+static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans, double* share_us = nullptr) {
     const size_t lds_limit = (size_t)device_max_lds();
     int64_t steps_total = 0;                                   // of the modules the skinny kernel will serve
     for (int i = 0; i < n; ++i)
@@ -1901,6 +1965,40 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
         }
         if (st == RTN_ERR_CONFIG) st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);    // the module's own plan
         if (st != RTN_OK) return st;
+        if (share_us) share_us[i] = 0.0;
+    }
+    // Sets of alike modules (the errors of a call are those of the plans above).  Remembered for classes of rows: routing changes them
+    // with every call.
+    constexpr int kSet = 16;
+    std::vector<char> in_set((size_t)n, 0);
+    for (int i = 0; i < n; ++i) {
+        if (in_set[i] || args[i].M > 16 || plans[i].path != 1) continue;
+        int member[kSet], count = 0, rows[kRowClassCount] = {};
+        for (int j = i; j < n && count < kSet; ++j)
+            if (!in_set[j] && args[j].M <= 16 && plans[j].path == 1 && args[j].N == args[i].N && args[j].K == args[i].K && args[j].bits == args[i].bits &&
+                args[j].g == args[i].g)
+                member[count++] = j;
+        // (two modules whose own plans split K go to the block kernel together, as they have: 13.7 us, 12.4 as a set here)
+        if (count < 2 || (count == 2 && plans[member[0]].split_k + plans[member[1]].split_k > 2)) continue;
+        int64_t key = 0;
+        bool one_shape = true;
+        for (int k = 0; k < count; ++k) {
+            const LinearPlan &p = plans[member[k]], &first = plans[i];
+            one_shape = one_shape && p.split_k == 1 && p.waves_n == first.waves_n && p.waves_k == first.waves_k && p.prefetch == first.prefetch;
+            int c = 0;
+            while (kRowClasses[c] < args[member[k]].M) ++c;
+            ++rows[c];
+            key += (int64_t)1 << (5 * c);
+        }
+        static Remembered<ModuleSetPlan> remembered;
+        const ModuleSetPlan set = remembered.get({key, args[i].N, args[i].K, args[i].g, 0, lds_limit, args[i].bits, one_shape ? 1 + plans[i].waves_n * 64 + plans[i].waves_k * 4 + plans[i].prefetch : 0}, [&] { return module_set_plan(args[i], rows, one_shape ? &plans[i] : nullptr); });
+        for (int k = 0; k < count && set.wn > 0; ++k) {
+            LinearPlan& p = plans[member[k]];
+            p.prefetch = set.nb; p.waves_n = set.wn; p.waves_k = set.wk;
+            p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
+            if (share_us) share_us[member[k]] = set.us / count;
+            in_set[member[k]] = 1;
+        }
     }
     return RTN_OK;
 }
@@ -1959,7 +2057,7 @@ static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) 
 // 128: eight of 2048 x 7168 at 2 to 16 rows 30.5 us and 15.9, int8 31.0 and 22.4, 5280 x 6144 37.2 and 30.9; small modules
 // stay there (eight of 1024 x 2048 5.6, 7.4 here), as do few rows (2048 x 7168 at 1 to 8).  The modules alone in their launch go on
 // to the small-batch kernel's grouped launches.
-static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out) {
+static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out, const double* share_us = nullptr) {
     std::vector<double> own_us((size_t)n, 0.0);
     std::vector<char> state((size_t)n, kAlone);
     int small = 0;
@@ -1971,7 +2069,7 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         if (args[i].M > kMaxMergedRows || (args[i].M <= 4 && !grouped(i))) continue;
         if (grouped(i) && bytes < 24e6 && args[i].M * args[i].K * 2 < 100 << 10) continue;      // none of these was ahead
         state[i] = grouped(i) ? kSmall : kOpen;
-        own_us[i] = grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
+        own_us[i] = share_us && share_us[i] > 0.0 ? share_us[i] : grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
     }
     int launches = 0;
     // up to eight modules of i's class from i on that are in `wanted`, after those in l; their time apart
@@ -1999,6 +2097,31 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
     for (char kind : {kOpen, kSmall})
         for (int i = 0; i < n; ++i) {
             if (state[i] != kind) continue;
+            if (kind == kSmall && share_us && share_us[i] > 0.0) {
+                // a set with a plan of its own: all of it here, in launches of like size, or none (14 of 1056 x 7168, up to 12 rows: 23 us on
+                // the small-batch kernel, 25 as two launches here, 36 as one of eight and the others there)
+                int member[16], count = 0;
+                for (int j = i; j < n && count < 16; ++j)
+                    if (state[j] == kSmall && share_us[j] == share_us[i] && args[j].N == args[i].N && args[j].K == args[i].K && args[j].bits == args[i].bits && args[j].g == args[i].g)
+                        member[count++] = j;
+                const int parts = (count + rtn::kMaxBlockGroup - 1) / rtn::kMaxBlockGroup;
+                SharedLaunch part[2];
+                bool all = count >= 2;
+                double together = 0.0, line = 1.0;
+                for (int k = 0, at = 0; k < parts && all; ++k) {
+                    part[k].count = (count - at) / (parts - k);
+                    std::copy(member + at, member + at + part[k].count, part[k].member);
+                    at += part[k].count;
+                    plan_set(args, &part[k], workspace_nbytes);
+                    all = part[k].plan.us >= 0.0;
+                    together += part[k].plan.us;
+                    line = std::min(line, together_line(part[k].count, 16, false));
+                }
+                all = all && together <= line * share_us[i] * count;
+                for (int k = 0; k < parts && all; ++k) take(part[k]);
+                for (int k = 0; k < count && !all; ++k) state[member[k]] = kAlone;
+                continue;
+            }
             SharedLaunch set, filled;
             set.count = 0;
             double apart = gather(&set, i, i, kind);
@@ -2041,10 +2164,11 @@ rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_wor
         const rtn_status st = module_args(mods[i], dev_workspace, &args[i]);
         if (st != RTN_OK) return st;
     }
-    const rtn_status st = grouped_plans(args.data(), n_mods, workspace_nbytes, plans.data());
+    std::vector<double> share_us((size_t)n_mods);
+    const rtn_status st = grouped_plans(args.data(), n_mods, workspace_nbytes, plans.data(), share_us.data());
     if (st != RTN_OK) return st;
     std::vector<SharedLaunch> launches((size_t)n_mods);
-    launches.resize((size_t)grouped_blocks(args.data(), plans.data(), n_mods, workspace_nbytes, launches.data()));
+    launches.resize((size_t)grouped_blocks(args.data(), plans.data(), n_mods, workspace_nbytes, launches.data(), share_us.data()));
     std::vector<char> left((size_t)n_mods, 1);
     for (const SharedLaunch& l : launches) {
         if (l.count == 1) continue;

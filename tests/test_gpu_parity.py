@@ -325,6 +325,28 @@ def test_grouped_calls_with_rows_of_their_own_each_time(rtn, bits, g, K):
             H.assert_linear_close(_to_np(m["C"]), O.rtn_linear(_to_np(m["A"]), codes, scales, gg), f"call {call} module {i} of {rows[i]} rows")
 
 
+@pytest.mark.parametrize("bits,g,N,K,rows", [
+    (4, 128, 16, 512, [1, 2]),                              # one tile-row, one chunk: fewer than any workgroup shape takes
+    (4, 32, 272, 2048, [1, 16, 3]),
+    (8, 0, 528, 2304, [5, 2, 1, 7, 16, 4]),
+    (8, 128, 304, 7168, [1, 6, 3, 12, 5, 2, 10]),           # splits of K in the plans of their own
+    (4, 128, 272, 7168, [16, 1, 11, 9, 16, 2, 10, 3, 4, 14]),   # slices in one stage and in several
+    (4, 0, 272, 2048, [1 + i % 5 for i in range(19)]),      # more than a set holds
+])
+def test_grouped_sets_of_alike_modules(rtn, bits, g, N, K, rows):
+    """Modules of one N, K and precision share a workgroup shape in the small-batch kernel, or go to the block kernel as a whole."""
+    mods, refs = [], []
+    for i, M in enumerate(rows):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i % 4)
+        A = synth.activation(M, K, seed=500 + i, device=DEV)
+        mods.append(dict(A=A, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A), codes, scales, gg))
+    rtn.LayerPlan(mods).run_grouped()
+    torch.cuda.synchronize()
+    for i, (m, ref) in enumerate(zip(mods, refs)):
+        H.assert_linear_close(_to_np(m["C"]), ref, f"module {i} of {rows[i]} rows")
+
+
 @pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),
                                       (8, 128, 2304), (8, 0, 2304)])
 @pytest.mark.parametrize("M", [17, 33, 65, 128, 161])
