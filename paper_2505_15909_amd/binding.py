@@ -98,6 +98,11 @@ def _load() -> C.CDLL:
 
 
 _lib = _load()
+try:                                                      # the small calls in native code (csrc/rtn_native.cpp); without it they take 5.3 us of host time
+    from . import _native
+    _native.bind(C.cast(_lib.rtn_linear, C.c_void_p).value, C.cast(_lib.rtn_linear_asym, C.c_void_p).value)
+except ImportError:
+    _native = None
 EXPORTS = ["rtn_status_str", "rtn_layout_version", "rtn_qweight_nbytes", "rtn_scales_nbytes",
            "rtn_workspace_nbytes", "rtn_quantize", "rtn_quantize_host_staging_nbytes", "rtn_quantize_from_host", "rtn_linear", "rtn_linear_ex", "rtn_linear_query",
            "rtn_problem_status", "rtn_linear_validate", "rtn_linear_noalloc", "rtn_unpack", "rtn_dequantize", "rtn_gemm_fp16", "rtn_dense_weight_nbytes", "rtn_linear_dense",
@@ -177,6 +182,11 @@ def make_cfg(cfg):
 def rtn_linear(A: torch.Tensor, qweight: torch.Tensor, scales: torch.Tensor, bits: int, group_size: int,
                out: torch.Tensor = None, workspace: torch.Tensor = None, cfg=None) -> torch.Tensor:
     """A fp16 [M, K], packed qweight, scales fp16 [N, K/g] -> C fp16 [M, N]."""
+    if _native is not None and out is not None and workspace is not None and cfg is None:
+        st = _native.linear(A, qweight, scales, bits, group_size, out, workspace)
+        if st is not None:                                # (None: not for native code, see there)
+            _check(st, "rtn_linear")
+            return out
     _dev_fp16(A, "A")
     M, K = A.shape
     N = scales.shape[0]
@@ -357,6 +367,11 @@ def rtn_dequantize_asym(qweight, scales, zeros, N, K, bits, group_size, out=None
 
 
 def rtn_linear_asym(A, qweight, scales, zeros, bits, group_size, out=None, workspace=None):
+    if _native is not None and out is not None and workspace is not None:
+        st = _native.linear_asym(A, qweight, scales, zeros, bits, group_size, out, workspace)
+        if st is not None:
+            _check(st, "rtn_linear_asym")
+            return out
     _dev_fp16(A, "A")
     M, K = A.shape
     N = scales.shape[0]

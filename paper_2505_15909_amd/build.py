@@ -7,6 +7,7 @@ import subprocess
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "librtn_gfx950.so")
+NATIVE_PATH = os.path.join(PKG_DIR, "_native.so")
 SOURCES = ["rtn_api.hip", "rtn_quantize.hip", "rtn_linear.hip", "rtn_linear_wide.hip", "rtn_linear_block4.hip", "rtn_linear_block4z.hip",
            "rtn_linear_block8.hip", "rtn_linear_block8z.hip", "rtn_gemm_tile.hip", "rtn_bench.hip"]
 # The block kernel's instantiations are translation units of their own so that they compile side by side (one unit takes minutes).  They
@@ -19,6 +20,21 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compiles the binding's native calls (host code only) against the installed PyTorch."""
+    import sysconfig
+    from importlib.util import find_spec
+    torch_dir = os.path.dirname(find_spec("torch").origin)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(torch_dir, "include"),
+           "-I" + os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include", "-o", NATIVE_PATH,
+           os.path.join(CSRC, "rtn_native.cpp"), "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True, cwd=CSRC)
+    return NATIVE_PATH
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:
@@ -38,7 +54,9 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
+        native = pool.submit(build_native, verbose)
         objs = list(pool.map(compile_one, SOURCES))
+        native.result()
     for name, parts in JOINED.items():
         whole, parts = os.path.join(obj_dir, name), [os.path.join(obj_dir, p) for p in parts]
         subprocess.run(["ld", "-r", "-o", whole + ".joined", *parts], check=True)

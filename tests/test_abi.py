@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2505_15909_amd as rtn
 from oracle import rtn_oracle as O
@@ -396,3 +397,26 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("what", ["cpu tensor", "float32", "subclass", "not a tensor", "missing", "numpy int", "too few"])
+def test_native_call_leaves_what_is_not_plain_to_the_python_code(what):
+    """The binding's native call answers None, not an error of its own, for anything that it does not take; Python then raises as it did."""
+    from paper_2505_15909_amd import binding
+    assert binding._native is not None, "the native part of the binding is not built"
+
+    class Sub(torch.Tensor):
+        pass
+
+    A, q, s = torch.zeros((1, 512), dtype=torch.float16), torch.zeros(4096, dtype=torch.uint8), torch.zeros((16, 4), dtype=torch.float16)
+    args = [A, q, s, 4, 128, torch.zeros((1, 16), dtype=torch.float16), torch.zeros(256, dtype=torch.uint8)]
+    change = {"float32": (0, A.float()), "subclass": (1, q.as_subclass(Sub)), "not a tensor": (2, "scales"), "missing": (6, None), "numpy int": (3, np.int64(4))}
+    if what in change:
+        args[change[what][0]] = change[what][1]
+    if what == "too few":
+        args.pop()
+    assert binding._native.linear(*args) is None
+    assert binding._native.linear_asym(*args[:3], s, *args[3:]) is None
+    if what == "cpu tensor":
+        with pytest.raises(ValueError):
+            rtn.rtn_linear(*args[:5], out=args[5], workspace=args[6])

@@ -325,6 +325,36 @@ def test_grouped_calls_with_rows_of_their_own_each_time(rtn, bits, g, K):
             H.assert_linear_close(_to_np(m["C"]), O.rtn_linear(_to_np(m["A"]), codes, scales, gg), f"call {call} module {i} of {rows[i]} rows")
 
 
+@pytest.mark.parametrize("M", [1, 16, 40])
+@pytest.mark.parametrize("zp", [False, True])
+def test_native_call_is_the_python_call(rtn, monkeypatch, M, zp):
+    """With all buffers given a call goes through the binding's native part: the same bits, on the current stream, and the same errors."""
+    from paper_2505_15909_amd import binding
+    N, K = 272, 1024
+    W, A = synth.normal_weight(N, K, 0.02, seed=3, device=DEV), synth.activation(M, K, seed=4, device=DEV)
+    q, *sz = rtn.rtn_quantize_asym(W, 4, 128) if zp else rtn.rtn_quantize(W, 4, 128)
+    call = rtn.rtn_linear_asym if zp else rtn.rtn_linear
+    ws = torch.empty(max(256, rtn.rtn_workspace_nbytes(M, N, K, 4, 128)), dtype=torch.uint8, device=DEV)
+
+    def run(stream):
+        C = torch.zeros((M, N), dtype=torch.float16, device=DEV)
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            assert call(A, q, *sz, 4, 128, out=C, workspace=ws) is C
+        errors = []
+        for bad in ((A[:, ::2], q, *sz, 4, 128), (A, q, *sz, 5, 128), (A, q, *sz, 4, 96), (A[:, :1000].contiguous(), q, *sz, 4, 128)):
+            with pytest.raises((ValueError, rtn.RtnError)) as e:
+                call(*bad, out=C, workspace=ws)
+            errors.append((e.type, str(e.value)))
+        torch.cuda.synchronize()
+        return C, errors
+
+    C, errors = run(torch.cuda.Stream())
+    monkeypatch.setattr(binding, "_native", None)
+    C2, errors2 = run(torch.cuda.Stream())
+    assert torch.equal(C, C2) and errors == errors2 and C.abs().max() > 0
+
+
 @pytest.mark.parametrize("bits,g,N,K,rows", [
     (4, 128, 16, 512, [1, 2]),                              # one tile-row, one chunk: fewer than any workgroup shape takes
     (4, 32, 272, 2048, [1, 16, 3]),
