@@ -17,9 +17,9 @@
 //     instructions (the swizzle is in which piece a lane fetches);
 //   - a step runs in phases of 16 MFMAs; each phase reads the operands of the next one, so no MFMA waits for the LDS;
 //   - the one barrier of a step stands before its last phase, whose operands are in registers by then.  From there on
-//     the step's stage is free: the last phase reads the next step's first operands and requests a later step's tiles
-//     into the freed stage, so a request has a step (two, where the stages are short) to arrive and the matrix cores
-//     work across the barrier;
+//     the step's stage is free: the last phase reads the next step's first operands, and it and the phases behind it
+//     request a later step's tiles into the freed stage, so a request has a step (two, where the stages are short) to
+//     arrive and the matrix cores work across the barrier;
 //   - the MFMAs take the weights as their first operand: a lane then holds four consecutive columns of a row and the
 //     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
 // Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
@@ -109,6 +109,12 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // from HBM and get three; three for the short dense tile's activations, whose steps are half as long (4096 x 14336 at
     // 2048 rows: 223 -> 190 us).  Four for the short packed tile gained nothing.
     constexpr int SA = BSRC == 0 && MBW == 4 ? 3 : 2, SB = BSRC == 0 ? 3 : 2;
+    // The requests of a step, up to 64 KiB a compute unit, kept the wavefronts from issuing their MFMAs when they all stood in the one
+    // phase behind the barrier.  The activations' go out in AP phases from the barrier on, the dense weights', which have a
+    // stage more, from phase BP behind it.  With the order of the MFMAs below: dense 8192 x 8192 x 8192 788 -> 761 us, 8192 x
+    // 28672 at 4096 rows 1411 -> 1360, 28672 x 4096 at 1024 203 -> 194; int8 8192 x 8192 at 8192 862 -> 848, 28672 x 4096 at 2048 418
+    // -> 406.  Not the 4-bit tiles: that of 256 rows spills 15 registers for it and loses 1 %, that of 128 has few requests.
+    constexpr int AP = BSRC == 0 || (BSRC == 8 && MBW == 8) ? 2 : 1, BP = BSRC == 0 && PH == 4 ? 2 : 0;
     constexpr int U = BSRC == 0 ? 6 : 4;                     // steps per turn of the loop: every stage index is a literal
     // one object per stage: the compiler then knows that a load into one stage cannot touch reads of the other
     __shared__ __align__(16) uint8_t lds_a0[A_BYTES], lds_a1[A_BYTES], lds_a2[SA > 2 ? A_BYTES : 16];
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 
     // One step = PH phases of 16 MFMAs; every phase reads the operands of the next one.  The last phase's operands are in
     // registers when the barrier before it is passed, so from there on this step's stage is free: the last phase reads
-    // the next step's first operands and requests the tiles of the step after the next into the stage just freed.
+    // the next step's first operands, and from it on the tiles of a later step are requested into the stage just freed.
     auto step = [&](int u, int t) {
 #pragma unroll
         for (int ph = 0; ph < PH; ++ph) {
@@ -242,8 +248,10 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
             for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
+                for (int k = 0; k < 4; ++k) {
+                    const int r = b & 1 ? 3 - k : k;     // back and forth: one operand always stays (0.5-0.8 % less time)
                     acc[h * 4 + b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[i][r], aop[ph & 1][b], acc[h * 4 + b][r], 0, 0, 0);
+                }
             // weights on their way into LDS, spread over the phases: what the last phase stores belongs to the step after the
             // next (into the stage just freed), and the phase before the barrier stores nothing that the barrier would wait for
             int words = 0;
@@ -265,17 +273,27 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                     b_fill((u + 1) & 3, 3);
                 }
             }
-            if (ph == PH - 1) {
+            const int pa = (ph + 1) % PH;                     // phases since the barrier
+            int vm = 0;
+            const int fu = pa == 0 ? u : u + U - 1, ft = pa == 0 ? t : t - 1;    // the step whose stage that barrier freed
+            if (pa < AP) {
 #pragma unroll
-                for (int k = 0; k < NA; ++k) a_dma(u % SA, t + SA, k);
+                for (int k = pa * NA / AP; k < (pa + 1) * NA / AP; ++k) a_dma(fu % SA, ft + SA, k);
+                vm += NA / AP;
                 __builtin_amdgcn_sched_barrier(0x78F);       // everything but memory loads may cross: the counted waits rely on their order
-                if constexpr (BSRC == 0) {
+            }
+            if constexpr (BSRC == 0) {
+                if (BP == 0 ? pa == 0 : pa >= BP) {
+                    constexpr int EACH = BP == 0 ? NB : NB / (PH - BP);
 #pragma unroll
-                    for (int k = 0; k < NB; ++k) b_dma(u % SB, t + SB, k);
-                } else if constexpr (BSRC == 4) {
-                    if ((u & 1) == 0) b_load_packed((u >> 1) & 1, t + 4);      // chunk t/2 has just been used up
+                    for (int k = (pa - BP) * EACH; k < (pa - BP + 1) * EACH; ++k) b_dma(fu % SB, ft + SB, k);
+                    vm += EACH;
+                }
+            } else if (pa == AP - 1) {
+                if constexpr (BSRC == 4) {
+                    if ((fu & 1) == 0) { b_load_packed((fu >> 1) & 1, ft + 4); vm += 4; }    // chunk ft / 2 has just been used up
                 } else {
-                    b_load_packed((u + 1) & 1, t + 3);
+                    b_load_packed((fu + 1) & 1, ft + 3); vm += 4;
                 }
             }
             const int rd = ((ph + 1) % HB == 0 || HB == 1) ? 8 : 4;
@@ -286,7 +304,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                 if (words == 4) __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
                 else if (words == 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
                 else if (words == 1) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-                if (ph == PH - 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                if (g < vm) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
             if (words) __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -306,11 +324,12 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
     for (int v = 0; v < SA; ++v) {
 #pragma unroll
-        for (int k = 0; k < NA; ++k) a_dma(v, v, k);
+        for (int k = 0; k < (v == SA - 1 ? NA / AP : NA); ++k) a_dma(v, v, k);       // (the rest, in the first step)
         if constexpr (BSRC == 0) {
             __builtin_amdgcn_sched_barrier(0);
+            if (v < SA - 1 || BP == 0)
 #pragma unroll
-            for (int k = 0; k < NB; ++k) b_dma(v + SB - SA, v + SB - SA, k);
+                for (int k = 0; k < NB; ++k) b_dma(v + SB - SA, v + SB - SA, k);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -321,8 +340,8 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
         for (int w = 0; w < (PH == 2 ? 2 : 1); ++w) b_fill(1, w);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (BSRC == 8) b_load_packed(0, 2);
-    wait_and_barrier<(SA - 1) * NA + (BSRC == 0 ? (SB - 1) * NB : BSRC == 8 ? 4 : 0)>();
+    if constexpr (BSRC == 8 && AP == 1) b_load_packed(0, 2);
+    wait_and_barrier<(SA - 2) * NA + NA / AP + (BSRC == 0 ? (SB - (BP == 0 ? 1 : 2)) * NB : BSRC == 8 && AP == 1 ? 4 : 0)>();
     read_phase(0, 0);
     __builtin_amdgcn_sched_barrier(0);
 
