@@ -103,18 +103,20 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     const int sg = local / group.blocks[gi];                 // K split
     constexpr int TM = 32 * MBW;
     constexpr int A_BYTES = TM * 128, B_BYTES = kTN * 128;
-    constexpr int HB = MBW / 4;                              // phases per 32-column slice (four row blocks each)
-    constexpr int PH = 2 * HB;                               // phases per step
+    constexpr int PH = MBW / 2;                              // phases per step (two row blocks, 64 columns each)
     // Stages in LDS (a request has SA or SB steps less a phase to arrive), at most 160 KiB in all.  Dense weights stream
     // from HBM and get three; three for the short dense tile's activations, whose steps are half as long (4096 x 14336 at
     // 2048 rows: 223 -> 190 us).  Four for the short packed tile gained nothing.
     constexpr int SA = BSRC == 0 && MBW == 4 ? 3 : 2, SB = BSRC == 0 ? 3 : 2;
     // The requests of a step, up to 64 KiB a compute unit, kept the wavefronts from issuing their MFMAs when they all stood in the one
     // phase behind the barrier.  The activations' go out in AP phases from the barrier on, the dense weights', which have a
-    // stage more, from phase BP behind it.  With the order of the MFMAs below: dense 8192 x 8192 x 8192 788 -> 761 us, 8192 x
-    // 28672 at 4096 rows 1411 -> 1360, 28672 x 4096 at 1024 203 -> 194; int8 8192 x 8192 at 8192 862 -> 848, 28672 x 4096 at 2048 418
-    // -> 406.  Not the 4-bit tiles: that of 256 rows spills 15 registers for it and loses 1 %, that of 128 has few requests.
-    constexpr int AP = BSRC == 0 || (BSRC == 8 && MBW == 8) ? 2 : 1, BP = BSRC == 0 && PH == 4 ? 2 : 0;
+    // stage more, from phase BP behind it: dense 8192 x 8192 x 8192 788 -> 761 us, 8192 x 28672 at 4096 rows 1411 -> 1360, 28672 x
+    // 4096 at 1024 203 -> 194; int8 8192 x 8192 at 8192 862 -> 848; int4 there 818 -> 803.  The 128-row packed tiles have few.
+    constexpr int AP = BSRC == 0 || MBW == 8 ? 2 : 1, BP = BSRC == 0 && PH == 4 ? 2 : 0;
+    // The activation operands of the next phase take the place of this one's, row block by row block, but for the last phase of a step:
+    // with two sets the 256-row packed tiles, which unpack as well, spill (int4 8192 x 8192 at 8192 rows 803 us, 800 this way; int8 811 and
+    // 806).  Dense tiles have the registers, and are 1 % faster with two sets.
+    constexpr bool IN_PLACE = BSRC != 0 && MBW == 8;
     constexpr int U = BSRC == 0 ? 6 : 4;                     // steps per turn of the loop: every stage index is a literal
     // one object per stage: the compiler then knows that a load into one stage cannot touch reads of the other
     __shared__ __align__(16) uint8_t lds_a0[A_BYTES], lds_a1[A_BYTES], lds_a2[SA > 2 ? A_BYTES : 16];
@@ -218,21 +220,26 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     const uint32_t a_rd = (uint32_t)((wm * (TM / 2) + nl) * 128);
     const uint32_t b_rd = (uint32_t)((wn * 64 + nl) * 128);
     const uint32_t po0 = (uint32_t)((kq ^ (nl & 7)) * 16), po1 = (uint32_t)(((4 + kq) ^ (nl & 7)) * 16);
-    half8_t aop[2][4], bop[2][4];                            // operands of two phases / two slices
-    auto read_phase = [&](int u, int ph) {                   // operands of phase ph of step u (mod U)
-        const int i = ph / HB, h = ph % HB;
-        const uint32_t po = i ? po1 : po0;
-        if (h == 0) {
+    half8_t aop[2][2][2], bop[2][4];                         // operands: of two phases, row block, slice; of a step, slice
+    auto set = [](int u, int ph) { return IN_PLACE ? u & 1 : ph & 1; };
+    auto read_a = [&](int u, int ph, int b) {                // row block b of phase ph of step u (mod U)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bop[i][r] = *reinterpret_cast<const half8_t*>(stage_b(u % SB) + b_rd + r * 2048 + po);
-        }
+        for (int i = 0; i < 2; ++i)
+            aop[set(u, ph)][b][i] = *reinterpret_cast<const half8_t*>(stage_a(u % SA) + a_rd + (ph * 2 + b) * 2048 + (i ? po1 : po0));
+    };
+    auto read_b = [&](int u, int r) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) aop[ph & 1][b] = *reinterpret_cast<const half8_t*>(stage_a(u % SA) + a_rd + (h * 4 + b) * 2048 + po);
+        for (int i = 0; i < 2; ++i) bop[i][r] = *reinterpret_cast<const half8_t*>(stage_b(u % SB) + b_rd + r * 2048 + (i ? po1 : po0));
     };
 
     // One step = PH phases of 16 MFMAs; every phase reads the operands of the next one.  The last phase's operands are in
     // registers when the barrier before it is passed, so from there on this step's stage is free: the last phase reads
     // the next step's first operands, and from it on the tiles of a later step are requested into the stage just freed.
+    // The two slices of a step go into an accumulator one right after the other: that draws less power than to come back for it later
+    // (from registers alone, on the whole chip, 2.05 PFLOP/s against 1.95), and power is what bounds a full chip.  It takes all of a step's
+    // weight operands in registers; the last phase replaces them as it goes.  Against a slice after the other: dense 8192 x 8192 x 8192
+    // 768 -> 746 us, 4096 x 14336 at 2048 rows 188 -> 181; int4 830 -> 800, 8192 x 28672 at 4096 rows 1451 -> 1392; int8 832 -> 806, 1472
+    // -> 1402.  The 128-row packed tiles, which seldom fill the chip, are level.
     auto step = [&](int u, int t) {
 #pragma unroll
         for (int ph = 0; ph < PH; ++ph) {
@@ -243,35 +250,35 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                 else wait_and_barrier<0>();
                 __builtin_amdgcn_sched_barrier(0);
             }
-            read_phase(ph == PH - 1 ? u + 1 : u, ph == PH - 1 ? 0 : ph + 1);
-            const int i = ph / HB, h = ph % HB;
+            auto mfma = [&](int b, int r) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+                for (int i = 0; i < 2; ++i)
+                    acc[ph * 2 + b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[i][r], aop[set(u, ph)][b][i], acc[ph * 2 + b][r], 0, 0, 0);
+            };
+            if (IN_PLACE && ph < PH - 1) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int r = b & 1 ? 3 - k : k;     // back and forth: one operand always stays (0.5-0.8 % less time)
-                    acc[h * 4 + b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[i][r], aop[ph & 1][b], acc[h * 4 + b][r], 0, 0, 0);
+                for (int b = 0; b < 2; ++b) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mfma(b, r);
+                    read_a(u, ph + 1, b);
                 }
-            // weights on their way into LDS, spread over the phases: what the last phase stores belongs to the step after the
-            // next (into the stage just freed), and the phase before the barrier stores nothing that the barrier would wait for
+            } else {
+                for (int b = 0; b < 2; ++b) read_a(ph == PH - 1 ? u + 1 : u, ph == PH - 1 ? 0 : ph + 1, b);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    mfma(r & 1, r);
+                    mfma(~r & 1, r);
+                    if (ph == PH - 1) read_b(u + 1, r);
+                }
+            }
+            // weights on their way into LDS: not in the phase before the barrier, which would wait for the stores; in the last one, which
+            // has most operands, only where there are two phases (they belong to the step after the next then, into the stage just freed)
             int words = 0;
-            if constexpr (BSRC != 0) {
-                if (ph == PH - 1) {
-                    words = PH == 2 ? 2 : 1;
-#pragma unroll
-                    for (int w = 0; w < words; ++w) b_fill((u + 2) & 3, w);
-                } else if (PH == 2) {
-                    words = 2;
-#pragma unroll
-                    for (int w = 2; w < 4; ++w) b_fill((u + 1) & 3, w);
-                } else if (ph == 0) {
-                    words = 2;
-#pragma unroll
-                    for (int w = 1; w < 3; ++w) b_fill((u + 1) & 3, w);
-                } else if (ph == 1) {
-                    words = 1;
-                    b_fill((u + 1) & 3, 3);
-                }
+            if (BSRC != 0 && (PH == 2 || ph < 2)) {
+                words = 2;
+                const int w = PH == 2 ? 2 - 2 * ph : 2 * ph;
+                b_fill((u + (PH == 2 && ph == 1 ? 2 : 1)) & 3, w);
+                b_fill((u + (PH == 2 && ph == 1 ? 2 : 1)) & 3, w + 1);
             }
             const int pa = (ph + 1) % PH;                     // phases since the barrier
             int vm = 0;
@@ -296,14 +303,14 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                     b_load_packed((fu + 1) & 1, ft + 3); vm += 4;
                 }
             }
-            const int rd = ((ph + 1) % HB == 0 || HB == 1) ? 8 : 4;
 #pragma unroll
             for (int g = 0; g < 8; ++g) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                if (g * 2 < rd) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                if (words == 4) __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-                else if (words == 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-                else if (words == 1) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                if (ph == PH - 1) {
+                    if (g < 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    if (g & 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                } else if (IN_PLACE ? g % 4 == 3 : g < 4) __builtin_amdgcn_sched_group_barrier(0x100, IN_PLACE ? 2 : 1, 0);
+                if (words) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
                 if (g < vm) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             }
             if (words) __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
@@ -337,12 +344,14 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
         for (int w = 0; w < 4; ++w) b_fill(0, w);
 #pragma unroll
-        for (int w = 0; w < (PH == 2 ? 2 : 1); ++w) b_fill(1, w);
+        for (int w = 0; w < (PH == 2 ? 2 : 0); ++w) b_fill(1, w);
     }
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (BSRC == 8 && AP == 1) b_load_packed(0, 2);
     wait_and_barrier<(SA - 2) * NA + NA / AP + (BSRC == 0 ? (SB - (BP == 0 ? 1 : 2)) * NB : BSRC == 8 && AP == 1 ? 4 : 0)>();
-    read_phase(0, 0);
+    for (int b = 0; b < 2; ++b) read_a(0, 0, b);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) read_b(0, r);
     __builtin_amdgcn_sched_barrier(0);
 
     for (int t = 0;; t += U) {            // T is even; leaving between two steps keeps every wait inside an exact count
