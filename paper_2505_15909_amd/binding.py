@@ -1,8 +1,8 @@
 """Thin ctypes binding over the C ABI of include/rtn.h.
 
-Argument marshalling only: every step of the path runs in the HIP kernels of the shared
-library.  PyTorch supplies device memory and the current stream, nothing else.  There is
-no fallback: if the library cannot be loaded, importing this module raises.
+Argument marshalling only (plain calls of the linear layer: in the native module): every step
+of the path runs in the HIP kernels of the shared library.  PyTorch supplies device memory and
+the current stream, nothing else.  There is no fallback: if the library cannot be loaded, importing this module raises.
 """
 from __future__ import annotations
 

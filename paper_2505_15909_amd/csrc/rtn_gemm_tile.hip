@@ -20,6 +20,7 @@
 //     the step's stage is free: the last phase reads the next step's first operands, and it and the phases behind it
 //     request a later step's tiles into the freed stage, so a request has a step (two, where the stages are short) to
 //     arrive and the matrix cores work across the barrier;
+//   - the two slices of a step go into an accumulator one right after the other (see the step below);
 //   - the MFMAs take the weights as their first operand: a lane then holds four consecutive columns of a row and the
 //     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
 // Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
