@@ -182,6 +182,11 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
         w_lane[q] = (uint32_t)nt * (uint32_t)p.KL * 1024u + lane * 16;
         s_lane[q] = (uint32_t)(nt * 16 + nl) * (uint32_t)p.G * 2u;
     }
+    // Marked as read once (2) but for 4-bit weights in tall tiles, which other row tiles come back to: without the mark 28672 x 4096 at 512
+    // rows 94.0 -> 91.5 us, at 2048 371 -> 369, 8192 x 28672 at 512 in four splits 197 -> 189, 10240 x 8192 at 1024 156 -> 152.  8-bit
+    // weights take twice the room (4096 x 14336 at 1024 rows 144 -> 151 without it), and few row tiles are short (8192 x 28672 at 257
+    // rows int4 126 -> 131).
+    constexpr int STREAM = BSRC == 4 && MBW == 8 ? 0 : 2;
     auto b_load_packed = [&](int set, int t) {               // the unit of step t
         const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
         const uint32_t kc = ks >> 1;
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q], (int)(j * 2u), 0);
-            breg[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rb, w_lane[q], (int)(tile * 1024u), 2 /* nt */);
+            breg[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rb, w_lane[q], (int)(tile * 1024u), STREAM);
         }
     };
     // word w of the step: tile-row w >> 1, 32-column operand w & 1
