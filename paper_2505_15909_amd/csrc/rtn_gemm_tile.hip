@@ -174,7 +174,8 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // packed tile per tile-row -- two steps at 4 bit, one at 8 bit -- and its scales; two units are in registers ----
     constexpr int SPU = BSRC == 4 ? 2 : 1;                   // steps per unit
     u32x4_t breg[2][2];
-    uint16_t sreg[2][2];
+    uint16_t sreg[2][2];                                     // (8 bit)
+    uint32_t s_next[2], s_pair[2];                           // (4 bit) scales of two units
     uint32_t w_lane[2], s_lane[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -187,21 +188,36 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // weights take twice the room (4096 x 14336 at 1024 rows 144 -> 151 without it), and few row tiles are short (8192 x 28672 at 257
     // rows int4 126 -> 131).
     constexpr int STREAM = BSRC == 4 && MBW == 8 ? 0 : 2;
+    auto group_of = [&](uint32_t kc) { return __umulhi(kc, p.cpg_inv) + (kc & p.cpg_one); };      // branch-free
+    // Scales of 4-bit weights come for two units at once, the second one's in the lanes of odd kq: a load of two bytes a lane touches 16 cache
+    // lines (8192 x 28672 at 4096 rows 1381 -> 1362 us, 28672 x 4096 at 2048 381 -> 375, 8192 x 8192 at 8192 with half of them left out
+    // 772 -> 766).
     auto b_load_packed = [&](int set, int t) {               // the unit of step t
         const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
         const uint32_t kc = ks >> 1;
-        const uint32_t j = __umulhi(kc, p.cpg_inv) + (kc & p.cpg_one);   // branch-free group index
         const uint32_t tile = SPU == 2 ? kc : ks;
+        if (BSRC == 4 && set == 0) {
+            const uint32_t a = group_of(kc), b = group_of((uint32_t)(ks0 + min(t + 2, T - 1)) >> 1);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) s_next[q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q] + (kq & 1 ? b : a) * 2u, 0, 0);
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q], (int)(j * 2u), 0);
+            if constexpr (BSRC == 8) sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q], (int)(group_of(kc) * 2u), 0);
             breg[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rb, w_lane[q], (int)(tile * 1024u), STREAM);
+        }
+    };
+    auto s_take = [&]() {                                    // rows of 16 lanes: the even ones' scales and the odd ones', each in all lanes
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const auto r = __builtin_amdgcn_permlane16_swap(s_next[q], s_next[q], false, false);
+            s_pair[q] = r[0] | r[1] << 16;
         }
     };
     // word w of the step: tile-row w >> 1, 32-column operand w & 1
     auto b_store_packed = [&](int set, int half, int stage, int w) {
         const int q = w >> 1, o = w & 1;
-        const half_t s = __builtin_bit_cast(half_t, sreg[set][q]);
+        const half_t s = BSRC == 4 ? __builtin_bit_cast(half2_t, s_pair[q])[set] : __builtin_bit_cast(half_t, sreg[set][q]);
         const half2_t s2 = {s, s};
         Half8Words h;
         if constexpr (BSRC == 4) h.v = unpack_word4(breg[set][q][2 * half + o], magic);
@@ -252,7 +268,8 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
             if (ph == PH - 1) {
                 // the next step's tiles have landed: only what was requested after them may be outstanding
                 if constexpr (BSRC == 0) wait_and_barrier<(SA - 2) * NA + (SB - 2) * NB>();
-                else if (BSRC == 8 || (u & 1)) wait_and_barrier<4>();        // the packed unit requested in the last step
+                else if (BSRC == 8 || u == 1) wait_and_barrier<4>();         // the packed unit requested in the last step
+                else if (u == 3) wait_and_barrier<2>();                      // (without scales)
                 else wait_and_barrier<0>();
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -282,6 +299,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
             int words = 0;
             if (BSRC != 0 && (PH == 2 || ph < 2)) {
                 words = 2;
+                if (BSRC == 4 && u == (PH == 2 ? 2 : 3) && ph == (PH == 2 ? 1 : 0)) s_take();      // from here on the next two units
                 const int w = PH == 2 ? 2 - 2 * ph : 2 * ph;
                 b_fill((u + (PH == 2 && ph == 1 ? 2 : 1)) & 3, w);
                 b_fill((u + (PH == 2 && ph == 1 ? 2 : 1)) & 3, w + 1);
@@ -304,7 +322,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                 }
             } else if (pa == AP - 1) {
                 if constexpr (BSRC == 4) {
-                    if ((fu & 1) == 0) { b_load_packed((fu >> 1) & 1, ft + 4); vm += 4; }    // chunk ft / 2 has just been used up
+                    if ((fu & 1) == 0) { b_load_packed((fu >> 1) & 1, ft + 4); vm += fu == 0 ? 4 : 2; }    // chunk ft / 2 has just been used up
                 } else {
                     b_load_packed((fu + 1) & 1, ft + 3); vm += 4;
                 }
@@ -347,6 +365,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
         __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (BSRC != 0) {
+        if constexpr (BSRC == 4) s_take();
 #pragma unroll
         for (int w = 0; w < 4; ++w) b_fill(0, w);
 #pragma unroll

@@ -707,6 +707,23 @@ def test_tile_kernel_covers_every_tile(rtn, M, N, K):
         assert np.array_equal(_to_np(rtn.rtn_gemm_fp16(A_t, W_t, workspace=ws)).astype(np.float32), ref)
 
 
+@pytest.mark.parametrize("rows16,split", [(4, 1), (8, 1), (4, 5), (8, 5), (8, 12)])
+@pytest.mark.parametrize("g", [128, 256, 512, 1536])
+def test_tile_kernel_scales_of_two_units(rtn, g, rows16, split):
+    """4-bit tiles load the scales of two 128-column units at once: every group's scale is another power of two, shares of K of 12, 3, 2 and 1
+    units (an odd first unit, a pair that ends past the share).  Sums are multiples of 1/8 below 2^15, exact in fp32, so the result is the
+    exact one rounded once."""
+    M, N, K = 70, 272, 1536
+    rng = np.random.default_rng(g + rows16 + split)
+    A = rng.integers(-2, 3, (M, K)).astype(np.float16)
+    codes = rng.integers(-8, 8, (N, K)).astype(np.int8)
+    scales = np.exp2(-rng.integers(0, 4, (N, K // g))).astype(np.float16)
+    ref = A.astype(np.float32) @ (codes * np.repeat(scales.astype(np.float32), g, axis=1)).T
+    qw, sc = torch.from_numpy(O.pack_gfx950(codes, 4)).to(DEV), torch.from_numpy(scales).to(DEV)
+    C = rtn.rtn_linear(torch.from_numpy(A).to(DEV), qw, sc, 4, g, cfg=dict(path=4, m_rows16=rows16, split_k=split))
+    assert np.array_equal(_to_np(C), ref.astype(np.float16))
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 16, 128), (128, 128, 128), (200, 400, 2560), (1030, 272, 1024), (520, 4112, 384)])
 def test_dense_gemm_and_dual_path(rtn, M, N, K):
     """rtn_gemm_fp16 against an fp64 product of the same fp16 operands, and the dequantise-then-GEMM path of
