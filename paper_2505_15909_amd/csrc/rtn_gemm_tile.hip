@@ -426,7 +426,14 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
             const int row = h * 8 + (lane >> 3), piece = lane & 7;
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(mine + row * 128 + ((piece ^ (row & 7)) * 16));
             const int m = m0 + wm * (TM / 2) + b * 16 + row, n = n0 + wn * 64 + piece * 8;
-            if (m < p.M && n < p.N) *reinterpret_cast<u32x4_t*>(p.C + (int64_t)m * p.N + n) = v;
+            if (m >= p.M || n >= p.N) continue;
+            // Marked as streaming with dense weights: results that stay in the caches push the operands out (28672 x 4096 at 2048 rows 365 -> 340
+            // us, where the vendor library takes 342; 8192 x 8192 x 8192 736 -> 726; dequantise + GEMM 28672 x 4096 at 2048 rows 417 -> 394 us, 4096 x 4096 at 8192 208 -> 194, 8192 x 28672 at 4096 1405 -> 1401; with
+            // a kernel that reads the results behind it 457 -> 432, 227 -> 224).  Packed weights are read from HBM anyway, and such a reader
+            // is then 0.5 % slower (28672 x 4096 at 2048 rows 407 -> 409).
+            u32x4_t* c = reinterpret_cast<u32x4_t*>(p.C + (int64_t)m * p.N + n);
+            if constexpr (BSRC == 0) __builtin_nontemporal_store(v, c);
+            else *c = v;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
