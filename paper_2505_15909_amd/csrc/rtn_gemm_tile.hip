@@ -24,8 +24,8 @@
 //   - the MFMAs take the weights as their first operand: a lane then holds four consecutive columns of a row and the
 //     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
 // Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
-// 440 -> 395 us; 8192 x 28672 at 4096: int4 1556 -> 1445, dense 1490 -> 1376; 8192 x 8192 x 8192 dense 905 -> 770 us =
-// 1.43 PFLOP/s, where the vendor library reached 1.57 in bursts).  v_mfma_f32_32x32x16_f16 is 6 % faster on a quarter of
+// 440 -> 395 us; 8192 x 28672 at 4096: int4 1556 -> 1445, dense 1490 -> 1376; 8192 x 8192 x 8192 dense 905 -> 770 us; by
+// now, with what is said below, 364, 1345, 1304 and 726 = 1.51 PFLOP/s, the vendor library's time to 1 %).  v_mfma_f32_32x32x16_f16 is 6 % faster on a quarter of
 // the chip and 5 % slower on all of it (twice the accumulator traffic per flop); a raised wavefront priority around the
 // MFMAs is 5-8 % slower.
 //
@@ -163,8 +163,16 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
     for (int i = 0; i < NB; ++i)
         b_lane[i] = (wave * NB + i) * 8 + st_row < b_rows ? ((uint32_t)((wave * NB + i) * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u : kNoRow;
+    // Two addresses and an addition, where registers are short, for four (the kernel spilled four registers; it is as fast, 0.5 % either way):
+    // rows past M are beyond the resource by themselves, K < 2^23 keeps 256 rows of offsets in 32 bits.
+    const uint32_t a_first = ((uint32_t)(wave * NA * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u;
+    auto a_off = [&](int i) {
+        uint32_t next, o = i < 2 ? a_first : a_lane[2];
+        if (i & 1) asm volatile("v_add_u32 %0, %1, %2" : "=v"(next) : "s"(16u * (uint32_t)p.K), "v"(o));
+        return i & 1 ? next : o;
+    };
     auto a_dma = [&](int stage, int t, int i) {
-        load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, a_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
+        load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, BSRC == 4 && IN_PLACE ? a_off(i) : a_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
     };
     auto b_dma = [&](int stage, int t, int i) {
         load_to_lds(rb, stage_b(stage) + (wave * NB + i) * 1024, b_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
@@ -427,10 +435,10 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(mine + row * 128 + ((piece ^ (row & 7)) * 16));
             const int m = m0 + wm * (TM / 2) + b * 16 + row, n = n0 + wn * 64 + piece * 8;
             if (m >= p.M || n >= p.N) continue;
-            // Marked as streaming with dense weights: results that stay in the caches push the operands out (28672 x 4096 at 2048 rows 365 -> 340
-            // us, where the vendor library takes 342; 8192 x 8192 x 8192 736 -> 726; dequantise + GEMM 28672 x 4096 at 2048 rows 417 -> 394 us, 4096 x 4096 at 8192 208 -> 194, 8192 x 28672 at 4096 1405 -> 1401; with
-            // a kernel that reads the results behind it 457 -> 432, 227 -> 224).  Packed weights are read from HBM anyway, and such a reader
-            // is then 0.5 % slower (28672 x 4096 at 2048 rows 407 -> 409).
+            // Marked as streaming with dense weights: results that stay in the caches push the operands out (28672 x 4096 at 2048 rows
+            // 365 -> 340 us, where the vendor library takes 342; 8192 x 8192 x 8192 736 -> 726; dequantise + GEMM 28672 x 4096 at 2048
+            // rows 417 -> 394, 4096 x 4096 at 8192 208 -> 194, with a kernel that reads the results behind it 457 -> 432, 227 -> 224).
+            // With packed weights nothing is gained, and such a reader is 0.5 % slower (28672 x 4096 at 2048 rows 407 -> 409).
             u32x4_t* c = reinterpret_cast<u32x4_t*>(p.C + (int64_t)m * p.N + n);
             if constexpr (BSRC == 0) __builtin_nontemporal_store(v, c);
             else *c = v;
