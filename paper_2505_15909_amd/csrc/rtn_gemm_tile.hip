@@ -25,9 +25,9 @@
 //     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
 // Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
 // 440 -> 395 us; 8192 x 28672 at 4096: int4 1556 -> 1445, dense 1490 -> 1376; 8192 x 8192 x 8192 dense 905 -> 770 us; by
-// now, with what is said below, 364, 1345, 1304 and 726 = 1.51 PFLOP/s, the vendor library's time to 1 %).  v_mfma_f32_32x32x16_f16 is 6 % faster on a quarter of
-// the chip and 5 % slower on all of it (twice the accumulator traffic per flop); a raised wavefront priority around the
-// MFMAs is 5-8 % slower.
+// now, with what is said below, 364, 1345, 1304 and 726 = 1.51 PFLOP/s, the vendor library's time to 1 %).
+// v_mfma_f32_32x32x16_f16 is 6 % faster on a quarter of the chip and 5 % slower on all of it (twice the accumulator traffic
+// per flop); a raised wavefront priority around the MFMAs is 5-8 % slower.
 //
 // A launch takes several independent problems: its workgroups find theirs by a scan over first[], whose order (longest first)
 // lets the short ones fill the last round.  A launch of one problem takes the time it took without the table.
@@ -163,8 +163,9 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
     for (int i = 0; i < NB; ++i)
         b_lane[i] = (wave * NB + i) * 8 + st_row < b_rows ? ((uint32_t)((wave * NB + i) * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u : kNoRow;
-    // Two addresses and an addition, where registers are short, for four (the kernel spilled four registers; it is as fast, 0.5 % either way):
-    // rows past M are beyond the resource by themselves, K < 2^23 keeps 256 rows of offsets in 32 bits.
+    // Where registers are short two of the four addresses are the other two plus a row group: with four the 4-bit tall tile spills as many
+    // registers, at the same speed (28672 x 4096 at 2048 rows 380 us, 383 spilling; 8192 x 8192 at 8192 796 and 789).  Rows past M
+    // are beyond the resource by themselves there; K < 2^23 keeps the offsets of 256 rows in 32 bits.
     const uint32_t a_first = ((uint32_t)(wave * NA * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u;
     auto a_off = [&](int i) {
         uint32_t next, o = i < 2 ? a_first : a_lane[2];
