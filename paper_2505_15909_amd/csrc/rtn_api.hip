@@ -1887,64 +1887,81 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
 // One launch of the small-batch kernel for alike modules (N, K, precision and groups; up to sixteen of 1 to 16 rows): one workgroup shape for
 // all of them.  A plan of each module's own leaves out that its workgroups share compute units with the others': every one gets the LDS of
 // the largest slice, so eight modules of 2048 x 7168 with 1 to 8 rows were 224 workgroups of 4 x 4 wavefronts and, for the one-row module,
-// 128 of 1 x 7, one a compute unit: a second round for 96 of them (16.7 us; as 256 of 4 x 3 13.9).  Modelled time: a start, 0.77 us for every
+// 128 of 1 x 7, one a compute unit: a second round for 96 of them (16.6 us; as 256 of 4 x 3 13.3).  Modelled time: a start, 0.77 us for every
 // further round, the weights at 7.2 TB/s (8 bit: 9.2) by what the fullest compute unit streams over the mean, what the wavefronts in
-// flight can request, the staged rows at 11.4 TB/s, 0.15 us per thousand wavefronts; slices that take several stages are a launch of their
-// own.  Fitted to 5979 launches of 110 sets (1024 to 8192 columns, K 2048 to 7168, 2 to 16 modules of 1 to 16 rows, groups of 64, 128 and
-// a row): 8 % rms near the best; the pick is 3 % behind the best measured shape on the mean, 19 at most (plans of their own: 18 and 65).
+// flight can request, the staged rows at 11.4 TB/s, 0.15 us per thousand wavefronts; modules whose slice takes several stages are a launch
+// of their own.  Against 34 thousand launches of 2480 sets (1024 to 6208 columns, K 2048 to 14336, 2 to 16 modules of 1 to 16 rows, groups of
+// 64, 128 and a row) it is 2 % slow near the best shape, 8 % rms; the pick is 1.8 % behind the best of fourteen shapes on the mean, more than
+// 10 % behind in 5 % of the sets, 31 % at most.
 struct ModuleSetPlan { int wn, wk, nb; double us; };
-constexpr int kRowClasses[] = {1, 2, 3, 4, 6, 8, 10, 12, 14, 16};
-constexpr int kRowClassCount = sizeof(kRowClasses) / sizeof(kRowClasses[0]);
-// rows: modules of each class.  own: the plan that they would all have by themselves, or null: kept where the best is not 6 % ahead.
-static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, const LinearPlan* own) {
+constexpr int kModuleSet = 16, kSetRows = 16;                  // modules of a set at most (those of a launch), rows of one
+constexpr int kSetWavesN[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16}, kSetWavesK[] = {1, 2, 3, 4, 5, 7, 8};
+constexpr double kSetStart = 2.9;                              // us of a launch
+constexpr int64_t kSetStage = (int64_t)150 << 10;              // a larger slice goes through its workgroup in stages or fills its LDS
+// Chunks that the wavefronts of a workgroup along K take in all; 0 for a shape that leaves more than a quarter of them idle (none of these
+// was the fastest by more than 0.1 % on the mean).
+static int64_t set_chunks(int64_t KC, int wk) {
+    const int64_t all = (KC + wk - 1) / wk * wk;
+    return wk <= KC && 3 * all <= 4 * KC ? all : 0;
+}
+// rows[m]: modules of m rows.  own: the plan that they would all have by themselves, or null: kept where the best is not 6 % ahead.  wn is
+// 0 where no shape can run the module of the most rows (those of fewer rows run wherever it does).
+static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, const LinearPlan* own, size_t lds_limit) {
     const int64_t NT = like.N / 16, KC = like.K / chunk_k(like.bits);
     const double stream = like.bits == 8 ? 9.2e6 : 7.23e6;
     LinearArgs a = like;
-    a.M = 1;
+    int most = kSetRows;
+    while (most > 1 && rows[most] == 0) --most;
     LinearPlan p = {};
-    p.path = 1; p.prefetch = p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
+    p.path = 1; p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
     ModuleSetPlan best = {0, 0, 0, 0.0}, kept = best;
-    for (int wn : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16})
-        for (int wk : {1, 2, 3, 4, 5, 7, 8}) {
-            if (wn > NT || wk > KC || wn * wk < 4 || wn * wk > 16) continue;
-            const int64_t per = (KC + wk - 1) / wk, each = (NT + wn - 1) / wn;
-            p.waves_n = wn; p.waves_k = wk;
-            const size_t row = rtn::linear_stages(a, p).slice, sums = wk > 1 ? (size_t)(wk - 1) * wn * 1024 : 0;
-            // modules whose slice is staged at once, and those that take it in stages
+    for (int wk : kSetWavesK) {
+        const int64_t chunks = set_chunks(KC, wk);
+        if (chunks == 0) continue;
+        p.waves_k = wk;
+        double fixed[17] = {}, requests[17] = {};            // us by wn; requests: by the chunks in flight
+        for (int nb = 1; nb <= (chunks > wk ? 2 : 1); ++nb) {
+            p.prefetch = nb; p.waves_n = 1;
+            a.M = 1;
+            const size_t row = rtn::linear_stages(a, p).slice;
+            const bool stages = row * most > (size_t)kSetStage;      // (they depend on the chunks in flight)
+            // modules whose slice is staged at once, and those that take it in stages: a launch each
             int count[2] = {};
-            size_t staged[2] = {}, lds[2] = {sums, (size_t)66 << 10};
-            for (int c = 0; c < kRowClassCount; ++c) {
-                if (rows[c] == 0) continue;
-                const size_t slice = row * kRowClasses[c];
-                const int kind = slice > (size_t)150 << 10;
-                count[kind] += rows[c];
-                staged[kind] += slice * rows[c];
-                if (kind == 0) lds[0] = std::max(lds[0], slice);
+            size_t staged[2] = {}, lds[2] = {};
+            for (int m = 1; m <= most && (nb == 1 || stages); ++m) {
+                if (rows[m] == 0) continue;
+                rtn::StagePlan s = {0, 1, row * m, row * m};
+                a.M = m;
+                if (s.slice > (size_t)kSetStage) s = rtn::linear_stages(a, p);
+                const int kind = s.nstage > 1;
+                count[kind] += rows[m];
+                staged[kind] += s.slice * rows[m];
+                lds[kind] = std::max(lds[kind], s.lds);
             }
-            for (int nb = 1; nb <= (per > 1 ? 2 : 1); ++nb) {
-                double us = 0.0;
-                for (int kind = 0; kind < 2; ++kind) {
+            a.M = most;
+            for (int wn : kSetWavesN) {
+                if (wn > NT || wn * wk < 4 || wn * wk > 16) continue;
+                p.waves_n = wn;
+                if (nb == 1 || stages) fixed[wn] = requests[wn] = 0.0;
+                for (int kind = 0; kind < 2 && (nb == 1 || stages); ++kind) {
                     if (count[kind] == 0) continue;
-                    const double n = (double)(count[kind] * each), bytes = (double)count[kind] * NT * KC * 4096.0;
-                    const double resident = (double)std::max<size_t>(1, std::min((size_t)(32 / (wn * wk)), rtn::kMaxLdsBytes / std::max<size_t>(lds[kind], 1)));
-                    const double fullest = std::max(1.0, std::ceil(n / 256.0) * 256.0 * wn * KC * 4096.0 / bytes);
-                    const double flight = std::min(n / 256.0, resident) * wn * wk * nb * 4096.0 * 256.0;
-                    const double t = 2.9 + 0.774 * (std::ceil(n / (256.0 * resident)) - 1.0) + bytes / stream * std::pow(fullest, 0.703) + bytes * 0.33 / flight +
-                                     (double)staged[kind] * each / 11.4e6 + 0.152e-3 * n * wn * wk;
-                    us += kind == 0 ? t : 0.88 * t + (count[0] > 0 ? 3.7 : 0.0);
+                    const int64_t workgroups = count[kind] * ((NT + wn - 1) / wn);
+                    const int64_t by_lds = (int64_t)(rtn::kMaxLdsBytes / std::max(lds[kind], (size_t)(wk - 1) * wn * 1024));
+                    const int64_t resident = std::max<int64_t>(1, std::min<int64_t>(32 / (wn * wk), by_lds));
+                    const double n = (double)workgroups, bytes = (double)count[kind] * NT * KC * 4096.0;
+                    const double fullest = std::max(1.0, (double)((workgroups + 255) / 256 * 256 * wn * KC) * 4096.0 / bytes);
+                    fixed[wn] += kSetStart + 0.774 * (double)((workgroups + 256 * resident - 1) / (256 * resident) - 1) + bytes / stream * std::pow(fullest, 0.703) +
+                                (double)staged[kind] * (n / count[kind]) / 11.4e6 + 0.152e-3 * n * wn * wk;
+                    requests[wn] += bytes * 0.33 / (std::min(n / 256.0, (double)resident) * wn * wk * 4096.0 * 256.0);
                 }
-                us *= 1.0 + 0.033 * (std::log2((double)wn) - 1.5) + 0.034 * (std::log2((double)wk) - 1.0) + 0.057 * (nb - 1.5);
-                if (best.wn == 0 || us < best.us) best = {wn, wk, nb, us};
+                const double shape = 1.0 + 0.033 * (std::log2((double)wn) - 1.5) + 0.034 * (std::log2((double)wk) - 1.0) + 0.057 * (nb - 1.5);
+                const double us = (fixed[wn] + requests[wn] / nb) * shape;
                 if (own && own->waves_n == wn && own->waves_k == wk && own->prefetch == nb) kept = {wn, wk, nb, us};
+                if ((best.wn == 0 || us < best.us) && rtn::linear_plan_fits(a, p, lds_limit)) best = {wn, wk, nb, us};
             }
         }
-    if (kept.wn > 0 && best.us > 0.94 * kept.us) best = kept;
-    p.waves_n = best.wn; p.waves_k = best.wk; p.prefetch = best.nb;
-    for (int c = 0; c < kRowClassCount && best.wn > 0; ++c) {
-        a.M = kRowClasses[c];
-        if (rows[c] > 0 && !rtn::linear_plan_fits(a, p, (size_t)device_max_lds())) best.wn = 0;
     }
-    return best;
+    return kept.wn > 0 && (best.wn == 0 || best.us > 0.94 * kept.us) ? kept : best;
 }
 
 // share_us: a module's part of the modelled time of its set, 0 for a module in none.
@@ -1967,37 +1984,36 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
         if (st != RTN_OK) return st;
         if (share_us) share_us[i] = 0.0;
     }
-    // Sets of alike modules (the errors of a call are those of the plans above).  Remembered for classes of rows: routing changes them
-    // with every call.
-    constexpr int kSet = 16;
-    std::vector<char> in_set((size_t)n, 0);
+    // Sets of alike modules (the errors of a call are those of the plans above)
+    std::vector<char> tried((size_t)n, 0);                     // in a set, whether or not a shape was found for it
+    auto candidate = [&](int i) { return !tried[i] && args[i].M <= 16 && plans[i].path == 1; };
     for (int i = 0; i < n; ++i) {
-        if (in_set[i] || args[i].M > 16 || plans[i].path != 1) continue;
-        int member[kSet], count = 0, rows[kRowClassCount] = {};
-        for (int j = i; j < n && count < kSet; ++j)
-            if (!in_set[j] && args[j].M <= 16 && plans[j].path == 1 && args[j].N == args[i].N && args[j].K == args[i].K && args[j].bits == args[i].bits &&
-                args[j].g == args[i].g)
+        if (!candidate(i)) continue;
+        int member[kModuleSet], count = 0, rows[kSetRows + 1] = {};
+        for (int j = i; j < n && count < kModuleSet; ++j)
+            if (candidate(j) && args[j].N == args[i].N && args[j].K == args[i].K && args[j].bits == args[i].bits && args[j].g == args[i].g)
                 member[count++] = j;
+        for (int k = 0; k < count; ++k) tried[member[k]] = 1;
         // (two modules whose own plans split K go to the block kernel together, as they have: 13.7 us, 12.4 as a set here)
         if (count < 2 || (count == 2 && plans[member[0]].split_k + plans[member[1]].split_k > 2)) continue;
-        int64_t key = 0;
+        int64_t key[2] = {};
         bool one_shape = true;
+        const LinearPlan first = plans[i];
         for (int k = 0; k < count; ++k) {
-            const LinearPlan &p = plans[member[k]], &first = plans[i];
+            const LinearPlan& p = plans[member[k]];
             one_shape = one_shape && p.split_k == 1 && p.waves_n == first.waves_n && p.waves_k == first.waves_k && p.prefetch == first.prefetch;
-            int c = 0;
-            while (kRowClasses[c] < args[member[k]].M) ++c;
-            ++rows[c];
-            key += (int64_t)1 << (5 * c);
         }
+        for (int k = 0; k < count; ++k) ++rows[args[member[k]].M];
+        for (int m = 0; m < kSetRows; ++m) key[m / 12] |= (int64_t)rows[m + 1] << (5 * (m % 12));
         static Remembered<ModuleSetPlan> remembered;
-        const ModuleSetPlan set = remembered.get({key, args[i].N, args[i].K, args[i].g, 0, lds_limit, args[i].bits, one_shape ? 1 + plans[i].waves_n * 64 + plans[i].waves_k * 4 + plans[i].prefetch : 0}, [&] { return module_set_plan(args[i], rows, one_shape ? &plans[i] : nullptr); });
+        const int own = one_shape ? 1 + first.waves_n * 64 + first.waves_k * 4 + first.prefetch : 0;
+        const ModuleSetPlan set = remembered.get({key[0], args[i].N, args[i].K, args[i].g, (size_t)key[1], lds_limit, args[i].bits, own},
+                                                 [&] { return module_set_plan(args[i], rows, one_shape ? &first : nullptr, lds_limit); });
         for (int k = 0; k < count && set.wn > 0; ++k) {
             LinearPlan& p = plans[member[k]];
             p.prefetch = set.nb; p.waves_n = set.wn; p.waves_k = set.wk;
             p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
             if (share_us) share_us[member[k]] = set.us / count;
-            in_set[member[k]] = 1;
         }
     }
     return RTN_OK;

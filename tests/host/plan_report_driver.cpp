@@ -152,6 +152,25 @@ int main() {
                 for (int k = 0; k < l[i].count; ++k) printf(" %d %d", l[i].member[k], alone ? 0 : l[i].plan.split[k]);
                 printf("]");
             }
+        } else if (!strcmp(what, "sets")) {                    // workspace n, then M N K bits g each -> status, then plan and [share, 1 if the plan can run] of each module
+            long ws;                                           // share: of the modelled time of its set, in picoseconds, 0 in none
+            int n;
+            if (scanf("%ld %d", &ws, &n) != 2 || n < 1 || n > 64) return 1;
+            LinearArgs a[64];
+            LinearPlan plan[64];
+            double share_us[64];
+            for (int i = 0; i < n; ++i) {
+                long M, N, K, g;
+                int bits;
+                if (scanf("%ld %ld %ld %d %ld", &M, &N, &K, &bits, &g) != 5) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
+            }
+            const rtn_status st = grouped_plans(a, n, (size_t)ws, plan, share_us);
+            printf("%d", (int)st);
+            for (int i = 0; st == RTN_OK && i < n; ++i) {
+                print_plan(a[i], plan[i]);
+                printf(" [%ld %d]", (long)(share_us[i] * 1e6), rtn::linear_plan_fits(a[i], plan[i], (size_t)device_max_lds()) ? 1 : 0);
+            }
         } else if (!strcmp(what, "layer") || !strcmp(what, "grouped")) {   // bits g workspace n, then M N K each
             // layer -> 1 if one launch, plans; grouped -> status, [launch of each]
             long g, ws;

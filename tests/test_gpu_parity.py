@@ -361,6 +361,8 @@ def test_native_call_is_the_python_call(rtn, monkeypatch, M, zp):
     (8, 0, 528, 2304, [5, 2, 1, 7, 16, 4]),
     (8, 128, 304, 7168, [1, 6, 3, 12, 5, 2, 10]),           # splits of K in the plans of their own
     (4, 128, 272, 7168, [16, 1, 11, 9, 16, 2, 10, 3, 4, 14]),   # slices in one stage and in several
+    (4, 128, 1040, 4096, [16, 15, 16, 14]),                 # the widest staged slices: shapes that cannot hold them are passed over
+    (4, 64, 272, 6144, [13, 12, 16, 3, 10, 13]),            # 13 rows fill the LDS in one stage or come in several, by the shape
     (4, 0, 272, 2048, [1 + i % 5 for i in range(19)]),      # more than a set holds
 ])
 def test_grouped_sets_of_alike_modules(rtn, bits, g, N, K, rows):

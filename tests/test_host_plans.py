@@ -1,6 +1,7 @@
 """The plans behind a call, on the CPU: a small host program (tests/host/plan_report_driver.cpp) holds the library's planning
 code and prints, for each problem it reads, the launches the call would issue.  Nothing is launched."""
 import os
+import random
 import re
 import shutil
 import subprocess
@@ -497,6 +498,39 @@ def test_grouped_plans_are_made_for_classes_of_rows(ask):
         for rows in ([5] * 8, [16] * 8, [33] * 8, [17, 3, 2, 16, 40, 1, 9, 12]):
             for s in _grouped(ask, [(M, 1024, 14336, 4, 128) for M in rows], workspace):
                 assert sum(rows[m] * 1024 * 4 * k for m, k in s if k > 1) <= workspace, (rows, workspace, s)
+
+
+def _sets(ask, calls, workspace=16 * MIB):
+    """Of each grouped call and each of its modules: (plan, share of its set's modelled time, whether the plan can run)."""
+    lines = [f"sets {workspace} {len(mods)} " + " ".join(" ".join(map(str, m)) for m in mods) for mods in calls]
+    out = []
+    for line in ask(lines, raw=True):
+        groups = [tuple(map(int, g.split())) for g in re.findall(r"\[(.*?)\]", line)]
+        assert line.split()[0] == "0"
+        out.append([(dict(zip(FIELDS, p)), share, fits) for p, (share, fits) in zip(groups[::2], groups[1::2])])
+    return out
+
+
+def _drawn_sets(seed, calls):
+    """Calls of two to sixteen alike modules of up to 16 rows: N, K, precision, groups and rows drawn."""
+    rng = random.Random(seed)
+    for _ in range(calls):
+        bits, K = rng.choice((4, 4, 8)), 512 * rng.choice((4, 7, 8, 12, 13, 14, 28))
+        N, g, most = 16 * int(2 ** rng.uniform(4, 9)), rng.choice((128, 128, 64, 32, 0)), rng.randint(1, 16)
+        yield [(rng.randint(1, most), N, K, bits, g) for _ in range(rng.randint(2, 16))]
+
+
+def test_alike_modules_of_a_grouped_call_share_a_shape_that_runs(ask):
+    """The first sets are ones whose fastest modelled shape cannot hold the rows of the largest module: all of their modules, and those of
+    drawn sets, share the fastest shape of those that can."""
+    calls = [[(16, 1024, 4096, 4, 128)] * 8, [(15, 1024, 4096, 4, 128), (16, 1024, 4096, 4, 128)] * 2, [(14, 1024, 6656, 4, 128)] * 8,
+             [(16, 2048, 3584, 4, 128)] * 4, [(M, 2048, 7168, 4, 128) for M in (16, 1, 11, 9, 16, 2, 10, 3)], *_drawn_sets(5, 600)]
+    for mods, modules in zip(calls, _sets(ask, calls)):
+        assert all(fits for _, _, fits in modules), mods
+        if len(mods) == 2 and not modules[0][1]:              # a pair whose own plans split K makes no set
+            continue
+        assert all(share > 0 for _, share, _ in modules), mods
+        assert len({(p["waves_n"], p["waves_k"], p["prefetch"], p["split_k"]) for p, _, _ in modules}) == 1, mods
 
 
 def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
