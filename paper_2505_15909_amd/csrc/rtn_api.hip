@@ -396,7 +396,7 @@ int64_t two_launches_modelled(bool dense, int64_t M, int64_t N, int64_t K, size_
 
 // Plans above 16 rows are the best of some hundred modelled candidates, 5-30 us of host time: remembered per problem in a
 // table of fixed size (an entry gives way to the next one that falls on it).
-template <typename Value> struct Remembered {
+template <typename Value, size_t kEntries = 1024> struct Remembered {
     struct Key {
         int64_t M, N, K, g;
         size_t workspace, lds;
@@ -405,7 +405,6 @@ template <typename Value> struct Remembered {
             return M == o.M && N == o.N && K == o.K && g == o.g && workspace == o.workspace && lds == o.lds && bits == o.bits && kind == o.kind;
         }
     };
-    static constexpr size_t kEntries = 1024;
     struct Entry { Key key; Value value; bool used; };
     std::mutex mutex;
     Entry table[kEntries] = {};
@@ -1964,6 +1963,42 @@ static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, co
     return kept.wn > 0 && (best.wn == 0 || best.us > 0.94 * kept.us) ? kept : best;
 }
 
+// The rows that a set is planned for.  In a mixture-of-experts model they change with every call, so a plan is made, and remembered, for what
+// its time depends on.  Up to `sure` rows a slice is staged at once whatever the shape: these modules stand for one of the most rows and the
+// others of the mean, or, beside larger ones, of half as many.  From `never` rows on it goes in stages in every shape: these count as their
+// largest.  In between every row counts.  40 thousand lists drawn for eight modules of 1 to 16 rows are planned as 86 with 2048 or
+// 4096 columns, 1145 with 6144 and 367 with 7168; the model puts the pick 0.01 % behind that for the rows themselves on the mean of 6000 drawn sets, 3.8 % at most.
+static void module_set_rows(const LinearArgs* args, const int* member, int count, int* rows) {
+    const LinearArgs& like = args[member[0]];
+    const int64_t chunk = chunk_k(like.bits), KC = like.K / chunk;
+    int64_t padded = KC;
+    for (int wk : kSetWavesK) padded = std::max(padded, set_chunks(KC, wk));
+    auto slice = [&](int64_t m, int64_t chunks) { return m * (chunks * chunk + 8) * 2; };
+    int sure = 0, never = kSetRows + 1;
+    while (sure < kSetRows && slice(sure + 1, padded) <= kSetStage) ++sure;
+    while (never > 1 && slice(never - 1, KC) > (int64_t)rtn::kMaxLdsBytes) --never;
+    int few = 0, most_few = 0, sum = 0, many = 0, most = 0;
+    for (int k = 0; k < count; ++k) {
+        const int m = (int)args[member[k]].M;
+        if (m <= sure) {
+            ++few;
+            most_few = std::max(most_few, m);
+            sum += m;
+        } else if (m < never) {
+            ++rows[m];
+        } else {
+            ++many;
+            most = std::max(most, m);
+        }
+    }
+    if (many > 0) rows[most] += many;
+    if (few == 0) return;
+    const bool all = few == count;
+    const int top = all ? most_few : sure, others = all ? (sum - top + (count - 1) / 2) / (count - 1) : (sure + 1) / 2;
+    ++rows[top];
+    rows[std::max(1, others)] += few - 1;
+}
+
 // share_us: a module's part of the modelled time of its set, 0 for a module in none.
 static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans, double* share_us = nullptr) {
     const size_t lds_limit = (size_t)device_max_lds();
@@ -2003,9 +2038,9 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
             const LinearPlan& p = plans[member[k]];
             one_shape = one_shape && p.split_k == 1 && p.waves_n == first.waves_n && p.waves_k == first.waves_k && p.prefetch == first.prefetch;
         }
-        for (int k = 0; k < count; ++k) ++rows[args[member[k]].M];
+        module_set_rows(args, member, count, rows);
         for (int m = 0; m < kSetRows; ++m) key[m / 12] |= (int64_t)rows[m + 1] << (5 * (m % 12));
-        static Remembered<ModuleSetPlan> remembered;
+        static Remembered<ModuleSetPlan, 4096> remembered;
         const int own = one_shape ? 1 + first.waves_n * 64 + first.waves_k * 4 + first.prefetch : 0;
         const ModuleSetPlan set = remembered.get({key[0], args[i].N, args[i].K, args[i].g, (size_t)key[1], lds_limit, args[i].bits, own},
                                                  [&] { return module_set_plan(args[i], rows, one_shape ? &first : nullptr, lds_limit); });

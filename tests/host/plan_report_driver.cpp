@@ -171,6 +171,21 @@ int main() {
                 print_plan(a[i], plan[i]);
                 printf(" [%ld %d]", (long)(share_us[i] * 1e6), rtn::linear_plan_fits(a[i], plan[i], (size_t)device_max_lds()) ? 1 : 0);
             }
+        } else if (!strcmp(what, "set_rows")) {                // N K bits g n, then M each -> [modules of 1, 2, .. 16 rows] that such a set is planned for
+            long N, K, g;
+            int bits, n, member[kModuleSet], rows[kSetRows + 1] = {};
+            if (scanf("%ld %ld %d %ld %d", &N, &K, &bits, &g, &n) != 5 || n < 2 || n > kModuleSet) return 1;
+            LinearArgs a[kModuleSet];
+            for (int i = 0; i < n; ++i) {
+                long M;
+                if (scanf("%ld", &M) != 1 || M < 1 || M > kSetRows) return 1;
+                a[i] = problem(M, N, K, bits, g > 0 ? g : K, true);
+                member[i] = i;
+            }
+            module_set_rows(a, member, n, rows);
+            printf("0 [");
+            for (int m = 1; m <= kSetRows; ++m) printf("%d ", rows[m]);
+            printf("]");
         } else if (!strcmp(what, "layer") || !strcmp(what, "grouped")) {   // bits g workspace n, then M N K each
             // layer -> 1 if one launch, plans; grouped -> status, [launch of each]
             long g, ws;

@@ -533,6 +533,19 @@ def test_alike_modules_of_a_grouped_call_share_a_shape_that_runs(ask):
         assert len({(p["waves_n"], p["waves_k"], p["prefetch"], p["split_k"]) for p, _, _ in modules}) == 1, mods
 
 
+@pytest.mark.parametrize("K,bits,most", [(2048, 4, 136), (4096, 4, 136), (6144, 4, 1145), (7168, 4, 400), (7168, 8, 400), (14336, 4, 300)])
+def test_routing_meets_few_plans_of_a_set(ask, K, bits, most):
+    """Eight modules whose rows are drawn anew each call: 4000 calls ask for no more plans than stated, out of some 3900 lists of rows and well
+    under the 4096 that are remembered, and each is made for as many modules and for at least the most rows, so that it can run them."""
+    rng = random.Random(K + bits)
+    drawn = [[rng.randint(1, 16) for _ in range(8)] for _ in range(4000)]
+    lines = ask([f"set_rows 2048 {K} {bits} 128 8 " + " ".join(map(str, rows)) for rows in drawn], raw=True)
+    lists = [tuple(map(int, line.split("[")[1].rstrip("] ").split())) for line in lines]
+    assert len({tuple(sorted(rows)) for rows in drawn}) > 3700 and len(set(lists)) <= most
+    for rows, planned in zip(drawn, lists):
+        assert sum(planned) == 8 and max(m + 1 for m, c in enumerate(planned) if c) >= max(rows), (rows, planned)
+
+
 def test_zero_point_problems_reach_every_workgroup_of_the_block_kernel(ask):
     """The problems that the GPU tests run with zero points: row blocks and wavefronts along K of their plans."""
     for (p, want), (status, launches) in zip(H.BLOCK_ZERO_POINTS.items(), ask([f"asym {' '.join(map(str, p))} {64 * MIB}" for p in H.BLOCK_ZERO_POINTS])):
