@@ -1999,8 +1999,9 @@ static void module_set_rows(const LinearArgs* args, const int* member, int count
     rows[std::max(1, others)] += few - 1;
 }
 
-// share_us: a module's part of the modelled time of its set, 0 for a module in none.
-static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans, double* share_us = nullptr) {
+// A module's set (-1: in none) and its part of the set's modelled time.
+struct SetShare { int set; double us; };
+static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_nbytes, LinearPlan* plans, SetShare* share) {
     const size_t lds_limit = (size_t)device_max_lds();
     int64_t steps_total = 0;                                   // of the modules the skinny kernel will serve
     for (int i = 0; i < n; ++i)
@@ -2017,7 +2018,7 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
         }
         if (st == RTN_ERR_CONFIG) st = resolve_plan(a, nullptr, workspace_nbytes, &plans[i]);    // the module's own plan
         if (st != RTN_OK) return st;
-        if (share_us) share_us[i] = 0.0;
+        share[i] = {-1, 0.0};
     }
     // Sets of alike modules (the errors of a call are those of the plans above)
     std::vector<char> tried((size_t)n, 0);                     // in a set, whether or not a shape was found for it
@@ -2048,7 +2049,7 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
             LinearPlan& p = plans[member[k]];
             p.prefetch = set.nb; p.waves_n = set.wn; p.waves_k = set.wk;
             p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
-            if (share_us) share_us[member[k]] = set.us / count;
+            share[member[k]] = {i, set.us / count};
         }
     }
     return RTN_OK;
@@ -2065,8 +2066,8 @@ static double grouped_share_us(const LinearArgs& a, int n) {
 
 // A set of a grouped call's modules on the block kernel.  In a mixture-of-experts model their rows change with every call, so a plan is
 // made, and remembered, for classes of rows, up to 8 or 16 and then by 32, in an order of its own: all lists of up to 16 rows of like modules
-// share two plans (eight experts with rows drawn anew each call 0.4 us of host time, 25 for a plan of their own).  With more than 16 rows in
-// the set its time is that of the rows themselves.
+// share two plans (all the plans of a call of eight experts with rows drawn anew take 1.2 us of host time, 25 with a plan here for each list).
+// With more than 16 rows in the set its time is that of the rows themselves.
 static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) {
     int64_t most = 0;
     for (int k = 0; k < l->count; ++k) most = std::max(most, args[l->member[k]].M);
@@ -2104,23 +2105,31 @@ static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) 
 // A grouped call's modules of up to 512 rows: together on the block kernel where that is modelled ahead of the launches that go out
 // otherwise.  Modules with a launch of their own (kOpen) make up the sets, in order; the small ones, which the small-batch kernel's
 // grouped launches serve, fill the places left where that is modelled level (200, 100 and six times 1 to 6 rows of 4096 x 4096: 0.98,
-// measured 30.0 and 34.2 us), and then make sets of their own.  Measured against the small-batch kernel, int4 group
-// 128: eight of 2048 x 7168 at 2 to 16 rows 30.5 us and 15.9, int8 31.0 and 22.4, 5280 x 6144 37.2 and 30.9; small modules
-// stay there (eight of 1024 x 2048 5.6, 7.4 here), as do few rows (2048 x 7168 at 1 to 8).  The modules alone in their launch go on
-// to the small-batch kernel's grouped launches.
-static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, SharedLaunch* out, const double* share_us = nullptr) {
+// measured 30.0 and 34.2 us), and then make sets of their own, those of one shape (module_set_plan) as a whole or not at all, with modules
+// of other shapes or by themselves.  Measured against the small-batch kernel, int4 group 128: eight of 2048 x 7168 at 9 to 16 rows 27.7 us and
+// 17.4, int8 35.1 and 23.4, 5280 x 6144 39.4 and 32.0; 1024 x 4096 stay there (8.1, 8.4 here), as do few rows (2048 x 7168 at 1 to 8
+// 14.9, 15.5 here).  Of 3218 drawn sets the choice is 0.7 % behind the better kernel on the mean, more than 5 % in 155.  The modules alone
+// in their launch go on to the small-batch kernel's grouped launches.
+static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n, size_t workspace_nbytes, const SetShare* share,
+                          SharedLaunch* out) {
     std::vector<double> own_us((size_t)n, 0.0);
     std::vector<char> state((size_t)n, kAlone);
+    std::vector<int64_t> most((size_t)n, 0);                   // rows of a module, or of the largest in its set
+    std::vector<int> open((size_t)n, 0), verdict((size_t)n, -1);   // small modules of a set (or the module itself) still open; see gather_whole
     int small = 0;
     double bytes = 0.0;
     auto grouped = [&](int i) { return plans[i].path == 1 && plans[i].split_k == 1 && plans[i].m_blocks == 1; };
-    for (int i = 0; i < n; ++i)
+    auto lead = [&](int i) { return share[i].set < 0 ? i : share[i].set; };    // a set goes by its first module
+    for (int i = 0; i < n; ++i) {
         if (grouped(i)) { ++small; bytes += (double)args[i].N * args[i].K * args[i].bits / 8.0; }
+        most[lead(i)] = std::max(most[lead(i)], args[i].M);
+    }
     for (int i = 0; i < n; ++i) {
         if (args[i].M > kMaxMergedRows || (args[i].M <= 4 && !grouped(i))) continue;
-        if (grouped(i) && bytes < 24e6 && args[i].M * args[i].K * 2 < 100 << 10) continue;      // none of these was ahead
+        if (grouped(i) && bytes < 24e6 && most[lead(i)] * args[i].K * 2 < 100 << 10) continue;  // none of these was ahead
         state[i] = grouped(i) ? kSmall : kOpen;
-        own_us[i] = share_us && share_us[i] > 0.0 ? share_us[i] : grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
+        if (grouped(i)) ++open[lead(i)];
+        own_us[i] = share[i].set >= 0 ? share[i].us : grouped(i) ? grouped_share_us(args[i], std::min(small, 16)) : own_plan_us(args[i], plans[i], workspace_nbytes);
     }
     int launches = 0;
     // up to eight modules of i's class from i on that are in `wanted`, after those in l; their time apart
@@ -2128,6 +2137,23 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         double apart = 0.0;
         for (int j = from; j < n && l->count < rtn::kMaxBlockGroup; ++j) {
             if (state[j] != wanted || !one_block_class(args[i], args[j])) continue;
+            apart += own_us[j];
+            l->member[l->count++] = j;
+        }
+        return apart;
+    };
+    // the small modules of i's class from i on, a set's whole or not at all
+    auto gather_whole = [&](SharedLaunch* l, int i) {
+        double apart = 0.0;
+        l->count = 0;
+        for (int j = i, places = rtn::kMaxBlockGroup; j < n; ++j) {
+            if (state[j] != kSmall || !one_block_class(args[i], args[j])) continue;
+            int& v = verdict[lead(j)];
+            if (v / 2 != i || v < 0) {                         // the first of its set here
+                v = 2 * i + (open[lead(j)] <= places ? 1 : 0);
+                if (v & 1) places -= open[lead(j)];
+            }
+            if (!(v & 1)) continue;
             apart += own_us[j];
             l->member[l->count++] = j;
         }
@@ -2142,21 +2168,38 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         return l->plan.us >= 0.0 && l->plan.us <= line * apart;
     };
     auto take = [&](const SharedLaunch& l) {
-        for (int k = 0; k < l.count; ++k) state[l.member[k]] = kDone;
+        for (int k = 0; k < l.count; ++k) {
+            if (state[l.member[k]] == kSmall) --open[lead(l.member[k])];
+            state[l.member[k]] = kDone;
+        }
         out[launches++] = l;
     };
     for (char kind : {kOpen, kSmall})
         for (int i = 0; i < n; ++i) {
             if (state[i] != kind) continue;
-            if (kind == kSmall && share_us && share_us[i] > 0.0) {
-                // a set with a plan of its own: all of it here, in launches of like size, or none (14 of 1056 x 7168, up to 12 rows: 23 us on
-                // the small-batch kernel, 25 as two launches here, 36 as one of eight and the others there)
-                int member[16], count = 0;
-                for (int j = i; j < n && count < 16; ++j)
-                    if (state[j] == kSmall && share_us[j] == share_us[i] && args[j].N == args[i].N && args[j].K == args[i].K && args[j].bits == args[i].bits && args[j].g == args[i].g)
-                        member[count++] = j;
+            SharedLaunch set, filled;
+            if (kind == kSmall) {
+                if (open[lead(i)] < rtn::kMaxBlockGroup) {
+                    const double apart = gather_whole(&set, i);
+                    if (set.count > open[lead(i)] && ahead(&set, apart, false)) {
+                        take(set);
+                        continue;
+                    }
+                    for (int k = 0; k < set.count; ++k)
+                        if (share[set.member[k]].set < 0) state[set.member[k]] = kAlone;
+                    if (state[i] == kAlone) continue;
+                }
+                if (share[i].set < 0) {
+                    state[i] = kAlone;
+                    continue;
+                }
+                // a set with a plan of its own: what larger modules left of it here, in launches of like size, or none (14 of 1056 x 7168, up
+                // to 12 rows: 23 us on the small-batch kernel, 25 as two launches here, 36 as one of eight and the others there)
+                int member[kModuleSet], count = 0;
+                for (int j = i; j < n; ++j)
+                    if (state[j] == kSmall && share[j].set == share[i].set) member[count++] = j;
                 const int parts = (count + rtn::kMaxBlockGroup - 1) / rtn::kMaxBlockGroup;
-                SharedLaunch part[2];
+                SharedLaunch part[kModuleSet / rtn::kMaxBlockGroup];
                 bool all = count >= 2;
                 double together = 0.0, line = 1.0;
                 for (int k = 0, at = 0; k < parts && all; ++k) {
@@ -2168,33 +2211,32 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
                     together += part[k].plan.us;
                     line = std::min(line, together_line(part[k].count, 16, false));
                 }
-                all = all && together <= line * share_us[i] * count;
+                all = all && together <= line * share[i].us * count;
                 for (int k = 0; k < parts && all; ++k) take(part[k]);
                 for (int k = 0; k < count && !all; ++k) state[member[k]] = kAlone;
                 continue;
             }
-            SharedLaunch set, filled;
             set.count = 0;
-            double apart = gather(&set, i, i, kind);
+            double apart = gather(&set, i, i, kOpen);
             const bool together = ahead(&set, apart, false);
-            if (kind == kOpen) {
-                if (together) apart = set.plan.us;
-                filled = set;
-                apart += gather(&filled, i, 0, kSmall);
-                if (filled.count > set.count && ahead(&filled, apart, true)) {
-                    take(filled);
-                    continue;
-                }
+            if (together) apart = set.plan.us;
+            filled = set;
+            apart += gather(&filled, i, 0, kSmall);
+            for (int k = set.count; k < filled.count; ++k) {   // what is left of a set pays its launch's start all the same
+                const int first = lead(filled.member[k]);
+                int taken = 0;
+                for (int x = set.count; x < filled.count; ++x) taken += lead(filled.member[x]) == first;
+                if (taken < open[first]) apart -= kSetStart / open[first];
             }
-            if (together) {
-                take(set);
-            } else if (kind == kOpen) {
+            if (filled.count > set.count && ahead(&filled, apart, true)) {
+                take(filled);
+                continue;
+            }
+            if (!together) {
                 set.count = 1;
                 set.member[0] = i;
-                take(set);
-            } else {
-                for (int k = 0; k < set.count; ++k) state[set.member[k]] = kAlone;
             }
+            take(set);
         }
     for (int i = 0; i < n; ++i)
         if (state[i] == kAlone) {
@@ -2204,32 +2246,57 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
     return launches;
 }
 
+// What a grouped call issues: launches of the block kernel, then the modules that are left, with their plans, which the small-batch
+// kernel's grouped launches serve or which go out by themselves.
+struct GroupedCall {
+    std::vector<SharedLaunch> blocks;
+    std::vector<int> left;
+    std::vector<LinearPlan> plans;
+};
+static rtn_status plan_grouped_call(const LinearArgs* args, int n, size_t workspace_nbytes, GroupedCall* call) {
+    std::vector<SetShare> share((size_t)n);
+    std::vector<LinearPlan> plans((size_t)n);
+    const rtn_status st = grouped_plans(args, n, workspace_nbytes, plans.data(), share.data());
+    if (st != RTN_OK) return st;
+    call->blocks.resize((size_t)n);
+    const int launches = grouped_blocks(args, plans.data(), n, workspace_nbytes, share.data(), call->blocks.data());
+    std::vector<char> gone((size_t)n, 0);
+    int kept = 0;
+    for (int i = 0; i < launches; ++i) {
+        const SharedLaunch l = call->blocks[i];
+        if (l.count == 1) continue;
+        for (int k = 0; k < l.count; ++k) gone[l.member[k]] = 1;
+        call->blocks[kept++] = l;
+    }
+    call->blocks.resize((size_t)kept);
+    call->left.reserve((size_t)n);
+    for (int i = 0; i < n; ++i) {
+        if (gone[i]) continue;
+        plans[call->left.size()] = plans[i];                   // (in order)
+        call->left.push_back(i);
+    }
+    call->plans.swap(plans);
+    return RTN_OK;
+}
+
 rtn_status rtn_grouped_forward(const rtn_module* mods, int n_mods, void* dev_workspace, size_t workspace_nbytes,
                                void* stream) {
     if (!mods) return RTN_ERR_NULL;
     if (n_mods <= 0) return RTN_ERR_SHAPE;
     if (!aligned16(dev_workspace)) return RTN_ERR_ALIGN;
     std::vector<LinearArgs> args((size_t)n_mods);
-    std::vector<LinearPlan> plans((size_t)n_mods);
     for (int i = 0; i < n_mods; ++i) {
         const rtn_status st = module_args(mods[i], dev_workspace, &args[i]);
         if (st != RTN_OK) return st;
     }
-    std::vector<double> share_us((size_t)n_mods);
-    const rtn_status st = grouped_plans(args.data(), n_mods, workspace_nbytes, plans.data(), share_us.data());
+    GroupedCall call;
+    const rtn_status st = plan_grouped_call(args.data(), n_mods, workspace_nbytes, &call);
     if (st != RTN_OK) return st;
-    std::vector<SharedLaunch> launches((size_t)n_mods);
-    launches.resize((size_t)grouped_blocks(args.data(), plans.data(), n_mods, workspace_nbytes, launches.data(), share_us.data()));
-    std::vector<char> left((size_t)n_mods, 1);
-    for (const SharedLaunch& l : launches) {
-        if (l.count == 1) continue;
+    for (const SharedLaunch& l : call.blocks)
         if (launch_shared(args.data(), l, false, stream) != hipSuccess) return RTN_ERR_HIP;
-        for (int k = 0; k < l.count; ++k) left[l.member[k]] = 0;
-    }
-    int n = 0;
-    for (int i = 0; i < n_mods; ++i)
-        if (left[i]) { args[n] = args[i]; plans[n] = plans[i]; ++n; }
-    const hipError_t e = n == 0 ? hipSuccess : rtn::launch_linear_grouped(args.data(), plans.data(), n, false, static_cast<hipStream_t>(stream));
+    const int n = (int)call.left.size();
+    for (int k = 0; k < n; ++k) args[k] = args[call.left[k]];  // (in order)
+    const hipError_t e = n == 0 ? hipSuccess : rtn::launch_linear_grouped(args.data(), call.plans.data(), n, false, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? RTN_OK : RTN_ERR_HIP;
 }
 

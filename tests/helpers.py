@@ -117,6 +117,11 @@ GROUPED_ON_BLOCKS = [([0, 1, 2, 3], [(16, 528, 7168, 4, 64), (9, 528, 7168, 4, 6
                      ([0, 2, 3], [(16, 528, 14336, 8, 0), (1, 512, 14336, 8, 0), (9, 544, 14336, 8, 0), (12, 528, 14336, 8, 0)]),
                      ([], [(4, 1024, 2048, 4, 128)] * 4)]
 
+# Alike modules of a grouped call that go to the block kernel in two launches: (N, K, bits, g), rows, modules of the first launch.
+GROUPED_IN_TWO_LAUNCHES = [((400, 7168, 4, 0), [11, 9, 11, 15, 14, 8, 14, 16, 3, 12, 3, 12, 12, 2, 14, 15], 8),
+                           ((592, 6144, 8, 0), [11, 14, 7, 13, 5, 13, 2, 14, 14, 11, 5, 7, 15, 4, 10], 7),
+                           ((2416, 13824, 4, 128), [4, 16, 5, 9, 12, 7, 16, 3, 14, 10, 11], 5)]
+
 # (M, N, K, bits, g) with zero points that the block kernel runs, and its 32-row blocks and wavefronts along K.
 BLOCK_ZERO_POINTS = {(70, 1040, 4096, 4, 128): (1, 1), (33, 304, 1024, 4, 0): (1, 2), (20, 304, 2048, 4, 128): (1, 4), (250, 8208, 1024, 4, 32): (2, 1),
                      (128, 304, 1024, 4, 128): (2, 2), (250, 304, 2048, 4, 128): (2, 4), (161, 12304, 1024, 4, 32): (3, 2),

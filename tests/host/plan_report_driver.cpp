@@ -137,8 +137,13 @@ int main() {
             bool tiles = false;
             int status = 0, count = 0;
             if (strlen(what) > 6) {
-                if (grouped_plans(a, n, (size_t)ws, plan) != RTN_OK) return 1;
-                count = grouped_blocks(a, plan, n, (size_t)ws, l);
+                GroupedCall call;
+                if (plan_grouped_call(a, n, (size_t)ws, &call) != RTN_OK) return 1;
+                for (const SharedLaunch& b : call.blocks) l[count++] = b;
+                for (int i : call.left) {
+                    l[count].count = 1;
+                    l[count++].member[0] = i;
+                }
             } else if (n > 1 && n <= 16 && merged_layer_plans(a, n, (size_t)ws, plan)) {
                 status = 1;
             } else {
@@ -158,18 +163,18 @@ int main() {
             if (scanf("%ld %d", &ws, &n) != 2 || n < 1 || n > 64) return 1;
             LinearArgs a[64];
             LinearPlan plan[64];
-            double share_us[64];
+            SetShare share[64];
             for (int i = 0; i < n; ++i) {
                 long M, N, K, g;
                 int bits;
                 if (scanf("%ld %ld %ld %d %ld", &M, &N, &K, &bits, &g) != 5) return 1;
                 a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
             }
-            const rtn_status st = grouped_plans(a, n, (size_t)ws, plan, share_us);
+            const rtn_status st = grouped_plans(a, n, (size_t)ws, plan, share);
             printf("%d", (int)st);
             for (int i = 0; st == RTN_OK && i < n; ++i) {
                 print_plan(a[i], plan[i]);
-                printf(" [%ld %d]", (long)(share_us[i] * 1e6), rtn::linear_plan_fits(a[i], plan[i], (size_t)device_max_lds()) ? 1 : 0);
+                printf(" [%ld %d]", (long)(share[i].us * 1e6), rtn::linear_plan_fits(a[i], plan[i], (size_t)device_max_lds()) ? 1 : 0);
             }
         } else if (!strcmp(what, "set_rows")) {                // N K bits g n, then M each -> [modules of 1, 2, .. 16 rows] that such a set is planned for
             long N, K, g;
@@ -187,7 +192,7 @@ int main() {
             for (int m = 1; m <= kSetRows; ++m) printf("%d ", rows[m]);
             printf("]");
         } else if (!strcmp(what, "layer") || !strcmp(what, "grouped")) {   // bits g workspace n, then M N K each
-            // layer -> 1 if one launch, plans; grouped -> status, [launch of each]
+            // layer -> 1 if one launch, plans; grouped -> status, [launch of each module that no launch of the block kernel has]
             long g, ws;
             int bits, n;
             if (scanf("%d %ld %ld %d", &bits, &g, &ws, &n) != 4 || n < 1 || n > 16) return 1;
@@ -199,10 +204,12 @@ int main() {
                 a[i] = problem(M, N, K, bits, g > 0 ? g : K, ws > 0);
             }
             if (what[0] == 'g') {
-                const rtn_status st = grouped_plans(a, n, (size_t)ws, plan);
+                GroupedCall call;
+                const rtn_status st = plan_grouped_call(a, n, (size_t)ws, &call);
                 printf("%d [", (int)st);
+                for (size_t k = 0; k < call.left.size(); ++k) a[k] = a[call.left[k]];
                 if (st == RTN_OK)
-                    for (int l : rtn::grouped_launches(a, plan, n, false)) printf("%d ", l);
+                    for (int l : rtn::grouped_launches(a, call.plans.data(), (int)call.left.size(), false)) printf("%d ", l);
                 printf("]\n");
                 continue;
             }

@@ -366,7 +366,7 @@ def test_native_call_is_the_python_call(rtn, monkeypatch, M, zp):
     (4, 0, 272, 2048, [1 + i % 5 for i in range(19)]),      # more than a set holds
 ])
 def test_grouped_sets_of_alike_modules(rtn, bits, g, N, K, rows):
-    """Modules of one N, K and precision share a workgroup shape in the small-batch kernel, or go to the block kernel as a whole."""
+    """Modules of one N, K and precision share a workgroup shape in the small-batch kernel (a set on the block kernel: below)."""
     mods, refs = [], []
     for i, M in enumerate(rows):
         codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i % 4)
@@ -377,6 +377,25 @@ def test_grouped_sets_of_alike_modules(rtn, bits, g, N, K, rows):
     torch.cuda.synchronize()
     for i, (m, ref) in enumerate(zip(mods, refs)):
         H.assert_linear_close(_to_np(m["C"]), ref, f"module {i} of {rows[i]} rows")
+
+
+@pytest.mark.parametrize("shape,rows,first", H.GROUPED_IN_TWO_LAUNCHES[:2])
+def test_grouped_set_in_two_launches_of_the_block_kernel(rtn, shape, rows, first):
+    """More than eight alike modules go to the block kernel in two launches that share the workspace (the plans are asserted in
+    tests/test_host_plans.py)."""
+    N, K, bits, g = shape
+    mods, refs = [], []
+    for i, M in enumerate(rows):
+        codes, scales, qw, sc, gg = _oracle_operands(N, K, bits, g, seed=i % 4)
+        A = synth.activation(M, K, seed=700 + i, device=DEV)
+        mods.append(dict(A=A, qweight=qw, scales=sc, bits=bits, group_size=g, C=torch.full((M, N), float("nan"), dtype=torch.float16, device=DEV)))
+        refs.append(O.rtn_linear(_to_np(A), codes, scales, gg))
+    plan = rtn.LayerPlan(mods, torch.empty(16 << 20, dtype=torch.uint8, device=DEV))
+    for call in range(2):
+        plan.run_grouped()
+        torch.cuda.synchronize()
+        for i, (m, ref) in enumerate(zip(mods, refs)):
+            H.assert_linear_close(_to_np(m["C"]), ref, f"call {call} module {i} of {rows[i]} rows")
 
 
 @pytest.mark.parametrize("bits,g,K", [(4, 128, 512), (4, 32, 1536), (4, 64, 4608), (4, 256, 4608), (4, 0, 4096), (8, 32, 768), (8, 64, 256),

@@ -533,6 +533,32 @@ def test_alike_modules_of_a_grouped_call_share_a_shape_that_runs(ask):
         assert len({(p["waves_n"], p["waves_k"], p["prefetch"], p["split_k"]) for p, _, _ in modules}) == 1, mods
 
 
+def test_sets_go_to_the_block_kernel_as_a_whole(ask):
+    """Drawn sets of alike modules: all of a set in launches of the block kernel of like size, or none; and of two kinds of modules with the
+    rows of 1 to 16, all of both in one launch, all of one, or none."""
+    seen, calls = set(), list(_drawn_sets(9, 500))
+    for mods in calls:
+        sizes = [len(s) for s in _grouped(ask, mods)]
+        assert sum(sizes) in (0, len(mods)) and (not sizes or max(sizes) - min(sizes) <= 1), (mods, sizes)
+        seen.add(len(sizes))
+    assert seen == {0, 1, 2}
+    for shape, rows, first in H.GROUPED_IN_TWO_LAUNCHES:
+        sets = _grouped(ask, [(M, *shape) for M in rows])
+        assert [[m for m, _ in s] for s in sets] == [list(range(first)), list(range(first, len(rows)))]
+    for mods in calls[:200]:
+        other = [(M, N + 64, K, bits, g) for M, N, K, bits, g in mods]
+        members = [m for s in _grouped(ask, mods + other) for m, _ in s]
+        assert all(sum(m // len(mods) == half for m in members) in (0, len(mods)) for half in (0, 1)), (mods, members)
+
+
+def test_what_larger_modules_leave_of_a_set_keeps_its_shape(ask):
+    """24 and 100 rows take six of ten small modules into their launch where that is modelled level; the four that are left are no reason for it:
+    their launch starts all the same."""
+    for rows in ([24, 15, 2, 7, 12, 11, 10, 2, 1, 1, 3, 100], [200, 100, 2, 5, 1, 3, 1, 4, 2, 2]):
+        sets = _grouped(ask, [(M, 4096, 2048, 4, 128) for M in rows])
+        assert [[m for m, _ in s] for s in sets] == [[m for m, M in enumerate(rows) if M > 16]]
+
+
 @pytest.mark.parametrize("K,bits,most", [(2048, 4, 136), (4096, 4, 136), (6144, 4, 1145), (7168, 4, 400), (7168, 8, 400), (14336, 4, 300)])
 def test_routing_meets_few_plans_of_a_set(ask, K, bits, most):
     """Eight modules whose rows are drawn anew each call: 4000 calls ask for no more plans than stated, out of some 3900 lists of rows and well
