@@ -1891,8 +1891,10 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
 // flight can request, the staged rows at 11.4 TB/s, 0.15 us per thousand wavefronts; modules whose slice takes several stages are a launch
 // of their own.  Against 34 thousand launches of 2480 sets (1024 to 6208 columns, K 2048 to 14336, 2 to 16 modules of 1 to 16 rows, groups of
 // 64, 128 and a row) it is 2 % slow near the best shape, 8 % rms; the pick is 1.8 % behind the best of fourteen shapes on the mean, more than
-// 10 % behind in 5 % of the sets, 31 % at most.
-struct ModuleSetPlan { int wn, wk, nb; double us; };
+// 10 % behind in 5 % of the sets, 31 % at most.  Of 466 drawn sets 9 are more than 10 % slower than with plans of their own (39 % at most), and
+// they take 0.87 of that time on the mean.
+struct ModuleSetPlan { int wn, wk; double us; };                // wn 0: no shape
+struct ModuleSetPlans { ModuleSetPlan chunks[2]; int own; };   // the fastest with one and with two chunks in flight; 1, 2: the modules' own is one
 constexpr int kModuleSet = 16, kSetRows = 16;                  // modules of a set at most (those of a launch), rows of one
 constexpr int kSetWavesN[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16}, kSetWavesK[] = {1, 2, 3, 4, 5, 7, 8};
 constexpr double kSetStart = 2.9;                              // us of a launch
@@ -1903,9 +1905,9 @@ static int64_t set_chunks(int64_t KC, int wk) {
     const int64_t all = (KC + wk - 1) / wk * wk;
     return wk <= KC && 3 * all <= 4 * KC ? all : 0;
 }
-// rows[m]: modules of m rows.  own: the plan that they would all have by themselves, or null: kept where the best is not 6 % ahead.  wn is
-// 0 where no shape can run the module of the most rows (those of fewer rows run wherever it does).
-static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, const LinearPlan* own, size_t lds_limit) {
+// rows[m]: modules of m rows.  own: the plan that they would all have by themselves, or null: kept where the best is not 6 % ahead.  A shape
+// has to run the module of the most rows; those of fewer rows run wherever it does.
+static ModuleSetPlans module_set_plans(const LinearArgs& like, const int* rows, const LinearPlan* own, size_t lds_limit) {
     const int64_t NT = like.N / 16, KC = like.K / chunk_k(like.bits);
     const double stream = like.bits == 8 ? 9.2e6 : 7.23e6;
     LinearArgs a = like;
@@ -1913,7 +1915,8 @@ static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, co
     while (most > 1 && rows[most] == 0) --most;
     LinearPlan p = {};
     p.path = 1; p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
-    ModuleSetPlan best = {0, 0, 0, 0.0}, kept = best;
+    ModuleSetPlans out = {};
+    ModuleSetPlan kept = {};
     for (int wk : kSetWavesK) {
         const int64_t chunks = set_chunks(KC, wk);
         if (chunks == 0) continue;
@@ -1955,12 +1958,19 @@ static ModuleSetPlan module_set_plan(const LinearArgs& like, const int* rows, co
                 }
                 const double shape = 1.0 + 0.033 * (std::log2((double)wn) - 1.5) + 0.034 * (std::log2((double)wk) - 1.0) + 0.057 * (nb - 1.5);
                 const double us = (fixed[wn] + requests[wn] / nb) * shape;
-                if (own && own->waves_n == wn && own->waves_k == wk && own->prefetch == nb) kept = {wn, wk, nb, us};
-                if ((best.wn == 0 || us < best.us) && rtn::linear_plan_fits(a, p, lds_limit)) best = {wn, wk, nb, us};
+                if (own && own->waves_n == wn && own->waves_k == wk && own->prefetch == nb) kept = {wn, wk, us};
+                ModuleSetPlan& best = out.chunks[nb - 1];
+                if ((best.wn == 0 || us < best.us) && rtn::linear_plan_fits(a, p, lds_limit)) best = {wn, wk, us};
             }
         }
     }
-    return kept.wn > 0 && (best.wn == 0 || best.us > 0.94 * kept.us) ? kept : best;
+    for (const ModuleSetPlan& best : out.chunks)
+        if (best.wn > 0 && best.us <= 0.94 * kept.us) return out;
+    if (kept.wn > 0) {
+        out.chunks[own->prefetch - 1] = kept;
+        out.own = own->prefetch;
+    }
+    return out;
 }
 
 // The rows that a set is planned for.  In a mixture-of-experts model they change with every call, so a plan is made, and remembered, for what
@@ -2021,6 +2031,8 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
         share[i] = {-1, 0.0};
     }
     // Sets of alike modules (the errors of a call are those of the plans above)
+    struct Set { int first, count; ModuleSetPlans plans; };
+    std::vector<Set> sets;
     std::vector<char> tried((size_t)n, 0);                     // in a set, whether or not a shape was found for it
     auto candidate = [&](int i) { return !tried[i] && args[i].M <= 16 && plans[i].path == 1; };
     for (int i = 0; i < n; ++i) {
@@ -2033,23 +2045,51 @@ static rtn_status grouped_plans(const LinearArgs* args, int n, size_t workspace_
         // (two modules whose own plans split K go to the block kernel together, as they have: 13.7 us, 12.4 as a set here)
         if (count < 2 || (count == 2 && plans[member[0]].split_k + plans[member[1]].split_k > 2)) continue;
         int64_t key[2] = {};
-        bool one_shape = true;
-        const LinearPlan first = plans[i];
+        const LinearPlan& first = plans[i];
+        bool one_shape = first.prefetch <= 2;
         for (int k = 0; k < count; ++k) {
             const LinearPlan& p = plans[member[k]];
             one_shape = one_shape && p.split_k == 1 && p.waves_n == first.waves_n && p.waves_k == first.waves_k && p.prefetch == first.prefetch;
         }
         module_set_rows(args, member, count, rows);
         for (int m = 0; m < kSetRows; ++m) key[m / 12] |= (int64_t)rows[m + 1] << (5 * (m % 12));
-        static Remembered<ModuleSetPlan, 4096> remembered;
+        static Remembered<ModuleSetPlans, 4096> remembered;
         const int own = one_shape ? 1 + first.waves_n * 64 + first.waves_k * 4 + first.prefetch : 0;
-        const ModuleSetPlan set = remembered.get({key[0], args[i].N, args[i].K, args[i].g, (size_t)key[1], lds_limit, args[i].bits, own},
-                                                 [&] { return module_set_plan(args[i], rows, one_shape ? &first : nullptr, lds_limit); });
-        for (int k = 0; k < count && set.wn > 0; ++k) {
-            LinearPlan& p = plans[member[k]];
-            p.prefetch = set.nb; p.waves_n = set.wn; p.waves_k = set.wk;
+        const ModuleSetPlans set = remembered.get({key[0], args[i].N, args[i].K, args[i].g, (size_t)key[1], lds_limit, args[i].bits, own},
+                                                  [&] { return module_set_plans(args[i], rows, one_shape ? &first : nullptr, lds_limit); });
+        if (set.chunks[0].wn == 0 && set.chunks[1].wn == 0) continue;
+        for (int k = 0; k < count; ++k) share[member[k]].set = i;
+        sets.push_back({i, count, set});
+    }
+    // Chunks in flight: the same for all that can share a launch (grouped_launches).  5 and 14 rows of 5680 x 4096 beside 8 of 1168 x 4096: 17.2 us
+    // as two launches, 11.5 as one; 449 calls of two kinds of modules take 0.96 of the time with plans of their own on the mean, and 15 of them
+    // more than 1.1 (64 with each set's fastest shape).
+    auto one_launch = [&](int i, int j) {
+        const int64_t chunk = chunk_k(args[i].bits);
+        return args[i].bits == args[j].bits && std::min(args[i].g, chunk) == std::min(args[j].g, chunk);
+    };
+    for (const Set& s : sets) {
+        double us[2] = {};
+        bool others[2] = {};                                   // modules of no set, by their chunks in flight
+        int alike = 0;
+        for (const Set& t : sets)
+            if (one_launch(s.first, t.first)) {
+                ++alike;
+                for (int c = 0; c < 2; ++c) us[c] += t.plans.chunks[c].wn > 0 ? t.plans.chunks[c].us : 1e6;
+            }
+        for (int j = 0; j < n; ++j)
+            if (share[j].set < 0 && plans[j].path == 1 && plans[j].split_k == 1 && plans[j].prefetch <= 2 && one_launch(s.first, j))
+                others[plans[j].prefetch - 1] = true;
+        for (int c = 0; c < 2; ++c)
+            if (others[1 - c] && !others[c]) us[c] += kSetStart;
+        const int c = alike == 1 && !others[0] && !others[1] && s.plans.own ? s.plans.own - 1 : us[1] < us[0] ? 1 : 0;
+        const ModuleSetPlan& set = s.plans.chunks[c].wn > 0 ? s.plans.chunks[c] : s.plans.chunks[1 - c];
+        for (int j = s.first; j < n; ++j) {
+            if (share[j].set != s.first) continue;
+            LinearPlan& p = plans[j];
+            p.prefetch = s.plans.chunks[c].wn > 0 ? 1 + c : 2 - c; p.waves_n = set.wn; p.waves_k = set.wk;
             p.split_k = p.m_rows16 = p.m_blocks = p.n_tiles16 = 1;
-            share[member[k]] = {i, set.us / count};
+            share[j].us = set.us / s.count;
         }
     }
     return RTN_OK;
@@ -2105,7 +2145,7 @@ static void plan_set(const LinearArgs* args, SharedLaunch* l, size_t workspace) 
 // A grouped call's modules of up to 512 rows: together on the block kernel where that is modelled ahead of the launches that go out
 // otherwise.  Modules with a launch of their own (kOpen) make up the sets, in order; the small ones, which the small-batch kernel's
 // grouped launches serve, fill the places left where that is modelled level (200, 100 and six times 1 to 6 rows of 4096 x 4096: 0.98,
-// measured 30.0 and 34.2 us), and then make sets of their own, those of one shape (module_set_plan) as a whole or not at all, with modules
+// measured 30.0 and 34.2 us), and then make sets of their own, those of one shape (module_set_plans) as a whole or not at all, with modules
 // of other shapes or by themselves.  Measured against the small-batch kernel, int4 group 128: eight of 2048 x 7168 at 9 to 16 rows 27.7 us and
 // 17.4, int8 35.1 and 23.4, 5280 x 6144 39.4 and 32.0; 1024 x 4096 stay there (8.1, 8.4 here), as do few rows (2048 x 7168 at 1 to 8
 // 14.9, 15.5 here).  Of 3218 drawn sets the choice is 0.7 % behind the better kernel on the mean, more than 5 % in 155.  The modules alone

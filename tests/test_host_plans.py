@@ -551,6 +551,18 @@ def test_sets_go_to_the_block_kernel_as_a_whole(ask):
         assert all(sum(m // len(mods) == half for m in members) in (0, len(mods)) for half in (0, 1)), (mods, members)
 
 
+def test_sets_that_share_a_launch_have_as_many_chunks_in_flight(ask):
+    """Modules of one precision and number of groups a chunk go out in one launch of the small-batch kernel only with as many chunks in flight:
+    sets of one call have them in common, and with the modules of no set where no other choice saves a launch's start."""
+    lone = _sets(ask, [[(14, 5680, 4096, 4, 128), (5, 5680, 4096, 4, 128)], [(14, 5680, 4096, 4, 128), (5, 5680, 4096, 4, 128), (8, 1168, 4096, 4, 128)]])
+    assert [p["prefetch"] for p, _, _ in lone[0]] == [2, 2] and [p["prefetch"] for p, _, _ in lone[1]] == [1, 1, 1]
+    for mods in _drawn_sets(13, 150):
+        if len(mods) < 3:                                      # (pairs that split K make no set)
+            continue
+        both = _sets(ask, [mods + [(M, N + 512, K, bits, g) for M, N, K, bits, g in mods]])[0]
+        assert all(share > 0 and fits for _, share, fits in both) and len({p["prefetch"] for p, _, _ in both}) == 1, mods
+
+
 def test_what_larger_modules_leave_of_a_set_keeps_its_shape(ask):
     """24 and 100 rows take six of ten small modules into their launch where that is modelled level; the four that are left are no reason for it:
     their launch starts all the same."""
