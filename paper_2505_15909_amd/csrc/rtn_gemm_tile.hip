@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // Scales of 4-bit weights come for two units at once, the second one's in the lanes of odd kq: a load of two bytes a lane touches 16 cache
     // lines (8192 x 28672 at 4096 rows 1381 -> 1362 us, 28672 x 4096 at 2048 381 -> 375, 8192 x 8192 at 8192 with half of them left out
     // 772 -> 766).
-    auto b_load_packed = [&](int set, int t) {               // the unit of step t
+    auto b_load_packed = [&](int set, int t) {               // the unit of step t; returns how many loads that takes
         const uint32_t ks = (uint32_t)(ks0 + min(t, T - 1));
         const uint32_t kc = ks >> 1;
         const uint32_t tile = SPU == 2 ? kc : ks;
@@ -215,6 +215,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
             if constexpr (BSRC == 8) sreg[set][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, s_lane[q], (int)(group_of(kc) * 2u), 0);
             breg[set][q] = __builtin_amdgcn_raw_buffer_load_b128(rb, w_lane[q], (int)(tile * 1024u), STREAM);
         }
+        return BSRC == 4 && set == 1 ? 2 : 4;
     };
     auto s_take = [&]() {                                    // rows of 16 lanes: the even ones' scales and the odd ones', each in all lanes
 #pragma unroll
@@ -331,9 +332,9 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                 }
             } else if (pa == AP - 1) {
                 if constexpr (BSRC == 4) {
-                    if ((fu & 1) == 0) { b_load_packed((fu >> 1) & 1, ft + 4); vm += fu == 0 ? 4 : 2; }    // chunk ft / 2 has just been used up
+                    if ((fu & 1) == 0) vm += b_load_packed((fu >> 1) & 1, ft + 4);       // chunk ft / 2 has just been used up
                 } else {
-                    b_load_packed((fu + 1) & 1, ft + 3); vm += 4;
+                    vm += b_load_packed((fu + 1) & 1, ft + 3);
                 }
             }
 #pragma unroll
