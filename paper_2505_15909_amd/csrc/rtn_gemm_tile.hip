@@ -168,12 +168,16 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // are beyond the resource by themselves there; K < 2^23 keeps the offsets of 256 rows in 32 bits.
     const uint32_t a_first = ((uint32_t)(wave * NA * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u;
     auto a_off = [&](int i) {
-        uint32_t next, o = i < 2 ? a_first : a_lane[2];
-        if (i & 1) asm volatile("v_add_u32 %0, %1, %2" : "=v"(next) : "s"(16u * (uint32_t)p.K), "v"(o));
-        return i & 1 ? next : o;
+        if constexpr (BSRC == 4 && IN_PLACE) {
+            uint32_t next, o = i < 2 ? a_first : a_lane[2];
+            if (i & 1) asm volatile("v_add_u32 %0, %1, %2" : "=v"(next) : "s"(16u * (uint32_t)p.K), "v"(o));
+            return i & 1 ? next : o;
+        } else {
+            return a_lane[i];
+        }
     };
     auto a_dma = [&](int stage, int t, int i) {
-        load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, BSRC == 4 && IN_PLACE ? a_off(i) : a_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
+        load_to_lds(ra, stage_a(stage) + (wave * NA + i) * 1024, a_off(i), (ks0 + min(t, T - 1)) * (kBK * 2));
     };
     auto b_dma = [&](int stage, int t, int i) {
         load_to_lds(rb, stage_b(stage) + (wave * NB + i) * 1024, b_lane[i], (ks0 + min(t, T - 1)) * (kBK * 2));
