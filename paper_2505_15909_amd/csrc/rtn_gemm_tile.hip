@@ -20,7 +20,7 @@
 //     the step's stage is free: the last phase reads the next step's first operands, and it and the phases behind it
 //     request a later step's tiles into the freed stage, so a request has a step (two, where the stages are short) to
 //     arrive and the matrix cores work across the barrier;
-//   - the two slices of a step go into an accumulator one right after the other (see the step below);
+//   - the two slices of a step go into an accumulator one right after the other, but for the 128-row 8-bit tile (see the step below);
 //   - the MFMAs take the weights as their first operand: a lane then holds four consecutive columns of a row and the
 //     results leave as whole 128-byte runs (as 2-byte stores in 32-byte runs the epilogue took 10 % of a K = 4096 tile).
 // Measured against staging through registers with the barrier at the end of each step (28672 x 4096 at 2048 rows: int4
@@ -118,6 +118,10 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // with two sets the 256-row packed tiles, which unpack as well, spill (int4 8192 x 8192 at 8192 rows 803 us, 800 this way; int8 811 and
     // 806).  Dense tiles have the registers, and are 1 % faster with two sets.
     constexpr bool IN_PLACE = BSRC != 0 && MBW == 8;
+    // The 128-row 8-bit tile takes one slice after the other: a last phase that also replaces both slices' weights waits for its LDS reads
+    // (4096 x 14336 at 200 rows 237 us, 221 this way; 8192 x 28672 472 and 440, in three splits 177 and 167; 4 bit and dense the other
+    // way, 3 and 1.5 %).
+    constexpr bool BY_SLICE = BSRC == 8 && MBW == 4;
     constexpr int U = BSRC == 0 ? 6 : 4;                     // steps per turn of the loop: every stage index is a literal
     // one object per stage: the compiler then knows that a load into one stage cannot touch reads of the other
     __shared__ __align__(16) uint8_t lds_a0[A_BYTES], lds_a1[A_BYTES], lds_a2[SA > 2 ? A_BYTES : 16];
@@ -256,12 +260,18 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     const uint32_t a_rd = (uint32_t)((wm * (TM / 2) + nl) * 128);
     const uint32_t b_rd = (uint32_t)((wn * 64 + nl) * 128);
     const uint32_t po0 = (uint32_t)((kq ^ (nl & 7)) * 16), po1 = (uint32_t)(((4 + kq) ^ (nl & 7)) * 16);
-    half8_t aop[2][2][2], bop[2][4];                         // operands: of two phases, row block, slice; of a step, slice
+    half8_t aop[2][2][2], bop[2][4];                         // operands: of two phases, row block, slice (slice, row block); of a step, slice
     auto set = [](int u, int ph) { return IN_PLACE ? u & 1 : ph & 1; };
     auto read_a = [&](int u, int ph, int b) {                // row block b of phase ph of step u (mod U)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
             aop[set(u, ph)][b][i] = *reinterpret_cast<const half8_t*>(stage_a(u % SA) + a_rd + (ph * 2 + b) * 2048 + (i ? po1 : po0));
+    };
+    auto read_slice = [&](int u, int i) {                    // all operands of a slice
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bop[i][r] = *reinterpret_cast<const half8_t*>(stage_b(u % SB) + b_rd + r * 2048 + (i ? po1 : po0));
+#pragma unroll
+        for (int b = 0; b < 4; ++b) aop[i][b >> 1][b & 1] = *reinterpret_cast<const half8_t*>(stage_a(u % SA) + a_rd + b * 2048 + (i ? po1 : po0));
     };
     auto read_b = [&](int u, int r) {
 #pragma unroll
@@ -275,7 +285,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     // (from registers alone, on the whole chip, 2.05 PFLOP/s against 1.95), and power is what bounds a full chip.  It takes all of a step's
     // weight operands in registers; the last phase replaces them as it goes.  Against a slice after the other: dense 8192 x 8192 x 8192
     // 768 -> 746 us, 4096 x 14336 at 2048 rows 188 -> 181; int4 830 -> 800, 8192 x 28672 at 4096 rows 1451 -> 1392; int8 832 -> 806, 1472
-    // -> 1402.  The 128-row packed tiles, which seldom fill the chip, are level.
+    // -> 1402; 128-row tiles int4 3 % and dense 1.5 % faster over 40 and 10 shapes, int8 4.3 % slower (BY_SLICE).
     auto step = [&](int u, int t) {
 #pragma unroll
         for (int ph = 0; ph < PH; ++ph) {
@@ -292,7 +302,14 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
                 for (int i = 0; i < 2; ++i)
                     acc[ph * 2 + b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[i][r], aop[set(u, ph)][b][i], acc[ph * 2 + b][r], 0, 0, 0);
             };
-            if (IN_PLACE && ph < PH - 1) {
+            if constexpr (BY_SLICE) {
+                read_slice(ph == PH - 1 ? u + 1 : u, PH - 1 - ph);
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[b][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bop[ph][r], aop[ph][b >> 1][b & 1], acc[b][r], 0, 0, 0);
+            } else if (IN_PLACE && ph < PH - 1) {
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
 #pragma unroll
@@ -344,7 +361,9 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
 #pragma unroll
             for (int g = 0; g < 8; ++g) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                if (ph == PH - 1) {
+                if (BY_SLICE) {
+                    if (g < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                } else if (ph == PH - 1) {
                     if (g < 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                     if (g & 1) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                 } else if (IN_PLACE ? g % 4 == 3 : g < 4) __builtin_amdgcn_sched_group_barrier(0x100, IN_PLACE ? 2 : 1, 0);
@@ -388,9 +407,13 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (BSRC == 8 && AP == 1) b_load_packed(0, 2);
     wait_and_barrier<(SA - 2) * NA + NA / AP + (BSRC == 0 ? (SB - (BP == 0 ? 1 : 2)) * NB : BSRC == 8 && AP == 1 ? 4 : 0)>();
-    for (int b = 0; b < 2; ++b) read_a(0, 0, b);
+    if constexpr (BY_SLICE) {
+        read_slice(0, 0);
+    } else {
+        for (int b = 0; b < 2; ++b) read_a(0, 0, b);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) read_b(0, r);
+        for (int r = 0; r < 4; ++r) read_b(0, r);
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     for (int t = 0;; t += U) {            // T is even; leaving between two steps keeps every wait inside an exact count
