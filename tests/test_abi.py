@@ -4,6 +4,7 @@ the oracle's selective-precision bookkeeping (Section 4)."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -392,7 +393,6 @@ def test_size_limits_are_refused_on_the_host():
 
 def test_bench_refuses_more_than_one_gpu():
     """This build measures one GPU; asking the benchmark for more exits with a message before touching a device."""
-    import subprocess
     import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
@@ -420,3 +420,25 @@ def test_native_call_leaves_what_is_not_plain_to_the_python_code(what):
     if what == "cpu tensor":
         with pytest.raises(ValueError):
             rtn.rtn_linear(*args[:5], out=args[5], workspace=args[6])
+
+
+def test_build_links_the_library_without_the_native_calls(monkeypatch, tmp_path):
+    """The binding runs without its native part, so what that needs and the library does not -- a host compiler, the headers of Python and
+    PyTorch -- may be missing: a warning, no module of an earlier build, and the library linked.  (No compiler runs here.)"""
+    from paper_2505_15909_amd import build
+    ran = []
+
+    def run(cmd, **kwargs):
+        if cmd[0] == "no-compiler":
+            raise subprocess.CalledProcessError(1, cmd)
+        ran.append(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+
+    monkeypatch.setenv("CXX", "no-compiler")
+    for name, value in (("PKG_DIR", tmp_path), ("LIB_PATH", tmp_path / "lib.so"), ("NATIVE_PATH", tmp_path / "_native.so")):
+        monkeypatch.setattr(build, name, str(value))
+    (tmp_path / "_native.so").write_text("of an earlier build")
+    monkeypatch.setattr(build.subprocess, "run", run)
+    with pytest.warns(RuntimeWarning, match="native calls were not built"):
+        assert build.build_library() == str(tmp_path / "lib.so")
+    assert (tmp_path / "lib.so").exists() and not (tmp_path / "_native.so").exists() and "-shared" in ran[-1]
