@@ -23,11 +23,16 @@ HIPCC_FLAGS = [
 
 
 def build_native(verbose: bool = False) -> str:
-    """Compiles the binding's native calls (host code only) against the installed PyTorch."""
+    """Compiles the binding's native calls (host code only) against the installed PyTorch.  The module says what it was compiled for: the
+    binding loads it with nothing else."""
+    import re
     import sysconfig
     from importlib.util import find_spec
     torch_dir = os.path.dirname(find_spec("torch").origin)
+    with open(os.path.join(torch_dir, "version.py")) as f:
+        version = re.search(r"__version__ = '([^']+)'", f.read()).group(1)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f'-DRTN_BUILT_FOR="torch {version}, Python {sysconfig.get_python_version()}"',
            "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(torch_dir, "include"),
            "-I" + os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include", "-o", NATIVE_PATH,
            os.path.join(CSRC, "rtn_native.cpp"), "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

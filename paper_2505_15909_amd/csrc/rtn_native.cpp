@@ -91,4 +91,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&module); }
+// built_for: the PyTorch and Python of this build
+PyMODINIT_FUNC PyInit__native() {
+    PyObject* const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", RTN_BUILT_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

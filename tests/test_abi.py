@@ -442,3 +442,12 @@ def test_build_links_the_library_without_the_native_calls(monkeypatch, tmp_path)
     with pytest.warns(RuntimeWarning, match="native calls were not built"):
         assert build.build_library() == str(tmp_path / "lib.so")
     assert (tmp_path / "lib.so").exists() and not (tmp_path / "_native.so").exists() and "-shared" in ran[-1]
+
+
+def test_native_calls_of_another_pytorch_are_left_alone(monkeypatch):
+    """The module reads PyTorch's objects by the layout it was compiled for: with another version the calls go through Python, with a warning."""
+    from paper_2505_15909_amd import binding
+    assert binding._load_native() is not None
+    monkeypatch.setattr(torch, "__version__", "1.0.0+other")
+    with pytest.warns(RuntimeWarning, match="compiled for torch 2"):
+        assert binding._load_native() is None
