@@ -355,6 +355,70 @@ def test_native_call_is_the_python_call(rtn, monkeypatch, M, zp):
     assert torch.equal(C, C2) and errors == errors2 and C.abs().max() > 0
 
 
+def _native_operands(rtn, zp, M=8, N=272, K=1024):
+    W, A = synth.normal_weight(N, K, 0.02, seed=3, device=DEV), synth.activation(M, K, seed=4, device=DEV)
+    q, *sz = rtn.rtn_quantize_asym(W, 4, 128) if zp else rtn.rtn_quantize(W, 4, 128)
+    return A, q, sz, torch.zeros((M, N), dtype=torch.float16, device=DEV), torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+
+
+@pytest.mark.parametrize("what", ["float32", "subclass", "numpy int", "bool", "no rows of scales", "nothing"])
+@pytest.mark.parametrize("zp", [False, True])
+def test_native_call_takes_plain_tensors_only(rtn, zp, what):
+    """Operands on the GPU, valid but for the one that is named: native code leaves the call to Python (None) for that one's sake, and takes it
+    with nothing changed."""
+    from paper_2505_15909_amd import binding
+
+    class Sub(torch.Tensor):
+        pass
+
+    A, q, sz, C, ws = _native_operands(rtn, zp)
+    native = binding._native.linear_asym if zp else binding._native.linear
+    args = [A, q, *sz, 4, 128, C, ws]
+    change = {"float32": (0, A.float()), "subclass": (1, q.as_subclass(Sub)), "numpy int": (-4, np.int64(4)), "bool": (-4, True),
+              "no rows of scales": (2, torch.tensor(1.0, dtype=torch.float16, device=DEV))}
+    if what in change:
+        args[change[what][0]] = change[what][1]
+    assert native(*args) == (0 if what == "nothing" else None)
+    torch.cuda.synchronize()
+    assert bool(C.any()) == (what == "nothing")
+
+
+@pytest.mark.parametrize("zp", [False, True])
+def test_native_call_waits_for_its_own_stream_only(rtn, zp):
+    """A call under torch.cuda.stream goes out behind that stream's work: behind a kernel that runs for a while, its results are not there yet
+    for a copy on the default stream, and they are once the stream is waited for."""
+    A, q, sz, C, ws = _native_operands(rtn, zp)
+    call = rtn.rtn_linear_asym if zp else rtn.rtn_linear
+    want = call(A, q, *sz, 4, 128).clone()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(200_000_000)
+        call(A, q, *sz, 4, 128, out=C, workspace=ws)
+    early = C.clone()
+    busy = not stream.query()
+    stream.synchronize()
+    assert busy and not early.any() and torch.equal(C, want)
+
+
+@pytest.mark.parametrize("M,zp", [(1, False), (8, True), (40, False)])
+def test_native_call_under_capture(rtn, M, zp):
+    """A graph records the call that native code makes; replays after eager work of its own take the inputs of the time, as the eager call does."""
+    A, q, sz, C, ws = _native_operands(rtn, zp, M, 272, 14336 if M == 8 else 1024)
+    call = rtn.rtn_linear_asym if zp else rtn.rtn_linear
+    call(A, q, *sz, 4, 128, out=C, workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert call(A, q, *sz, 4, 128, out=C, workspace=ws) is C
+    for seed in range(3):
+        A.copy_(synth.activation(*A.shape, seed=40 + seed, device=DEV))
+        want = call(A, q, *sz, 4, 128).clone()
+        C.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want) and C.any()
+
+
 @pytest.mark.parametrize("bits,g,N,K,rows", [
     (4, 128, 16, 512, [1, 2]),                              # one tile-row, one chunk: fewer than any workgroup shape takes
     (4, 32, 272, 2048, [1, 16, 3]),
