@@ -1886,7 +1886,7 @@ rtn_status rtn_linear_asym(const void* dev_A, int64_t M, const void* dev_qweight
 // One launch of the small-batch kernel for alike modules (N, K, precision and groups; up to sixteen of 1 to 16 rows): one workgroup shape for
 // all of them.  A plan of each module's own leaves out that its workgroups share compute units with the others': every one gets the LDS of
 // the largest slice, so eight modules of 2048 x 7168 with 1 to 8 rows were 224 workgroups of 4 x 4 wavefronts and, for the one-row module,
-// 128 of 1 x 7, one a compute unit: a second round for 96 of them (16.6 us; as 256 of 4 x 3 13.3).  Modelled time: a start, 0.77 us for every
+// 128 of 1 x 7, one a compute unit: a second round for 96 of them (16.6 us; as 256 of 4 x 3 13.5).  Modelled time: a start, 0.77 us for every
 // further round, the weights at 7.2 TB/s (8 bit: 9.2) by what the fullest compute unit streams over the mean, what the wavefronts in
 // flight can request, the staged rows at 11.4 TB/s, 0.15 us per thousand wavefronts; modules whose slice takes several stages are a launch
 // of their own.  Against 34 thousand launches of 2480 sets (1024 to 6208 columns, K 2048 to 14336, 2 to 16 modules of 1 to 16 rows, groups of

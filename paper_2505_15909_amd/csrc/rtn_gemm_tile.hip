@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads, 2) void tile_gemm_kernel(const TileGroup 
     for (int i = 0; i < NB; ++i)
         b_lane[i] = (wave * NB + i) * 8 + st_row < b_rows ? ((uint32_t)((wave * NB + i) * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u : kNoRow;
     // Where registers are short two of the four addresses are the other two plus a row group: with four the 4-bit tall tile spills as many
-    // registers, at the same speed (28672 x 4096 at 2048 rows 380 us, 383 spilling; 8192 x 8192 at 8192 796 and 789).  Rows past M
+    // registers, at the same speed to 1 % (28672 x 4096 at 2048 rows 380 us, 383 spilling; 8192 x 8192 at 8192 796 and 789).  Rows past M
     // are beyond the resource by themselves there; K < 2^23 keeps the offsets of 256 rows in 32 bits.
     const uint32_t a_first = ((uint32_t)(wave * NA * 8 + st_row) * (uint32_t)p.K + st_piece * 8) * 2u;
     auto a_off = [&](int i) {
@@ -528,8 +528,11 @@ void fill_common(TileParams& tp, const void* A, void* C, float* ws, int64_t M, i
 // 1.58 us with a 256-row tile and 1.00 with a 128-row one (packed weights; 1.54 and 0.87 dense), of a round that fills half
 // the chip or less 1.26 and 0.82 (1.12 and 0.87): the clock depends on how much of the chip is busy.  A round costs 6 us
 // besides; a split adds the reduce launch and the partial sums' trip through the workspace, mostly cache.  Fitted to 480
-// measured launches: thirteen shapes of 3072 to 28672 columns at 128 to 3072 rows, both heights, one to eight splits
-// (error 5 % rms; the pick is within 1 % of the best measured pair on average).
+// measured launches of this kernel when all requests of a step went out behind its barrier and each slice came back to its accumulators.
+// Against 2888 launches as it is -- thirteen shapes of 3072 to 28672 columns at 128 to 3072 rows, both heights, one to eight splits -- the
+// times are too long by 9 and 8 % at 4 bit (128- and 256-row tiles), by -4 and 3 % at 8 bit, 5-7 % rms, and dense ones by some 10 % (8192 x
+// 8192 x 8192 812 us here, 726 measured); alike enough for the pick, which is 0.1 % behind the best measured pair on the mean at 4 bit and
+// 0.5 % at 8 (4 and 9 % at most).
 double tile_model_us(bool dense, int rows16, int64_t M, int64_t N, int64_t K, int split_k) {
     const bool tall = rows16 == 8;
     const double half = tall ? (dense ? 1.12 : 1.26) : (dense ? 0.87 : 0.82);
