@@ -2155,7 +2155,7 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
     std::vector<double> own_us((size_t)n, 0.0);
     std::vector<char> state((size_t)n, kAlone);
     std::vector<int64_t> most((size_t)n, 0);                   // rows of a module, or of the largest in its set
-    std::vector<int> open((size_t)n, 0), verdict((size_t)n, -1);   // small modules of a set (or the module itself) still open; see gather_whole
+    std::vector<int> open((size_t)n, 0), decided((size_t)n, -1);   // small modules of a set (or the module itself) still open; see gather_whole
     int small = 0;
     double bytes = 0.0;
     auto grouped = [&](int i) { return plans[i].path == 1 && plans[i].split_k == 1 && plans[i].m_blocks == 1; };
@@ -2188,7 +2188,7 @@ static int grouped_blocks(const LinearArgs* args, const LinearPlan* plans, int n
         l->count = 0;
         for (int j = i, places = rtn::kMaxBlockGroup; j < n; ++j) {
             if (state[j] != kSmall || !one_block_class(args[i], args[j])) continue;
-            int& v = verdict[lead(j)];
+            int& v = decided[lead(j)];
             if (v / 2 != i || v < 0) {                         // the first of its set here
                 v = 2 * i + (open[lead(j)] <= places ? 1 : 0);
                 if (v & 1) places -= open[lead(j)];
